@@ -1,0 +1,231 @@
+// Band-limited rows: the sum over the grid's bins as a sum over fewer, wider-spaced frequencies.
+//
+// A point's model E(f) = exp(-2 pi i (sum_m a_m g_m(f) + f T)) is a chirp: around f it is a tone of
+// "time" t(f) = sum_m a_m g_m'(f) + T, and over a range of frequencies where |t(f) - t0| <= tb it
+// is determined by its values on a uniform grid of step h = 1 / (2 sigma tb), sigma > 1 (the
+// sampling theorem with oversampling sigma):
+//   E(f_k) = sum_q K((f_k - f_q) / h) exp(-2 pi i t0 (f_k - f_q)) E(f_q),
+// K a sinc windowed by the "exponential of semicircle" exp(beta (sqrt(1 - (2x/w)^2) - 1)) of
+// Barnett, Magland and af Klinteberg (SIAM J. Sci. Comput. 41, 2019), w nodes wide. With w from
+// Kaiser's estimate for 300 dB and beta = 0.98 pi (w/2) (1 - 1/sigma) the largest error over the
+// band is about 1e-14 (root mean square 3e-15): below the rounding of a phase of hundreds of
+// cycles. So the data side can be summed once per event, U_q = sum_k u_k K(..) exp(..), and
+// Z_det = sum_k u_k E_det(f_k) = sum_q U_q E_det(f_q) for every point whose t(f) stays inside
+// [t0 - tb, t0 + tb] on the rows' frequencies, with the same error in the adjoint's moments (f E
+// and g_m E are as band-limited as E).
+//
+// The grid is cut into panels (geometric in f) and a few wide segments from a panel to the top;
+// each has candidate row sets (bands) for a range of (t0, tb). The set-up of a group of 64 points
+// bounds t(f) over the group and takes, per segment, the band with the fewest rows that holds
+// it, or the grid's own bins where none does: a group's plan.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "gwl_common.h"
+
+namespace gwl {
+
+constexpr int MAXPANEL = 14;    // panels of the grid
+constexpr int MAXSEG = 20;      // panels and wide segments
+constexpr int MAXBRK = 63;      // frequency intervals on which t(f) is bounded
+constexpr int MAXCAND = 512;    // bands of all segments
+constexpr int PLAN_INTS = 64;   // a group's plan: rows in all, pieces, float64 path, rows per chunk;
+                                // then per piece its first row, its rows and its band (-1: bins)
+constexpr double BAND_FILL = 0.98;  // share of a band's half-width that a group may use
+
+struct BandCand {
+  double t0, tb;      // centre and half-width of the band (s)
+  double step;        // spacing of its rows (Hz)
+  int row0, rows;     // its rows in the event's tables
+  int i0, i1;         // the intervals that its rows' frequencies reach over
+};
+struct BandHead {
+  int nbrk, ncand, nseg, npanel;
+  int c0[MAXSEG + 1];      // each segment's bands, fewest rows first
+  int first[MAXSEG];       // the panel that a segment starts with
+  int k0[MAXSEG];          // its bins
+  int bins[MAXSEG];
+  double gp[MAXBRK + 1][NBASIS];  // g_m'(f) at the interval ends
+  double dg[MAXBRK][NBASIS];      // |change of g_m'| over an interval (each g_m' is monotone)
+  BandCand cand[MAXCAND];
+};
+
+// How a band's rows are made (host to device, at event creation).
+struct BandGen {
+  int src0, nsrc;     // the rows that it sums: a segment's bins, or the segment's widest band's rows
+  int src_half;       // their spacing in half bins (bins: 2; on a grid that is not uniform their
+                      // frequencies are read instead)
+  int half;           // its own spacing in half bins
+  int n0;             // first row at fa + n0 h, fa the first source row's frequency
+  int w;              // window width in rows
+  int row0, rows;
+  int klen;           // kernel values kept from koff, by half-bin distance (0: computed as needed)
+  int64_t koff;
+  double h, fa, t0, beta;
+  double hdf;         // half a bin (Hz)
+};
+
+struct BandLds {
+  float2 r[MAXBRK + 1];                      // lowest and highest t per interval over the group
+  unsigned long long ok[MAXCAND / 64 + 1];   // bands that hold the group
+  int plan[PLAN_INTS];
+};
+
+template <int CTRL>
+__device__ inline float dpp_max(float v) {
+  const int o = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false);
+  return fmaxf(v, __int_as_float(o));
+}
+// the largest of 64 lanes, in lane 63: within rows of 16, then across rows
+__device__ inline float wave_max_hi(float v) {
+  v = dpp_max<0x111>(v);  // row_shr:1
+  v = dpp_max<0x112>(v);
+  v = dpp_max<0x114>(v);
+  v = dpp_max<0x118>(v);
+  v = dpp_max<0x142>(v);  // row_bcast:15
+  return dpp_max<0x143>(v);  // row_bcast:31
+}
+
+// Step 1, by nw wavefronts that each hold the group's 64 points: bounds of t(f) over the group
+// on the intervals w, w + nw, .... Every g_m' is monotone, so over an interval t lies within
+// (t_i + t_i+1 -+ sum_m |a_m| |change of g_m'|) / 2. Points with a NaN coefficient do not count
+// (their value is NaN on any rows).
+template <int ND>
+__device__ inline void band_ranges(const BandHead* __restrict__ bh, const double (&a)[NBASIS], const double (&T)[ND],
+                                   int w, int nw, int lane, BandLds& s) {
+  double tlo = T[0], thi = T[0];
+#pragma unroll
+  for (int d = 1; d < ND; ++d) {
+    tlo = fmin(tlo, T[d]);
+    thi = fmax(thi, T[d]);
+  }
+  for (int i = w; i < bh->nbrk; i += nw) {
+    double t = 0.0, t1 = 0.0, v = 0.0;
+#pragma unroll
+    for (int m = 0; m < NBASIS; ++m) {
+      t = fma(a[m], bh->gp[i][m], t);
+      t1 = fma(a[m], bh->gp[i + 1][m], t1);
+      v = fma(fabs(a[m]), bh->dg[i][m], v);
+    }
+    const double mid = t + t1;
+    float hi = (float)fma(0.5, mid + v, thi), nlo = -(float)fma(0.5, mid - v, tlo);
+    const bool nan = !(hi == hi) || !(nlo == nlo);
+    hi = wave_max_hi(nan ? -__builtin_inff() : hi);
+    nlo = wave_max_hi(nan ? -__builtin_inff() : nlo);
+    if (lane == WAVE - 1) s.r[i] = make_float2(-nlo, hi);
+  }
+}
+
+// Step 2, after a barrier: the bands that hold the group, 64 per wavefront and turn.
+__device__ inline void band_hold(const BandHead* __restrict__ bh, int w, int nw, int lane, BandLds& s) {
+  for (int wd = w; wd * WAVE < bh->ncand; wd += nw) {
+    const int c = wd * WAVE + lane;
+    bool ok = false;
+    if (c < bh->ncand) {
+      const BandCand b = bh->cand[c];
+      float lo = __builtin_inff(), hi = -__builtin_inff();
+      for (int i = b.i0; i <= b.i1; ++i) {
+        lo = fminf(lo, s.r[i].x);
+        hi = fmaxf(hi, s.r[i].y);
+      }
+      const double lim = BAND_FILL * b.tb;
+      ok = (double)hi - b.t0 <= lim && b.t0 - (double)lo <= lim;
+    }
+    const unsigned long long m = __ballot(ok);
+    if (lane == 0) s.ok[wd] = m;
+  }
+}
+
+// Step 3, after a barrier, by one wavefront: the plan. Lane j holds segment j; the panels below
+// one wide segment (the cheapest, or none) and that segment are the pieces, neighbouring panels
+// that keep their bins one piece. `mixed`: a group whose rows are not clearly fewer than its bins
+// keeps the mixed-precision loop over all of them (the float64 loop over the rows costs about
+// 47 issue slots a row at three detectors against 38 a bin).
+__device__ inline void band_plan(const BandHead* __restrict__ bh, int64_t M, bool mixed, int nchunk, int lane,
+                                 BandLds& s) {
+  const int ns = bh->nseg, np = bh->npanel;
+  int rows = 0, row0 = 0, cand = -1, first = 0;
+  if (lane < ns) {
+    const int b0 = bh->c0[lane], nb = bh->c0[lane + 1] - b0, wd = b0 >> 6, sh = b0 & 63;
+    unsigned long long bits = 0;
+    if (nb > 0) {
+      bits = s.ok[wd] >> sh;
+      if (sh) bits |= s.ok[wd + 1] << (64 - sh);
+      if (nb < 64) bits &= (1ull << nb) - 1;
+    }
+    first = bh->first[lane];
+    rows = bh->bins[lane];
+    row0 = bh->k0[lane];
+    if (bits) {
+      cand = b0 + __ffsll((unsigned long long)bits) - 1;
+      rows = bh->cand[cand].rows;
+      row0 = bh->cand[cand].row0;
+    }
+  }
+  // rows of the panels before each panel
+  int pre = lane < np ? rows : 0;
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) {
+    const int o = __shfl_up(pre, off);
+    if (lane >= off) pre += o;
+  }
+  const int total = __shfl(pre, np - 1);
+  int excl = __shfl_up(pre, 1);
+  if (lane == 0) excl = 0;
+  const int below = __shfl(excl, first);
+  unsigned long long key = ~0ull;
+  if (lane == 0) key = (unsigned long long)total << 6;
+  else if (lane >= np && lane < ns && cand >= 0) key = ((unsigned long long)(below + rows) << 6) | (unsigned)lane;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const unsigned long long o = __shfl_xor(key, off);
+    key = o < key ? o : key;
+  }
+  const int wide = (int)(key & 63), all = (int)(key >> 6);   // wide = 0: none
+  const int nf = wide ? __shfl(first, wide) : np;            // panels that stay
+  const int wrows = __shfl(rows, wide), wrow0 = __shfl(row0, wide), wcand = __shfl(cand, wide);
+  if (wide && lane == nf) {
+    rows = wrows;
+    row0 = wrow0;
+    cand = wcand;
+  }
+  const int n = nf + (wide ? 1 : 0);
+  const unsigned long long dir = __ballot(lane < n && cand < 0);
+  const bool head = lane < n && !(cand < 0 && lane > 0 && ((dir >> (lane - 1)) & 1));
+  const unsigned long long heads = __ballot(head);
+  const unsigned long long after = lane < 63 ? heads >> (lane + 1) : 0;
+  const int next = after ? lane + __ffsll(after) : n;        // the next piece's lane
+  const int last = next - 1;
+  const int lrow0 = __shfl(row0, last & 63), lrows = __shfl(rows, last & 63);
+  if (head) {
+    const int idx = __popcll(heads & ((1ull << lane) - 1));
+    s.plan[4 + 3 * idx] = row0;
+    s.plan[5 + 3 * idx] = cand < 0 ? lrow0 + lrows - row0 : rows;
+    s.plan[6 + 3 * idx] = cand;
+  }
+  if (lane == 0) {
+    const bool f64 = !mixed || 5 * (int64_t)all <= 4 * M;
+    s.plan[0] = all;
+    s.plan[1] = (int)__popcll(heads);
+    s.plan[2] = f64 ? 1 : 0;
+    s.plan[3] = (all + nchunk - 1) / nchunk;
+  }
+}
+
+// Rows [q0, q1) of a group's pieces in order: fn(first row, end row, spacing). `get` reads the plan.
+template <class Get, class Fn>
+__device__ __forceinline__ void for_pieces(const BandHead* __restrict__ bh, double grid_step, int q0, int q1, Get get,
+                                           Fn fn) {
+  const int np = get(1);
+  int base = 0;
+  for (int i = 0; i < np && base < q1; ++i) {
+    const int row0 = get(4 + 3 * i), rows = get(5 + 3 * i), cand = get(6 + 3 * i);
+    const int lo = q0 > base ? q0 - base : 0, hi = q1 - base < rows ? q1 - base : rows;
+    if (lo < hi) fn(row0 + lo, row0 + hi, cand < 0 ? grid_step : bh->cand[cand].step);
+    base += rows;
+  }
+}
+
+}  // namespace gwl

@@ -215,7 +215,8 @@ __device__ __forceinline__ Row cut_row(Row r, int k, int kc) {
   return r;
 }
 
-// The bin loop of one wavefront: points in lanes, bins [k0, k1) of one event.
+// The bin loop of one wavefront: points in lanes, bins [k0, k1) of one event, added to the caller's
+// sums.
 // Mixed precision: the complex sums in float32 over blocks of NB bins, each block added into
 // float64; the adjoint moments in float64 throughout (see mixed_bin). CUT: each lane keeps only
 // its first kc bins.
@@ -224,10 +225,7 @@ __device__ __forceinline__ void bin_loop_mixed(TabP tab, GradP gtab,
                                                int k0, int k1, const double (&a)[NBASIS], const double (&T)[ND],
                                                const float (&cr)[ND], const float (&ci)[ND],
                                                double (&tot)[nz_of(ND, GRAD)], int kc = 0) {
-  constexpr int NZ = nz_of(ND, GRAD);
   constexpr int NF = 2 * ND;  // float32 block sums
-#pragma unroll
-  for (int z = 0; z < NZ; ++z) tot[z] = 0.0;
   int k = k0;
   if (k + NB <= k1) {
     // each bin's row is requested ahead of its use, two bins ahead in the forward loop and one
@@ -276,9 +274,6 @@ __device__ __forceinline__ void bin_loop_f64(TabP tab, GradP gtab,
                                              const double (&cr)[ND], const double (&ci)[ND],
                                              const double2* __restrict__ tbl, double (&z)[nz_of(ND, GRAD)],
                                              int kc = 0) {
-  constexpr int NZ = nz_of(ND, GRAD);
-#pragma unroll
-  for (int j = 0; j < NZ; ++j) z[j] = 0.0;
   if (k0 >= k1) return;
   // rows requested one bin ahead (two ahead measured no faster here and cost registers)
   RowF64<ND> cur = load_row_f64<ND>(tab, k0);
@@ -312,9 +307,6 @@ __device__ __forceinline__ void bin_loop_f64_rot(TabP tab, GradP gtab, int k0, i
                                                  const double (&T)[ND], const double (&cr)[ND],
                                                  const double (&ci)[ND], const double2* __restrict__ tbl, double step,
                                                  double (&z)[nz_of(ND, GRAD)]) {
-  constexpr int NZ = nz_of(ND, GRAD);
-#pragma unroll
-  for (int j = 0; j < NZ; ++j) z[j] = 0.0;
   if (k0 >= k1) return;
   double D[ND], pr[ND], pim[ND];
   D[0] = 0.0;
@@ -386,6 +378,34 @@ __device__ __forceinline__ void bin_loop_f64_rot(TabP tab, GradP gtab, int k0, i
       f64_mac<ND, GRAD, GradP>(cur, gtab, k, cs, sn, cr, ci, z);
       cur = nxt;
     }
+  }
+}
+
+// The mixed loop's sums in the float64 loop's units: its tables hold u / uref, and its phasor's
+// mean complex gain is divided out of the complex sums (the adjoint moments carry the gain in
+// c_det). Explicit fused multiply-adds: every kernel rounds alike.
+template <int ND, bool GRAD>
+__device__ __forceinline__ void mixed_units(const EventConst* __restrict__ ec, double (&tot)[nz_of(ND, GRAD)]) {
+  const double gr = ec->gain_r, gi = ec->gain_i, uref = ec->uref;
+#pragma unroll
+  for (int z = 0; z < 2 * ND; z += 2) {
+    const double re = tot[z], im = tot[z + 1];
+    tot[z] = uref * fma(re, gr, -(im * gi));
+    tot[z + 1] = uref * fma(re, gi, im * gr);
+  }
+#pragma unroll
+  for (int z = 2 * ND; z < nz_of(ND, GRAD); ++z) tot[z] *= uref;
+}
+
+// c_det for the mixed loop: the event's phasor gain times the float64 factors, in float32.
+template <int ND>
+__device__ __forceinline__ void mixed_factors(const EventConst* __restrict__ ec, const double (&crd)[ND],
+                                              const double (&cid)[ND], float (&cr)[ND], float (&ci)[ND]) {
+  const double gr = ec->gain_r, gi = ec->gain_i;
+#pragma unroll
+  for (int d = 0; d < ND; ++d) {
+    cr[d] = (float)fma(crd[d], gr, -(cid[d] * gi));
+    ci[d] = (float)fma(crd[d], gi, cid[d] * gr);
   }
 }
 

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "gwl_common.h"
 
 namespace gwl {
@@ -32,7 +34,7 @@ struct LoopShape {
   int pgmaj;    // 1: the dies take the point groups in turn (the set-up rows outweigh the table)
 };
 LoopShape make_shape(int64_t B, int64_t M, int W, int G, int setup, int sepepi = 0);
-size_t eval_lds_doubles(bool mixed, const LoopShape& sh);
+size_t eval_lds_doubles(bool table, const LoopShape& sh);
 
 // event preparation: per-bin tables, K_det and the float32 scale
 hipError_t launch_prep(int nd, const double* data, const double* psd, const double* fgrid, int64_t M, double df,
@@ -41,10 +43,21 @@ hipError_t launch_prep(int nd, const double* data, const double* psd, const doub
 int prep_blocks(int64_t M);
 size_t prep_scratch_doubles(int nd, int64_t M);  // size of `blockpart`
 
-// per-point set-up: theta[B][11] -> coef[NCOEF][Bp]; `scaled` (float32 tables) takes the
-// phasor gain from *ec into the adjoint projection rows, ec may be null when it is false
-hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, bool scaled, const double* theta, int64_t B,
-                        int64_t Bp, double* coef, hipStream_t s);
+// per-point set-up: theta[B][11] -> coef[NCOEF][Bp] (ec may be null); with band-limited rows also
+// each 64-point group's plan [npg][PLAN_INTS] for nchunk chunks (gwl_bands.h)
+struct BandHead;
+hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, const double* theta, int64_t B, int64_t Bp,
+                        double* coef, hipStream_t s, const BandHead* bands = nullptr, int64_t M = 0,
+                        bool mixed = false, int nchunk = 0, int* plan = nullptr);
+
+// band-limited rows: the bands of a grid (host; head.ncand = 0: none), and their rows made from
+// the grid's rows in tab (row numbers as head.cand[].row0); kv holds kvals kernel values
+struct BandGen;
+void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t row_base, BandHead& head,
+                std::vector<BandGen>& gen, int64_t& nrows, int64_t& kvals);
+void band_blocks(const std::vector<BandGen>& gen, int64_t M, std::vector<int2>& blk, int (&nblk)[2]);
+hipError_t launch_bands(int nd, bool uniform, const BandGen* gen, int ncand, const int2* blk, const int (&nblk)[2],
+                        double2* kv, void* tab, RowGradF64* gtab, hipStream_t s);
 
 // evaluation: set-up rows (coef, unless sh.setup), bin loop, reduction over the W chunks of a
 // workgroup and, for the value, over its G workgroups (part [G][nz][Bp] and cnt [npg], zero
@@ -54,23 +67,35 @@ hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, bool s
 // cut-off, else both null; rot: a float64 call on a uniform grid may take the detectors after
 // the first by rotation (ignored with the cut-off and in mixed precision); live (device, may be
 // null): only the first *live points are evaluated and written
-hipError_t launch_eval(int nd, bool mixed, bool grad, bool rot, const void* tab, const RowGradF64* gtab, const double* theta,
-                       const EventGeom& geo, const EventConst* ec, double* coef, int64_t B, int64_t Bp,
-                       int64_t M, const LoopShape& sh, double* part, unsigned int* cnt, double* logl,
-                       const double* fgrid, const double* kcum, const int64_t* live, hipStream_t s);
+struct EvalArgs {
+  const void *tab64, *tab32;
+  const RowGradF64* gtab;
+  const double* theta;
+  const EventGeom* geo;
+  const EventConst* ec;
+  const BandHead* bands;    // band-limited rows (null: every bin)
+  const int* plan;          // the groups' plans, unless sh.setup
+  double* coef;
+  int64_t B, Bp, M;
+  double* part;
+  unsigned int* cnt;
+  double* logl;
+  const double *fgrid, *kcum;
+  const int64_t* live;
+};
+hipError_t launch_eval(int nd, bool mixed, bool grad, bool rot, const EvalArgs& x, const LoopShape& sh, hipStream_t s);
 
 // the value's epilogue after an evaluation launch with sh.sepepi: part [G][nz][Bp] -> logl[B],
 // the G sums added in workgroup order (as the last-arriving workgroup adds them), then the value
 // from the set-up rows coef; fgrid, kcum (both or neither) for the ISCO cut-off; live as in
 // launch_eval
-hipError_t launch_value_epilogue(int nd, bool mixed, const EventConst* ec, const double* theta, const double* coef,
+hipError_t launch_value_epilogue(int nd, const EventConst* ec, const double* theta, const double* coef,
                                  int64_t B, int64_t Bp, int G, const double* part, double* logl, const double* fgrid,
                                  const double* kcum, int64_t M, const int64_t* live, hipStream_t s);
 
 // epilogue: partial sums [nchunk][nz][Bp] -> logL[B] (and grad[B][11]); the value alone reads the
 // set-up rows `coef`, the gradient evaluates the point model from theta
-// `scaled`: the partial sums came from the float32 tables, which hold u / uref
-hipError_t launch_epilogue(int nd, bool grad, bool scaled, const EventGeom& g, const EventConst* ec,
+hipError_t launch_epilogue(int nd, bool grad, const EventGeom& g, const EventConst* ec,
                            const double* theta, const double* coef, int64_t B, int64_t Bp, int nchunk,
                            const double* part, double* logl, double* gradout, hipStream_t s,
                            const double* fgrid = nullptr, const double* kcum = nullptr, int64_t M = 0);

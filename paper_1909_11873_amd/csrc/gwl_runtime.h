@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/gwlike.h"
+#include "gwl_bands.h"
 #include "gwl_common.h"
 #include "gwl_launch.h"
 
@@ -46,6 +47,8 @@ struct gwl_event_s {
   void* tab32 = nullptr;             // RowMixed<ndet>[M]
   gwl::RowGradF32* g32 = nullptr;    // [M]
   gwl::RowGradF64* g64 = nullptr;    // [M]
+  gwl::BandHead* bands = nullptr;    // band-limited rows, kept in tab64 and g64 after the bins (null: none)
+  int64_t M_loop = 0;                // rows that a typical point's loop walks (launch shapes)
   double* fgrid = nullptr;           // [M] grid frequencies (ISCO cut-off only)
   double* kcum = nullptr;            // [ndet][M + 1] running sums of the K_det terms (ISCO cut-off only)
   gwl::EventConst* ec = nullptr;     // device copy
@@ -53,6 +56,12 @@ struct gwl_event_s {
 };
 
 namespace gwl {
+
+// A launch whose chunks hold at most this many bins walks the bins: making a group's plan takes about 4 us
+// in a small call, a chunk of 16 bins less (1,000 points on one detector and 4,017 bins: 13.9 us a
+// call against 15.2 with plans; one point on three detectors and 16,225 bins, 32 bins a chunk: 22.7
+// against 18.8 with plans).
+constexpr int kBandMinChunk = 20;
 
 constexpr int64_t kMaxBatch = (int64_t)1 << 30;
 
@@ -72,12 +81,14 @@ size_t row32_bytes(int nd);
 // workspace of an evaluation launch: set-up rows [NCOEF][Bp] unless the kernel does the set-up,
 // then workgroup partial sums [G][nz][Bp] for the gradient or when G > 1 (doubles), and npg
 // completion counters for the value when G > 1
+// (and, with the set-up kernel, a plan per point group)
 size_t workspace_bytes(int64_t Bp, const LoopShape& sh, int nd, bool grad);
 size_t workspace_counters(const LoopShape& sh, bool grad);
 
 // launch shape of a call (autotuner cache, else a heuristic)
 LoopShape choose_shape(const gwl_event_s* ev, int64_t B, bool mixed, bool grad);
-LoopShape heuristic_shape(int64_t B, int64_t M, bool mixed, bool grad);
+// (M bins, of which a typical point's loop walks `rows` rows)
+LoopShape heuristic_shape(int64_t B, int64_t M, int64_t rows, bool mixed, bool grad);
 // number of bin chunks of the calibrated loop's adjoint (a heuristic)
 int heuristic_nchunk(int64_t B, int64_t M);
 

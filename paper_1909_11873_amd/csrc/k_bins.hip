@@ -32,6 +32,7 @@
 
 #include <type_traits>
 
+#include "gwl_bands.h"
 #include "gwl_bins.h"
 #include "gwl_common.h"
 #include "gwl_device.h"
@@ -68,23 +69,25 @@ LoopShape make_shape(int64_t B, int64_t M, int W, int G, int setup, int sepepi) 
 }
 
 // Dynamic LDS of a workgroup, in doubles: the set-up rows (NCOEF x 64) when the set-up runs here,
-// then the float64 phasor table (PH_TBL double2), which the cross-wavefront reduction reuses, or,
-// for mixed precision, the reduction buffer alone ((W - 1) x RED_Z x 64).
+// then the float64 phasor table (PH_TBL double2) and, with the set-up here, the group's plan, which the
+// cross-wavefront reduction reuses, or,
+// without the table, the reduction buffer alone ((W - 1) x RED_Z x 64).
 constexpr int RED_Z = 4;  // sums reduced per LDS pass
-size_t eval_lds_doubles(bool mixed, const LoopShape& sh) {
+size_t eval_lds_doubles(bool table, const LoopShape& sh) {
   const size_t rows = sh.setup ? (size_t)NCOEF * WAVE : 0;
   const size_t red = (size_t)(sh.W - 1) * RED_Z * WAVE;
-  const size_t tbl = mixed ? 0 : (size_t)2 * PH_TBL;
-  return rows + (red > tbl ? red : tbl);
+  const size_t tbl = table ? (size_t)2 * PH_TBL : 0;
+  const size_t plan = sh.setup && table ? (sizeof(BandLds) + 15) / 16 * 2 : 0;
+  return rows + (red > tbl + plan ? red : tbl + plan);
 }
 
 // logL of one point from its reduced sums and set-up values (A, c0, Q_det):
-//   sum_det [ uref Re(A E Q_det Z_det) - 1/2 A^2 |Q_det|^2 K_det ],  E = exp(-2 pi i c0).
+//   sum_det [ Re(A E Q_det Z_det) - 1/2 A^2 |Q_det|^2 K_det ],  E = exp(-2 pi i c0).
 // The fused multiply-adds are spelled out, so that the evaluation kernel and the separate value
 // epilogue round alike.
 template <int ND, int NZ>
 __device__ inline double value_from_rows(const double (&acc)[NZ], double amp, double c0f, const double (&qr)[ND],
-                                         const double (&qi)[ND], const EventConst& ec, double uref) {
+                                         const double (&qi)[ND], const EventConst& ec) {
   const double c0 = c0f - rint(c0f);
   double es, ecs;
   sincos_cycles_f64(c0, es, ecs);
@@ -94,43 +97,55 @@ __device__ inline double value_from_rows(const double (&acc)[NZ], double amp, do
   for (int d = 0; d < ND; ++d) {
     const double xr = amp * fma(er, qr[d], -(ei * qi[d]));
     const double xi = amp * fma(er, qi[d], ei * qr[d]);
-    const double dh = uref * fma(xr, acc[2 * d], -(xi * acc[2 * d + 1]));
+    const double dh = fma(xr, acc[2 * d], -(xi * acc[2 * d + 1]));
     const double hh = amp * amp * fma(qr[d], qr[d], qi[d] * qi[d]) * ec.K[d];
     out += fma(-0.5, hh, dh);
   }
   return out;
 }
 
-template <int ND, bool MIXED>
-using TabRow = typename std::conditional<MIXED, RowMixed<ND>, RowF64<ND>>::type;
+// What a launch's loop walks. LOOP_F64, LOOP_MIXED: every bin (or relative-binning edge), in float64
+// or mixed precision. LOOP_F64_BANDS: the pieces of each group's plan, in float64.
+// LOOP_MIXED_BANDS: a group of points whose plan's rows are clearly fewer than its bins walks the
+// plan in float64, another every bin in mixed precision.
+enum { LOOP_F64 = 0, LOOP_MIXED = 1, LOOP_F64_BANDS = 2, LOOP_MIXED_BANDS = 3 };
 
 // The tables are `const __restrict__` kernel arguments, so the compiler reads their wave-uniform
 // rows with scalar loads.
 // Wavefronts per SIMD that the register budget must allow (as the bin loop alone needs): the
 // reduction and epilogue after the loop would otherwise let the compiler take registers that
 // cost a wavefront per SIMD. The in-kernel set-up needs more and is not bounded.
-template <int ND, bool MIXED, bool GRAD, bool SETUP, bool CUT, bool ROT>
+template <int ND, int LOOP, bool GRAD, bool SETUP, bool CUT, bool ROT>
 constexpr int eval_waves_per_eu() {
-  return (SETUP || CUT) ? 1 : (ND > 3 ? 1 : (MIXED ? (GRAD ? 5 : 8) : (GRAD ? 4 : 5)));
+  return (SETUP || CUT) ? 1 : (ND > 3 ? 1 : (LOOP == LOOP_MIXED ? (GRAD ? 5 : 8) : (GRAD ? 4 : 5)));
 }
 
 // CUT: the optional ISCO cut-off; every lane keeps only the bins at or below its point's ISCO
 // frequency (isco_bins over fgrid), the wavefront stops at the last bin any of its lanes keeps,
 // and <h|h> takes the kept bins' share of K_det from the per-detector running sums kcum
 // [ND][M + 1]. ROT (float64, uniform grids): the detectors after the first take their phasors by
-// rotation from the first's (bin_loop_f64_rot).
-template <int ND, bool MIXED, bool GRAD, bool SETUP, bool CUT, bool ROT>
+// rotation from the first's (bin_loop_f64_rot). bh (the BANDS loops): the event's band-limited rows;
+// each group of points walks its plan's pieces (plan [npg][PLAN_INTS] from the set-up kernel, or made
+// here with the in-kernel set-up) instead of the bins [0, M), the chunks being equal shares of
+// the plan's rows.
+template <int ND, int LOOP, bool GRAD, bool SETUP, bool CUT, bool ROT>
 __global__ __launch_bounds__(WAVE * MAX_EVAL_WAVES)
-__attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, MIXED, GRAD, SETUP, CUT, ROT>()))) void k_eval(
-    const TabRow<ND, MIXED>* __restrict__ tab, const RowGradF64* __restrict__ gtab, const double* __restrict__ theta,
-    EventGeom geo, const EventConst* __restrict__ ec, double* __restrict__ coef, int64_t B, int64_t Bp, int64_t M,
-    LoopShape sh, double* __restrict__ part, unsigned int* __restrict__ cnt, double* __restrict__ logl,
+__attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT, ROT>()))) void k_eval(
+    const RowF64<ND>* __restrict__ tab, const RowMixed<ND>* __restrict__ tab32, const RowGradF64* __restrict__ gtab,
+    const double* __restrict__ theta, EventGeom geo, const EventConst* __restrict__ ec,
+    const BandHead* __restrict__ bh, const int* __restrict__ plan, double* __restrict__ coef, int64_t B, int64_t Bp,
+    int64_t M, LoopShape sh, double* __restrict__ part, unsigned int* __restrict__ cnt, double* __restrict__ logl,
     const double* __restrict__ fgrid, const double* __restrict__ kcum, const int64_t* __restrict__ live) {
   constexpr int NZ = nz_of(ND, GRAD);
+  constexpr bool TBL = LOOP != LOOP_MIXED;                     // the float64 phasor table
+  constexpr bool BANDS = LOOP == LOOP_F64_BANDS || LOOP == LOOP_MIXED_BANDS;
   extern __shared__ double lds[];
   double* rows_s = lds;                                        // [NCOEF][64] when SETUP
   double* tail = lds + (SETUP ? NCOEF * WAVE : 0);             // table, then the reduction buffer
   double2* tbl = reinterpret_cast<double2*>(tail);
+  // the group's plan when SETUP, after the table (all LDS is dynamic: a static object in front would
+  // leave the table's 16-byte entries at an 8-byte offset, which costs more than half the rate)
+  BandLds& bands_s = *reinterpret_cast<BandLds*>(tail + 2 * PH_TBL);
 
   // sh.pgmaj: each die takes whole point groups, all G workgroups of each (a point group's set-up
   // rows are read by one die only): a contiguous range of point-group-major items (balanced to
@@ -158,6 +173,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, MIXED, GRAD, SETUP, CUT
     pg = item - g * sh.npg;
   }
   // live: only the first *live points are evaluated (a batch whose length the device decides)
+  const int64_t Ball = B;
   if (live) {
     const int64_t nl = *live;
     B = nl < B ? nl : B;
@@ -168,7 +184,9 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, MIXED, GRAD, SETUP, CUT
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)pg * WAVE + lane;
-  const int64_t pc = p < B ? p : B - 1;                        // padding lanes repeat the last point
+  // padding lanes repeat the last point (of the whole batch: a group's plan, and with it a point's
+  // bits, do not depend on how many of its rows are live)
+  const int64_t pc = p < Ball ? p : Ball - 1;
   const int64_t c = (int64_t)g * sh.W + w;
   const int64_t k0l = c * sh.chunk;
   const int k0 = (int)(k0l < M ? k0l : M);
@@ -182,7 +200,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, MIXED, GRAD, SETUP, CUT
 
   // the float64 phasor table; with the in-kernel set-up and three or more wavefronts, the ones
   // that do not run a half of the set-up fill it meanwhile
-  if constexpr (!MIXED) {
+  if constexpr (TBL) {
     if (!SETUP || sh.W < 3) fill_phasor_table(tbl);
     else if (w >= 2) fill_phasor_table(tbl, 2 * WAVE);
   }
@@ -198,10 +216,12 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, MIXED, GRAD, SETUP, CUT
       if (w == wx) setup_lds_extrinsic<ND>(th, geo, ec, rows_s, lane);
     }
   }
-  if (SETUP || !MIXED) __syncthreads();
+  if (SETUP || TBL) __syncthreads();
 
   double a[NBASIS], T[ND];
   double tot[NZ];
+#pragma unroll
+  for (int z = 0; z < NZ; ++z) tot[z] = 0.0;
   bool in_range = true;
   if constexpr (SETUP) {
 #pragma unroll
@@ -211,52 +231,69 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, MIXED, GRAD, SETUP, CUT
     // a point whose phase could leave the supported range gets NaN sums (and value)
     in_range = rows_in_range<ND>(a, T, ec);
     if (!in_range) a[0] = __builtin_nan("");
+    if constexpr (BANDS) {                                     // the group's plan, by the whole workgroup
+      band_ranges<ND>(bh, a, T, w, sh.W, lane, bands_s);
+      __syncthreads();
+      band_hold(bh, w, sh.W, lane, bands_s);
+      __syncthreads();
+      if (w == 0) band_plan(bh, M, LOOP == LOOP_MIXED_BANDS, sh.nchunk, lane, bands_s);
+      __syncthreads();
+    }
   }
-  // c_det = E G Q_det from the set-up rows (the adjoint's projection factors)
-  auto lds_factors = [&](double (&crd)[ND], double (&cid)[ND]) {
-    double egr, egi;
-    phase_gain(rows_s[CO_C0 * WAVE + lane], (MIXED && ec) ? ec->gain_r : 1.0, (MIXED && ec) ? ec->gain_i : 0.0, egr,
-               egi);
+  // c_det = E Q_det from the set-up rows (the adjoint's projection factors)
+  double crd[ND], cid[ND];
+  if constexpr (SETUP) {
 #pragma unroll
-    for (int d = 0; d < ND; ++d) {
-      adjoint_factor(egr, egi, rows_s[(CO_QR + d) * WAVE + lane], rows_s[(CO_QI + d) * WAVE + lane], crd[d], cid[d]);
+    for (int d = 0; d < ND; ++d) crd[d] = cid[d] = 0.0;
+    if constexpr (GRAD) {
+      double egr, egi;
+      phase_gain(rows_s[CO_C0 * WAVE + lane], 1.0, 0.0, egr, egi);
+#pragma unroll
+      for (int d = 0; d < ND; ++d)
+        adjoint_factor(egr, egi, rows_s[(CO_QR + d) * WAVE + lane], rows_s[(CO_QI + d) * WAVE + lane], crd[d], cid[d]);
     }
-  };
-  if constexpr (MIXED) {
-    float cr[ND], ci[ND];
-    if constexpr (SETUP) {
-#pragma unroll
-      for (int d = 0; d < ND; ++d) cr[d] = ci[d] = 0.0f;
-      if constexpr (GRAD) {
-        double crd[ND], cid[ND];
-        lds_factors(crd, cid);
-#pragma unroll
-        for (int d = 0; d < ND; ++d) {
-          cr[d] = (float)crd[d];
-          ci[d] = (float)cid[d];
-        }
-      }
-    } else {
-      load_coef<ND, float>(coef, Bp, pc, GRAD, a, T, cr, ci);
-    }
-    bin_loop_mixed<ND, GRAD, const TabRow<ND, MIXED>*, const RowGradF64*, CUT>(tab, gtab, k0, k1, a, T, cr, ci, tot,
-                                                                                kc);
   } else {
-    double cr[ND], ci[ND];
-    if constexpr (SETUP) {
+    load_coef<ND, double>(coef, Bp, pc, GRAD, a, T, crd, cid);
+  }
+  // a number of the group's plan
+  auto get = [&](int i) {
+    if constexpr (SETUP) return __builtin_amdgcn_readfirstlane(bands_s.plan[i]);
+    else return plan[(int64_t)pg * PLAN_INTS + i];
+  };
+  bool f64path = LOOP != LOOP_MIXED;
+  if constexpr (LOOP == LOOP_MIXED_BANDS) f64path = get(2) != 0;     // scalar branch
+  if (!f64path) {
+    if constexpr (LOOP == LOOP_MIXED || LOOP == LOOP_MIXED_BANDS) {
+      float cr[ND], ci[ND];
+      if constexpr (GRAD) {
+        mixed_factors<ND>(ec, crd, cid, cr, ci);
+      } else {
 #pragma unroll
-      for (int d = 0; d < ND; ++d) cr[d] = ci[d] = 0.0;
-      if constexpr (GRAD) lds_factors(cr, ci);
-    } else {
-      load_coef<ND, double>(coef, Bp, pc, GRAD, a, T, cr, ci);
+        for (int d = 0; d < ND; ++d) cr[d] = ci[d] = 0.0f;
+      }
+      bin_loop_mixed<ND, GRAD, const RowMixed<ND>*, const RowGradF64*, CUT>(tab32, gtab, k0, k1, a, T, cr, ci, tot,
+                                                                            kc);
+      mixed_units<ND, GRAD>(ec, tot);
     }
-    to_table_units<ND>(a, T);
-    if constexpr (ROT)
-      bin_loop_f64_rot<ND, GRAD, const TabRow<ND, MIXED>*, const RowGradF64*>(tab, gtab, k0, k1, a, T, cr, ci, tbl,
-                                                                              ec->grid_df, tot);
-    else
-      bin_loop_f64<ND, GRAD, const TabRow<ND, MIXED>*, const RowGradF64*, CUT>(tab, gtab, k0, k1, a, T, cr, ci, tbl,
-                                                                                tot, kc);
+  } else {
+    if constexpr (LOOP != LOOP_MIXED) {
+      to_table_units<ND>(a, T);
+      auto walk = [&](int ka, int kb, double step) {
+        if constexpr (ROT)
+          bin_loop_f64_rot<ND, GRAD, const RowF64<ND>*, const RowGradF64*>(tab, gtab, ka, kb, a, T, crd, cid, tbl, step,
+                                                                           tot);
+        else
+          bin_loop_f64<ND, GRAD, const RowF64<ND>*, const RowGradF64*, CUT>(tab, gtab, ka, kb, a, T, crd, cid, tbl, tot,
+                                                                            kc);
+      };
+      if constexpr (BANDS) {
+        const int rows = get(0), chunk = get(3);
+        const int q0 = (int)c * chunk, q1 = q0 + chunk < rows ? q0 + chunk : rows;
+        for_pieces(bh, ec->grid_df, q0, q1, get, walk);
+      } else {
+        walk(k0, k1, ec->grid_df);
+      }
+    }
   }
 
   // the W chunk sums of this workgroup, added in wavefront order by the first wavefront; the
@@ -326,7 +363,6 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, MIXED, GRAD, SETUP, CUT
 #pragma unroll
       for (int d = 0; d < ND; ++d) e.K[d] = kcum[(int64_t)d * (M + 1) + kc];
     }
-    if (MIXED) apply_gain<ND>(e, tot);
     double qr[ND], qi[ND], amp, c0f;
     if constexpr (SETUP) {
       amp = in_range ? rows_s[CO_AMP * WAVE + lane] : __builtin_nan("");
@@ -345,58 +381,50 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, MIXED, GRAD, SETUP, CUT
         qi[d] = coef[(CO_QI + d) * Bp + pc];
       }
     }
-    if (p < B) logl[p] = value_from_rows<ND, NZ>(tot, amp, c0f, qr, qi, e, MIXED ? e.uref : 1.0);
+    if (p < B) logl[p] = value_from_rows<ND, NZ>(tot, amp, c0f, qr, qi, e);
   }
 }
 
-template <int ND, bool MIXED, bool GRAD>
-static hipError_t eval_setup(bool setup, bool cut, bool rot, const void* tab, const RowGradF64* gtab, const double* theta,
-                             const EventGeom& geo, const EventConst* ec, double* coef, int64_t B, int64_t Bp,
-                             int64_t M, const LoopShape& sh, double* part, unsigned int* cnt, double* logl,
-                             const double* fgrid, const double* kcum, const int64_t* live, hipStream_t s) {
+template <int ND, int LOOP, bool GRAD>
+static hipError_t eval_loop(bool cut, bool rot, const EvalArgs& x, const LoopShape& sh, hipStream_t s) {
   const dim3 grid((unsigned)(sh.gper * NXCD)), block((unsigned)(sh.W * WAVE));
-  const size_t lds = eval_lds_doubles(MIXED, sh) * sizeof(double);
-  const TabRow<ND, MIXED>* t = (const TabRow<ND, MIXED>*)tab;
-#define GWL_EVAL(ST, CU, RO)                                                                                  \
-  hipLaunchKernelGGL((k_eval<ND, MIXED, GRAD, ST, CU, RO>), grid, block, lds, s, t, gtab, theta, geo, ec, coef, B, \
-                     Bp, M, sh, part, cnt, logl, fgrid, kcum, live)
-  if (cut) {
-    if (setup) GWL_EVAL(true, true, false); else GWL_EVAL(false, true, false);
-  } else if (MIXED || !rot) {
-    if (setup) GWL_EVAL(true, false, false); else GWL_EVAL(false, false, false);
-  } else {
-    if constexpr (!MIXED) {
-      if (setup) GWL_EVAL(true, false, true); else GWL_EVAL(false, false, true);
+  const size_t lds = eval_lds_doubles(LOOP != LOOP_MIXED, sh) * sizeof(double);
+#define GWL_EVAL(ST, CU, RO)                                                                                        \
+  hipLaunchKernelGGL((k_eval<ND, LOOP, GRAD, ST, CU, RO>), grid, block, lds, s, (const RowF64<ND>*)x.tab64,         \
+                     (const RowMixed<ND>*)x.tab32, x.gtab, x.theta, *x.geo, x.ec, x.bands, x.plan, x.coef, x.B, x.Bp, \
+                     x.M, sh, x.part, x.cnt, x.logl, x.fgrid, x.kcum, x.live)
+  const bool setup = sh.setup != 0;
+  if constexpr (LOOP == LOOP_F64 || LOOP == LOOP_MIXED) {
+    if (cut) {
+      if (setup) GWL_EVAL(true, true, false); else GWL_EVAL(false, true, false);
+      return hipGetLastError();
     }
   }
+  if constexpr (LOOP != LOOP_MIXED) {
+    if (rot) {
+      if (setup) GWL_EVAL(true, false, true); else GWL_EVAL(false, false, true);
+      return hipGetLastError();
+    }
+  }
+  if (setup) GWL_EVAL(true, false, false); else GWL_EVAL(false, false, false);
 #undef GWL_EVAL
   return hipGetLastError();
 }
 
 template <int ND>
-static hipError_t eval_nd(bool mixed, bool grad, bool cut, bool rot, const void* tab, const RowGradF64* gtab,
-                          const double* theta, const EventGeom& geo, const EventConst* ec, double* coef,
-                          int64_t B, int64_t Bp, int64_t M, const LoopShape& sh, double* part, unsigned int* cnt,
-                          double* logl, const double* fgrid, const double* kcum, const int64_t* live,
+static hipError_t eval_nd(bool mixed, bool grad, bool cut, bool rot, const EvalArgs& x, const LoopShape& sh,
                           hipStream_t s) {
-  const bool st = sh.setup != 0;
-#define GWL_EV(MX, GR) \
-  return eval_setup<ND, MX, GR>(st, cut, rot, tab, gtab, theta, geo, ec, coef, B, Bp, M, sh, part, cnt, logl, fgrid, \
-                                kcum, live, s)
-  if (mixed) {
-    if (grad) GWL_EV(true, true);
-    GWL_EV(true, false);
-  }
-  if (grad) GWL_EV(false, true);
-  GWL_EV(false, false);
-#undef GWL_EV
+#define GWL_LOOP(L) grad ? eval_loop<ND, L, true>(cut, rot, x, sh, s) : eval_loop<ND, L, false>(cut, rot, x, sh, s)
+  if (x.bands) return mixed ? (GWL_LOOP(LOOP_MIXED_BANDS)) : (GWL_LOOP(LOOP_F64_BANDS));
+  return mixed ? (GWL_LOOP(LOOP_MIXED)) : (GWL_LOOP(LOOP_F64));
+#undef GWL_LOOP
 }
 
 // The value's epilogue as a kernel of its own (LoopShape::sepepi): one thread per point adds the
 // G workgroup sums in workgroup order, as the last-arriving workgroup of k_eval does, and forms
 // the value from the set-up rows, so both paths give the same bits.
 constexpr int EPI_BLOCK = 256;
-template <int ND, bool MIXED, bool CUT>
+template <int ND, bool CUT>
 __global__ __launch_bounds__(EPI_BLOCK) void k_value_epilogue(const EventConst* __restrict__ ec,
                                                               const double* __restrict__ theta,
                                                               const double* __restrict__ coef, int64_t B, int64_t Bp,
@@ -426,7 +454,6 @@ __global__ __launch_bounds__(EPI_BLOCK) void k_value_epilogue(const EventConst* 
 #pragma unroll
     for (int d = 0; d < ND; ++d) e.K[d] = kcum[(int64_t)d * (M + 1) + kc];
   }
-  if (MIXED) apply_gain<ND>(e, tot);
   double qr[ND], qi[ND];
   const double amp = coef[CO_AMP * Bp + p], c0f = coef[CO_C0 * Bp + p];
 #pragma unroll
@@ -434,26 +461,22 @@ __global__ __launch_bounds__(EPI_BLOCK) void k_value_epilogue(const EventConst* 
     qr[d] = coef[(CO_QR + d) * Bp + p];
     qi[d] = coef[(CO_QI + d) * Bp + p];
   }
-  logl[p] = value_from_rows<ND, NZ>(tot, amp, c0f, qr, qi, e, MIXED ? e.uref : 1.0);
+  logl[p] = value_from_rows<ND, NZ>(tot, amp, c0f, qr, qi, e);
 }
 
-hipError_t launch_value_epilogue(int nd, bool mixed, const EventConst* ec, const double* theta, const double* coef,
+hipError_t launch_value_epilogue(int nd, const EventConst* ec, const double* theta, const double* coef,
                                  int64_t B, int64_t Bp, int G, const double* part, double* logl, const double* fgrid,
                                  const double* kcum, int64_t M, const int64_t* live, hipStream_t s) {
   if (!coef || !part || G < 1) return hipErrorInvalidValue;
   const bool cut = fgrid != nullptr;
   if (cut && !kcum) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((B + EPI_BLOCK - 1) / EPI_BLOCK));
-#define GWL_VEPI(N, MX, CU)                                                                                   \
-  hipLaunchKernelGGL((k_value_epilogue<N, MX, CU>), grid, dim3(EPI_BLOCK), 0, s, ec, theta, coef, B, Bp, G, \
+#define GWL_VEPI(N, CU)                                                                                       \
+  hipLaunchKernelGGL((k_value_epilogue<N, CU>), grid, dim3(EPI_BLOCK), 0, s, ec, theta, coef, B, Bp, G, \
                      part, logl, fgrid, kcum, M, live)
 #define GWL_VEPI_ND(N)                                               \
   case N:                                                            \
-    if (mixed) {                                                     \
-      if (cut) GWL_VEPI(N, true, true); else GWL_VEPI(N, true, false);    \
-    } else {                                                         \
-      if (cut) GWL_VEPI(N, false, true); else GWL_VEPI(N, false, false);  \
-    }                                                                \
+    if (cut) GWL_VEPI(N, true); else GWL_VEPI(N, false);             \
     break;
   switch (nd) {
     GWL_VEPI_ND(1)
@@ -467,21 +490,18 @@ hipError_t launch_value_epilogue(int nd, bool mixed, const EventConst* ec, const
   return hipGetLastError();
 }
 
-hipError_t launch_eval(int nd, bool mixed, bool grad, bool rot, const void* tab, const RowGradF64* gtab, const double* theta,
-                       const EventGeom& geo, const EventConst* ec, double* coef, int64_t B, int64_t Bp,
-                       int64_t M, const LoopShape& sh, double* part, unsigned int* cnt, double* logl,
-                       const double* fgrid, const double* kcum, const int64_t* live, hipStream_t s) {
+hipError_t launch_eval(int nd, bool mixed, bool grad, bool rot, const EvalArgs& x, const LoopShape& sh, hipStream_t s) {
   if (sh.W < 1 || sh.W > MAX_EVAL_WAVES || sh.G < 1) return hipErrorInvalidValue;
-  if ((grad || sh.G > 1) && !part) return hipErrorInvalidValue;
-  if (!grad && sh.G > 1 && !sh.sepepi && !cnt) return hipErrorInvalidValue;
-  if (!sh.setup && !coef) return hipErrorInvalidValue;
-  const bool cut = fgrid != nullptr;
-  if (cut && !kcum) return hipErrorInvalidValue;
+  if ((grad || sh.G > 1) && !x.part) return hipErrorInvalidValue;
+  if (!grad && sh.G > 1 && !sh.sepepi && !x.cnt) return hipErrorInvalidValue;
+  if (!sh.setup && (!x.coef || (x.bands && !x.plan))) return hipErrorInvalidValue;
+  const bool cut = x.fgrid != nullptr;
+  if (cut && (!x.kcum || x.bands)) return hipErrorInvalidValue;
   switch (nd) {
-    case 1: return eval_nd<1>(mixed, grad, cut, rot, tab, gtab, theta, geo, ec, coef, B, Bp, M, sh, part, cnt, logl, fgrid, kcum, live, s);
-    case 2: return eval_nd<2>(mixed, grad, cut, rot, tab, gtab, theta, geo, ec, coef, B, Bp, M, sh, part, cnt, logl, fgrid, kcum, live, s);
-    case 3: return eval_nd<3>(mixed, grad, cut, rot, tab, gtab, theta, geo, ec, coef, B, Bp, M, sh, part, cnt, logl, fgrid, kcum, live, s);
-    case 4: return eval_nd<4>(mixed, grad, cut, rot, tab, gtab, theta, geo, ec, coef, B, Bp, M, sh, part, cnt, logl, fgrid, kcum, live, s);
+    case 1: return eval_nd<1>(mixed, grad, cut, rot, x, sh, s);
+    case 2: return eval_nd<2>(mixed, grad, cut, rot, x, sh, s);
+    case 3: return eval_nd<3>(mixed, grad, cut, rot, x, sh, s);
+    case 4: return eval_nd<4>(mixed, grad, cut, rot, x, sh, s);
   }
   return hipErrorInvalidValue;
 }

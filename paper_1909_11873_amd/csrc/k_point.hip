@@ -4,6 +4,7 @@
 // the evaluation kernel).
 #include <hip/hip_runtime.h>
 
+#include "gwl_bands.h"
 #include "gwl_bins.h"
 #include "gwl_common.h"
 #include "gwl_device.h"
@@ -13,35 +14,55 @@
 
 namespace gwl {
 
-// Set-up: one workgroup of two wavefronts per 64 points. The intrinsic half of the point model
-// (phase coefficients, constant phase, amplitude) runs on one wavefront and the extrinsic half
-// (sky, orientation, per-detector delays and projection factors) on the other, at once, into
-// LDS rows; each wavefront then writes half of the rows, with the phase-range check and the
-// adjoint factors taken from the LDS rows as setup_rows takes them (the same rows, bit for bit,
-// as one thread running setup_rows; NaN rows for a point outside the model's domain or range).
-constexpr int SETUP_WAVES = 2;
+// Set-up: one workgroup per 64 points. The intrinsic half of the point model (phase coefficients,
+// constant phase, amplitude) runs on one wavefront and the extrinsic half (sky, orientation,
+// per-detector delays and projection factors) on another, at once, into LDS rows; each of the two
+// then writes half of the rows, with the phase-range check and the adjoint factors taken from
+// the LDS rows (NaN rows for a point outside the model's domain or range). On an event with
+// band-limited rows four wavefronts share the bounds of t(f) over the group, and the group's plan
+// is left in plan[pg] (float32 units and gains are the evaluation kernel's affair).
+constexpr int SETUP_WAVES = 2, SETUP_WAVES_BANDS = 4;
 
 template <int ND>
-__global__ __launch_bounds__(SETUP_WAVES * WAVE) void k_setup(EventGeom g, const EventConst* __restrict__ ec,
-                                                              bool scaled, const double* __restrict__ theta,
-                                                              int64_t B, int64_t Bp, double* __restrict__ coef) {
+__global__ __launch_bounds__(SETUP_WAVES_BANDS * WAVE) void k_setup(EventGeom g, const EventConst* __restrict__ ec,
+                                                                    const BandHead* __restrict__ bh, int64_t M,
+                                                                    bool mixed, int nchunk,
+                                                                    const double* __restrict__ theta, int64_t B,
+                                                                    int64_t Bp, double* __restrict__ coef,
+                                                                    int* __restrict__ plan) {
   __shared__ double rows_s[NCOEF * WAVE];
+  __shared__ BandLds bands_s;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // < Bp: Bp is a multiple of 64
   const int64_t pc = p < B ? p : B - 1;                  // padding lanes repeat the last point
-  setup_halves<ND>(w, lane, theta + pc * NPARAM, g, ec, rows_s);
+  if (w < 2) setup_halves<ND>(w, lane, theta + pc * NPARAM, g, ec, rows_s);
   __syncthreads();
-  setup_rows_write<ND>(w, lane, rows_s, ec, scaled, true, coef, Bp, p);
+  if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ec, false, true, coef, Bp, p);
+  if (!bh) return;
+  double a[NBASIS], T[ND];
+#pragma unroll
+  for (int m = 0; m < NBASIS; ++m) a[m] = rows_s[(CO_A + m) * WAVE + lane];
+#pragma unroll
+  for (int d = 0; d < ND; ++d) T[d] = rows_s[(CO_T + d) * WAVE + lane];
+  if (!rows_in_range<ND>(a, T, ec)) a[0] = __builtin_nan("");
+  band_ranges<ND>(bh, a, T, w, SETUP_WAVES_BANDS, lane, bands_s);
+  __syncthreads();
+  band_hold(bh, w, SETUP_WAVES_BANDS, lane, bands_s);
+  __syncthreads();
+  if (w != 0) return;
+  band_plan(bh, M, mixed, nchunk, lane, bands_s);
+  plan[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }
 
-hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, bool scaled, const double* theta, int64_t B,
-                        int64_t Bp, double* coef, hipStream_t s) {
-  if (scaled && !ec) return hipErrorInvalidValue;
+hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, const double* theta, int64_t B, int64_t Bp,
+                        double* coef, hipStream_t s, const BandHead* bands, int64_t M, bool mixed, int nchunk,
+                        int* plan) {
   if (Bp % WAVE != 0 || B < 1 || B > Bp) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(Bp / WAVE));
+  if (bands && (!ec || !plan || nchunk < 1)) return hipErrorInvalidValue;
+  dim3 grid((unsigned)(Bp / WAVE)), block((unsigned)((bands ? SETUP_WAVES_BANDS : SETUP_WAVES) * WAVE));
 #define GWL_SETUP(N) \
-  case N: hipLaunchKernelGGL(k_setup<N>, grid, dim3(SETUP_WAVES * WAVE), 0, s, g, ec, scaled, theta, B, Bp, coef); break;
+  case N: hipLaunchKernelGGL(k_setup<N>, grid, block, 0, s, g, ec, bands, M, mixed, nchunk, theta, B, Bp, coef, plan); break;
   switch (nd) {
     GWL_SETUP(1)
     GWL_SETUP(2)
@@ -65,7 +86,7 @@ constexpr int EPG_WAVES = 4;
 template <int ND>
 __global__ __launch_bounds__(EPG_WAVES * WAVE) void k_epilogue_grad(EventGeom g, const EventConst* __restrict__ ec,
                                                                     const double* __restrict__ theta, int64_t B,
-                                                                    int64_t Bp, int nchunk, bool scaled,
+                                                                    int64_t Bp, int nchunk,
                                                                     const double* __restrict__ part,
                                                                     double* __restrict__ logl,
                                                                     double* __restrict__ grad,
@@ -88,7 +109,6 @@ __global__ __launch_bounds__(EPG_WAVES * WAVE) void k_epilogue_grad(EventGeom g,
   double acc[NZ];
 #pragma unroll
   for (int z = 0; z < NZ; ++z) acc[z] = acc_s[z][lane];
-  if (scaled) apply_gain<ND>(e, acc);
   double th[NPARAM];
 #pragma unroll
   for (int i = 0; i < NPARAM; ++i) th[i] = theta[p * NPARAM + i];
@@ -98,26 +118,25 @@ __global__ __launch_bounds__(EPG_WAVES * WAVE) void k_epilogue_grad(EventGeom g,
     for (int d = 0; d < ND; ++d) e.K[d] = kcum[(int64_t)d * (M + 1) + kc];
   }
   const double nan = __builtin_nan("");
-  const double uref = scaled ? e.uref : 1.0;
 #pragma unroll 1
   for (int j = w; j < NPARAM; j += EPG_WAVES) {
     bool valid;
     double value;
-    const double gj = epilogue_gradient_pass<ND>(acc, th, g, e, uref, j, valid, value);
+    const double gj = epilogue_gradient_pass<ND>(acc, th, g, e, 1.0, j, valid, value);
     grad[p * NPARAM + j] = valid ? gj : nan;
     if (j == 0) logl[p] = valid ? value : nan;
   }
 }
 
-hipError_t launch_epilogue(int nd, bool grad, bool scaled, const EventGeom& g, const EventConst* ec, const double* theta,
+hipError_t launch_epilogue(int nd, bool grad, const EventGeom& g, const EventConst* ec, const double* theta,
                            const double*, int64_t B, int64_t Bp, int nchunk, const double* part, double* logl,
                            double* gradout, hipStream_t s, const double* fgrid, const double* kcum, int64_t M) {
   if (!grad) return hipErrorInvalidValue;  // the value's epilogue runs in the evaluation kernel
   dim3 grid((unsigned)((B + WAVE - 1) / WAVE));
 #define GWL_EPI(N)                                                                                                  \
   case N:                                                                                                           \
-    hipLaunchKernelGGL(k_epilogue_grad<N>, grid, dim3(EPG_WAVES * WAVE), 0, s, g, ec, theta, B, Bp, nchunk, scaled, \
-                       part, logl, gradout, fgrid, kcum, M);                                                        \
+    hipLaunchKernelGGL(k_epilogue_grad<N>, grid, dim3(EPG_WAVES * WAVE), 0, s, g, ec, theta, B, Bp, nchunk, part, \
+                       logl, gradout, fgrid, kcum, M);                                                        \
     break;
   switch (nd) {
     GWL_EPI(1)

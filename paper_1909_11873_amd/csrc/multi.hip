@@ -132,6 +132,8 @@ __global__ __launch_bounds__(BLOCK, (ND <= 3 ? (GRAD && MIXED && !ANYF64 ? 5 : 4
     const int k0 = c * ev.chunk;
     const int k1 = k0 + ev.chunk < ev.M ? k0 + ev.chunk : ev.M;
     double tot[NZ];
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) tot[z] = 0.0;
     double a[NBASIS], T[ND];
     bool f64path = !MIXED;
     if constexpr (MIXED && ANYF64) f64path = ev.f64 != 0;  // wave-uniform (scalar) branch

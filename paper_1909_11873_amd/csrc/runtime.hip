@@ -14,7 +14,9 @@
 #include <vector>
 
 #include "../../include/gwlike.h"
+#include "gwl_bands.h"
 #include "gwl_common.h"
+#include "gwl_device.h"
 #include "gwl_launch.h"
 #include "gwl_runtime.h"
 
@@ -148,9 +150,95 @@ const char* gwl_last_error(void) { return g_err.c_str(); }
 
 const char* gwl_version(void) { return "gwlike 0.1 (gfx950)"; }
 
+}  // extern "C"
+
+namespace gwl {
+
+// bands: whether the event may walk band-limited rows (a relative-binning event's grid tables are
+// replaced by its edges', and the calibrated loop and the ISCO cut-off walk every bin)
+static gwl_status event_create(const double* data, const double* psd, const gwl_detector* dets, int ndet,
+                               const double* fgrid, int64_t M, double df, double gmst, unsigned flags, void* stream,
+                               bool bands, gwl_event* out);
+
+// Band-limited rows of a new event whose grid rows are queued on s: the rows' tables follow the
+// grid's in tab64 and g64 (allocated with room for them).
+struct BandHost {
+  BandHead head;
+  std::vector<BandGen> gen;
+  std::vector<int2> blk;
+  int nblk[2] = {0, 0};
+  int64_t nrows = 0, kvals = 0;
+};
+
+static hipError_t make_bands(gwl_event ev, bool uniform, const BandHost& b, hipStream_t s) {
+  BandGen* gen = nullptr;
+  int2* blk = nullptr;
+  double2* kv = nullptr;
+  hipError_t e = hipMalloc((void**)&ev->bands, sizeof(BandHead));
+  // one scratch allocation: the bands, the workgroups' rows, the kernel values
+  const size_t ng = sizeof(BandGen) * b.gen.size(), nb = sizeof(int2) * b.blk.size();
+  const size_t og = 0, ob = (ng + 255) / 256 * 256, ok = ob + (nb + 255) / 256 * 256;
+  char* scratch = nullptr;
+  if (e == hipSuccess) e = hipMalloc((void**)&scratch, ok + sizeof(double2) * (size_t)(b.kvals + 1));
+  if (e == hipSuccess) {
+    gen = (BandGen*)(scratch + og);
+    blk = (int2*)(scratch + ob);
+    kv = (double2*)(scratch + ok);
+    e = hipMemcpyAsync(ev->bands, &b.head, sizeof(BandHead), hipMemcpyHostToDevice, s);
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(gen, b.gen.data(), ng, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(blk, b.blk.data(), nb, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess)
+    e = launch_bands(ev->ndet, uniform, gen, (int)b.gen.size(), blk, b.nblk, kv, ev->tab64, ev->g64, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (scratch) (void)hipFree(scratch);
+  return e;
+}
+
+// Rows that a point of a black-hole binary near the data's time origin walks (chirp mass ten solar
+// masses, arrival within 0.125 s): what a launch's shape is chosen for.
+static int64_t typical_rows(const BandHead& h, int64_t M) {
+  if (h.ncand == 0) return M;
+  std::vector<int64_t> rows((size_t)h.nseg);
+  for (int s = 0; s < h.nseg; ++s) {
+    rows[s] = h.bins[s];
+    for (int c = h.c0[s]; c < h.c0[s + 1]; ++c) {
+      const BandCand& b = h.cand[c];
+      // -tau(f) at the lowest frequency of the band's rows, from g_0' = -5/3 f^-8/3
+      const double tau = 5.0 / 256.0 * pow(10.0 * kTsun, -5.0 / 3.0) * pow(M_PI, -8.0 / 3.0) * -0.6 * h.gp[b.i0][0];
+      const double lim = BAND_FILL * b.tb;
+      if (0.125 - b.t0 <= lim && b.t0 + 0.125 + tau <= lim) {
+        rows[s] = std::min<int64_t>(rows[s], b.rows);
+        break;
+      }
+    }
+  }
+  int64_t below = 0, best = -1;
+  for (int p = 0; p < h.npanel; ++p) {
+    for (int s = h.npanel; s < h.nseg; ++s)
+      if (h.first[s] == p && (best < 0 || below + rows[s] < best)) best = below + rows[s];
+    below += rows[p];
+  }
+  return best < 0 ? below : std::min(best, below);
+}
+
+}  // namespace gwl
+
+extern "C" {
+
 gwl_status gwl_event_create(const double* data, const double* psd, const gwl_detector* dets, int ndet,
                             const double* fgrid, int64_t M, double df, double gmst, unsigned flags, void* stream,
                             gwl_event* out) {
+  return event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, !(flags & GWL_F_ISCO_CUTOFF), out);
+}
+
+}  // extern "C"
+
+namespace gwl {
+
+static gwl_status event_create(const double* data, const double* psd, const gwl_detector* dets, int ndet,
+                               const double* fgrid, int64_t M, double df, double gmst, unsigned flags, void* stream,
+                               bool bands, gwl_event* out) {
   clear_error();
   if (!out) return fail(GWL_E_INVALID, "out is null");
   *out = nullptr;
@@ -172,16 +260,35 @@ gwl_status gwl_event_create(const double* data, const double* psd, const gwl_det
   for (int d = 0; d < ndet; ++d) ev->dets[d] = dets[d];
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipGetDevice(&ev->device);
+  // the grid on the host: its step, whether the float64 loop may carry detector phasors by a fixed
+  // rotation, and its bands
+  std::vector<double> fh((size_t)M);
+  if (e == hipSuccess) e = hipMemcpyAsync(fh.data(), fgrid, sizeof(double) * M, hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) {
+    gwl_event_destroy(ev);
+    return hip_fail(e, "grid read-back");
+  }
+  double step = 1.0;
+  const bool uniform = grid_is_uniform(fh, step);
+  BandHost bh;
+  bh.head.ncand = 0;
+  if (bands) plan_bands(fh, uniform, step, M + TAB_PAD, bh.head, bh.gen, bh.nrows, bh.kvals);
+  band_blocks(bh.gen, M, bh.blk, bh.nblk);
+  ev->M_loop = bands ? typical_rows(bh.head, M) : M;
+  const int64_t rows = M + TAB_PAD + (bh.nrows > 0 ? bh.nrows + TAB_PAD : 0);
   const int nblk = prep_blocks(M);
   double* blockpart = nullptr;
-  if (e == hipSuccess) e = hipMalloc(&ev->tab64, row64_bytes(ndet) * (M + TAB_PAD));
+  e = hipMalloc(&ev->tab64, row64_bytes(ndet) * rows);
   if (e == hipSuccess) e = hipMalloc(&ev->tab32, row32_bytes(ndet) * (M + TAB_PAD));
   if (e == hipSuccess)
     e = hipMemsetAsync((char*)ev->tab64 + row64_bytes(ndet) * M, 0, row64_bytes(ndet) * TAB_PAD, s);
+  if (e == hipSuccess && bh.nrows > 0)
+    e = hipMemsetAsync((char*)ev->tab64 + row64_bytes(ndet) * (rows - TAB_PAD), 0, row64_bytes(ndet) * TAB_PAD, s);
   if (e == hipSuccess)
     e = hipMemsetAsync((char*)ev->tab32 + row32_bytes(ndet) * M, 0, row32_bytes(ndet) * TAB_PAD, s);
   if (e == hipSuccess) e = hipMalloc((void**)&ev->g32, sizeof(RowGradF32) * M);
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->g64, sizeof(RowGradF64) * M);
+  if (e == hipSuccess) e = hipMalloc((void**)&ev->g64, sizeof(RowGradF64) * (bh.nrows > 0 ? rows : M));
   if (e == hipSuccess) e = hipMalloc((void**)&ev->ec, sizeof(EventConst));
   if (e == hipSuccess) e = hipMalloc((void**)&blockpart, sizeof(double) * prep_scratch_doubles(ndet, M));
   if (e == hipSuccess)
@@ -198,20 +305,14 @@ gwl_status gwl_event_create(const double* data, const double* psd, const gwl_det
     return fail(GWL_E_INVALID, "rejected inputs: every PSD value and frequency must be finite and positive and "
                                "every data value finite");
   }
-  // the grid's step, and whether the float64 loop may carry detector phasors by a fixed rotation
-  {
-    std::vector<double> fh((size_t)M);
-    e = hipMemcpyAsync(fh.data(), fgrid, sizeof(double) * M, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess) {
-      ev->ech.uniform = grid_is_uniform(fh, ev->ech.grid_df) ? 1 : 0;
-      e = hipMemcpyAsync(ev->ec, &ev->ech, sizeof(EventConst), hipMemcpyHostToDevice, s);
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-      gwl_event_destroy(ev);
-      return hip_fail(e, "grid read-back");
-    }
+  ev->ech.uniform = uniform ? 1 : 0;
+  ev->ech.grid_df = step;
+  e = hipMemcpyAsync(ev->ec, &ev->ech, sizeof(EventConst), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess && bh.nrows > 0) e = make_bands(ev, uniform, bh, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) {
+    gwl_event_destroy(ev);
+    return hip_fail(e, "event preparation");
   }
   if (flags & GWL_F_ISCO_CUTOFF) {
     st = isco_tables(ev, fgrid, psd, s);
@@ -223,6 +324,10 @@ gwl_status gwl_event_create(const double* data, const double* psd, const gwl_det
   *out = ev;
   return GWL_OK;
 }
+
+}  // namespace gwl
+
+extern "C" {
 
 // Relative-binning edges on the grid: the bins where floor(dpsi(f) / eps) changes, plus both
 // ends, with dpsi(f) = 2 pi sum_gamma sign(gamma) (f / f_gamma)^gamma over the post-Newtonian
@@ -260,7 +365,7 @@ gwl_status gwl_event_create_rb(const double* data, const double* psd, const gwl_
   if (flags & GWL_F_ISCO_CUTOFF)
     return fail(GWL_E_UNSUPPORTED, "the ISCO cut-off is not available with relative binning");
   gwl_event ev = nullptr;
-  gwl_status st = gwl_event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, &ev);
+  gwl_status st = event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, false, &ev);
   if (st != GWL_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   // grid on the host, edges
@@ -284,7 +389,7 @@ gwl_status gwl_event_create_rb(const double* data, const double* psd, const gwl_
   e = hipMalloc((void**)&th, sizeof(double) * NPARAM);
   if (e == hipSuccess) e = hipMalloc((void**)&coef, sizeof(double) * NCOEF * WAVE);
   if (e == hipSuccess) e = hipMemcpyAsync(th, theta_fid, sizeof(double) * NPARAM, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = launch_setup(nd, ev->geom, nullptr, false, th, 1, WAVE, coef, s);
+  if (e == hipSuccess) e = launch_setup(nd, ev->geom, nullptr, th, 1, WAVE, coef, s);
   if (e == hipSuccess)
     e = hipMemcpyAsync(hcoef.data(), coef, sizeof(double) * NCOEF * WAVE, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -341,6 +446,7 @@ gwl_status gwl_event_create_rb(const double* data, const double* psd, const gwl_
   ev->g64 = g64;
   ev->M_full = ev->M;
   ev->M = nedge;
+  ev->M_loop = nedge;
   ev->rb_idx = idx;
   *out = ev;
   return GWL_OK;
@@ -495,7 +601,7 @@ gwl_status gwl_event_create_cal(const double* data, const double* psd, const gwl
   if (flags & GWL_F_ISCO_CUTOFF)
     return fail(GWL_E_UNSUPPORTED, "the ISCO cut-off is not available with the calibration model");
   gwl_event ev = nullptr;
-  gwl_status st = gwl_event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, &ev);
+  gwl_status st = event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, false, &ev);
   if (st != GWL_OK) return st;
   std::vector<double> fh, ph;
   st = read_grid(fgrid, psd, ndet, M, (hipStream_t)stream, fh, ph);
@@ -550,6 +656,7 @@ gwl_status gwl_event_destroy(gwl_event ev) {
   if (ev->tab32) (void)hipFree(ev->tab32);
   if (ev->g32) (void)hipFree(ev->g32);
   if (ev->g64) (void)hipFree(ev->g64);
+  if (ev->bands) (void)hipFree(ev->bands);
   if (ev->fgrid) (void)hipFree(ev->fgrid);
   if (ev->kcum) (void)hipFree(ev->kcum);
   if (ev->ec) (void)hipFree(ev->ec);
@@ -668,13 +775,13 @@ gwl_status gwl_logl_batch_live(gwl_event ev, const double* theta, int64_t B, con
   if (st != GWL_OK) return st;
   const bool mixed = use_mixed(ev, prec);
   // the shape for B, with at least enough workgroups per point group that a quarter of the point
-  // groups still give every CU two workgroups (chunks of at least 32 bins): a partly live batch
+  // groups still give every CU two workgroups (chunks of at least 16 rows): a partly live batch
   // then still fills the chip. The G workgroup sums go to the separate epilogue kernel (the
   // set-up in either kernel): at these workgroup counts the last-arriver's device-scope fences
   // cost more than the second launch (on c1 shapes with 8192 points, 240 against 196 us)
   LoopShape sh = choose_shape(ev, B, mixed, false);
   const int64_t want = (4 * 2 * 256 + sh.npg - 1) / sh.npg;
-  const int64_t gcap = std::max<int64_t>(1, ev->M / (32 * (int64_t)sh.W));
+  const int64_t gcap = std::max<int64_t>(1, ev->M_loop / (16 * (int64_t)sh.W));
   const int G = (int)std::min<int64_t>(std::max<int64_t>(sh.G, want), std::max<int64_t>(gcap, sh.G));
   sh = make_shape(B, ev->M, sh.W, G, sh.setup, 1);
   return run_logl(ev, theta, B, mixed, false, sh, logl, nullptr, (hipStream_t)stream, live);
@@ -739,7 +846,7 @@ gwl_status gwl_waveform(const double* theta, int64_t B, const gwl_detector* dets
   double* coef = nullptr;
   hipError_t e = hipMallocAsync((void**)&coef, sizeof(double) * NCOEF * (size_t)Bp, s);
   if (e != hipSuccess) return hip_fail(e, "workspace");
-  e = launch_setup(ndet, g, nullptr, false, theta, B, Bp, coef, s);
+  e = launch_setup(ndet, g, nullptr, theta, B, Bp, coef, s);
   if (e == hipSuccess) e = launch_waveform(ndet, g, coef, B, Bp, fgrid, M, out, s);
   hipError_t e2 = hipFreeAsync(coef, s);
   if (e != hipSuccess) return hip_fail(e, "waveform launch");
@@ -763,7 +870,8 @@ static bool coef_in_workspace(const LoopShape& sh, bool grad) { return !sh.setup
 size_t workspace_bytes(int64_t Bp, const LoopShape& sh, int nd, bool grad) {
   const size_t coef = coef_in_workspace(sh, grad) ? (size_t)NCOEF * Bp : 0;
   const size_t part = (grad || sh.G > 1) ? (size_t)sh.G * nz_of(nd, grad) * Bp : 0;
-  return sizeof(double) * (coef + part);
+  const size_t plan = sh.setup ? 0 : sizeof(int) * PLAN_INTS * (size_t)(Bp / WAVE);
+  return sizeof(double) * (coef + part) + plan;
 }
 
 size_t workspace_counters(const LoopShape& sh, bool grad) {
@@ -883,21 +991,25 @@ hipError_t enqueue_logl(gwl_event ev, const double* theta, int64_t B, bool mixed
   const bool with_coef = coef_in_workspace(sh, grad);
   double* coef = with_coef ? ws : nullptr;
   double* part = (grad || sh.G > 1) ? ws + (with_coef ? (size_t)NCOEF * Bp : 0) : nullptr;
+  const size_t npart = (grad || sh.G > 1) ? (size_t)sh.G * nz_of(ev->ndet, grad) * Bp : 0;
+  int* plan = sh.setup ? nullptr : (int*)(ws + (with_coef ? (size_t)NCOEF * Bp : 0) + npart);
+  const BandHead* bands = sh.chunk > kBandMinChunk ? ev->bands : nullptr;
   hipError_t e = hipSuccess;
-  if (!sh.setup) e = launch_setup(ev->ndet, ev->geom, ev->ec, mixed, theta, B, Bp, coef, s);
+  if (!sh.setup)
+    e = launch_setup(ev->ndet, ev->geom, ev->ec, theta, B, Bp, coef, s, bands, ev->M, mixed, sh.nchunk, plan);
   hipEvent_t pa = nullptr, pb = nullptr;
   const bool prof = e == hipSuccess && prof_begin(s, pa, pb);
-  if (e == hipSuccess)
-    e = launch_eval(ev->ndet, mixed, grad, ev->ech.uniform != 0, mixed ? ev->tab32 : ev->tab64, ev->g64, theta,
-                    ev->geom, ev->ec, coef, B, Bp, ev->M, sh, part, cnt, logl, ev->fgrid, ev->kcum, live, s);
+  const EvalArgs x = {ev->tab64, ev->tab32, ev->g64, theta, &ev->geom, ev->ec, bands, plan, coef, B, Bp, ev->M,
+                      part, cnt, logl, ev->fgrid, ev->kcum, live};
+  if (e == hipSuccess) e = launch_eval(ev->ndet, mixed, grad, ev->ech.uniform != 0, x, sh, s);
   // the value's reduction over the G workgroups in its own kernel (timed with the evaluation)
   if (e == hipSuccess && !grad && sh.G > 1 && sh.sepepi)
-    e = launch_value_epilogue(ev->ndet, mixed, ev->ec, theta, coef, B, Bp, sh.G, part, logl, ev->fgrid, ev->kcum,
-                              ev->M, live, s);
+    e = launch_value_epilogue(ev->ndet, ev->ec, theta, coef, B, Bp, sh.G, part, logl, ev->fgrid, ev->kcum, ev->M, live,
+                              s);
   if (prof) prof_end(s, pa, pb);
   if (e == hipSuccess && grad)
-    e = launch_epilogue(ev->ndet, true, mixed, ev->geom, ev->ec, theta, coef, B, Bp, sh.G, part, logl, gradout, s,
-                        ev->fgrid, ev->kcum, ev->M);
+    e = launch_epilogue(ev->ndet, true, ev->geom, ev->ec, theta, coef, B, Bp, sh.G, part, logl, gradout, s, ev->fgrid,
+                        ev->kcum, ev->M);
   return e;
 }
 

@@ -135,35 +135,46 @@ bool save_cache(const char* path) {
   return true;
 }
 
-// Rows of P >= 11 values: a fixed, valid parameter point with a small per-point variation, then
-// zeros (calibration node values); the cost of the evaluation does not depend on the values.
+// Rows of P >= 11 values: valid parameter points spread over chirp masses of 10 to 60, arrival
+// times within 0.1 s and the sky (a group's rows depend on its shortest mass and its times), then
+// zeros (calibration node values).
 __global__ void k_fill_theta(double* theta, int64_t B, int P) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= B) return;
   const double row[NPARAM] = {30.0, 0.8, 0.1, -0.2, 400.0, 2.0, -0.5, 0.6, 1.0, 0.7, 0.0};
   for (int i = 0; i < NPARAM; ++i) theta[p * P + i] = row[i];
   for (int i = NPARAM; i < P; ++i) theta[p * P + i] = 0.0;
-  theta[p * P + 0] += 1e-6 * (double)(p % 1024);
+  const double x = 0.6180339887498949 * (double)(p % 4096), y = 0.7548776662466927 * (double)(p % 4096);
+  theta[p * P + 0] = 10.0 + 50.0 * (x - floor(x));
+  theta[p * P + 5] = 6.2 * (y - floor(y));
+  theta[p * P + 10] = 0.2 * (x + y - floor(x + y)) - 0.1;
 }
 
 }  // namespace
 
 namespace gwl {
 
-LoopShape heuristic_shape(int64_t B, int64_t M, bool mixed, bool grad) {
-  // eight wavefronts per workgroup, enough workgroups for about eight wavefronts per SIMD (1024
-  // SIMDs) while chunks keep at least 32 bins, and the set-up inside the kernel when the whole
-  // launch is small (a set-up launch and its gap are then a large part of the call)
+// Shapes without a measured entry. `rows` is what a typical group walks (its bins, or its band-limited
+// rows). About 4,096 wavefronts (four per SIMD; more measured no faster, the float64 loop's registers
+// allow five), 16 per workgroup (8 for the gradient, and for batches that fill the chip by themselves),
+// while a wavefront keeps 6 rows (12 for the gradient, whose partial sums are three times as many)
+// and a point's sums come from at most 32 workgroups. The set-up runs in the kernel, whose later
+// workgroups then overlap it, and the sums of several workgroups go to the second kernel: both were the
+// faster form at every size tried from 1 to 65,536 points (on 1 to 3 detectors, 4 to 128 s; for
+// instance 16,384 points at three detectors and 8 s 117 us against 123 with the set-up apart).
+// Where that many wavefronts leave so few bins each that the bins are walked directly
+// (kBandMinChunk), the split is chosen for the bins, at least 8 a wavefront.
+LoopShape heuristic_shape(int64_t B, int64_t M, int64_t rows, bool mixed, bool grad) {
   (void)mixed;
-  (void)grad;
-  const int W = 8;
   const int64_t npg = (B + WAVE - 1) / WAVE;
-  int64_t G = (8192 + npg * W - 1) / (npg * W);
-  const int64_t gmax = std::max<int64_t>(1, (M + 32 * W - 1) / (32 * W));
-  if (G > gmax) G = gmax;
-  if (G < 1) G = 1;
-  const int setup = npg * G <= 512 ? 1 : 0;
-  return make_shape(B, M, W, (int)G, setup);
+  const int W = grad || npg >= 512 ? 8 : 16;
+  const int64_t fill = std::min<int64_t>(32, (4096 + npg * W - 1) / (npg * W));
+  auto split = [&](int64_t n, int64_t least) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(fill, (n + least * W - 1) / (least * W)));
+  };
+  const LoopShape direct = make_shape(B, M, W, split(M, 8), 1, 1);
+  if (rows < M && direct.chunk <= kBandMinChunk) return direct;
+  return make_shape(B, M, W, split(rows, grad ? 12 : 6), 1, 1);
 }
 
 int heuristic_nchunk(int64_t B, int64_t M) {
@@ -203,7 +214,7 @@ LoopShape choose_shape(const gwl_event_s* ev, int64_t B, bool mixed, bool grad) 
     if (it != g_cache.end())
       return make_shape(B, ev->M, it->second.W, it->second.G, it->second.setup, it->second.sepepi);
   }
-  return heuristic_shape(B, ev->M, mixed, grad);
+  return heuristic_shape(B, ev->M, ev->M_loop, mixed, grad);
 }
 
 }  // namespace gwl
@@ -230,7 +241,7 @@ gwl_status gwl_autotune(const char* cache_path, gwl_event ev, int64_t B, gwl_pre
   // candidate shapes: W in {4, 5, 8, 10, 16} wavefronts per workgroup, G in powers of two up to
   // chunks of 16 bins (and the heuristic's G), the set-up in or out of the kernel; launches of
   // more than 64 wavefronts per SIMD are skipped
-  const LoopShape h = heuristic_shape(B, ev->M, mixed, grad);
+  const LoopShape h = heuristic_shape(B, ev->M, ev->M_loop, mixed, grad);
   const int64_t npg = (B + WAVE - 1) / WAVE;
   std::vector<LoopShape> shapes;
   auto add1 = [&](int W, int G, int setup, int sepepi) {

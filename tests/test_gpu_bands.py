@@ -1,0 +1,132 @@
+"""Band-limited rows against the sum over every bin.
+
+A group of 64 points whose chirps stay inside a band of arrival times walks a few hundred
+band-limited rows in place of the grid's bins; a launch whose chunks hold at most 20 bins walks the
+bins. Two launch layouts of the same event therefore compare the two sums directly. The rows
+reproduce each bin's phasor to about 1e-14 (1e-13 in the worst chirp at a panel's edge), so a point's
+values differ by at most 1e-13 sum_k |A Q u_k| <= 1e-13 |h| |d| (norms of signal and data in the noise-weighted
+inner product), and its gradient by the same share of its scale.
+"""
+import json
+import math
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import gw_oracle as o
+from paper_1909_11873_amd import gwlike as gw
+from paper_1909_11873_amd import synth
+from tests.helpers import event_inputs, scaled_grad_error
+
+DEV = torch.device("cuda:0")
+CACHE = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1909_11873_amd",
+                     "tuning_gfx950.json")
+
+
+@pytest.mark.parametrize("sigma", [1.25, 1.4, 1.6, 2.0, 2.5, 3.0])
+def test_windowed_sinc_reproduces_tones_of_its_band(sigma):
+    """The rows' kernel, from its definition: a tone of any time within the band, anywhere between two
+    rows, to 2e-14; a tone beyond the band's far side (the first alias) is not reproduced."""
+    w = math.ceil(292.0 / (2.285 * 2.0 * math.pi * (1.0 - 1.0 / sigma)))
+    beta = 0.98 * math.pi * 0.5 * w * (1.0 - 1.0 / sigma)
+    x = np.linspace(0.0, 1.0, 33)[:, None] - np.arange(-(w // 2) - 1, w // 2 + 3)[None, :]
+    r2 = 1.0 - (2.0 * x / w) ** 2
+    k = np.where(r2 > 0, np.sinc(x) * np.exp(beta * (np.sqrt(np.maximum(r2, 0.0)) - 1.0)), 0.0)
+    for nu in np.linspace(-0.5 / sigma, 0.5 / sigma, 41):       # cycles per row
+        got = k @ np.exp(-2j * np.pi * nu * np.arange(-(w // 2) - 1, w // 2 + 3))
+        assert np.abs(got - np.exp(-2j * np.pi * nu * np.linspace(0.0, 1.0, 33))).max() <= 2e-14
+    alias = k @ np.exp(-2j * np.pi * (1.0 - 0.5 / sigma) * np.arange(-(w // 2) - 1, w // 2 + 3))
+    assert np.abs(alias - np.exp(-2j * np.pi * (1.0 - 0.5 / sigma) * np.linspace(0.0, 1.0, 33))).max() > 0.5
+
+
+def _layout(path, nd, M, prec, grad, batch, waves, groups, setup):
+    npg = (batch + 63) // 64
+    entry = {"ndet": nd, "mixed": int(prec == "mixed"), "grad": int(grad), "M": M,
+             "npg_bucket": 1 << (npg - 1).bit_length(), "waves": waves, "groups": groups, "setup": setup,
+             "sepepi": 0, "ms": 1.0}
+    with open(path, "w") as fh:
+        fh.write('{"arch": "gfx950", "entries": [\n  ' + json.dumps(entry) + "\n]}\n")
+    gw.autotune_load(path)
+
+
+def _points(kind, n, seed):
+    rng = np.random.default_rng(seed)
+    th = synth.prior_draw(rng, n, mc_range=(1.0, 1.5) if kind == "light" else (10.0, 60.0))
+    if kind == "late":                    # arrival times spread beyond every band around zero
+        th[:, 10] = rng.uniform(-6.0, 6.0, n)
+    if kind == "wide":                    # most groups in the widest bands
+        th[:, 10] = rng.uniform(-0.3, 0.3, n)
+    if kind == "narrow":                  # a converged sampler's batch
+        th[:, 10] = rng.uniform(-1e-3, 1e-3, n)
+    if kind == "invalid":                 # NaN rows and a far outlier among ordinary points
+        th[3, 1] = 1.5
+        th[70, 10] = 1e9
+        th[130:194, 1] = -1.0             # a whole group
+    return th
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["prior", "late", "wide", "narrow", "light", "invalid"])
+@pytest.mark.parametrize("nd,duration,f_lo,f_hi,uniform", [
+    (3, 8.0, 20.0, 1024.0, True), (2, 17.0, 20.0, 611.0, True), (1, 4.0, 11.0, 1024.0, True),
+    (3, 8.0, 20.0, 400.0, False), (2, 32.0, 20.0, 500.0, True)])
+def test_rows_match_every_bin(kind, nd, duration, f_lo, f_hi, uniform, tmp_path):
+    df = 1.0 / duration
+    f = synth.freq_grid(f_lo, f_hi, df)
+    if not uniform:                       # increasing, with steps between 0.6 and 1.4 of the mean
+        f = f + 0.2 * df * np.sin(np.arange(len(f)) * 1.7)
+    M = len(f)
+    psd = np.stack([synth.psd_fit(f)] * nd)
+    dets = np.array([synth.detector_rad(n) for n in ("D1", "D2", "D3")[:nd]])
+    data = np.stack([synth.noise(900 + i, psd[i], df) for i in range(nd)]) + o.strain_all(synth.THETA0_BBH, dets, f).numpy()
+    th = _points(kind, 257, 5)
+    if kind != "invalid":
+        th[0] = synth.THETA0_BBH
+    t = torch.tensor(th, device=DEV)
+    ev = gw.Event(torch.tensor(data, device=DEV), torch.tensor(psd, device=DEV), dets, torch.tensor(f, device=DEV), df)
+    path = str(tmp_path / "layout.json")
+    groups = -(-M // (16 * 20))           # 16 wavefronts x groups: chunks of at most 20 bins
+    dn = math.sqrt(sum(float((4 * df * np.abs(d) ** 2 / s).sum()) for d, s in zip(data, psd)))
+    try:
+        for prec in ("fp64", "mixed"):
+            for grad in (False, True):
+                got = []
+                for waves, grp, setup in ((16, groups, 0), (4, 1, 0), (16, 3, 1), (1, 2, 1)):
+                    _layout(path, nd, M, prec, grad, len(th), waves, grp, setup)
+                    v, g = gw.logl_grad(t, ev, prec) if grad else (gw.logl(t, ev, prec), torch.zeros(len(th), 11))
+                    got.append((v.cpu().numpy(), g.cpu().numpy()))
+                bins, gbins = got[0]
+                ok = np.isfinite(bins)
+                beyond = 1e9 * f[-1] >= 2.0 ** 39   # the outlier's phase: outside the range that is evaluated
+                assert ok.sum() == (257 - 65 - beyond if kind == "invalid" else 257)
+                # |h|^2 <= 2 (<d|h> - logL) <= ..., bounded from logL = <d|h> - |h|^2 / 2 and <d|h> <= |d| |h|
+                hn = dn + np.sqrt(np.maximum(dn ** 2 - 2.0 * bins[ok], 0.0))
+                tol = 1e-13 * hn * dn + 1e-9 if prec == "fp64" else 1e-3
+                for v, g in got[1:]:
+                    assert np.array_equal(np.isfinite(v), ok)
+                    err = np.abs(v[ok] - bins[ok])
+                    assert (err <= tol).all(), (prec, grad, err.max())
+                    if grad:
+                        e = scaled_grad_error(g[ok], gbins[ok])
+                        assert e.max() <= (2e-9 if prec == "fp64" else 1e-3), (prec, e.max())
+    finally:
+        ev.close()
+        gw.autotune_load(CACHE)
+
+
+@pytest.mark.gpu
+def test_grids_without_bands_keep_their_bins():
+    """Grids that are not increasing, or too short to have bands, give the oracle's values as before."""
+    for f_hi, flip in ((300.0, True), (30.0, False)):
+        spec, f, psd, data, dets = event_inputs(1, f_hi=f_hi)
+        if flip:                          # the same bins in descending order
+            f, psd, data = f[::-1].copy(), psd[:, ::-1].copy(), data[:, ::-1].copy()
+        th = synth.theta_batch(spec, 5)
+        ev = gw.Event(torch.tensor(data, device=DEV), torch.tensor(psd, device=DEV), dets, torch.tensor(f, device=DEV),
+                      spec.df)
+        ref = o.logl(th, data, psd, dets, f, spec.df).numpy()
+        for prec, tol in (("fp64", 1e-6), ("mixed", 1e-3)):
+            assert np.abs(gw.logl(torch.tensor(th, device=DEV), ev, prec).cpu().numpy() - ref).max() <= tol
+        ev.close()
