@@ -39,44 +39,12 @@ __device__ inline bool rows_in_range(const double* a, const double* T, const Eve
   return fma(tmax, ec->fmax, bound) < PHASE_LIMIT;
 }
 
-// Set-up rows (layout CO_*) of one point; false if the point is outside the model's domain or,
-// given the event (ec), its phase could exceed PHASE_LIMIT cycles somewhere on the grid.
-// With `scaled` (float32 tables) the event's (gain_r, gain_i) undoes the mean gain of the bin
-// loop's phasor (1 for float64 tables). It enters the adjoint projection factors
-// c_det = E G Q_det, E = exp(-2 pi i c0), through which the adjoint bin loop keeps only the one
-// real part of each moment that the gradient uses. A relative-binning event's fiducial phase
-// coefficients and shifts are subtracted from the bin loop's rows (ec may be null: no offsets).
-template <int ND>
-__device__ inline bool setup_rows(const double (&th)[NPARAM], const EventGeom& g, const EventConst* ec, bool scaled,
-                                  double (&rows)[NCOEF]) {
-  const double gr = (scaled && ec) ? ec->gain_r : 1.0, gi = (scaled && ec) ? ec->gain_i : 0.0;
-  PointModel<double> pm;
-  point_model<double, ND>(th, g, pm);
-#pragma unroll
-  for (int j = 0; j < NCOEF; ++j) rows[j] = 0.0;
-#pragma unroll
-  for (int m = 0; m < NBASIS; ++m) rows[CO_A + m] = pm.a[m] - (ec ? ec->fa[m] : 0.0);
-  double egr, egi;
-  phase_gain(pm.c0, gr, gi, egr, egi);
-#pragma unroll
-  for (int d = 0; d < ND; ++d) {
-    rows[CO_T + d] = pm.tdet[d] - (ec ? ec->fT[d] : 0.0);
-    rows[CO_QR + d] = pm.qr[d];
-    rows[CO_QI + d] = pm.qi[d];
-    adjoint_factor(egr, egi, pm.qr[d], pm.qi[d], rows[CO_CR + d], rows[CO_CI + d]);
-  }
-  rows[CO_C0] = pm.c0;
-  rows[CO_AMP] = pm.amp;
-  const bool in_range = rows_in_range<ND>(&rows[CO_A], &rows[CO_T], ec);
-  return pm.valid && in_range;
-}
-
 // The in-kernel set-up in two halves, each writing its rows of one point into the LDS rows
 // [NCOEF][WAVE] (lane = point), so that two wavefronts can run them at once. The intrinsic half
 // writes CO_A (less the fiducial's), CO_C0 and CO_AMP, NaN for a point outside the model's
 // domain; the extrinsic half writes CO_T (less the fiducial's), CO_QR and CO_QI. The phase
 // range check and the adjoint factors c_det then come from these rows (rows_in_range,
-// phase_gain), with the same arithmetic as setup_rows.
+// phase_gain).
 __device__ inline void setup_lds_intrinsic(const double (&th)[NPARAM], const EventConst* ec, double* rows_s, int lane) {
   PointModel<double> pm;
   point_intrinsic<double>(th, pm);
@@ -222,16 +190,6 @@ __device__ inline double epilogue_gradient_pass(const double (&acc)[nz_of(ND, tr
   value = tot.v;
   valid = pm.valid;
   return tot.d[0] + kTwoPi * uref * pm.amp.v * sm;
-}
-
-template <int ND>
-__device__ inline double epilogue_gradient(const double (&acc)[nz_of(ND, true)], const double (&th)[NPARAM],
-                                           const EventGeom& g, const EventConst& ec, double uref, bool& valid,
-                                           double (&gout)[NPARAM]) {
-  double value = 0.0;
-#pragma unroll 1
-  for (int j = 0; j < NPARAM; ++j) gout[j] = epilogue_gradient_pass<ND>(acc, th, g, ec, uref, j, valid, value);
-  return value;
 }
 
 }  // namespace gwl

@@ -13,8 +13,11 @@ namespace gwl {
 // and wavefront 1 the extrinsic half into the LDS rows rows_s [NCOEF][WAVE] (theta rows of P
 // columns, the first 11 the signal parameters); after a barrier, setup_rows_write has each
 // wavefront write half of the rows [NCOEF][Bp], with the phase-range check and the adjoint
-// factors taken from the LDS rows as setup_rows takes them, so the rows equal setup_rows' bit
-// for bit; every row is NaN for a point outside the model's domain or range, or with !ok.
+// factors taken from the LDS rows; every row is NaN for a point outside the model's domain or
+// range, or with !ok. With `scaled` (float32 tables) the event's (gain_r, gain_i) undoes the mean gain
+// of the bin loop's phasor in the adjoint projection factors c_det = E G Q_det, through which
+// the adjoint loop keeps only the one real part of each moment that the gradient uses. A
+// relative-binning event's fiducial phase coefficients and shifts are subtracted (ec may be null).
 template <int ND>
 __device__ inline void setup_halves(int w, int lane, const double* __restrict__ theta_row, const EventGeom& g,
                                     const EventConst* ec, double* rows_s) {

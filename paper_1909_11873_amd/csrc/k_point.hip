@@ -52,6 +52,7 @@ __global__ __launch_bounds__(SETUP_WAVES_BANDS * WAVE) void k_setup(EventGeom g,
   __syncthreads();
   if (w != 0) return;
   band_plan(bh, M, mixed, nchunk, lane, bands_s);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
   plan[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }
 

@@ -2,13 +2,15 @@
 // HIP graph (the batch axis of the paper's parallel prior sampling, section 3, extended over
 // events).
 //
-// Work items are (event, 64-point group, bin chunk) with one chunk length for all events, so
-// items cost about the same; events are queued shortest first, items of an event chunk-major.
-// Every wavefront of the persistent kernel takes items from an atomic counter until the queue
-// is empty; each item writes its own partial sums, which a multi-event epilogue launch adds in
-// chunk order (deterministic). A per-event counter stamps the device clock when the last item
-// of the event completes. The graph is: reset (counters and start stamp, by a kernel) ->
-// per-point set-up for all events -> persistent bin loop -> epilogue for all events.
+// Work items are (64-point group of an event, chunk of its plan's rows). The set-up of a group makes
+// its plan (gwl_bands.h: the band-limited rows, or the bins, that its points walk), cuts it into chunks of
+// about one length for all events, so that items cost about the same, and appends them to the
+// queue; events are queued shortest first. Every wavefront of the persistent kernel takes items
+// from an atomic counter until the queue is empty; each item writes its own partial sums, which a
+// multi-event epilogue launch adds in chunk order (deterministic, whatever the queue's order). A
+// per-event counter stamps the device clock when the last item of the event completes. The graph
+// is: reset (counters and start stamp, by a kernel) -> per-point set-up and queue for all events ->
+// persistent loop -> epilogue for all events.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -19,30 +21,39 @@
 #include <numeric>
 #include <vector>
 
+#include "gwl_bands.h"
 #include "gwl_bins.h"
 #include "gwl_epilogue.h"
 #include "gwl_runtime.h"
+#include "gwl_setup.h"
 
 using namespace gwl;
 
 namespace gwl {
 
-constexpr int MULTI_PT_BLOCK = 128;
+constexpr int MULTI_SETUP_WAVES = 4;  // wavefronts per group of 64 points in the set-up
+constexpr int MULTI_EPI_BLOCK = 256;  // points per workgroup of the value's epilogue
+// bins per chunk of a group that walks its bins: the length that the 64-event workload's tuning found
+// when every group did
+constexpr int MULTI_BIN_CHUNK = 1536;
 
 struct MultiEvDev {
-  const void* tab;         // RowMixed<ND> or RowF64<ND> [M]
-  const void* gtab;        // RowGradF64 [M] (adjoint basis, both precisions)
+  const void* tab64;       // RowF64<ND>: bins (or edges), then the band-limited rows
+  const void* tab32;       // RowMixed<ND> [M]
+  const void* gtab;        // RowGradF64 (adjoint basis, both precisions)
   const EventConst* ec;
+  const BandHead* bands;   // null: every bin
   double* coef;            // [NCOEF][Bp]
-  double* part;            // [nchunk][NZ][Bp]
+  double* part;            // [nslot][NZ][Bp]
   int64_t Bp;
-  int M, chunk, nchunk, npg;
-  int item0, nitems;       // first item in the queue, item count
-  int f64;                 // 1: float64 tables and loop (every event of a float64 plan, and the
+  int M, nslot, npg;       // nslot: most chunks that a group may have
+  int f64;                 // 1: float64 loop on every row (every event of a float64 plan, and the
                            // relative-binning events of a mixed one)
-  int rot;                 // 1: the float64 loop on a uniform grid rotates the detectors' phasors
-  double step;             // the uniform grid's spacing (rot)
+  int rot;                 // 1: a uniform grid: the float64 loop rotates the detectors' phasors
+  double step;             // the grid's spacing
 };
+
+constexpr int PLAN_CHUNKS = PLAN_INTS - 1;  // a group's plan also holds its number of chunks
 
 struct MultiIODev {
   const double* theta;     // [B][11]
@@ -53,21 +64,22 @@ struct MultiIODev {
 
 struct MultiCtl {
   unsigned int next;       // queue head
-  unsigned int pad;
+  unsigned int total;      // items in the queue
   unsigned long long t0;   // device clock at the start of the launch
   unsigned long long tend; // device clock at the end of the epilogue
 };
 
 __global__ void k_multi_reset(MultiCtl* __restrict__ ctl, unsigned int* __restrict__ done,
-                              unsigned long long* __restrict__ tev, int E) {
+                              unsigned int* __restrict__ items_of, unsigned long long* __restrict__ tev, int E) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < E) {
     done[i] = 0u;
+    items_of[i] = 0u;
     tev[i] = 0ull;
   }
   if (i == 0) {
     ctl->next = 0u;
-    ctl->pad = 0u;
+    ctl->total = 0u;
     ctl->t0 = wall_clock64();
     ctl->tend = 0ull;
   }
@@ -76,40 +88,79 @@ __global__ void k_multi_reset(MultiCtl* __restrict__ ctl, unsigned int* __restri
 // device clock stamp (a calibrated event's completion)
 __global__ void k_multi_stamp(unsigned long long* __restrict__ t) { *t = wall_clock64(); }
 
+// Set-up rows and plan of one group per workgroup (as k_setup), and the group's items: chunks of
+// about `chunk` rows, all appended at once. The items' order in the queue may differ from run to run
+// with the workgroups' timing; their results do not.
 template <int ND>
-__global__ __launch_bounds__(MULTI_PT_BLOCK) void k_multi_setup(const MultiEvDev* __restrict__ evs,
-                                                                 const EventGeom* __restrict__ geoms,
-                                                                 const MultiIODev* __restrict__ io,
-                                                                 const int* __restrict__ blk_ev,
-                                                                 const int* __restrict__ blk_p0) {
-  const int e = blk_ev[blockIdx.x];
-  const int64_t p = (int64_t)blk_p0[blockIdx.x] + threadIdx.x;
-  const MultiEvDev ev = evs[e];
-  const MultiIODev o = io[e];
-  if (p >= ev.Bp) return;
+__global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
+    const MultiEvDev* __restrict__ evs, const EventGeom* __restrict__ geoms, const MultiIODev* __restrict__ io,
+    const int2* __restrict__ grp, int mixed, int chunk, MultiCtl* __restrict__ ctl, unsigned int* __restrict__ items_of,
+    int2* __restrict__ items, int* __restrict__ plans) {
+  __shared__ double rows_s[NCOEF * WAVE];
+  __shared__ BandLds bands_s;
+  __shared__ int base_s;
+  const int2 gp = grp[blockIdx.x];
+  const MultiEvDev ev = evs[gp.x];
+  const MultiIODev o = io[gp.x];
+  const EventGeom geo = geoms[gp.x];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  const int lane = (int)(threadIdx.x % WAVE);
+  const int64_t p = (int64_t)gp.y * WAVE + lane;
   const int64_t pc = p < o.B ? p : o.B - 1;
-  double th[NPARAM];
+  if (w < 2) setup_halves<ND>(w, lane, o.theta + pc * NPARAM, geo, ev.ec, rows_s);
+  __syncthreads();
+  if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ev.ec, false, true, ev.coef, ev.Bp, p);
+  if (ev.bands) {
+    double a[NBASIS], T[ND];
 #pragma unroll
-  for (int i = 0; i < NPARAM; ++i) th[i] = o.theta[pc * NPARAM + i];
-  double rows[NCOEF];
-  const bool valid = setup_rows<ND>(th, geoms[e], ev.ec, ev.f64 == 0, rows);
-  const double nan = __builtin_nan("");
+    for (int m = 0; m < NBASIS; ++m) a[m] = rows_s[(CO_A + m) * WAVE + lane];
 #pragma unroll
-  for (int j = 0; j < NCOEF; ++j) ev.coef[j * ev.Bp + p] = valid ? rows[j] : nan;
+    for (int d = 0; d < ND; ++d) T[d] = rows_s[(CO_T + d) * WAVE + lane];
+    if (!rows_in_range<ND>(a, T, ev.ec)) a[0] = __builtin_nan("");
+    band_ranges<ND>(ev.bands, a, T, w, MULTI_SETUP_WAVES, lane, bands_s);
+    __syncthreads();
+    band_hold(ev.bands, w, MULTI_SETUP_WAVES, lane, bands_s);
+    __syncthreads();
+    if (w != 0) return;
+    band_plan(ev.bands, ev.M, mixed && !ev.f64, 1, lane, bands_s);
+  } else {
+    if (w != 0) return;
+    if (lane == 0) {                                   // the bins as one piece
+      bands_s.plan[0] = bands_s.plan[5] = ev.M;
+      bands_s.plan[1] = 1;
+      bands_s.plan[2] = ev.f64;
+      bands_s.plan[4] = 0;
+      bands_s.plan[6] = -1;
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
+  if (lane == 0) {
+    const int rows = bands_s.plan[2] ? bands_s.plan[0] : ev.M;
+    int n = (rows + chunk - 1) / chunk;
+    if (n > ev.nslot) n = ev.nslot;
+    bands_s.plan[3] = (rows + n - 1) / n;
+    bands_s.plan[PLAN_CHUNKS] = n;
+    base_s = (int)atomicAdd(&ctl->total, (unsigned int)n);
+    atomicAdd(&items_of[gp.x], (unsigned int)n);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
+  const int n = bands_s.plan[PLAN_CHUNKS], base = base_s;
+  for (int c = lane; c < n; c += WAVE) items[base + c] = make_int2((int)blockIdx.x, c);
+  plans[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }
 
-// Persistent bin loop: one wavefront per item, items from the shared counter. ANYF64: a mixed
-// plan that also holds float64 (relative-binning) events, which take the float64 loop.
-template <int ND, bool MIXED, bool GRAD, bool ANYF64>
-__global__ __launch_bounds__(BLOCK, (ND <= 3 ? (GRAD && MIXED && !ANYF64 ? 5 : 4) : 3)) void k_multi_bins(
-    const MultiEvDev* __restrict__ evs, int E, int total, const MultiIODev* __restrict__ io,
+// Persistent loop: one wavefront per item, items from the shared counter.
+template <int ND, bool MIXED, bool GRAD>
+__global__ __launch_bounds__(BLOCK, (ND <= 3 ? 4 : 3)) void k_multi_bins(
+    const MultiEvDev* __restrict__ evs, const MultiIODev* __restrict__ io, const int2* __restrict__ grp,
+    const int2* __restrict__ items, const int* __restrict__ plans, const unsigned int* __restrict__ items_of,
     MultiCtl* __restrict__ ctl, unsigned int* __restrict__ done, unsigned long long* __restrict__ tev) {
   constexpr int NZ = nz_of(ND, GRAD);
-  constexpr bool TBL = !MIXED || ANYF64;
-  __shared__ double2 tbl[TBL ? PH_TBL : 1];  // the float64 phasor table
-  if constexpr (TBL) fill_phasor_table(tbl);
+  __shared__ double2 tbl[PH_TBL];  // the float64 phasor table
+  fill_phasor_table(tbl);
   __syncthreads();
   const int lane = threadIdx.x % WAVE;
+  const int total = (int)__builtin_amdgcn_readfirstlane(ctl->total);
   for (;;) {
     // One ticket per wavefront. Every lane takes part in the atomic (lane 0 adds 1, the others
     // 0) and the first lane's old value is read back as a scalar, so the loop is wave-uniform:
@@ -119,84 +170,118 @@ __global__ __launch_bounds__(BLOCK, (ND <= 3 ? (GRAD && MIXED && !ANYF64 ? 5 : 4
     const unsigned int ticket = atomicAdd(&ctl->next, lane == 0 ? 1u : 0u);
     const int it = (int)__builtin_amdgcn_readfirstlane(ticket);
     if (it >= total) break;
-    // event of this item: queue order is event order, item0 increasing
-    int e = 0;
-    while (e + 1 < E && evs[e + 1].item0 <= it) ++e;
+    const int2 item = items[it];
+    const int2 gp = grp[item.x];
+    const int e = gp.x, c = item.y;
     const MultiEvDev ev = evs[e];
+    const int* plan = plans + (int64_t)item.x * PLAN_INTS;
     const int64_t B = io[e].B;
-    const int local = it - ev.item0;
-    const int c = local / ev.npg;
-    const int pg = local - c * ev.npg;
-    const int64_t p = (int64_t)pg * WAVE + lane;
+    const int64_t p = (int64_t)gp.y * WAVE + lane;
     const int64_t pc = p < B ? p : B - 1;
-    const int k0 = c * ev.chunk;
-    const int k1 = k0 + ev.chunk < ev.M ? k0 + ev.chunk : ev.M;
+    const bool f64path = plan[2] != 0;                 // scalar branch
+    const int rows = f64path ? plan[0] : ev.M, q0 = c * plan[3];
+    const int q1 = q0 + plan[3] < rows ? q0 + plan[3] : rows;
     double tot[NZ];
 #pragma unroll
     for (int z = 0; z < NZ; ++z) tot[z] = 0.0;
-    double a[NBASIS], T[ND];
-    bool f64path = !MIXED;
-    if constexpr (MIXED && ANYF64) f64path = ev.f64 != 0;  // wave-uniform (scalar) branch
+    double a[NBASIS], T[ND], crd[ND], cid[ND];
+    load_coef<ND, double>(ev.coef, ev.Bp, pc, GRAD, a, T, crd, cid);
     if (!f64path) {
       if constexpr (MIXED) {
         float cr[ND], ci[ND];
-        load_coef<ND, float>(ev.coef, ev.Bp, pc, GRAD, a, T, cr, ci);
-        bin_loop_mixed<ND, GRAD>((const_as_ptr<RowMixed<ND>>)ev.tab, (const_as_ptr<RowGradF64>)ev.gtab, k0, k1, a,
-                                 T, cr, ci, tot);
+        if constexpr (GRAD) {
+          mixed_factors<ND>(ev.ec, crd, cid, cr, ci);
+        } else {
+#pragma unroll
+          for (int d = 0; d < ND; ++d) cr[d] = ci[d] = 0.0f;
+        }
+        bin_loop_mixed<ND, GRAD>((const_as_ptr<RowMixed<ND>>)ev.tab32, (const_as_ptr<RowGradF64>)ev.gtab, q0, q1, a, T,
+                                 cr, ci, tot);
+        mixed_units<ND, GRAD>(ev.ec, tot);
       }
     } else {
-      if constexpr (TBL) {
-        double cr[ND], ci[ND];
-        load_coef<ND, double>(ev.coef, ev.Bp, pc, GRAD, a, T, cr, ci);
-        to_table_units<ND>(a, T);
-        if (ev.rot)
-          bin_loop_f64_rot<ND, GRAD>((const_as_ptr<RowF64<ND>>)ev.tab, (const_as_ptr<RowGradF64>)ev.gtab, k0, k1, a,
-                                     T, cr, ci, tbl, ev.step, tot);
-        else
-          bin_loop_f64<ND, GRAD>((const_as_ptr<RowF64<ND>>)ev.tab, (const_as_ptr<RowGradF64>)ev.gtab, k0, k1, a, T,
-                                 cr, ci, tbl, tot);
-      }
+      to_table_units<ND>(a, T);
+      for_pieces(
+          ev.bands, ev.step, q0, q1, [&](int i) { return plan[i]; },
+          [&](int ka, int kb, double step) {
+            if (ev.rot)
+              bin_loop_f64_rot<ND, GRAD>((const_as_ptr<RowF64<ND>>)ev.tab64, (const_as_ptr<RowGradF64>)ev.gtab, ka, kb,
+                                         a, T, crd, cid, tbl, step, tot);
+            else
+              bin_loop_f64<ND, GRAD>((const_as_ptr<RowF64<ND>>)ev.tab64, (const_as_ptr<RowGradF64>)ev.gtab, ka, kb, a,
+                                     T, crd, cid, tbl, tot);
+          });
     }
     global_as_ptr<double> part = (global_as_ptr<double>)ev.part;
 #pragma unroll
     for (int z = 0; z < NZ; ++z) part[((int64_t)c * NZ + z) * ev.Bp + p] = tot[z];
     const unsigned int prev = atomicAdd(&done[e], lane == 0 ? 1u : 0u);
     const unsigned int d = __builtin_amdgcn_readfirstlane(prev);
-    if (d + 1u == (unsigned int)ev.nitems && lane == 0) tev[e] = wall_clock64();
+    if (d + 1u == items_of[e] && lane == 0) tev[e] = wall_clock64();
   }
 }
 
-template <int ND, bool GRAD>
-__global__ __launch_bounds__(MULTI_PT_BLOCK) void k_multi_epilogue(const MultiEvDev* __restrict__ evs,
-                                                                    const EventGeom* __restrict__ geoms,
-                                                                    const MultiIODev* __restrict__ io,
-                                                                    const int* __restrict__ blk_ev,
-                                                                    const int* __restrict__ blk_p0,
-                                                                    MultiCtl* __restrict__ ctl) {
-  constexpr int NZ = nz_of(ND, GRAD);
-  const int e = blk_ev[blockIdx.x];
-  const int64_t p = (int64_t)blk_p0[blockIdx.x] + threadIdx.x;
-  const MultiEvDev ev = evs[e];
-  const MultiIODev o = io[e];
-  const bool scaled = ev.f64 == 0;
+// The gradient's epilogue: one workgroup of four wavefronts per group, as k_epilogue_grad. The
+// wavefronts add the group's partial sums over its chunks together, then share the dual-number
+// passes. (With every group walking its bins in up to 163 chunks one lane per point, with all sums
+// of eight chunks in flight, was the faster form; a group now has a handful of chunks.)
+constexpr int MULTI_EPG_WAVES = 4;
+template <int ND>
+__global__ __launch_bounds__(MULTI_EPG_WAVES * WAVE) void k_multi_epilogue_grad(
+    const MultiEvDev* __restrict__ evs, const EventGeom* __restrict__ geoms, const MultiIODev* __restrict__ io,
+    const int2* __restrict__ grp, const int* __restrict__ plans, MultiCtl* __restrict__ ctl) {
+  constexpr int NZ = nz_of(ND, true);
+  __shared__ double acc_s[NZ][WAVE];
+  const int2 gp = grp[blockIdx.x];
+  const MultiEvDev ev = evs[gp.x];
+  const MultiIODev o = io[gp.x];
+  const int n = plans[(int64_t)blockIdx.x * PLAN_INTS + PLAN_CHUNKS];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  const int lane = (int)(threadIdx.x % WAVE);
+  const int64_t p = (int64_t)gp.y * WAVE + lane;
+  for (int z = w; z < NZ; z += MULTI_EPG_WAVES) {
+    double a = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < n; ++c) a += ev.part[((int64_t)c * NZ + z) * ev.Bp + p];
+    acc_s[z][lane] = a;
+  }
+  __syncthreads();
   if (p < o.B) {
     const EventConst ec = *ev.ec;
-    double acc[NZ];
-    gather<NZ>(ev.part, ev.nchunk, ev.Bp, p, acc);
-    if (scaled) apply_gain<ND>(ec, acc);
-    if constexpr (GRAD) {
-      double th[NPARAM];
+    double acc[NZ], th[NPARAM];
 #pragma unroll
-      for (int i = 0; i < NPARAM; ++i) th[i] = o.theta[p * NPARAM + i];
-      const double nan = __builtin_nan("");
+    for (int z = 0; z < NZ; ++z) acc[z] = acc_s[z][lane];
+#pragma unroll
+    for (int i = 0; i < NPARAM; ++i) th[i] = o.theta[p * NPARAM + i];
+    const double nan = __builtin_nan("");
+#pragma unroll 1
+    for (int j = w; j < NPARAM; j += MULTI_EPG_WAVES) {
       bool valid;
-      double gout[NPARAM];
-      const double v = epilogue_gradient<ND>(acc, th, geoms[e], ec, scaled ? ec.uref : 1.0, valid, gout);
-      o.logl[p] = valid ? v : nan;
-#pragma unroll
-      for (int j = 0; j < NPARAM; ++j) o.grad[p * NPARAM + j] = valid ? gout[j] : nan;
-    } else {
-      o.logl[p] = epilogue_value_rows<ND, NZ>(acc, ev.coef, ev.Bp, p, ec, scaled ? ec.uref : 1.0);
+      double value;
+      const double gj = epilogue_gradient_pass<ND>(acc, th, geoms[gp.x], ec, 1.0, j, valid, value);
+      o.grad[p * NPARAM + j] = valid ? gj : nan;
+      if (j == 0) o.logl[p] = valid ? value : nan;
+    }
+  }
+  if (threadIdx.x == 0) atomicMax(&ctl->tend, wall_clock64());
+}
+
+// The value's epilogue: a thread per point, four groups per workgroup.
+template <int ND>
+__global__ __launch_bounds__(MULTI_EPI_BLOCK) void k_multi_epilogue(
+    const MultiEvDev* __restrict__ evs, const MultiIODev* __restrict__ io, const int2* __restrict__ grp, int ngrp,
+    const int* __restrict__ plans, MultiCtl* __restrict__ ctl) {
+  constexpr int NZ = nz_of(ND, false);
+  const int g = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (MULTI_EPI_BLOCK / WAVE) + threadIdx.x / WAVE));
+  if (g < ngrp) {
+    const int2 gp = grp[g];
+    const MultiEvDev ev = evs[gp.x];
+    const MultiIODev o = io[gp.x];
+    const int64_t p = (int64_t)gp.y * WAVE + threadIdx.x % WAVE;
+    if (p < o.B) {
+      double acc[NZ];
+      gather<NZ>(ev.part, plans[(int64_t)g * PLAN_INTS + PLAN_CHUNKS], ev.Bp, p, acc);
+      o.logl[p] = epilogue_value_rows<ND, NZ>(acc, ev.coef, ev.Bp, p, *ev.ec, 1.0);
     }
   }
   if (threadIdx.x == 0) atomicMax(&ctl->tend, wall_clock64());
@@ -208,20 +293,21 @@ struct gwl_plan_s {
   int device = 0;
   int E = 0, nd = 0;
   bool mixed = false, grad = false;
-  bool anyf64 = false;         // a mixed plan with float64 (relative-binning) events
   std::vector<int64_t> B;
   std::vector<gwl_event> evs;  // the events (event order)
   std::vector<int> cal;        // calibrated events (event index): their own kernels, after the graph
   std::vector<int> order;      // queue position -> event index
-  int total = 0, grid = 0, nptblk = 0, chunk = 0;
+  int total = 0, grid = 0, ngrp = 0, chunk = 0;  // total: items when every group walks a typical one's rows
   bool descending = false;     // queue order: events by descending work instead of ascending
   double clock_khz = 0.0;
   gwl::MultiEvDev* d_evs = nullptr;   // in queue order
   gwl::EventGeom* d_geoms = nullptr;  // in queue order
   gwl::MultiIODev* d_io = nullptr;    // in queue order
   gwl::MultiIODev* h_io = nullptr;    // pinned host staging
-  int* d_blk = nullptr;               // [2][nptblk]: event (queue index), first point
-  void* d_ctl = nullptr;              // MultiCtl, done[E], tev[E]
+  int2* d_grp = nullptr;              // [ngrp]: event (queue index), point group
+  int2* d_items = nullptr;            // the queue: group, chunk
+  int* d_plans = nullptr;             // [ngrp][PLAN_INTS]
+  void* d_ctl = nullptr;              // MultiCtl, done[E], items_of[E], tev[E]
   unsigned long long* h_stamps = nullptr;  // pinned: t0, tend, tev[E]
   double* ws = nullptr;
   hipStream_t cap = nullptr;
@@ -243,9 +329,9 @@ namespace {
 // Set to false to switch the multi-event plan off.
 constexpr bool kMultiEnabled = true;
 
-size_t ctl_bytes(int E) {
-  return sizeof(gwl::MultiCtl) + sizeof(unsigned int) * (size_t)((E + 1) & ~1) + sizeof(unsigned long long) * E;
-}
+// offset of the events' time stamps behind the control block and the two counters per event
+size_t tev_offset(int E) { return sizeof(gwl::MultiCtl) + 2 * sizeof(unsigned int) * (size_t)E; }
+size_t ctl_bytes(int E) { return tev_offset(E) + sizeof(unsigned long long) * E; }
 
 // precision of calibrated event e's own kernels in plan pl (as its single call would take)
 bool mixed_cal(const gwl_plan_s* pl, int e) { return pl->mixed && use_mixed(pl->evs[e], GWL_MIXED); }
@@ -265,7 +351,9 @@ void plan_free(gwl_plan pl) {
   if (pl->d_evs) (void)hipFree(pl->d_evs);
   if (pl->d_geoms) (void)hipFree(pl->d_geoms);
   if (pl->d_io) (void)hipFree(pl->d_io);
-  if (pl->d_blk) (void)hipFree(pl->d_blk);
+  if (pl->d_grp) (void)hipFree(pl->d_grp);
+  if (pl->d_items) (void)hipFree(pl->d_items);
+  if (pl->d_plans) (void)hipFree(pl->d_plans);
   if (pl->d_ctl) (void)hipFree(pl->d_ctl);
   if (pl->ws) (void)hipFree(pl->ws);
   if (pl->h_io) (void)hipHostFree(pl->h_io);
@@ -279,37 +367,33 @@ hipError_t enqueue_multi_nd(gwl_plan pl, hipStream_t s) {
   unsigned char* ctl = (unsigned char*)pl->d_ctl;
   gwl::MultiCtl* c = (gwl::MultiCtl*)ctl;
   unsigned int* done = (unsigned int*)(ctl + sizeof(gwl::MultiCtl));
-  unsigned long long* tev =
-      (unsigned long long*)(ctl + sizeof(gwl::MultiCtl) + sizeof(unsigned int) * (size_t)((E + 1) & ~1));
-  const int* blk_ev = pl->d_blk;
-  const int* blk_p0 = pl->d_blk + pl->nptblk;
-  hipLaunchKernelGGL(gwl::k_multi_reset, dim3((E + 255) / 256), dim3(256), 0, s, c, done, tev, E);
-  if (pl->nptblk > 0)   // no point outside calibrated events: only the reset and the (empty) queue
-    hipLaunchKernelGGL(gwl::k_multi_setup<ND>, dim3(pl->nptblk), dim3(gwl::MULTI_PT_BLOCK), 0, s,
-                       (const gwl::MultiEvDev*)pl->d_evs, (const gwl::EventGeom*)pl->d_geoms,
-                       (const gwl::MultiIODev*)pl->d_io, blk_ev, blk_p0);
-#define GWL_MB(MX, GR, AF)                                                                                         \
-  hipLaunchKernelGGL((gwl::k_multi_bins<ND, MX, GR, AF>), dim3(pl->grid), dim3(gwl::BLOCK), 0, s,               \
-                     (const gwl::MultiEvDev*)pl->d_evs, E, pl->total, (const gwl::MultiIODev*)pl->d_io, c, done, tev)
+  unsigned int* items_of = done + E;
+  unsigned long long* tev = (unsigned long long*)(ctl + tev_offset(E));
+  const gwl::MultiEvDev* evs = pl->d_evs;
+  const gwl::EventGeom* geoms = pl->d_geoms;
+  const gwl::MultiIODev* io = pl->d_io;
+  const int2* grp = pl->d_grp;
+  hipLaunchKernelGGL(gwl::k_multi_reset, dim3((E + 255) / 256), dim3(256), 0, s, c, done, items_of, tev, E);
+  if (pl->ngrp == 0) return hipGetLastError();   // no point outside calibrated events: only the reset
+  hipLaunchKernelGGL(gwl::k_multi_setup<ND>, dim3(pl->ngrp), dim3(gwl::MULTI_SETUP_WAVES * gwl::WAVE), 0, s, evs, geoms,
+                     io, grp, pl->mixed ? 1 : 0, pl->chunk, c, items_of, pl->d_items, pl->d_plans);
+#define GWL_MB(MX, GR)                                                                                         \
+  hipLaunchKernelGGL((gwl::k_multi_bins<ND, MX, GR>), dim3(pl->grid), dim3(gwl::BLOCK), 0, s, evs, io, grp,    \
+                     (const int2*)pl->d_items, (const int*)pl->d_plans, (const unsigned int*)items_of, c, done, tev)
   if (pl->mixed) {
-    if (pl->anyf64) {
-      if (pl->grad) GWL_MB(true, true, true); else GWL_MB(true, false, true);
-    } else {
-      if (pl->grad) GWL_MB(true, true, false); else GWL_MB(true, false, false);
-    }
+    if (pl->grad) GWL_MB(true, true); else GWL_MB(true, false);
   } else {
-    if (pl->grad) GWL_MB(false, true, false); else GWL_MB(false, false, false);
+    if (pl->grad) GWL_MB(false, true); else GWL_MB(false, false);
   }
 #undef GWL_MB
-  if (pl->nptblk == 0) return hipGetLastError();
-  if (pl->grad)
-    hipLaunchKernelGGL((gwl::k_multi_epilogue<ND, true>), dim3(pl->nptblk), dim3(gwl::MULTI_PT_BLOCK), 0, s,
-                       (const gwl::MultiEvDev*)pl->d_evs, (const gwl::EventGeom*)pl->d_geoms,
-                       (const gwl::MultiIODev*)pl->d_io, blk_ev, blk_p0, c);
-  else
-    hipLaunchKernelGGL((gwl::k_multi_epilogue<ND, false>), dim3(pl->nptblk), dim3(gwl::MULTI_PT_BLOCK), 0, s,
-                       (const gwl::MultiEvDev*)pl->d_evs, (const gwl::EventGeom*)pl->d_geoms,
-                       (const gwl::MultiIODev*)pl->d_io, blk_ev, blk_p0, c);
+  if (pl->grad) {
+    hipLaunchKernelGGL(gwl::k_multi_epilogue_grad<ND>, dim3(pl->ngrp), dim3(gwl::MULTI_EPG_WAVES * gwl::WAVE), 0, s, evs,
+                       geoms, io, grp, (const int*)pl->d_plans, c);
+  } else {
+    constexpr int per = gwl::MULTI_EPI_BLOCK / gwl::WAVE;
+    hipLaunchKernelGGL(gwl::k_multi_epilogue<ND>, dim3((pl->ngrp + per - 1) / per), dim3(gwl::MULTI_EPI_BLOCK), 0, s,
+                       evs, io, grp, pl->ngrp, (const int*)pl->d_plans, c);
+  }
   return hipGetLastError();
 }
 
@@ -324,27 +408,21 @@ hipError_t enqueue_multi(gwl_plan pl, hipStream_t s) {
 }
 
 template <int ND>
-hipError_t occupancy_nd(bool mixed, bool grad, bool anyf64, int* nblk) {
-#define GWL_OCC(MX, GR, AF) \
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(nblk, gwl::k_multi_bins<ND, MX, GR, AF>, gwl::BLOCK, 0)
+hipError_t occupancy_nd(bool mixed, bool grad, int* nblk) {
+#define GWL_OCC(MX, GR) return hipOccupancyMaxActiveBlocksPerMultiprocessor(nblk, gwl::k_multi_bins<ND, MX, GR>, gwl::BLOCK, 0)
   if (mixed) {
-    if (anyf64) {
-      if (grad) GWL_OCC(true, true, true); else GWL_OCC(true, false, true);
-    } else {
-      if (grad) GWL_OCC(true, true, false); else GWL_OCC(true, false, false);
-    }
-  } else {
-    if (grad) GWL_OCC(false, true, false); else GWL_OCC(false, false, false);
+    if (grad) GWL_OCC(true, true); else GWL_OCC(true, false);
   }
+  if (grad) GWL_OCC(false, true); else GWL_OCC(false, false);
 #undef GWL_OCC
 }
 
-hipError_t occupancy(int nd, bool mixed, bool grad, bool anyf64, int* nblk) {
+hipError_t occupancy(int nd, bool mixed, bool grad, int* nblk) {
   switch (nd) {
-    case 1: return occupancy_nd<1>(mixed, grad, anyf64, nblk);
-    case 2: return occupancy_nd<2>(mixed, grad, anyf64, nblk);
-    case 3: return occupancy_nd<3>(mixed, grad, anyf64, nblk);
-    case 4: return occupancy_nd<4>(mixed, grad, anyf64, nblk);
+    case 1: return occupancy_nd<1>(mixed, grad, nblk);
+    case 2: return occupancy_nd<2>(mixed, grad, nblk);
+    case 3: return occupancy_nd<3>(mixed, grad, nblk);
+    case 4: return occupancy_nd<4>(mixed, grad, nblk);
   }
   return hipErrorInvalidValue;
 }
@@ -385,14 +463,12 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
   pl->evs.assign(evs, evs + E);
   for (int e = 0; e < E; ++e)
     if (evs[e]->ncal > 0) pl->cal.push_back(e);
-  // a mixed plan runs its relative-binning events on the float64 loop, as single calls do
-  for (int e = 0; e < E; ++e) pl->anyf64 |= pl->mixed && !use_mixed(evs[e], prec);
 
-  // one chunk length for all events: the largest power of two in [1024, 16384] that still
-  // gives at least four items per resident wavefront
+  // one chunk length for all events: the largest power of two in [128, 4096] rows that still gives at
+  // least four items per resident wavefront
   hipError_t err = hipSuccess;
   int occ = 0, ncu = 0, clk = 0;
-  err = occupancy(nd, pl->mixed, pl->grad, pl->anyf64, &occ);
+  err = occupancy(nd, pl->mixed, pl->grad, &occ);
   if (err == hipSuccess) err = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, pl->device);
   if (err == hipSuccess) err = hipDeviceGetAttribute(&clk, hipDeviceAttributeWallClockRate, pl->device);
   if (err != hipSuccess) {
@@ -407,12 +483,12 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
     int64_t n = 0;
     for (int e = 0; e < E; ++e) {
       if (B_e[e] == 0 || evs[e]->ncal > 0) continue;
-      n += ((B_e[e] + WAVE - 1) / WAVE) * ((evs[e]->M + chunk - 1) / chunk);
+      n += ((B_e[e] + WAVE - 1) / WAVE) * ((evs[e]->M_loop + chunk - 1) / chunk);
     }
     return n;
   };
-  int chunk = 1024;
-  for (int c = 16384; c >= 1024; c >>= 1) {
+  int chunk = 128;
+  for (int c = 4096; c >= 128; c >>= 1) {
     if (items_for(c) >= 4 * resident) {
       chunk = c;
       break;
@@ -420,7 +496,21 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
   }
   if (chunk_req > 0) chunk = chunk_req;
   const int64_t total = items_for(chunk);
-  if (total > ((int64_t)1 << 30)) {
+  // most chunks of a group of event e: enough for half as many rows again as a typical group's, and for
+  // its bins in chunks of MULTI_BIN_CHUNK
+  auto slots = [&](const gwl_event ev) {
+    const int64_t rows = std::min<int64_t>((ev->M_loop + ev->M_loop / 2 + chunk - 1) / chunk, (ev->M + chunk - 1) / chunk);
+    const int64_t bins = (ev->M + std::max(chunk, MULTI_BIN_CHUNK) - 1) / std::max(chunk, MULTI_BIN_CHUNK);
+    return std::max<int64_t>(1, std::max(rows, bins));
+  };
+  int64_t capacity = 0, ngroups = 0;
+  for (int e = 0; e < E; ++e) {
+    if (evs[e]->ncal > 0) continue;
+    const int64_t n = (B_e[e] + WAVE - 1) / WAVE;
+    ngroups += n;
+    capacity += n * slots(evs[e]);
+  }
+  if (total > ((int64_t)1 << 30) || capacity > ((int64_t)1 << 30)) {
     plan_free(pl);
     return fail(GWL_E_SHAPE, "too many work items (%lld)", (long long)total);
   }
@@ -432,7 +522,7 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
   pl->order.resize(E);
   std::iota(pl->order.begin(), pl->order.end(), 0);
   std::stable_sort(pl->order.begin(), pl->order.end(), [&](int a, int b) {
-    const double wa = (double)B_e[a] * (double)evs[a]->M, wb = (double)B_e[b] * (double)evs[b]->M;
+    const double wa = (double)B_e[a] * (double)evs[a]->M_loop, wb = (double)B_e[b] * (double)evs[b]->M_loop;
     return descending ? wa > wb : wa < wb;
   });
 
@@ -440,9 +530,9 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
   const int NZ = nz_of(nd, pl->grad);
   std::vector<MultiEvDev> hev(E);
   std::vector<EventGeom> hgeo(E);
-  std::vector<int> blk_ev, blk_p0;
+  std::vector<int2> grp;
+  grp.reserve((size_t)ngroups);
   size_t ws_doubles = 0;
-  int item0 = 0;
   for (int q = 0; q < E; ++q) {
     const int e = pl->order[q];
     const gwl_event ev = evs[e];
@@ -452,25 +542,20 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
     d.npg = (int)((B + WAVE - 1) / WAVE);
     d.Bp = (int64_t)d.npg * WAVE;
     d.M = (int)ev->M;
-    d.chunk = chunk;
-    d.nchunk = B > 0 ? (int)((ev->M + chunk - 1) / chunk) : 0;
-    d.item0 = item0;
-    d.nitems = d.npg * d.nchunk;
-    item0 += d.nitems;
+    d.nslot = (int)slots(ev);
     d.f64 = use_mixed(ev, prec) ? 0 : 1;
-    d.rot = d.f64 && ev->ech.uniform != 0 ? 1 : 0;
+    d.rot = ev->ech.uniform != 0 ? 1 : 0;
     d.step = ev->ech.grid_df;
-    d.tab = d.f64 ? ev->tab64 : ev->tab32;
+    d.tab64 = ev->tab64;
+    d.tab32 = ev->tab32;
     d.gtab = ev->g64;
     d.ec = ev->ec;
-    ws_doubles += (size_t)NCOEF * d.Bp + (size_t)d.nchunk * NZ * d.Bp;
+    d.bands = ev->bands;
+    ws_doubles += (size_t)NCOEF * d.Bp + (size_t)d.nslot * NZ * d.Bp;
     hgeo[q] = ev->geom;
-    for (int64_t p0 = 0; p0 < d.Bp; p0 += MULTI_PT_BLOCK) {
-      blk_ev.push_back(q);
-      blk_p0.push_back((int)p0);
-    }
+    for (int pg = 0; pg < d.npg; ++pg) grp.push_back(make_int2(q, pg));
   }
-  pl->nptblk = (int)blk_ev.size();
+  pl->ngrp = (int)grp.size();
   err = hipMalloc((void**)&pl->ws, sizeof(double) * (ws_doubles > 0 ? ws_doubles : 1));
   size_t off = 0;
   for (int q = 0; q < E; ++q) {
@@ -478,22 +563,22 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
     d.coef = pl->ws + off;
     off += (size_t)NCOEF * d.Bp;
     d.part = pl->ws + off;
-    off += (size_t)d.nchunk * NZ * d.Bp;
+    off += (size_t)d.nslot * NZ * d.Bp;
   }
-  std::vector<int> blk(blk_ev);
-  blk.insert(blk.end(), blk_p0.begin(), blk_p0.end());
   if (err == hipSuccess) err = hipMalloc((void**)&pl->d_evs, sizeof(MultiEvDev) * E);
   if (err == hipSuccess) err = hipMalloc((void**)&pl->d_geoms, sizeof(EventGeom) * E);
   if (err == hipSuccess) err = hipMalloc((void**)&pl->d_io, sizeof(MultiIODev) * E);
-  if (err == hipSuccess) err = hipMalloc((void**)&pl->d_blk, sizeof(int) * (blk.empty() ? 1 : blk.size()));
+  if (err == hipSuccess) err = hipMalloc((void**)&pl->d_grp, sizeof(int2) * (grp.empty() ? 1 : grp.size()));
+  if (err == hipSuccess) err = hipMalloc((void**)&pl->d_items, sizeof(int2) * (size_t)(capacity > 0 ? capacity : 1));
+  if (err == hipSuccess) err = hipMalloc((void**)&pl->d_plans, sizeof(int) * PLAN_INTS * (grp.empty() ? 1 : grp.size()));
   if (err == hipSuccess) err = hipMalloc(&pl->d_ctl, ctl_bytes(E));
   if (err == hipSuccess) err = hipHostMalloc((void**)&pl->h_io, sizeof(MultiIODev) * E, hipHostMallocDefault);
   if (err == hipSuccess)
     err = hipHostMalloc((void**)&pl->h_stamps, sizeof(unsigned long long) * (2 + E), hipHostMallocDefault);
   if (err == hipSuccess) err = hipMemcpy(pl->d_evs, hev.data(), sizeof(MultiEvDev) * E, hipMemcpyHostToDevice);
   if (err == hipSuccess) err = hipMemcpy(pl->d_geoms, hgeo.data(), sizeof(EventGeom) * E, hipMemcpyHostToDevice);
-  if (err == hipSuccess && !blk.empty())
-    err = hipMemcpy(pl->d_blk, blk.data(), sizeof(int) * blk.size(), hipMemcpyHostToDevice);
+  if (err == hipSuccess && !grp.empty())
+    err = hipMemcpy(pl->d_grp, grp.data(), sizeof(int2) * grp.size(), hipMemcpyHostToDevice);
   if (err == hipSuccess) {
     memset(pl->h_io, 0, sizeof(MultiIODev) * E);
     err = hipMemcpy(pl->d_io, pl->h_io, sizeof(MultiIODev) * E, hipMemcpyHostToDevice);
@@ -605,8 +690,7 @@ gwl_status gwl_multi_launch(gwl_plan pl, const double* const* theta, double* con
   // calibrated events: their own set-up, bin-loop and epilogue kernels, each followed by a clock
   // stamp in the event's slot, dealt in turn to the plan's side streams after the graph (one small
   // event at a time leaves most of the chip idle); the caller's stream then waits for them all
-  unsigned long long* tev_dev = (unsigned long long*)((unsigned char*)pl->d_ctl + sizeof(MultiCtl) +
-                                                      sizeof(unsigned int) * (size_t)((pl->E + 1) & ~1));
+  unsigned long long* tev_dev = (unsigned long long*)((unsigned char*)pl->d_ctl + tev_offset(pl->E));
   if (!pl->cal.empty()) {
     constexpr int NS = gwl_plan_s::kCalStreams;
     err = hipEventRecord(pl->cal_fork, s);
@@ -639,7 +723,7 @@ gwl_status gwl_multi_launch(gwl_plan pl, const double* const* theta, double* con
   }
   if (event_latency_us) {
     const unsigned char* ctl = (const unsigned char*)pl->d_ctl;
-    const size_t tev_off = sizeof(MultiCtl) + sizeof(unsigned int) * (size_t)((pl->E + 1) & ~1);
+    const size_t tev_off = tev_offset(pl->E);
     err = hipMemcpyAsync(pl->h_stamps, ctl + offsetof(MultiCtl, t0), sizeof(unsigned long long) * 2,
                          hipMemcpyDeviceToHost, s);
     if (err == hipSuccess)

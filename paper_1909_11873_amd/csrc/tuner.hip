@@ -401,7 +401,7 @@ gwl_status gwl_multi_autotune(const char* cache_path, const gwl_event* evs, int 
   };
   // chunk lengths in powers of two, both queue orders; then 3/4 to 3/2 of the best length, in
   // eighths, in both orders
-  for (int chunk = 1024; err == hipSuccess && chunk <= 16384; chunk <<= 1)
+  for (int chunk = 128; err == hipSuccess && chunk <= 4096; chunk <<= 1)
     for (int desc = 0; desc < 2 && err == hipSuccess; ++desc) try_plan(chunk, desc);
   if (err == hipSuccess && best_chunk > 0) {
     const int c0 = best_chunk;

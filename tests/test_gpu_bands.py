@@ -117,6 +117,50 @@ def test_rows_match_every_bin(kind, nd, duration, f_lo, f_hi, uniform, tmp_path)
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("grad", [False, True])
+def test_plan_of_events_matches_every_bin(prec, grad, tmp_path):
+    """Groups that walk rows and groups that walk bins in one plan (points near the origin, spread over
+    the segment, and invalid ones; a short grid, an empty batch): the values and gradients of single
+    calls that walk every bin, the same bits on a second launch, in both queue orders."""
+    events, thetas, want = [], [], []
+    path = str(tmp_path / "layout.json")
+    try:
+        for kind, f_hi, n in (("prior", 700.0, 200), ("late", 300.0, 129), ("invalid", 611.0, 257), ("light", 40.0, 64),
+                              ("prior", 300.0, 0)):
+            spec, f, psd, data, dets = event_inputs(1, f_hi=f_hi)
+            t = torch.tensor(_points(kind, max(n, 257), 8)[:n], device=DEV)
+            ev = gw.Event(torch.tensor(data, device=DEV), torch.tensor(psd, device=DEV), dets,
+                          torch.tensor(f, device=DEV), spec.df)
+            if n:
+                _layout(path, 3, len(f), prec, grad, n, 16, -(-len(f) // 320), 0)
+                want.append(gw.logl_grad(t, ev, prec) if grad else (gw.logl(t, ev, prec), None))
+            else:
+                want.append((torch.empty(0), torch.empty(0, 11)))
+            events.append(ev)
+            thetas.append(t)
+        got = []
+        for order in ("ascending", "descending"):
+            plan = gw.MultiPlan(events, [len(t) for t in thetas], prec, with_grad=grad, order=order)
+            for _ in range(2):
+                v, g, _ = plan.launch(thetas)
+                got.append([x.cpu().numpy() for x in v] + ([x.cpu().numpy() for x in g] if grad else []))
+            plan.close()
+        for other in got[1:]:
+            assert all(np.array_equal(a, b, equal_nan=True) for a, b in zip(got[0], other))
+        for i, (v, g) in enumerate(want):
+            v = v.cpu().numpy()
+            ok = np.isfinite(v)
+            assert np.array_equal(np.isfinite(got[0][i]), ok)
+            assert (np.abs(got[0][i][ok] - v[ok]) <= (1e-7 if prec == "fp64" else 1e-3)).all()
+            if grad and len(v):
+                e = scaled_grad_error(got[0][len(want) + i][ok], g.cpu().numpy()[ok])
+                assert e.max() <= (2e-9 if prec == "fp64" else 1e-3), e.max()
+    finally:
+        gw.autotune_load(CACHE)
+
+
+@pytest.mark.gpu
 def test_grids_without_bands_keep_their_bins():
     """Grids that are not increasing, or too short to have bands, give the oracle's values as before."""
     for f_hi, flip in ((300.0, True), (30.0, False)):
