@@ -92,9 +92,10 @@ __device__ inline float wave_max_hi(float v) {
 // on the intervals w, w + nw, .... Every g_m' is monotone, so over an interval t lies within
 // (t_i + t_i+1 -+ sum_m |a_m| |change of g_m'|) / 2. Points with a NaN coefficient do not count
 // (their value is NaN on any rows).
+// `slope`: a further phase, of at most `slope` cycles per unit of ln f.
 template <int ND>
 __device__ inline void band_ranges(const BandHead* __restrict__ bh, const double (&a)[NBASIS], const double (&T)[ND],
-                                   int w, int nw, int lane, BandLds& s) {
+                                   int w, int nw, int lane, BandLds& s, double slope = 0.0) {
   double tlo = T[0], thi = T[0];
 #pragma unroll
   for (int d = 1; d < ND; ++d) {
@@ -102,7 +103,7 @@ __device__ inline void band_ranges(const BandHead* __restrict__ bh, const double
     thi = fmax(thi, T[d]);
   }
   for (int i = w; i < bh->nbrk; i += nw) {
-    double t = 0.0, t1 = 0.0, v = 0.0;
+    double t = 0.0, t1 = 0.0, v = 2.0 * slope * bh->gp[i][4];   // g_4 = ln f
 #pragma unroll
     for (int m = 0; m < NBASIS; ++m) {
       t = fma(a[m], bh->gp[i][m], t);
@@ -138,6 +139,17 @@ __device__ inline void band_hold(const BandHead* __restrict__ bh, int w, int nw,
   }
 }
 
+// The band of segment `lane` that holds the group with the fewest rows (-1: none).
+__device__ inline int band_of_segment(const BandHead* __restrict__ bh, int lane, const BandLds& s) {
+  if (lane >= bh->nseg) return -1;
+  const int b0 = bh->c0[lane], nb = bh->c0[lane + 1] - b0, wd = b0 >> 6, sh = b0 & 63;
+  if (nb == 0) return -1;
+  unsigned long long bits = s.ok[wd] >> sh;
+  if (sh) bits |= s.ok[wd + 1] << (64 - sh);
+  if (nb < 64) bits &= (1ull << nb) - 1;
+  return bits ? b0 + __ffsll(bits) - 1 : -1;
+}
+
 // Step 3, after a barrier, by one wavefront: the plan. Lane j holds segment j; the panels below
 // one wide segment (the cheapest, or none) and that segment are the pieces, neighbouring panels
 // that keep their bins one piece. `mixed`: a group whose rows are not clearly fewer than its bins
@@ -148,18 +160,11 @@ __device__ inline void band_plan(const BandHead* __restrict__ bh, int64_t M, boo
   const int ns = bh->nseg, np = bh->npanel;
   int rows = 0, row0 = 0, cand = -1, first = 0;
   if (lane < ns) {
-    const int b0 = bh->c0[lane], nb = bh->c0[lane + 1] - b0, wd = b0 >> 6, sh = b0 & 63;
-    unsigned long long bits = 0;
-    if (nb > 0) {
-      bits = s.ok[wd] >> sh;
-      if (sh) bits |= s.ok[wd + 1] << (64 - sh);
-      if (nb < 64) bits &= (1ull << nb) - 1;
-    }
+    cand = band_of_segment(bh, lane, s);
     first = bh->first[lane];
     rows = bh->bins[lane];
     row0 = bh->k0[lane];
-    if (bits) {
-      cand = b0 + __ffsll((unsigned long long)bits) - 1;
+    if (cand >= 0) {
       rows = bh->cand[cand].rows;
       row0 = bh->cand[cand].row0;
     }
@@ -211,6 +216,28 @@ __device__ inline void band_plan(const BandHead* __restrict__ bh, int64_t M, boo
     s.plan[1] = (int)__popcll(heads);
     s.plan[2] = f64 ? 1 : 0;
     s.plan[3] = (all + nchunk - 1) / nchunk;
+  }
+}
+
+// Step 3 on a calibrated event, whose segments are the calibration's node intervals: the plan keeps
+// the intervals apart, from plan[4 + 2 j] each interval's first row and its rows.
+__device__ inline void band_plan_cal(const BandHead* __restrict__ bh, int64_t M, bool mixed, int nchunk, int lane,
+                                     BandLds& s) {
+  const int cand = band_of_segment(bh, lane, s);
+  int rows = 0;
+  if (lane < bh->nseg) {
+    rows = cand < 0 ? bh->bins[lane] : bh->cand[cand].rows;
+    s.plan[4 + 2 * lane] = cand < 0 ? bh->k0[lane] : bh->cand[cand].row0;
+    s.plan[5 + 2 * lane] = rows;
+  }
+  int all = rows;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) all += __shfl_xor(all, off);
+  if (lane == 0) {
+    const bool f64 = !mixed || 5 * (int64_t)all <= 4 * M;
+    s.plan[0] = all;
+    s.plan[2] = f64 ? 1 : 0;
+    s.plan[3] = ((f64 ? all : (int)M) + nchunk - 1) / nchunk;
   }
 }
 

@@ -99,7 +99,7 @@ __host__ __device__ constexpr int nz_of(int nd, bool grad) { return grad ? 3 * n
 // Detector calibration model: per detector, nnode amplitude and nnode phase node values
 // interpolated in ln f by a cubic spline whose value at a bin depends on the four nodes around
 // it. The weights of those four nodes are per-bin constants; the window of four nodes is fixed
-// over a node interval, and the bin loop's chunks never cross an interval.
+// over a node interval; the bin loop takes a chunk interval by interval.
 constexpr int MAXNODE = 16;
 struct RowCal32 {
   float w[4];
@@ -107,17 +107,17 @@ struct RowCal32 {
 struct RowCal64 {
   double w[4];
 };
-constexpr int MAXCALCHUNK = 96;
 struct CalShape {
   int nnode;              // nodes per detector
-  int nchunk;             // chunks; each lies inside one node interval
-  int npg, nbpg, items, gper;
+  int nchunk;             // equal shares of a group's rows, one wavefront each
+  int npg, nbc, items, gper;
   int j0[MAXNODE];        // first node of each interval's window of four
-  int cj[MAXCALCHUNK];    // interval of each chunk
-  int ck[MAXCALCHUNK + 1];// first bin of each chunk; ck[nchunk] = M
+  int k0[MAXNODE];        // first bin of each interval; k0[nnode - 1] = M
 };
-// Calibrated sums: Z_det (2 ND); adjoint: + the uncalibrated model's moments (ND + 8) + per
-// detector the window moments of the amplitude (4) and phase (4) nodes
+// Calibrated sums: Z_det (2 ND); adjoint: + the uncalibrated model's moments (ND + 8), all per chunk
+// [nchunk][nz_of], + per detector the window moments of the amplitude (4) and phase (4) nodes, per
+// piece of a chunk in one interval: chunk c's piece of interval j at c + j of [nchunk + nnode - 2][8 ND]
 __host__ __device__ constexpr int nz_cal(int nd, bool grad) { return grad ? 11 * nd + NBASIS : 2 * nd; }
+__host__ __device__ constexpr int nz_win(int nd, bool grad) { return grad ? 8 * nd : 0; }
 
 }  // namespace gwl

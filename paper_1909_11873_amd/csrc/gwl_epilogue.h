@@ -10,17 +10,17 @@
 
 namespace gwl {
 
-// E G: the constant phase factor E = exp(-2 pi i c0) (c0 in cycles) times the gain G. This and
-// adjoint_factor spell out their fused multiply-adds, so that every kernel forming c_det rounds
-// the same way (the in-kernel set-up and the set-up kernel give bitwise equal gradients).
-__device__ inline void phase_gain(double c0raw, double gr, double gi, double& egr, double& egi) {
+// The constant phase factor E = exp(-2 pi i c0) (c0 in cycles). adjoint_factor spells out its fused
+// multiply-adds, so that every kernel forming c_det rounds the same way (the in-kernel set-up and
+// the set-up kernel give bitwise equal gradients).
+__device__ inline void phase_factor(double c0raw, double& er, double& ei) {
   const double c0 = c0raw - rint(c0raw);
   double es, ecs;
   sincos_cycles_f64(c0, es, ecs);
-  egr = fma(ecs, gr, es * gi);
-  egi = fma(ecs, gi, -(es * gr));
+  er = ecs;
+  ei = -es;
 }
-// c_det = (E G) Q_det
+// c_det = E Q_det
 __device__ inline void adjoint_factor(double egr, double egi, double qr, double qi, double& cr, double& ci) {
   cr = fma(egr, qr, -(egi * qi));
   ci = fma(egr, qi, egi * qr);
@@ -44,7 +44,7 @@ __device__ inline bool rows_in_range(const double* a, const double* T, const Eve
 // writes CO_A (less the fiducial's), CO_C0 and CO_AMP, NaN for a point outside the model's
 // domain; the extrinsic half writes CO_T (less the fiducial's), CO_QR and CO_QI. The phase
 // range check and the adjoint factors c_det then come from these rows (rows_in_range,
-// phase_gain).
+// phase_factor).
 __device__ inline void setup_lds_intrinsic(const double (&th)[NPARAM], const EventConst* ec, double* rows_s, int lane) {
   PointModel<double> pm;
   point_intrinsic<double>(th, pm);
@@ -67,20 +67,6 @@ __device__ inline void setup_lds_extrinsic(const double (&th)[NPARAM], const Eve
   }
 }
 
-// Divide the measured mean gain of the float32 hardware phasor out of the complex sums Z_det
-// (the leading 2 ND entries; the adjoint moments carry the gain in c_det). Explicit fused
-// multiply-adds: every kernel that applies it rounds alike.
-template <int ND, int NZ>
-__device__ inline void apply_gain(const EventConst& ec, double (&acc)[NZ]) {
-  const double gr = ec.gain_r, gi = ec.gain_i;
-#pragma unroll
-  for (int z = 0; z < 2 * ND; z += 2) {
-    const double re = acc[z], im = acc[z + 1];
-    acc[z] = fma(re, gr, -(im * gi));
-    acc[z + 1] = fma(re, gi, im * gr);
-  }
-}
-
 // Sum the per-chunk partials of one point in chunk order (deterministic). The chunk loop is
 // unrolled so that several chunks' loads are in flight before their adds, which still run in
 // chunk order; with one thread per point this loop is latency-bound otherwise.
@@ -95,31 +81,8 @@ __device__ inline void gather(const double* __restrict__ part, int nchunk, int64
   }
 }
 
-// logL = sum_det [ uref Re(A E Q_det Z_det) - 1/2 A^2 |Q_det|^2 K_det ],  E = exp(-2 pi i c0).
-// `acc` holds Z_det (re, im) first; uref = 1 for float64 tables.
-template <int ND, int NZ>
-__device__ inline double epilogue_value(const double (&acc)[NZ], const double (&th)[NPARAM], const EventGeom& g,
-                                        const EventConst& ec, double uref, bool& valid) {
-  PointModel<double> pm;
-  point_model<double, ND>(th, g, pm);
-  const double c0 = pm.c0 - rint(pm.c0);
-  double es, ecs;
-  sincos_cycles_f64(c0, es, ecs);
-  const double er = ecs, ei = -es;
-  double out = 0.0;
-#pragma unroll
-  for (int d = 0; d < ND; ++d) {
-    const double xr = pm.amp * (er * pm.qr[d] - ei * pm.qi[d]);
-    const double xi = pm.amp * (er * pm.qi[d] + ei * pm.qr[d]);
-    const double dh = uref * (xr * acc[2 * d] - xi * acc[2 * d + 1]);
-    const double hh = pm.amp * pm.amp * (pm.qr[d] * pm.qr[d] + pm.qi[d] * pm.qi[d]) * ec.K[d];
-    out += dh - 0.5 * hh;
-  }
-  valid = pm.valid;
-  return out;
-}
-
-// The same value from the point's set-up rows (A, Q_det and c0 as the point model gave them; a
+// logL = sum_det [ uref Re(A E Q_det Z_det) - 1/2 A^2 |Q_det|^2 K_det ], E = exp(-2 pi i c0), with
+// `acc` holding Z_det (re, im) first, from the point's set-up rows (A, Q_det and c0 as the point model gave them; a
 // point outside the model's domain has NaN rows and gets NaN), so the forward epilogue does not
 // evaluate the point model a second time.
 template <int ND, int NZ>

@@ -53,8 +53,9 @@ hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, const 
 // band-limited rows: the bands of a grid (host; head.ncand = 0: none), and their rows made from
 // the grid's rows in tab (row numbers as head.cand[].row0); kv holds kvals kernel values
 struct BandGen;
-void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t row_base, BandHead& head,
-                std::vector<BandGen>& gen, int64_t& nrows, int64_t& kvals);
+void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t row_base,
+                const std::vector<int64_t>& nodes, BandHead& head, std::vector<BandGen>& gen, int64_t& nrows,
+                int64_t& kvals);
 void band_blocks(const std::vector<BandGen>& gen, int64_t M, std::vector<int2>& blk, int (&nblk)[2]);
 hipError_t launch_bands(int nd, bool uniform, const BandGen* gen, int ncand, const int2* blk, const int (&nblk)[2],
                         double2* kv, void* tab, RowGradF64* gtab, hipStream_t s);
@@ -111,11 +112,25 @@ hipError_t launch_rb(int nd, const void* fine64, const RowGradF32* fine32g, cons
                      RowGradF32* g32, RowGradF64* g64, hipStream_t s);
 
 // calibrated model: set-up, bin loop and epilogue for theta[B][P], P = 11 + 2 nnode nd;
-// kcal per detector K1 [nnode], K2 [nnode][nnode]; calc is scratch [2 nnode nd][Bp]
-hipError_t launch_cal(int nd, bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const double* kcal,
-                      const void* tab, const void* gtab, const void* calw, const void* calt, const double* calB,
-                      const double* theta, int P, int64_t B, int64_t Bp, const CalShape& sh, double* coef,
-                      double* calc, double* part, double* logl, double* gradout, hipStream_t s);
+// kcal per detector K1 [nnode], K2 [nnode][nnode]; calc is scratch [2 nnode nd][Bp]; with
+// band-limited rows (bands, whose segments are the node intervals) plan is scratch
+// [npg][PLAN_INTS] and slope the cycles of calibration phase per unit of ln f and node difference
+struct CalTables {
+  const void *tab64, *tab32;
+  const RowGradF64* g64;
+  const RowGradF32* g32;
+  const RowCal64* w64;
+  const RowCal32* w32;
+  const double* t64;
+  const float* t32;
+  const double* basis;
+  const double* kcal;
+  const BandHead* bands;
+  double slope;
+};
+hipError_t launch_cal(int nd, bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const CalTables& t,
+                      const double* theta, int P, int64_t B, int64_t Bp, int64_t M, const CalShape& sh, double* coef,
+                      double* calc, double* part, int* plan, double* logl, double* gradout, hipStream_t s);
 
 // model strain on a grid: out[B][nd][M][2]
 hipError_t launch_waveform(int nd, const EventGeom& g, const double* coef, int64_t B, int64_t Bp,

@@ -39,6 +39,9 @@ struct gwl_event_s {
   double* kcal = nullptr;            // per detector: K1 [ncal], K2 [ncal][ncal]
   int cal_j0[gwl::MAXNODE] = {};
   int64_t cal_kb[gwl::MAXNODE] = {};
+  double cal_slope = 0.0;            // cycles of calibration phase per unit of ln f and node difference, at most
+  std::vector<double> band_f;        // while a calibrated event is made: its band-limited rows' frequencies
+  std::vector<int> band_seg;         //   and node intervals
   double df = 0.0;
   double gmst = 0.0;
   gwl_detector dets[GWL_MAX_DET] = {};
@@ -89,8 +92,6 @@ size_t workspace_counters(const LoopShape& sh, bool grad);
 LoopShape choose_shape(const gwl_event_s* ev, int64_t B, bool mixed, bool grad);
 // (M bins, of which a typical point's loop walks `rows` rows)
 LoopShape heuristic_shape(int64_t B, int64_t M, int64_t rows, bool mixed, bool grad);
-// number of bin chunks of the calibrated loop's adjoint (a heuristic)
-int heuristic_nchunk(int64_t B, int64_t M);
 
 // multi-event plans: build with an explicit chunk length (0 = heuristic) and queue order; the
 // tuner's cached choice for a workload (chunk 0 and ascending order when none is cached)

@@ -14,10 +14,8 @@ namespace gwl {
 // columns, the first 11 the signal parameters); after a barrier, setup_rows_write has each
 // wavefront write half of the rows [NCOEF][Bp], with the phase-range check and the adjoint
 // factors taken from the LDS rows; every row is NaN for a point outside the model's domain or
-// range, or with !ok. With `scaled` (float32 tables) the event's (gain_r, gain_i) undoes the mean gain
-// of the bin loop's phasor in the adjoint projection factors c_det = E G Q_det, through which
-// the adjoint loop keeps only the one real part of each moment that the gradient uses. A
-// relative-binning event's fiducial phase coefficients and shifts are subtracted (ec may be null).
+// range, or with !ok. The adjoint projection factors are c_det = E Q_det, through which the adjoint
+// loop keeps only the one real part of each moment that the gradient uses. A relative-binning event's fiducial phase coefficients and shifts are subtracted (ec may be null).
 template <int ND>
 __device__ inline void setup_halves(int w, int lane, const double* __restrict__ theta_row, const EventGeom& g,
                                     const EventConst* ec, double* rows_s) {
@@ -28,7 +26,7 @@ __device__ inline void setup_halves(int w, int lane, const double* __restrict__ 
   else setup_lds_extrinsic<ND>(th, g, ec, rows_s, lane);
 }
 template <int ND>
-__device__ inline void setup_rows_write(int w, int lane, const double* rows_s, const EventConst* ec, bool scaled,
+__device__ inline void setup_rows_write(int w, int lane, const double* rows_s, const EventConst* ec,
                                         bool ok, double* __restrict__ coef, int64_t Bp, int64_t p) {
   double a[NBASIS], T[ND];
 #pragma unroll
@@ -47,9 +45,8 @@ __device__ inline void setup_rows_write(int w, int lane, const double* rows_s, c
     put(CO_C0, rows_s[CO_C0 * WAVE + lane]);
     put(CO_AMP, rows_s[CO_AMP * WAVE + lane]);
   } else {
-    const double gr = (scaled && ec) ? ec->gain_r : 1.0, gi = (scaled && ec) ? ec->gain_i : 0.0;
     double egr, egi;
-    phase_gain(rows_s[CO_C0 * WAVE + lane], gr, gi, egr, egi);
+    phase_factor(rows_s[CO_C0 * WAVE + lane], egr, egi);
 #pragma unroll
     for (int d = 0; d < MAXDET; ++d) {
       double qr = 0.0, qi = 0.0, cr = 0.0, ci = 0.0;

@@ -44,8 +44,13 @@ void basis_slopes(double f, double (&g)[NBASIS]) {
 // The bands of a strictly increasing grid (head.ncand = 0 when there is nothing to gain). Rows are
 // numbered from `row_base`. Uniform grids space a band's rows by a multiple of half a bin, so
 // that the kernel's values depend on an index difference only.
-void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t row_base, BandHead& head,
-                std::vector<BandGen>& gen, int64_t& nrows, int64_t& kvals) {
+//
+// `nodes`, when given, are the first bins of segments that rows may not be shared across (the last
+// element is M): the calibration's node intervals, on each of which the model's factor is one cubic. The
+// rows' frequencies then stay within a quarter of the interval's ends, where that cubic is tame.
+void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t row_base,
+                const std::vector<int64_t>& nodes, BandHead& head, std::vector<BandGen>& gen, int64_t& nrows,
+                int64_t& kvals) {
   memset(&head, 0, sizeof head);
   gen.clear();
   nrows = kvals = 0;
@@ -62,7 +67,9 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
     if (k - ends.back() >= kMinBins && M - k >= kMinBins) ends.push_back(k);
   }
   ends.push_back(M);
+  if (!nodes.empty()) ends = nodes;
   const int np = (int)ends.size() - 1;
+  if (np > MAXSEG) return;
   head.npanel = np;
   struct Cand {
     BandGen g;
@@ -78,7 +85,13 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
     head.k0[s] = (int)ka;
     head.bins[s] = (int)nb;
     std::vector<Cand> list;
-    const double fa = f[(size_t)ka], width = f[(size_t)kb - 1] - fa, df = uniform ? step : width / (double)(nb - 1);
+    if (nb < kMinBins) {                                       // (node intervals may be short, or empty)
+      segs.push_back(list);
+      return;
+    }
+    const double fa = f[(size_t)ka], flow = (nodes.empty() ? 0.5 : 0.8) * fa;
+    const double fhigh = nodes.empty() ? HUGE_VAL : 1.25 * f[(size_t)kb - 1];
+    const double width = f[(size_t)kb - 1] - fa, df = uniform ? step : width / (double)(nb - 1);
     // the band of the fewest rows centred at t0 with half-width tb or a little more, of sources from
     // fs over ws (c.rows = 0: none)
     auto band = [&](double t0, double tb, double fs, double ws) {
@@ -91,7 +104,7 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
         const int half = (int)halves;
         const double h = 0.5 * half * df;
         const double rows_d = ceil(ws / h) + 2 * (w / 2) + 1, f0 = fs - (w / 2) * h;
-        if (f0 < 0.5 * fa || rows_d > 0.8 * (double)nb) continue;
+        if (f0 < flow || f0 + rows_d * h > fhigh || rows_d > 0.8 * (double)nb) continue;
         const int rows = (int)rows_d;
         if (best.c.rows && rows >= best.c.rows) continue;
         best.c.rows = rows;
@@ -118,7 +131,7 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
     // 1.6 times as far (half a second at least), centred at zero and, on panels where chirps are
     // long, on their side (t0 = -0.8 tb: from coalescence to the longest; -3 tb: a factor of two)
     const double tau = 5.0 / 256.0 * pow(kTsun, -5.0 / 3.0) * pow(M_PI * fa, -8.0 / 3.0);
-    const double grow = wide ? exp2(0.25) : exp2(0.5), far = std::max(wide ? 0.36 : 0.5, 1.6 * tau);
+    const double grow = wide || tau < 0.3 ? exp2(0.25) : exp2(0.5), far = std::max(wide ? 0.36 : 0.5, 1.6 * tau);
     std::vector<std::pair<double, double>> want;               // (t0, tb)
     for (double tb = kTbMin; tb < far * grow; tb *= grow) want.push_back({0.0, tb});
     if (!wide && tau >= 0.3)
@@ -169,7 +182,7 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
     segs.push_back(keep);
   };
   for (int p = 0; p < np; ++p) add_segment(p);
-  for (int p = std::max(0, np - 1 - kWide); p < np - 1; ++p) add_segment(p);
+  for (int p = std::max(0, np - 1 - kWide); p < np - 1 && nodes.empty(); ++p) add_segment(p);
   head.nseg = (int)segs.size();
   // the intervals on which t(f) is bounded, over every frequency that a row has
   double f0 = flo, f1 = fhi;

@@ -247,7 +247,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     for (int d = 0; d < ND; ++d) crd[d] = cid[d] = 0.0;
     if constexpr (GRAD) {
       double egr, egi;
-      phase_gain(rows_s[CO_C0 * WAVE + lane], 1.0, 0.0, egr, egi);
+      phase_factor(rows_s[CO_C0 * WAVE + lane], egr, egi);
 #pragma unroll
       for (int d = 0; d < ND; ++d)
         adjoint_factor(egr, egi, rows_s[(CO_QR + d) * WAVE + lane], rows_s[(CO_QI + d) * WAVE + lane], crd[d], cid[d]);

@@ -17,6 +17,7 @@
 // sum_k w_ki Im(c w_cal,k) (phase), q = u p exp(i dphi), w_cal = (1 + dA) q.
 #include <hip/hip_runtime.h>
 
+#include "gwl_bands.h"
 #include "gwl_bins.h"
 #include "gwl_common.h"
 #include "gwl_device.h"
@@ -26,32 +27,61 @@
 
 namespace gwl {
 
-// Set-up of a calibrated call: the point model's rows as k_setup writes them (two wavefronts per
-// 64 points, one per half of the model), and the calibration node values turned from theta's
-// columns 11.. into rows calc [ncal][Bp], each wavefront copying half of them; every row of a
-// point with a non-finite node value is NaN.
+// Set-up of a calibrated call: the point model's rows as k_setup writes them (two wavefronts, one
+// per half of the model), and the calibration node values turned from theta's columns 11.. into
+// rows calc [ncal][Bp], each of the two copying half of them; every row of a point with a non-finite node
+// value is NaN. With band-limited rows four wavefronts bound the group's arrival times as k_setup's
+// do, widened by the calibration phase: within a node interval (and a quarter beyond) the spline's slope
+// is at most four times the largest difference of neighbouring node values per node spacing.
+constexpr int SETUP_CAL_WAVES = 2, SETUP_CAL_WAVES_BANDS = 4;
 template <int ND>
-__global__ __launch_bounds__(2 * WAVE) void k_setup_cal(EventGeom g, const EventConst* __restrict__ ec, bool scaled,
-                                                        const double* __restrict__ theta, int P, int ncal, int64_t B,
-                                                        int64_t Bp, double* __restrict__ coef,
-                                                        double* __restrict__ calc) {
+__global__ __launch_bounds__(SETUP_CAL_WAVES_BANDS * WAVE) void k_setup_cal(
+    EventGeom g, const EventConst* __restrict__ ec, const BandHead* __restrict__ bh, double slope, int64_t M, bool mixed,
+    CalShape sh, const double* __restrict__ theta, int P, int ncal, int64_t B, int64_t Bp, double* __restrict__ coef,
+    double* __restrict__ calc, int* __restrict__ plan) {
   __shared__ double rows_s[NCOEF * WAVE];
   __shared__ int ok_s[2][WAVE];
+  __shared__ double diff_s[2][WAVE];
+  __shared__ BandLds bands_s;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // < Bp: Bp is a multiple of 64
   const int64_t pc = p < B ? p : B - 1;                  // padding lanes repeat the last point
-  setup_halves<ND>(w, lane, theta + pc * P, g, ec, rows_s);
-  const int half = (ncal + 1) / 2, j0 = w * half, j1 = w == 0 ? half : ncal;
-  bool ok = true;
-  for (int j = j0; j < j1; ++j) {
-    const double v = theta[pc * P + NPARAM + j];
-    ok &= isfinite(v);
-    calc[(int64_t)j * Bp + p] = v;
+  if (w < 2) {
+    setup_halves<ND>(w, lane, theta + pc * P, g, ec, rows_s);
+    const int half = (ncal + 1) / 2, j0 = w * half, j1 = w == 0 ? half : ncal;
+    bool ok = true;
+    double diff = 0.0, last = j0 > 0 ? theta[pc * P + NPARAM + j0 - 1] : 0.0;
+    for (int j = j0; j < j1; ++j) {
+      const double v = theta[pc * P + NPARAM + j];
+      ok &= isfinite(v);
+      calc[(int64_t)j * Bp + p] = v;
+      // node j of a detector's amplitudes (the first nnode) or phases
+      const int node = j % (2 * sh.nnode);
+      if (node > sh.nnode) diff = fmax(diff, fabs(v - last));
+      last = v;
+    }
+    ok_s[w][lane] = ok ? 1 : 0;
+    diff_s[w][lane] = diff;
   }
-  ok_s[w][lane] = ok ? 1 : 0;
   __syncthreads();
-  setup_rows_write<ND>(w, lane, rows_s, ec, scaled, ok_s[0][lane] && ok_s[1][lane], coef, Bp, p);
+  const bool ok = ok_s[0][lane] && ok_s[1][lane];
+  if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ec, ok, coef, Bp, p);
+  if (!bh) return;
+  double a[NBASIS], T[ND];
+#pragma unroll
+  for (int m = 0; m < NBASIS; ++m) a[m] = rows_s[(CO_A + m) * WAVE + lane];
+#pragma unroll
+  for (int d = 0; d < ND; ++d) T[d] = rows_s[(CO_T + d) * WAVE + lane];
+  if (!ok || !rows_in_range<ND>(a, T, ec)) a[0] = __builtin_nan("");
+  band_ranges<ND>(bh, a, T, w, SETUP_CAL_WAVES_BANDS, lane, bands_s, slope * fmax(diff_s[0][lane], diff_s[1][lane]));
+  __syncthreads();
+  band_hold(bh, w, SETUP_CAL_WAVES_BANDS, lane, bands_s);
+  __syncthreads();
+  if (w != 0) return;
+  band_plan_cal(bh, M, mixed, sh.nchunk, lane, bands_s);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
+  plan[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }
 
 // One bin of the calibrated loop. T_ is float (mixed: hardware phasors, float32 products) or
@@ -125,18 +155,30 @@ __device__ __forceinline__ void cal_bin(const Row r, const CalRow cw, T_ t, Grad
   }
 }
 
-// Workgroup -> (chunk, point group) as in the plain loop; a chunk is a piece of one interval
-// (intervals are cut into pieces of similar length, so chunks cost about the same).
-__device__ __forceinline__ bool locate_cal(const CalShape& sh, int& c, int& j, int64_t& k0, int64_t& k1, int& pg) {
+// Where a group's rows lie: per node interval its first row and rows, from the group's plan or the
+// grid's bins, and the rows of a chunk. `rows64`: the plan's, walked in float64.
+struct CalRows {
+  const int* pl;
+  const CalShape& sh;
+  bool rows64;
+  int chunk;
+  __device__ __forceinline__ CalRows(const CalShape& shape, const int* __restrict__ plan, int pg)
+      : pl(plan ? plan + (int64_t)pg * PLAN_INTS : nullptr), sh(shape) {
+    rows64 = pl && pl[2] != 0;
+    const int M = sh.k0[sh.nnode - 1];
+    chunk = pl ? pl[3] : (M + sh.nchunk - 1) / sh.nchunk;
+  }
+  __device__ __forceinline__ int row0(int j) const { return rows64 ? pl[4 + 2 * j] : sh.k0[j]; }
+  __device__ __forceinline__ int rows(int j) const { return rows64 ? pl[5 + 2 * j] : sh.k0[j + 1] - sh.k0[j]; }
+};
+
+// Workgroup -> four chunks of a point group, as the plain loop deals them to the dies.
+__device__ __forceinline__ bool locate_cal(const CalShape& sh, int& c, int& pg) {
   const int bid = blockIdx.x;
   const int item = (bid % NXCD) * sh.gper + bid / NXCD;
   if (item >= sh.items) return false;
-  c = item / sh.nbpg;
-  pg = (item - c * sh.nbpg) * WAVES_PER_BLOCK + (int)(threadIdx.x / WAVE);
-  if (pg >= sh.npg) return false;
-  j = sh.cj[c];
-  k0 = sh.ck[c];
-  k1 = sh.ck[c + 1];
+  pg = item / sh.nbc;
+  c = (item - pg * sh.nbc) * WAVES_PER_BLOCK + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   return true;
 }
 
@@ -147,58 +189,42 @@ constexpr int cal_waves_per_eu() {
   return (MIXED && GRAD && ND <= 3) ? 3 : 1;
 }
 
+// With a plan the float64 kernel takes the groups on float64 rows (all of them in a float64 call) and the
+// mixed kernel the others: two launches, so that each keeps its own registers.
 template <int ND, bool MIXED, bool GRAD>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(cal_waves_per_eu<ND, MIXED, GRAD>()))) void k_bins_cal(const void* __restrict__ tabv, const void* __restrict__ gtabv,
                                                     const void* __restrict__ calwv, const void* __restrict__ caltv,
-                                                    const double* __restrict__ calB, const double* __restrict__ coef,
-                                                    const double* __restrict__ calc, int64_t B, int64_t Bp,
-                                                    CalShape sh, double* __restrict__ part) {
+                                                    const double* __restrict__ calB, const EventConst* __restrict__ ec,
+                                                    const double* __restrict__ coef,
+                                                    const double* __restrict__ calc, const int* __restrict__ plan,
+                                                    int64_t B, int64_t Bp, CalShape sh, double* __restrict__ part) {
   typedef typename std::conditional<MIXED, float, double>::type T_;
   constexpr int NZ = nz_cal(ND, GRAD);
   __shared__ double2 tbl[MIXED ? 1 : PH_TBL];  // the float64 phasor table
   // mixed adjoint: the float64 totals of the 8 ND window moments stay in LDS (one column per
   // lane, so no barrier), which keeps the kernel at three wavefronts per SIMD instead of two
-  constexpr int NNODE = 8 * ND, NZU = NZ - NNODE;
-  __shared__ double ntot[MIXED && GRAD ? NNODE : 1][MIXED && GRAD ? BLOCK : 1];
+  constexpr int NNODE = GRAD ? 8 * ND : 0, NZU = NZ - NNODE;
+  __shared__ double ntot[MIXED && GRAD ? 8 * ND : 1][MIXED && GRAD ? BLOCK : 1];
+  int c, pg;
+  if (!locate_cal(sh, c, pg)) return;                  // whole workgroup
+  const CalRows cr_(sh, plan, pg);
+  if (plan && cr_.rows64 == MIXED) return;             // whole workgroup: the other kernel's group
   if constexpr (!MIXED) {
     fill_phasor_table(tbl);
     __syncthreads();
   }
-  int c, j, pg;
-  int64_t k0, k1;
-  if (!locate_cal(sh, c, j, k0, k1, pg)) return;
+  if (c >= sh.nchunk) return;
   const int64_t p = (int64_t)pg * WAVE + (threadIdx.x % WAVE);
   const int64_t pc = p < B ? p : B - 1;
   double a[NBASIS], T[ND];
   T_ cr[ND], ci[ND];
-  load_coef<ND, T_>(coef, Bp, pc, GRAD, a, T, cr, ci);
-  if constexpr (!MIXED) to_table_units<ND>(a, T);  // the float64 phase runs in 1/PH_TBL cycles
-  // this point's amplitude and phase node values in the window of the chunk's interval, turned
-  // into the cubics' coefficients: k[p] = sum_i v_i B[i][p] (1 added to the amplitude's k[0])
-  T_ kA[ND][4], kP[ND][4];
-  {
-    const int n = sh.nnode, j0 = sh.j0[j];
-    const double* Bj = calB + (int64_t)j * 16;
-#pragma unroll
-    for (int d = 0; d < ND; ++d) {
-      T_ va[4], vp[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        va[i] = (T_)calc[(int64_t)(2 * n * d + j0 + i) * Bp + pc];
-        vp[i] = (T_)calc[(int64_t)(2 * n * d + n + j0 + i) * Bp + pc];
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        T_ sa = q == 0 ? (T_)1 : (T_)0, sp = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          sa = fma(va[i], (T_)Bj[i * 4 + q], sa);
-          sp = fma(vp[i], (T_)Bj[i * 4 + q], sp);
-        }
-        kA[d][q] = sa;
-        kP[d][q] = sp;
-      }
-    }
+  if constexpr (MIXED) {
+    double crd[ND], cid[ND];
+    load_coef<ND, double>(coef, Bp, pc, GRAD, a, T, crd, cid);
+    mixed_factors<ND>(ec, crd, cid, cr, ci);
+  } else {
+    load_coef<ND, double>(coef, Bp, pc, GRAD, a, T, cr, ci);
+    to_table_units<ND>(a, T);                          // the float64 phase runs in 1/PH_TBL cycles
   }
   double tot[NZ];
 #pragma unroll
@@ -219,21 +245,58 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(cal_waves
       for (int zz = 0; zz < NZ; ++zz) tot[zz] += (double)z[zz];
     }
   };
-  if constexpr (MIXED) {
-    const RowMixed<ND>* tab = (const RowMixed<ND>*)tabv;
-    const RowGradF32* gt = (const RowGradF32*)gtabv;
-    const RowCal32* cw = (const RowCal32*)calwv;
-    const float* ct = (const float*)caltv;
-    // float32 blocks of NB bins added into float64; each bin's rows are requested one bin ahead
-    // (the tables carry zero padding rows past the last bin). Only the adjoint reads the weights.
-    int k = (int)k0;
-    const int kend = (int)k1;
-    if (k < kend) {
+  const int n = sh.nnode;
+  const double unit = MIXED ? ec->uref : 1.0;          // the float32 tables hold u / uref
+  double* win = part + (int64_t)sh.nchunk * NZU * Bp;  // window moments [nchunk + n - 2][NNODE][Bp]
+  // this chunk's rows, interval by interval
+  const int q0 = c * cr_.chunk, q1 = q0 + cr_.chunk;
+  int base = 0;
+  for (int j = 0; j < n - 1 && base < q1; ++j) {
+    const int row0 = cr_.row0(j), rows = cr_.rows(j);
+    const int lo = q0 > base ? q0 - base : 0, hi = q1 - base < rows ? q1 - base : rows;
+    base += rows;
+    if (lo >= hi) continue;
+    const int k0 = row0 + lo, k1 = row0 + hi;
+    // this point's amplitude and phase node values in the interval's window, turned into the
+    // cubics' coefficients: k[p] = sum_i v_i B[i][p] (1 added to the amplitude's k[0])
+    T_ kA[ND][4], kP[ND][4];
+    {
+      const int j0 = sh.j0[j];
+      const double* Bj = calB + (int64_t)j * 16;
+#pragma unroll
+      for (int d = 0; d < ND; ++d) {
+        T_ va[4], vp[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          va[i] = (T_)calc[(int64_t)(2 * n * d + j0 + i) * Bp + pc];
+          vp[i] = (T_)calc[(int64_t)(2 * n * d + n + j0 + i) * Bp + pc];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          T_ sa = q == 0 ? (T_)1 : (T_)0, sp = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            sa = fma(va[i], (T_)Bj[i * 4 + q], sa);
+            sp = fma(vp[i], (T_)Bj[i * 4 + q], sp);
+          }
+          kA[d][q] = sa;
+          kP[d][q] = sp;
+        }
+      }
+    }
+    if constexpr (MIXED) {
+      const RowMixed<ND>* tab = (const RowMixed<ND>*)tabv;
+      const RowGradF32* gt = (const RowGradF32*)gtabv;
+      const RowCal32* cw = (const RowCal32*)calwv;
+      const float* ct = (const float*)caltv;
+      // float32 blocks of NB bins added into float64; each bin's rows are requested one bin ahead
+      // (the tables carry zero padding rows past the last bin). Only the adjoint reads the weights.
+      int k = k0;
       RowMixed<ND> cur = load_row_mixed<ND>(tab, k);
       RowCal32 cwc;
       if constexpr (GRAD) cwc = cw[k];
       float tc = ct[k];
-      for (; k + NB <= kend; k += NB) {
+      for (; k + NB <= k1; k += NB) {
         float z[NZ];
 #pragma unroll
         for (int zz = 0; zz < NZ; ++zz) z[zz] = 0.0f;
@@ -250,30 +313,24 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(cal_waves
         }
         flush(z);
       }
-      if (k < kend) {
+      if (k < k1) {
         float z[NZ];
 #pragma unroll
         for (int zz = 0; zz < NZ; ++zz) z[zz] = 0.0f;
-        for (; k < kend; ++k)
+        for (; k < k1; ++k)
           cal_bin<ND, GRAD, float>(load_row_mixed<ND>(tab, k), cw[k], ct[k], gt, k, a, T, cr, ci, kA, kP, tbl, z);
         flush(z);
       }
-    }
-    if constexpr (GRAD) {
-#pragma unroll
-      for (int i = 0; i < NNODE; ++i) tot[NZU + i] = ntot[i][threadIdx.x];
-    }
-  } else {
-    const RowF64<ND>* tab = (const RowF64<ND>*)tabv;
-    const RowGradF64* gt = (const RowGradF64*)gtabv;
-    const RowCal64* cw = (const RowCal64*)calwv;
-    const double* ct = (const double*)caltv;
-    if (k0 < k1) {
-      RowF64<ND> cur = load_row_f64<ND>(tab, (int)k0);
+    } else {
+      const RowF64<ND>* tab = (const RowF64<ND>*)tabv;
+      const RowGradF64* gt = (const RowGradF64*)gtabv;
+      const RowCal64* cw = (const RowCal64*)calwv;
+      const double* ct = (const double*)caltv;
+      RowF64<ND> cur = load_row_f64<ND>(tab, k0);
       RowCal64 cwc;
       if constexpr (GRAD) cwc = cw[k0];
       double tc = ct[k0];
-      for (int k = (int)k0; k < (int)k1; ++k) {
+      for (int k = k0; k < k1; ++k) {
         const RowF64<ND> nxt = load_row_f64<ND>(tab, k + 1);
         RowCal64 cwn;
         if constexpr (GRAD) cwn = cw[k + 1];
@@ -284,158 +341,166 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(cal_waves
         tc = tn;
       }
     }
+    if constexpr (GRAD) {                              // the interval's window moments
+#pragma unroll
+      for (int i = 0; i < NNODE; ++i) {
+        double v;
+        if constexpr (MIXED) {
+          v = ntot[i][threadIdx.x];
+          ntot[i][threadIdx.x] = 0.0;
+        } else {
+          v = tot[NZU + i];
+          tot[NZU + i] = 0.0;
+        }
+        win[((int64_t)(c + j) * NNODE + i) * Bp + p] = unit * v;
+      }
+    }
+  }
+  if constexpr (MIXED) {   // the float64 loop's units (as mixed_units)
+    const double gr = ec->gain_r, gi = ec->gain_i;
+#pragma unroll
+    for (int z = 0; z < 2 * ND; z += 2) {
+      const double re = tot[z], im = tot[z + 1];
+      tot[z] = unit * fma(re, gr, -(im * gi));
+      tot[z + 1] = unit * fma(re, gi, im * gr);
+    }
+#pragma unroll
+    for (int z = 2 * ND; z < NZU; ++z) tot[z] *= unit;
   }
 #pragma unroll
-  for (int zz = 0; zz < NZ; ++zz) part[((int64_t)c * NZ + zz) * Bp + p] = tot[zz];
+  for (int zz = 0; zz < NZU; ++zz) part[((int64_t)c * NZU + zz) * Bp + p] = tot[zz];
 }
 
-// Epilogue, one workgroup per 64 points. The value alone takes one wavefront. The adjoint takes
-// four, which first share the gather: the value sums one component at a time and the window
-// moments of one detector and kind (amplitude or phase) at a time, each summed in chunk order.
-// Chunks come in interval order and an interval's window of four nodes starts at
-// clamp(j - 1, 0, n - 4), which never moves back and moves by at most one node, so a node's
-// moment is final once the window has moved past it: the task keeps the window in four
+// Epilogue, one workgroup of four wavefronts per 64 points, which share the gather. For the value the
+// wavefronts also share the detectors' K_det terms, and the first forms it from the set-up rows. The
+// adjoint's window moments are gathered one detector and kind (amplitude or phase) at a time, each
+// summed in chunk order. Chunks come in interval order and an interval's window of four nodes
+// starts at clamp(j - 1, 0, n - 4), which never moves back and moves by at most one node, so a
+// node's moment is final once the window has moved past it: the task keeps the window in four
 // registers and turns each finished node into its gradient at once. The 11 signal-parameter
 // derivatives (one dual-number pass each, the first also giving the value) are then dealt to
 // the wavefronts in turn.
 constexpr int EPC_WAVES = 4;
 
-// With alpha the point's amplitude node values for a detector: r_i = K1_i + (K2 alpha)_i. The
-// effective K_det = K_det + 2 alpha.K1 + alpha.K2.alpha = K_det + sum_i alpha_i (2 K1_i + (r_i - K1_i)),
-// and the amplitude node gradient takes 2 r_i.
+// With alpha the point's amplitude node values for a detector (rows al [n][Bp] of calc):
+// r_i = K1_i + (K2 alpha)_i. The effective K_det = K_det + 2 alpha.K1 + alpha.K2.alpha
+// = K_det + sum_i alpha_i (K1_i + r_i), and the amplitude node gradient takes 2 r_i.
 __device__ __forceinline__ double cal_r(const double* __restrict__ K1, const double* __restrict__ K2,
-                                        const double* __restrict__ al, int n, int i) {
+                                        const double* __restrict__ al, int64_t Bp, int n, int i) {
   double r = K1[i];
-  for (int l = 0; l < n; ++l) r += K2[i * n + l] * al[l];
+#pragma unroll 4
+  for (int l = 0; l < n; ++l) r = fma(K2[i * n + l], al[(int64_t)l * Bp], r);
   return r;
 }
 
 template <int ND, bool GRAD>
-__global__ __launch_bounds__((GRAD ? EPC_WAVES : 1) * WAVE) void k_epilogue_cal(
+__global__ __launch_bounds__(EPC_WAVES * WAVE) void k_epilogue_cal(
     EventGeom g, const EventConst* __restrict__ ec, const double* __restrict__ kcal, const double* __restrict__ theta,
-    int P, int64_t B, int64_t Bp, CalShape sh, bool scaled, const double* __restrict__ part, double* __restrict__ logl,
+    int P, int64_t B, int64_t Bp, CalShape sh, const int* __restrict__ plan, const double* __restrict__ coef,
+    const double* __restrict__ calc, const double* __restrict__ part, double* __restrict__ logl,
     double* __restrict__ grad) {
-  constexpr int NZ = nz_cal(ND, GRAD), NZU = nz_of(ND, GRAD);
-  constexpr int MA = 3 * ND + NBASIS, MB = MA + 4 * ND;
-  constexpr int NW = GRAD ? EPC_WAVES : 1;
+  constexpr int NZU = nz_of(ND, GRAD), NNODE = 8 * ND, NW = EPC_WAVES;
   __shared__ double acc_s[NZU][WAVE];
   __shared__ double ks_s[ND][WAVE];   // K_det's calibration term per point
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
-  const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // p < Bp: the partial sums have Bp rows
+  const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // p < Bp: the partial sums and set-up rows have Bp rows
   const int n = sh.nnode, nchunk = sh.nchunk;
-  if constexpr (GRAD) {
-    for (int z = w; z < NZU; z += NW) {
-      double a = 0.0;
+  for (int z = w; z < NZU; z += NW) {
+    double a = 0.0;
 #pragma unroll 8
-      for (int c = 0; c < nchunk; ++c) a += part[((int64_t)c * NZ + z) * Bp + p];
-      acc_s[z][lane] = a;
-    }
-  } else {
-    // one wavefront: every component in one chunk loop, so that their loads for several chunks
-    // are in flight together
-    double a[NZU];
-#pragma unroll
-    for (int z = 0; z < NZU; ++z) a[z] = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < nchunk; ++c) {
-#pragma unroll
-      for (int z = 0; z < NZU; ++z) a[z] += part[((int64_t)c * NZ + z) * Bp + p];
-    }
-#pragma unroll
-    for (int z = 0; z < NZU; ++z) acc_s[z][lane] = a[z];
+    for (int c = 0; c < nchunk; ++c) a += part[((int64_t)c * NZU + z) * Bp + p];
+    acc_s[z][lane] = a;
   }
-  const bool live = p < B;
   const double nan = __builtin_nan("");
-  const EventConst e = *ec;
-  const double uref = scaled ? e.uref : 1.0;
+  const double amp = coef[CO_AMP * Bp + p];              // NaN for an invalid point
+  // the tasks start with the wavefront after the one that took the last sum
+  int t = w - NZU % NW;
+  if (t < 0) t += NW;
   if constexpr (GRAD) {
-    // node gradients: amplitude uref A m_i - 1/2 A^2 |Q_det|^2 2 r_i, phase -uref A m_i
-    int t = w - NZU % NW;
-    if (t < 0) t += NW;
-    if (t < 2 * ND) {
-      const int64_t pc = live ? p : B - 1;
-      double th[NPARAM];
-#pragma unroll
-      for (int i = 0; i < NPARAM; ++i) th[i] = theta[pc * P + i];
-      PointModel<double> pm;
-      point_model<double, ND>(th, g, pm);
-      for (; t < 2 * ND; t += NW) {
-        const int d = t >> 1, kind = t & 1;
-        const double* al = theta + pc * P + NPARAM + 2 * n * d;
-        const double* K1 = kcal + (int64_t)d * (n + n * n);
-        const double* K2 = K1 + n;
-        double hh = 0.0;   // A^2 |Q_det|^2 (selected with constant indices: pm stays in registers)
-#pragma unroll
-        for (int dd = 0; dd < ND; ++dd)
-          if (dd == d) hh = pm.amp * pm.amp * (pm.qr[dd] * pm.qr[dd] + pm.qi[dd] * pm.qi[dd]);
-        double* out = grad + pc * P + NPARAM + 2 * n * d + (kind ? n : 0);
-        const int base = (kind ? MB : MA) + 4 * d;
-        double ks = 0.0;   // the amplitude task also sums K_det's calibration term
-        auto finish = [&](int i, double m) {
-          double x;
-          if (kind) {
-            x = -uref * pm.amp * m;
-          } else {
-            const double r = cal_r(K1, K2, al, n, i);
-            ks += al[i] * (2.0 * K1[i] + (r - K1[i]));
-            x = uref * pm.amp * m - 0.5 * hh * (2.0 * r);
-          }
-          if (live) out[i] = pm.valid ? x : nan;
-        };
-        double win[4] = {0.0, 0.0, 0.0, 0.0};
-        int wb = 0;   // the window holds nodes wb .. wb + 3
-        for (int c = 0; c < nchunk; ++c) {
-          const int j0 = sh.j0[sh.cj[c]];
-          for (; wb < j0; ++wb) {
-            finish(wb, win[0]);
-            win[0] = win[1];
-            win[1] = win[2];
-            win[2] = win[3];
-            win[3] = 0.0;
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) win[i] += part[((int64_t)c * NZ + base + i) * Bp + p];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (wb + i < n) finish(wb + i, win[i]);
-        for (int i = wb + 4; i < n; ++i) finish(i, 0.0);
-        if (!kind) ks_s[d][lane] = ks;
-      }
-    }
-  } else {
-    const int64_t pc = live ? p : B - 1;
-    for (int d = 0; d < ND; ++d) {
-      const double* al = theta + pc * P + NPARAM + 2 * n * d;
+    // node gradients: amplitude A m_i - 1/2 A^2 |Q_det|^2 2 r_i, phase -A m_i
+    const CalRows cr_(sh, plan, (int)blockIdx.x);
+    const double* win = part + (int64_t)nchunk * NZU * Bp;
+    for (; t < 2 * ND; t += NW) {
+      const int d = t >> 1, kind = t & 1;
+      const double* al = calc + (int64_t)(2 * n * d) * Bp + p;
       const double* K1 = kcal + (int64_t)d * (n + n * n);
       const double* K2 = K1 + n;
+      const double qr = coef[(int64_t)(CO_QR + d) * Bp + p], qi = coef[(int64_t)(CO_QI + d) * Bp + p];
+      const double hh = amp * amp * (qr * qr + qi * qi);
+      double* out = grad + p * P + NPARAM + 2 * n * d + (kind ? n : 0);
+      const int wbase = (kind ? 4 * ND : 0) + 4 * d;
+      double ks = 0.0;   // the amplitude task also sums K_det's calibration term
+      auto finish = [&](int i, double m) {
+        double x;
+        if (kind) {
+          x = -amp * m;
+        } else {
+          const double r = cal_r(K1, K2, al, Bp, n, i);
+          ks = fma(al[(int64_t)i * Bp], K1[i] + r, ks);
+          x = amp * m - hh * r;
+        }
+        if (p < B) out[i] = x;
+      };
+      double mom[4] = {0.0, 0.0, 0.0, 0.0};
+      int wb = 0;   // the window holds nodes wb .. wb + 3
+      int base = 0;
+      for (int j = 0; j < n - 1; ++j) {
+        const int rows = cr_.rows(j);
+        if (rows == 0) continue;
+        for (; wb < sh.j0[j]; ++wb) {
+          finish(wb, mom[0]);
+          mom[0] = mom[1];
+          mom[1] = mom[2];
+          mom[2] = mom[3];
+          mom[3] = 0.0;
+        }
+        // the chunks that hold a piece of the interval
+        const int ca = base / cr_.chunk, cb = (base + rows - 1) / cr_.chunk;
+        base += rows;
+#pragma unroll 4
+        for (int c = ca; c <= cb; ++c) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) mom[i] += win[((int64_t)(c + j) * NNODE + wbase + i) * Bp + p];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (wb + i < n) finish(wb + i, mom[i]);
+      for (int i = wb + 4; i < n; ++i) finish(i, 0.0);
+      if (!kind) ks_s[d][lane] = ks;
+    }
+  } else {
+    for (; t < ND; t += NW) {
+      const double* al = calc + (int64_t)(2 * n * t) * Bp + p;
+      const double* K1 = kcal + (int64_t)t * (n + n * n);
       double ks = 0.0;
-      for (int i = 0; i < n; ++i) ks += al[i] * (2.0 * K1[i] + (cal_r(K1, K2, al, n, i) - K1[i]));
-      ks_s[d][lane] = ks;
+      for (int i = 0; i < n; ++i) ks = fma(al[(int64_t)i * Bp], K1[i] + cal_r(K1, K1 + n, al, Bp, n, i), ks);
+      ks_s[t][lane] = ks;
     }
   }
   __syncthreads();
-  if (!live) return;
-  double acc[NZU];
+  if (p >= B) return;
+  EventConst ek = *ec;
 #pragma unroll
-  for (int z = 0; z < NZU; ++z) acc[z] = acc_s[z][lane];
-  if (scaled) apply_gain<ND>(e, acc);
-  double th[NPARAM];
-#pragma unroll
-  for (int i = 0; i < NPARAM; ++i) th[i] = theta[p * P + i];
-  EventConst ek = e;
-#pragma unroll
-  for (int d = 0; d < ND; ++d) ek.K[d] = e.K[d] + ks_s[d][lane];
-  bool valid;
+  for (int d = 0; d < ND; ++d) ek.K[d] += ks_s[d][lane];
   if constexpr (!GRAD) {
-    const double v = epilogue_value<ND, NZU>(acc, th, g, ek, uref, valid);
-    logl[p] = valid ? v : nan;
+    if (w != 0) return;
+    double acc[NZU];
+#pragma unroll
+    for (int z = 0; z < NZU; ++z) acc[z] = acc_s[z][lane];
+    logl[p] = epilogue_value_rows<ND, NZU>(acc, coef, Bp, p, ek, 1.0);
   } else {
+    double acc[NZU], th[NPARAM];
+#pragma unroll
+    for (int z = 0; z < NZU; ++z) acc[z] = acc_s[z][lane];
+#pragma unroll
+    for (int i = 0; i < NPARAM; ++i) th[i] = theta[p * P + i];
 #pragma unroll 1
     for (int j = w; j < NPARAM; j += NW) {
+      bool valid;
       double value;
-      const double gj = epilogue_gradient_pass<ND>(acc, th, g, ek, uref, j, valid, value);
+      const double gj = epilogue_gradient_pass<ND>(acc, th, g, ek, 1.0, j, valid, value);
       grad[p * P + j] = valid ? gj : nan;
       if (j == 0) logl[p] = valid ? value : nan;
     }
@@ -443,43 +508,43 @@ __global__ __launch_bounds__((GRAD ? EPC_WAVES : 1) * WAVE) void k_epilogue_cal(
 }
 
 template <int ND>
-static hipError_t cal_nd(bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const double* kcal,
-                         const void* tab, const void* gtab, const void* calw, const void* calt, const double* calB,
-                         const double* theta, int P, int64_t B, int64_t Bp, const CalShape& sh, double* coef,
-                         double* calc, double* part, double* logl, double* gradout, hipStream_t s) {
+static hipError_t cal_nd(bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const CalTables& t,
+                         const double* theta, int P, int64_t B, int64_t Bp, int64_t M, const CalShape& sh, double* coef,
+                         double* calc, double* part, int* plan, double* logl, double* gradout, hipStream_t s) {
   const int ncal = 2 * sh.nnode * ND;
-  if (Bp % WAVE != 0 || B < 1 || B > Bp) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_setup_cal<ND>, dim3((unsigned)(Bp / WAVE)), dim3(2 * WAVE), 0, s, g, ec, mixed, theta, P, ncal,
-                     B, Bp, coef, calc);
+  if (Bp % WAVE != 0 || B < 1 || B > Bp || (t.bands && !plan)) return hipErrorInvalidValue;
+  const int waves = t.bands ? SETUP_CAL_WAVES_BANDS : SETUP_CAL_WAVES;
+  hipLaunchKernelGGL(k_setup_cal<ND>, dim3((unsigned)(Bp / WAVE)), dim3(waves * WAVE), 0, s, g, ec, t.bands, t.slope, M,
+                     mixed, sh, theta, P, ncal, B, Bp, coef, calc, plan);
+  const int* pl = t.bands ? plan : nullptr;
   const dim3 grid((unsigned)(sh.gper * NXCD)), block(BLOCK);
-#define GWL_CB(MX, GR) \
-  hipLaunchKernelGGL((k_bins_cal<ND, MX, GR>), grid, block, 0, s, tab, gtab, calw, calt, calB, (const double*)coef, \
-                     (const double*)calc, B, Bp, sh, part)
+#define GWL_CB(MX, GR)                                                                                              \
+  hipLaunchKernelGGL((k_bins_cal<ND, MX, GR>), grid, block, 0, s, MX ? t.tab32 : t.tab64,                           \
+                     MX ? (const void*)t.g32 : (const void*)t.g64, MX ? (const void*)t.w32 : (const void*)t.w64,    \
+                     MX ? (const void*)t.t32 : (const void*)t.t64, t.basis, ec, (const double*)coef,                \
+                     (const double*)calc, pl, B, Bp, sh, part)
   if (mixed) {
     if (grad) GWL_CB(true, true); else GWL_CB(true, false);
-  } else {
+  }
+  if (!mixed || pl) {
     if (grad) GWL_CB(false, true); else GWL_CB(false, false);
   }
 #undef GWL_CB
-  const dim3 egrid((unsigned)((B + WAVE - 1) / WAVE));
-  if (grad)
-    hipLaunchKernelGGL((k_epilogue_cal<ND, true>), egrid, dim3(EPC_WAVES * WAVE), 0, s, g, ec, kcal, theta, P, B, Bp,
-                       sh, mixed, (const double*)part, logl, gradout);
-  else
-    hipLaunchKernelGGL((k_epilogue_cal<ND, false>), egrid, dim3(WAVE), 0, s, g, ec, kcal, theta, P, B, Bp, sh, mixed,
-                       (const double*)part, logl, gradout);
+  const dim3 egrid((unsigned)((B + WAVE - 1) / WAVE)), eblock(EPC_WAVES * WAVE);
+#define GWL_CE(GR)                                                                                                   \
+  hipLaunchKernelGGL((k_epilogue_cal<ND, GR>), egrid, eblock, 0, s, g, ec, t.kcal, theta, P, B, Bp, sh, pl,          \
+                     (const double*)coef, (const double*)calc, (const double*)part, logl, gradout)
+  if (grad) GWL_CE(true); else GWL_CE(false);
+#undef GWL_CE
   return hipGetLastError();
 }
 
-hipError_t launch_cal(int nd, bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const double* kcal,
-                      const void* tab, const void* gtab, const void* calw, const void* calt, const double* calB,
-                      const double* theta, int P, int64_t B, int64_t Bp, const CalShape& sh, double* coef,
-                      double* calc, double* part, double* logl, double* gradout, hipStream_t s) {
+hipError_t launch_cal(int nd, bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const CalTables& t,
+                      const double* theta, int P, int64_t B, int64_t Bp, int64_t M, const CalShape& sh, double* coef,
+                      double* calc, double* part, int* plan, double* logl, double* gradout, hipStream_t s) {
   switch (nd) {
-#define GWL_CN(N)                                                                                                   \
-  case N:                                                                                                           \
-    return cal_nd<N>(mixed, grad, g, ec, kcal, tab, gtab, calw, calt, calB, theta, P, B, Bp, sh, coef, calc, part, \
-                     logl, gradout, s);
+#define GWL_CN(N) \
+  case N: return cal_nd<N>(mixed, grad, g, ec, t, theta, P, B, Bp, M, sh, coef, calc, part, plan, logl, gradout, s);
     GWL_CN(1)
     GWL_CN(2)
     GWL_CN(3)

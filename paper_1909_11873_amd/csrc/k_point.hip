@@ -38,7 +38,7 @@ __global__ __launch_bounds__(SETUP_WAVES_BANDS * WAVE) void k_setup(EventGeom g,
   const int64_t pc = p < B ? p : B - 1;                  // padding lanes repeat the last point
   if (w < 2) setup_halves<ND>(w, lane, theta + pc * NPARAM, g, ec, rows_s);
   __syncthreads();
-  if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ec, false, true, coef, Bp, p);
+  if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ec, true, coef, Bp, p);
   if (!bh) return;
   double a[NBASIS], T[ND];
 #pragma unroll

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
   const int64_t pc = p < o.B ? p : o.B - 1;
   if (w < 2) setup_halves<ND>(w, lane, o.theta + pc * NPARAM, geo, ev.ec, rows_s);
   __syncthreads();
-  if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ev.ec, false, true, ev.coef, ev.Bp, p);
+  if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ev.ec, true, ev.coef, ev.Bp, p);
   if (ev.bands) {
     double a[NBASIS], T[ND];
 #pragma unroll

@@ -155,10 +155,11 @@ const char* gwl_version(void) { return "gwlike 0.1 (gfx950)"; }
 namespace gwl {
 
 // bands: whether the event may walk band-limited rows (a relative-binning event's grid tables are
-// replaced by its edges', and the calibrated loop and the ISCO cut-off walk every bin)
+// replaced by its edges', and the ISCO cut-off walks every bin); nnode: calibration nodes per
+// detector, whose intervals the rows then keep to (0: none)
 static gwl_status event_create(const double* data, const double* psd, const gwl_detector* dets, int ndet,
                                const double* fgrid, int64_t M, double df, double gmst, unsigned flags, void* stream,
-                               bool bands, gwl_event* out);
+                               bool bands, int nnode, gwl_event* out);
 
 // Band-limited rows of a new event whose grid rows are queued on s: the rows' tables follow the
 // grid's in tab64 and g64 (allocated with room for them).
@@ -195,6 +196,19 @@ static hipError_t make_bands(gwl_event ev, bool uniform, const BandHost& b, hipS
   return e;
 }
 
+// First bins of the calibration's node intervals (nnode - 1 of them, equal in ln f; then M).
+static void cal_intervals(const std::vector<double>& f, int nnode, std::vector<int64_t>& first) {
+  const int64_t M = (int64_t)f.size();
+  const double x0 = log(f.front()), h = (log(f.back()) - x0) / (nnode - 1);
+  first.assign((size_t)nnode, M);
+  for (int64_t k = M - 1; k >= 0; --k) {
+    const double s = std::min(std::max((log(f[(size_t)k]) - x0) / h, 0.0), (double)(nnode - 1));
+    first[(size_t)std::min(std::max((int)floor(s), 0), nnode - 2)] = k;
+  }
+  first[0] = 0;
+  for (int j = nnode - 2; j >= 1; --j) first[j] = std::min(first[j], first[j + 1]);  // empty: where the next starts
+}
+
 // Rows that a point of a black-hole binary near the data's time origin walks (chirp mass ten solar
 // masses, arrival within 0.125 s): what a launch's shape is chosen for.
 static int64_t typical_rows(const BandHead& h, int64_t M) {
@@ -229,7 +243,7 @@ extern "C" {
 gwl_status gwl_event_create(const double* data, const double* psd, const gwl_detector* dets, int ndet,
                             const double* fgrid, int64_t M, double df, double gmst, unsigned flags, void* stream,
                             gwl_event* out) {
-  return event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, !(flags & GWL_F_ISCO_CUTOFF), out);
+  return event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, !(flags & GWL_F_ISCO_CUTOFF), 0, out);
 }
 
 }  // extern "C"
@@ -238,7 +252,7 @@ namespace gwl {
 
 static gwl_status event_create(const double* data, const double* psd, const gwl_detector* dets, int ndet,
                                const double* fgrid, int64_t M, double df, double gmst, unsigned flags, void* stream,
-                               bool bands, gwl_event* out) {
+                               bool bands, int nnode, gwl_event* out) {
   clear_error();
   if (!out) return fail(GWL_E_INVALID, "out is null");
   *out = nullptr;
@@ -273,8 +287,18 @@ static gwl_status event_create(const double* data, const double* psd, const gwl_
   const bool uniform = grid_is_uniform(fh, step);
   BandHost bh;
   bh.head.ncand = 0;
-  if (bands) plan_bands(fh, uniform, step, M + TAB_PAD, bh.head, bh.gen, bh.nrows, bh.kvals);
-  band_blocks(bh.gen, M, bh.blk, bh.nblk);
+  if (bands) {
+    std::vector<int64_t> nodes;
+    if (nnode > 0) cal_intervals(fh, nnode, nodes);
+    plan_bands(fh, uniform, step, M + TAB_PAD, nodes, bh.head, bh.gen, bh.nrows, bh.kvals);
+    band_blocks(bh.gen, M, bh.blk, bh.nblk);
+    for (int sg = 0; nnode > 0 && sg < bh.head.nseg; ++sg)
+      for (int c = bh.head.c0[sg]; c < bh.head.c0[sg + 1]; ++c)
+        for (int q = 0; q < bh.gen[c].rows; ++q) {
+          ev->band_f.push_back(bh.gen[c].fa + (double)(bh.gen[c].n0 + q) * bh.gen[c].h);
+          ev->band_seg.push_back(sg);
+        }
+  }
   ev->M_loop = bands ? typical_rows(bh.head, M) : M;
   const int64_t rows = M + TAB_PAD + (bh.nrows > 0 ? bh.nrows + TAB_PAD : 0);
   const int nblk = prep_blocks(M);
@@ -365,7 +389,7 @@ gwl_status gwl_event_create_rb(const double* data, const double* psd, const gwl_
   if (flags & GWL_F_ISCO_CUTOFF)
     return fail(GWL_E_UNSUPPORTED, "the ISCO cut-off is not available with relative binning");
   gwl_event ev = nullptr;
-  gwl_status st = event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, false, &ev);
+  gwl_status st = event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, false, 0, &ev);
   if (st != GWL_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   // grid on the host, edges
@@ -487,7 +511,6 @@ static void cal_tables(const std::vector<double>& f, const std::vector<double>& 
   w.assign((size_t)M * 4, 0.0);
   tloc.assign((size_t)M, 0.0);
   std::vector<double> W((size_t)M * n, 0.0);  // weights over all nodes (for K1, K2)
-  std::vector<int> jk((size_t)M);
   for (int j = 0; j < n - 1; ++j) j0[j] = std::min(std::max(j - 1, 0), n - 4);
   for (int64_t k = 0; k < M; ++k) {
     double s = (log(f[k]) - x0) / h;
@@ -505,13 +528,10 @@ static void cal_tables(const std::vector<double>& f, const std::vector<double>& 
     wn[n - 1] -= wn[n + 1];
     for (int i = 0; i < 4; ++i) w[(size_t)k * 4 + i] = wn[j0[j] + i + 1];
     for (int i = 0; i < n; ++i) W[(size_t)k * n + i] = wn[i + 1];
-    jk[(size_t)k] = j;
   }
-  for (int j = 0; j <= n - 1; ++j) kb[j] = M;
-  for (int64_t k = M - 1; k >= 0; --k) kb[jk[(size_t)k]] = k;
-  kb[0] = 0;
-  for (int j = n - 2; j >= 1; --j) kb[j] = std::min(kb[j], kb[j + 1]);  // empty intervals start where the next does
-  kb[n - 1] = M;
+  std::vector<int64_t> first;
+  cal_intervals(f, n, first);
+  for (int j = 0; j < n; ++j) kb[j] = first[(size_t)j];
   kcal.assign((size_t)nd * (n + n * n), 0.0);
   for (int d = 0; d < nd; ++d) {
     double* K1 = kcal.data() + (size_t)d * (n + n * n);
@@ -543,11 +563,15 @@ static gwl_status attach_cal(gwl_event ev, const std::vector<double>& frow, cons
   std::vector<double> w, tl, kc, kc_rows, basis, wfull, tfull;
   int j0full[MAXNODE];
   int64_t kbfull[MAXNODE];
-  // the rows' weights (their spline moments are not used: any positive PSD will do), then the
-  // moments over the grid
-  const std::vector<double> psd_rows((size_t)M * ndet, 1.0);
-  cal_tables(frow, psd_rows, ndet, ev->df, nnode, w, tl, ev->cal_j0, ev->cal_kb, kc_rows);
-  cal_tables(fgrid, psd, ndet, ev->df, nnode, wfull, tfull, j0full, kbfull, kc);
+  if (&frow == &fgrid) {
+    cal_tables(fgrid, psd, ndet, ev->df, nnode, w, tl, ev->cal_j0, ev->cal_kb, kc);
+  } else {
+    // the rows' weights (their spline moments are not used: any positive PSD will do), then the
+    // moments over the grid
+    const std::vector<double> psd_rows((size_t)M * ndet, 1.0);
+    cal_tables(frow, psd_rows, ndet, ev->df, nnode, w, tl, ev->cal_j0, ev->cal_kb, kc_rows);
+    cal_tables(fgrid, psd, ndet, ev->df, nnode, wfull, tfull, j0full, kbfull, kc);
+  }
   cal_basis(nnode, ev->cal_j0, basis);
   std::vector<RowCal32> w32((size_t)M);
   for (int64_t k = 0; k < M; ++k)
@@ -559,16 +583,35 @@ static gwl_status attach_cal(gwl_event ev, const std::vector<double>& frow, cons
   w.resize((size_t)(M + TAB_PAD) * 4, 0.0);
   tl.resize((size_t)(M + TAB_PAD), 0.0);
   std::vector<float> t32(tl.begin(), tl.end());
+  // the band-limited rows that follow: their interval's cubic at their own frequency, also a little
+  // beyond the interval's ends
+  const double x0 = log(frow.front()), hx = (log(frow.back()) - x0) / (nnode - 1);
+  for (size_t r = 0; r < ev->band_f.size(); ++r) {
+    const int j = ev->band_seg[r];
+    const double t = (log(ev->band_f[r]) - x0) / hx - j;
+    tl.push_back(t);
+    for (int i = 0; i < 4; ++i) {
+      const double* Bi = &basis[((size_t)j * 4 + i) * 4];
+      w.push_back(fma(fma(fma(Bi[3], t, Bi[2]), t, Bi[1]), t, Bi[0]));
+    }
+  }
+  if (!ev->band_f.empty()) {
+    tl.resize(tl.size() + TAB_PAD, 0.0);
+    w.resize(w.size() + TAB_PAD * 4, 0.0);
+  }
+  std::vector<double>().swap(ev->band_f);
+  std::vector<int>().swap(ev->band_seg);
+  ev->cal_slope = 4.0 / (2.0 * M_PI * hx);
   hipError_t e = hipMalloc((void**)&ev->cal32, sizeof(RowCal32) * (M + TAB_PAD));
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->cal64, sizeof(RowCal64) * (M + TAB_PAD));
+  if (e == hipSuccess) e = hipMalloc((void**)&ev->cal64, sizeof(double) * w.size());
   if (e == hipSuccess) e = hipMalloc((void**)&ev->calt32, sizeof(float) * (M + TAB_PAD));
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->calt64, sizeof(double) * (M + TAB_PAD));
+  if (e == hipSuccess) e = hipMalloc((void**)&ev->calt64, sizeof(double) * tl.size());
   if (e == hipSuccess) e = hipMalloc((void**)&ev->calB, sizeof(double) * basis.size());
   if (e == hipSuccess) e = hipMalloc((void**)&ev->kcal, sizeof(double) * kc.size());
   if (e == hipSuccess) e = hipMemcpy(ev->cal32, w32.data(), sizeof(RowCal32) * (M + TAB_PAD), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(ev->cal64, w.data(), sizeof(RowCal64) * (M + TAB_PAD), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(ev->cal64, w.data(), sizeof(double) * w.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ev->calt32, t32.data(), sizeof(float) * (M + TAB_PAD), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(ev->calt64, tl.data(), sizeof(double) * (M + TAB_PAD), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(ev->calt64, tl.data(), sizeof(double) * tl.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ev->calB, basis.data(), sizeof(double) * basis.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ev->kcal, kc.data(), sizeof(double) * kc.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(e, "calibration tables");
@@ -601,7 +644,7 @@ gwl_status gwl_event_create_cal(const double* data, const double* psd, const gwl
   if (flags & GWL_F_ISCO_CUTOFF)
     return fail(GWL_E_UNSUPPORTED, "the ISCO cut-off is not available with the calibration model");
   gwl_event ev = nullptr;
-  gwl_status st = event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, false, &ev);
+  gwl_status st = event_create(data, psd, dets, ndet, fgrid, M, df, gmst, flags, stream, true, nnode, &ev);
   if (st != GWL_OK) return st;
   std::vector<double> fh, ph;
   st = read_grid(fgrid, psd, ndet, M, (hipStream_t)stream, fh, ph);
@@ -681,46 +724,50 @@ gwl_status gwl_event_info(gwl_event ev, int* ndet, int64_t* M, double* df) {
   return GWL_OK;
 }
 
-// Calibrated evaluation: chunks are pieces of node intervals; workspace from the stream pool.
-// ws_given: a workspace of ws_bytes bytes owned by the caller (a multi-event plan), used instead of
-// the event's own workspace on s
+}  // extern "C"
+
+namespace gwl {
+
+// Launch shape of a calibrated call: every point group's rows in nchunk equal shares, one wavefront
+// each, for about as many wavefronts as the chip holds at the loop's registers (four per SIMD for the
+// value, two for the adjoint: a part-filled second round costs a whole one), of at least 24 rows.
+static CalShape cal_shape(const gwl_event_s* ev, int64_t B, bool grad) {
+  CalShape sh;
+  memset(&sh, 0, sizeof sh);
+  const int n = ev->ncal;
+  sh.nnode = n;
+  sh.npg = (int)((B + WAVE - 1) / WAVE);
+  const int64_t fill = ((grad ? 2048 : 4096) + sh.npg - 1) / sh.npg;
+  sh.nchunk = (int)std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(fill, 4), ev->M_loop / 24, 128}));
+  sh.nbc = (sh.nchunk + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
+  sh.items = sh.npg * sh.nbc;
+  sh.gper = (sh.items + NXCD - 1) / NXCD;
+  for (int j = 0; j < n - 1; ++j) sh.j0[j] = ev->cal_j0[j];
+  for (int j = 0; j < n; ++j) sh.k0[j] = (int)ev->cal_kb[j];
+  return sh;
+}
+
+// set-up rows, calibration rows, sums per chunk, window moments per piece, a plan per point group
+static size_t cal_bytes(const gwl_event_s* ev, const CalShape& sh, bool grad) {
+  const size_t Bp = (size_t)sh.npg * WAVE, nd = ev->ndet, n = ev->ncal;
+  return sizeof(double) * Bp * (NCOEF + 2 * n * nd + sh.nchunk * (size_t)nz_of((int)nd, grad) +
+                                (sh.nchunk + n - 2) * (size_t)nz_win((int)nd, grad)) +
+         sizeof(int) * PLAN_INTS * (size_t)sh.npg;
+}
+
+}  // namespace gwl
+
+extern "C" {
+
+// Calibrated evaluation, in the event's workspace for s, or (a multi-event plan) in ws_given of
+// ws_bytes bytes, owned by the caller.
 static gwl_status run_logl_cal(gwl_event ev, const double* theta, int64_t B, bool mixed, bool grad, double* logl,
                                double* gradout, hipStream_t s, void* ws_given = nullptr, size_t ws_bytes = 0) {
   const int nd = ev->ndet, n = ev->ncal;
-  CalShape sh;
-  memset(&sh, 0, sizeof sh);
-  sh.nnode = n;
-  sh.npg = (int)((B + WAVE - 1) / WAVE);
-  // chunks of about M / want bins, none crossing a node interval (intervals in ln f hold very
-  // different numbers of bins, so each is cut into its own number of pieces)
-  // forward: about six rounds of 8192 wavefronts (on the c1 shapes 48 chunks per point group, the
-  // count the uncalibrated loop's tuning found best for its own chunked launch, which the calibrated
-  // loop keeps; fewer left the chip's second round of wavefronts partly empty); adjoint: the
-  // heuristic, since each of its chunks writes 11 N_det + 8 partial sums per point and more chunks
-  // measured slower
-  const int tuned = grad ? heuristic_nchunk(B, ev->M)
-                         : (int)std::min<int64_t>(ev->M, (6 * 8192 + sh.npg - 1) / sh.npg);
-  const int want = std::min(tuned, MAXCALCHUNK - (n - 1));
-  const int64_t target = std::max<int64_t>(1, (ev->M + want - 1) / want);
-  int nc = 0;
-  for (int j = 0; j < n - 1; ++j) {
-    const int64_t a = ev->cal_kb[j], len = ev->cal_kb[j + 1] - a;
-    const int pieces = (int)std::max<int64_t>(1, (len + target - 1) / target);
-    if (nc + pieces > MAXCALCHUNK) return fail(GWL_E_INTERNAL, "calibrated loop: too many chunks");
-    for (int q = 0; q < pieces; ++q, ++nc) {
-      sh.cj[nc] = j;
-      sh.ck[nc] = (int)(a + len * q / pieces);
-    }
-  }
-  sh.ck[nc] = (int)ev->M;
-  sh.nchunk = nc;
-  sh.nbpg = (sh.npg + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
-  sh.items = sh.nchunk * sh.nbpg;
-  sh.gper = (sh.items + NXCD - 1) / NXCD;
-  for (int j = 0; j < n - 1; ++j) sh.j0[j] = ev->cal_j0[j];
+  const CalShape sh = cal_shape(ev, B, grad);
   const int64_t Bp = (int64_t)sh.npg * WAVE;
-  const int nchunk = sh.nchunk, ncal = 2 * n * nd;
-  const size_t bytes = sizeof(double) * ((size_t)NCOEF * Bp + (size_t)ncal * Bp + (size_t)nchunk * nz_cal(nd, grad) * Bp);
+  const int ncal = 2 * n * nd;
+  const size_t bytes = cal_bytes(ev, sh, grad);
   void* ws = ws_given;
   if (ws_given) {
     if (ws_bytes < bytes) return fail(GWL_E_INTERNAL, "calibrated loop: workspace of %zu bytes, %zu needed", ws_bytes, bytes);
@@ -731,10 +778,11 @@ static gwl_status run_logl_cal(gwl_event ev, const double* theta, int64_t B, boo
   double* coef = (double*)ws;
   double* calc = coef + (size_t)NCOEF * Bp;
   double* part = calc + (size_t)ncal * Bp;
-  hipError_t e = launch_cal(nd, mixed, grad, ev->geom, ev->ec, ev->kcal, mixed ? ev->tab32 : ev->tab64,
-                 mixed ? (const void*)ev->g32 : (const void*)ev->g64, mixed ? (const void*)ev->cal32 : (const void*)ev->cal64,
-                 mixed ? (const void*)ev->calt32 : (const void*)ev->calt64, ev->calB, theta, NPARAM + ncal, B, Bp, sh,
-                 coef, calc, part, logl, gradout, s);
+  int* plan = (int*)(part + ((size_t)sh.nchunk * nz_of(nd, grad) + (size_t)(sh.nchunk + n - 2) * nz_win(nd, grad)) * Bp);
+  const CalTables t = {ev->tab64, ev->tab32, ev->g64, ev->g32, ev->cal64, ev->cal32, ev->calt64, ev->calt32, ev->calB,
+                       ev->kcal, ev->bands, ev->cal_slope};
+  const hipError_t e = launch_cal(nd, mixed, grad, ev->geom, ev->ec, t, theta, NPARAM + ncal, B, Bp, ev->M, sh, coef,
+                                  calc, part, plan, logl, gradout, s);
   if (e != hipSuccess) return hip_fail(e, "launch");
   return GWL_OK;
 }
@@ -951,11 +999,7 @@ gwl_status event_workspace(gwl_event ev, hipStream_t s, size_t bytes, size_t ncn
 
 size_t call_workspace_bytes(const gwl_event_s* ev, int64_t B, bool mixed, bool grad) {
   const int64_t Bp = (B + WAVE - 1) / WAVE * WAVE;
-  if (ev->ncal > 0) {
-    // the calibrated loop uses at most MAXCALCHUNK chunks and 2 nnode nd calibration rows
-    return sizeof(double) * ((size_t)NCOEF * Bp + (size_t)2 * ev->ncal * ev->ndet * Bp +
-                             (size_t)MAXCALCHUNK * nz_cal(ev->ndet, grad) * Bp);
-  }
+  if (ev->ncal > 0) return cal_bytes(ev, cal_shape(ev, B, grad), grad);
   return workspace_bytes(Bp, choose_shape(ev, B, mixed, grad), ev->ndet, grad);
 }
 

@@ -177,18 +177,6 @@ LoopShape heuristic_shape(int64_t B, int64_t M, int64_t rows, bool mixed, bool g
   return make_shape(B, M, W, split(rows, grad ? 12 : 6), 1, 1);
 }
 
-int heuristic_nchunk(int64_t B, int64_t M) {
-  // aim for ~8 wavefronts per SIMD (1024 SIMDs) with chunks of at least 32 bins (short
-  // grids, e.g. relative-binning edges, still fill the chip; measured on 313 edges and 65,536
-  // points, 10 chunks of 32 beat 5 of 63)
-  const int64_t npg = (B + WAVE - 1) / WAVE;
-  int64_t want = (8192 + npg - 1) / npg;
-  const int64_t maxc = (M + 31) / 32;
-  if (want > maxc) want = maxc;
-  if (want < 1) want = 1;
-  return (int)want;
-}
-
 hipError_t fill_theta(double* theta, int64_t B, hipStream_t s, int P) {
   if (B <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill_theta, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, s, theta, B, P);

@@ -174,3 +174,42 @@ def test_grids_without_bands_keep_their_bins():
         for prec, tol in (("fp64", 1e-6), ("mixed", 1e-3)):
             assert np.abs(gw.logl(torch.tensor(th, device=DEV), ev, prec).cpu().numpy() - ref).max() <= tol
         ev.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["prior", "late", "wide", "light", "invalid"])
+@pytest.mark.parametrize("nd,nodes,sigma,f_hi", [(3, 10, 0.05, 700.0), (2, 4, 0.5, 400.0), (1, 16, 0.2, 1024.0)])
+def test_calibrated_rows_match_every_bin(kind, nd, nodes, sigma, f_hi):
+    """The calibrated loop on rows, which keep to the spline's node intervals, against the same bins with
+    two neighbours swapped: such a grid does not increase, so it has no rows. Node values up to half a
+    radian (a phase slope that widens the arrival times), values and all gradients."""
+    spec, f, psd, data, dets = event_inputs(1, f_hi=f_hi, ndet=nd)
+    k = len(f) // 2
+    order = np.r_[0:k, k + 1, k, k + 2:len(f)]
+    mk = lambda i: gw.Event(torch.tensor(np.ascontiguousarray(data[:, i]), device=DEV),
+                            torch.tensor(np.ascontiguousarray(psd[:, i]), device=DEV), dets,
+                            torch.tensor(f[i], device=DEV), spec.df, calibration_nodes=nodes)
+    ev, plain = mk(np.arange(len(f))), mk(order)
+    th = _points(kind, 257, 11)
+    rng = np.random.default_rng(12)
+    th = np.concatenate([th, sigma * rng.standard_normal((len(th), 2 * nodes * nd))], axis=1)
+    t = torch.tensor(th, device=DEV)
+    dn = math.sqrt(sum(float((4 * spec.df * np.abs(d) ** 2 / s).sum()) for d, s in zip(data, psd)))
+    for prec in ("fp64", "mixed"):
+        want = gw.logl(t, plain, prec).cpu().numpy()
+        ok = np.isfinite(want)
+        hn = dn + np.sqrt(np.maximum(dn ** 2 - 2.0 * want[ok], 0.0))
+        tol = 1e-13 * hn * dn + 1e-9 if prec == "fp64" else 1e-3
+        got = gw.logl(t, ev, prec).cpu().numpy()
+        assert np.array_equal(np.isfinite(got), ok)
+        assert (np.abs(got[ok] - want[ok]) <= tol).all(), (prec, np.abs(got[ok] - want[ok]).max())
+        v, g = (x.cpu().numpy() for x in gw.logl_grad(t, ev, prec))
+        vw, gw_ = (x.cpu().numpy() for x in gw.logl_grad(t, plain, prec))
+        assert np.array_equal(np.isfinite(v), ok) and np.array_equal(np.isfinite(g), np.isfinite(gw_))
+        assert (np.abs(v[ok] - want[ok]) <= tol).all()
+        e = scaled_grad_error(g[ok][:, :11], gw_[ok][:, :11])
+        c = np.abs(g[ok][:, 11:] - gw_[ok][:, 11:]) / np.abs(gw_[ok][:, 11:]).max(axis=1, keepdims=True)
+        lim = 2e-9 if prec == "fp64" else 1e-3
+        assert e.max() <= lim and c.max() <= lim, (prec, e.max(), c.max())
+    ev.close()
+    plain.close()
