@@ -182,11 +182,11 @@ __device__ __forceinline__ bool locate_cal(const CalShape& sh, int& c, int& pg) 
   return true;
 }
 
-// Wavefronts per SIMD the register budget must allow: three for the mixed adjoint up to three
-// detectors (its window moments' float64 totals live in LDS for that), otherwise no bound.
+// Wavefronts per SIMD the register budget must allow: two for the mixed adjoint (three spilled 93
+// registers, most of them inside the loop over intervals), otherwise no bound.
 template <int ND, bool MIXED, bool GRAD>
 constexpr int cal_waves_per_eu() {
-  return (MIXED && GRAD && ND <= 3) ? 3 : 1;
+  return (MIXED && GRAD) ? 2 : 1;
 }
 
 // With a plan the float64 kernel takes the groups on float64 rows (all of them in a float64 call) and the
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(cal_waves
   constexpr int NZ = nz_cal(ND, GRAD);
   __shared__ double2 tbl[MIXED ? 1 : PH_TBL];  // the float64 phasor table
   // mixed adjoint: the float64 totals of the 8 ND window moments stay in LDS (one column per
-  // lane, so no barrier), which keeps the kernel at three wavefronts per SIMD instead of two
+  // lane, so no barrier), which saves their registers
   constexpr int NNODE = GRAD ? 8 * ND : 0, NZU = NZ - NNODE;
   __shared__ double ntot[MIXED && GRAD ? 8 * ND : 1][MIXED && GRAD ? BLOCK : 1];
   int c, pg;
@@ -371,59 +371,66 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(cal_waves
   for (int zz = 0; zz < NZU; ++zz) part[((int64_t)c * NZU + zz) * Bp + p] = tot[zz];
 }
 
-// Epilogue, one workgroup of four wavefronts per 64 points, which share the gather. For the value the
+// Epilogue, one workgroup of four wavefronts (eight for the adjoint) per 64 points, which share the gather. For the value the
 // wavefronts also share the detectors' K_det terms, and the first forms it from the set-up rows. The
 // adjoint's window moments are gathered one detector and kind (amplitude or phase) at a time, each
 // summed in chunk order. Chunks come in interval order and an interval's window of four nodes
 // starts at clamp(j - 1, 0, n - 4), which never moves back and moves by at most one node, so a
 // node's moment is final once the window has moved past it: the task keeps the window in four
-// registers and turns each finished node into its gradient at once. The 11 signal-parameter
-// derivatives (one dual-number pass each, the first also giving the value) are then dealt to
-// the wavefronts in turn.
-constexpr int EPC_WAVES = 4;
+// registers and turns each finished node into its gradient at once. These tasks go to six of the
+// wavefronts while the other two take the halves of the point model for the signal parameters.
+constexpr int epc_waves(bool grad) { return grad ? 8 : 4; }
 
-// With alpha the point's amplitude node values for a detector (rows al [n][Bp] of calc):
+// With alpha the point's amplitude node values for a detector (loaded once, into registers):
 // r_i = K1_i + (K2 alpha)_i. The effective K_det = K_det + 2 alpha.K1 + alpha.K2.alpha
 // = K_det + sum_i alpha_i (K1_i + r_i), and the amplitude node gradient takes 2 r_i.
+__device__ __forceinline__ void cal_alpha(const double* __restrict__ calc, int64_t Bp, int n, double (&al)[MAXNODE]) {
+#pragma unroll
+  for (int l = 0; l < MAXNODE; ++l) al[l] = l < n ? calc[(int64_t)l * Bp] : 0.0;
+}
 __device__ __forceinline__ double cal_r(const double* __restrict__ K1, const double* __restrict__ K2,
-                                        const double* __restrict__ al, int64_t Bp, int n, int i) {
+                                        const double (&al)[MAXNODE], int n, int i) {
   double r = K1[i];
-#pragma unroll 4
-  for (int l = 0; l < n; ++l) r = fma(K2[i * n + l], al[(int64_t)l * Bp], r);
+#pragma unroll
+  for (int l = 0; l < MAXNODE; ++l)
+    if (l < n) r = fma(K2[i * n + l], al[l], r);
   return r;
 }
 
 template <int ND, bool GRAD>
-__global__ __launch_bounds__(EPC_WAVES * WAVE) void k_epilogue_cal(
+__global__ __launch_bounds__(epc_waves(GRAD) * WAVE) void k_epilogue_cal(
     EventGeom g, const EventConst* __restrict__ ec, const double* __restrict__ kcal, const double* __restrict__ theta,
     int P, int64_t B, int64_t Bp, CalShape sh, const int* __restrict__ plan, const double* __restrict__ coef,
     const double* __restrict__ calc, const double* __restrict__ part, double* __restrict__ logl,
     double* __restrict__ grad) {
-  constexpr int NZU = nz_of(ND, GRAD), NNODE = 8 * ND, NW = EPC_WAVES;
+  constexpr int NZU = nz_of(ND, GRAD), NNODE = 8 * ND, NW = epc_waves(GRAD);
   __shared__ double acc_s[NZU][WAVE];
   __shared__ double ks_s[ND][WAVE];   // K_det's calibration term per point
+  __shared__ double xs[GRAD ? GRAD_LDS : 1][WAVE];
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // p < Bp: the partial sums and set-up rows have Bp rows
   const int n = sh.nnode, nchunk = sh.nchunk;
-  for (int z = w; z < NZU; z += NW) {
-    double a = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < nchunk; ++c) a += part[((int64_t)c * NZU + z) * Bp + p];
-    acc_s[z][lane] = a;
-  }
-  const double nan = __builtin_nan("");
-  const double amp = coef[CO_AMP * Bp + p];              // NaN for an invalid point
-  // the tasks start with the wavefront after the one that took the last sum
-  int t = w - NZU % NW;
-  if (t < 0) t += NW;
+  gather_share<NZU, NW>(part, nchunk, Bp, p, w, lane, acc_s);
   if constexpr (GRAD) {
+    const int64_t pc = p < B ? p : B - 1;
+    double th[NPARAM];
+    GradParts<ND> r;
+    __syncthreads();
+    if (w < 2) {
+#pragma unroll
+      for (int i = 0; i < NPARAM; ++i) th[i] = theta[pc * P + i];
+      gradient_parts<ND>(w, lane, acc_s, th, g, xs, r);
+    }
+    const double amp = coef[CO_AMP * Bp + p];            // NaN for an invalid point
     // node gradients: amplitude A m_i - 1/2 A^2 |Q_det|^2 2 r_i, phase -A m_i
     const CalRows cr_(sh, plan, (int)blockIdx.x);
     const double* win = part + (int64_t)nchunk * NZU * Bp;
-    for (; t < 2 * ND; t += NW) {
-      const int d = t >> 1, kind = t & 1;
-      const double* al = calc + (int64_t)(2 * n * d) * Bp + p;
+    for (int i = w - 2; w >= 2 && i < 2 * ND; i += NW - 2) {
+      const int d = i >> 1, kind = i & 1;
+      const double* alp = calc + (int64_t)(2 * n * d) * Bp + p;
+      double al[MAXNODE];
+      cal_alpha(alp, Bp, kind ? 0 : n, al);
       const double* K1 = kcal + (int64_t)d * (n + n * n);
       const double* K2 = K1 + n;
       const double qr = coef[(int64_t)(CO_QR + d) * Bp + p], qi = coef[(int64_t)(CO_QI + d) * Bp + p];
@@ -436,32 +443,52 @@ __global__ __launch_bounds__(EPC_WAVES * WAVE) void k_epilogue_cal(
         if (kind) {
           x = -amp * m;
         } else {
-          const double r = cal_r(K1, K2, al, Bp, n, i);
-          ks = fma(al[(int64_t)i * Bp], K1[i] + r, ks);
+          const double r = cal_r(K1, K2, al, n, i);
+          ks = fma(alp[(int64_t)i * Bp], K1[i] + r, ks);
           x = amp * m - hh * r;
         }
         if (p < B) out[i] = x;
       };
       double mom[4] = {0.0, 0.0, 0.0, 0.0};
       int wb = 0;   // the window holds nodes wb .. wb + 3
-      int base = 0;
-      for (int j = 0; j < n - 1; ++j) {
-        const int rows = cr_.rows(j);
-        if (rows == 0) continue;
-        for (; wb < sh.j0[j]; ++wb) {
-          finish(wb, mom[0]);
-          mom[0] = mom[1];
-          mom[1] = mom[2];
-          mom[2] = mom[3];
-          mom[3] = 0.0;
-        }
-        // the chunks that hold a piece of the interval
-        const int ca = base / cr_.chunk, cb = (base + rows - 1) / cr_.chunk;
-        base += rows;
-#pragma unroll 4
-        for (int c = ca; c <= cb; ++c) {
+      // the pieces (chunk, interval) in order, WB at a time so that their loads are in flight together
+      constexpr int WB = 4;
+      int j = 0, ch = 0, end = cr_.rows(0);             // next piece; end: rows up to the end of interval j
+      while (j < n - 1) {
+        int jj[WB], at[WB], m = 0;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) mom[i] += win[((int64_t)(c + j) * NNODE + wbase + i) * Bp + p];
+        for (int q = 0; q < WB; ++q) {
+          while (j < n - 1 && (end <= ch * cr_.chunk || cr_.rows(j) == 0)) {   // nothing of interval j from here on
+            ++j;
+            if (j < n - 1) end += cr_.rows(j);
+          }
+          jj[q] = j < n - 1 ? j : 0;
+          at[q] = j < n - 1 ? ch + j : 0;
+          m += j < n - 1 ? 1 : 0;
+          if (j < n - 1 && end >= (ch + 1) * cr_.chunk) {
+            ++ch;
+          } else if (j < n - 1) {
+            ++j;
+            if (j < n - 1) end += cr_.rows(j);
+          }
+        }
+        double v[WB][4];
+#pragma unroll
+        for (int q = 0; q < WB; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[q][i] = q < m ? win[((int64_t)at[q] * NNODE + wbase + i) * Bp + p] : 0.0;
+#pragma unroll
+        for (int q = 0; q < WB; ++q) {
+          if (q >= m) break;
+          for (; wb < sh.j0[jj[q]]; ++wb) {
+            finish(wb, mom[0]);
+            mom[0] = mom[1];
+            mom[1] = mom[2];
+            mom[2] = mom[3];
+            mom[3] = 0.0;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) mom[i] += v[q][i];
         }
       }
 #pragma unroll
@@ -470,40 +497,34 @@ __global__ __launch_bounds__(EPC_WAVES * WAVE) void k_epilogue_cal(
       for (int i = wb + 4; i < n; ++i) finish(i, 0.0);
       if (!kind) ks_s[d][lane] = ks;
     }
+    __syncthreads();
+    if (w > 1 || p >= B) return;
+    double K[ND];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) K[d] = ec->K[d] + ks_s[d][lane];
+    gradient_finish<ND>(w, lane, th, K, xs, r, logl + p, grad + p * P);
   } else {
+    // the K_det terms start with the wavefront after the one that took the last sum
+    int t = w - NZU % NW;
+    if (t < 0) t += NW;
     for (; t < ND; t += NW) {
-      const double* al = calc + (int64_t)(2 * n * t) * Bp + p;
+      const double* alp = calc + (int64_t)(2 * n * t) * Bp + p;
+      double al[MAXNODE];
+      cal_alpha(alp, Bp, n, al);
       const double* K1 = kcal + (int64_t)t * (n + n * n);
       double ks = 0.0;
-      for (int i = 0; i < n; ++i) ks = fma(al[(int64_t)i * Bp], K1[i] + cal_r(K1, K1 + n, al, Bp, n, i), ks);
+      for (int i = 0; i < n; ++i) ks = fma(alp[(int64_t)i * Bp], K1[i] + cal_r(K1, K1 + n, al, n, i), ks);
       ks_s[t][lane] = ks;
     }
-  }
-  __syncthreads();
-  if (p >= B) return;
-  EventConst ek = *ec;
+    __syncthreads();
+    if (w != 0 || p >= B) return;
+    EventConst ek = *ec;
 #pragma unroll
-  for (int d = 0; d < ND; ++d) ek.K[d] += ks_s[d][lane];
-  if constexpr (!GRAD) {
-    if (w != 0) return;
+    for (int d = 0; d < ND; ++d) ek.K[d] += ks_s[d][lane];
     double acc[NZU];
 #pragma unroll
     for (int z = 0; z < NZU; ++z) acc[z] = acc_s[z][lane];
     logl[p] = epilogue_value_rows<ND, NZU>(acc, coef, Bp, p, ek, 1.0);
-  } else {
-    double acc[NZU], th[NPARAM];
-#pragma unroll
-    for (int z = 0; z < NZU; ++z) acc[z] = acc_s[z][lane];
-#pragma unroll
-    for (int i = 0; i < NPARAM; ++i) th[i] = theta[p * P + i];
-#pragma unroll 1
-    for (int j = w; j < NPARAM; j += NW) {
-      bool valid;
-      double value;
-      const double gj = epilogue_gradient_pass<ND>(acc, th, g, ek, 1.0, j, valid, value);
-      grad[p * P + j] = valid ? gj : nan;
-      if (j == 0) logl[p] = valid ? value : nan;
-    }
   }
 }
 
@@ -530,7 +551,7 @@ static hipError_t cal_nd(bool mixed, bool grad, const EventGeom& g, const EventC
     if (grad) GWL_CB(false, true); else GWL_CB(false, false);
   }
 #undef GWL_CB
-  const dim3 egrid((unsigned)((B + WAVE - 1) / WAVE)), eblock(EPC_WAVES * WAVE);
+  const dim3 egrid((unsigned)((B + WAVE - 1) / WAVE)), eblock(epc_waves(grad) * WAVE);
 #define GWL_CE(GR)                                                                                                   \
   hipLaunchKernelGGL((k_epilogue_cal<ND, GR>), egrid, eblock, 0, s, g, ec, t.kcal, theta, P, B, Bp, sh, pl,          \
                      (const double*)coef, (const double*)calc, (const double*)part, logl, gradout)

@@ -78,11 +78,9 @@ hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, const 
 // With the ISCO cut-off (fgrid and kcum given), <h|h> takes the kept bins' share of K_det; the
 // cut moves with the masses in steps, so it adds nothing to the derivative.
 //
-// One workgroup per 64 points, EPG_WAVES wavefronts (the epilogue needs about 256 registers, so a
-// SIMD holds one such wavefront and a CU four): the wavefronts first add the points' partial sums
-// over the chunks (in chunk order, each wavefront its share of the sums) into LDS, then each runs
-// the dual-number passes of the parameters j = w, w + EPG_WAVES, ...: three passes of latency
-// instead of eleven, and four times the SIMDs of one thread per point.
+// One workgroup per 64 points: EPG_WAVES wavefronts first add the points' partial sums over the
+// chunks (in chunk order, each wavefront its share of the sums) into LDS, then two of them take
+// the halves of the point model.
 constexpr int EPG_WAVES = 4;
 template <int ND>
 __global__ __launch_bounds__(EPG_WAVES * WAVE) void k_epilogue_grad(EventGeom g, const EventConst* __restrict__ ec,
@@ -95,38 +93,29 @@ __global__ __launch_bounds__(EPG_WAVES * WAVE) void k_epilogue_grad(EventGeom g,
                                                                     const double* __restrict__ kcum, int64_t M) {
   constexpr int NZ = nz_of(ND, true);
   __shared__ double acc_s[NZ][WAVE];
+  __shared__ double xs[GRAD_LDS][WAVE];
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // p < Bp: the partial sums have Bp rows
-  for (int z = w; z < NZ; z += EPG_WAVES) {
-    double a = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < nchunk; ++c) a += part[((int64_t)c * NZ + z) * Bp + p];
-    acc_s[z][lane] = a;
-  }
-  __syncthreads();
-  if (p >= B) return;
-  EventConst e = *ec;
-  double acc[NZ];
-#pragma unroll
-  for (int z = 0; z < NZ; ++z) acc[z] = acc_s[z][lane];
+  const int64_t pc = p < B ? p : B - 1;
+  gather_share<NZ, EPG_WAVES>(part, nchunk, Bp, p, w, lane, acc_s);
   double th[NPARAM];
 #pragma unroll
-  for (int i = 0; i < NPARAM; ++i) th[i] = theta[p * NPARAM + i];
-  if (fgrid) {
-    const int kc = isco_bins(th[0], th[1], fgrid, M, e);
+  for (int i = 0; i < NPARAM; ++i) th[i] = theta[pc * NPARAM + i];
+  __syncthreads();
+  GradParts<ND> r;
+  gradient_parts<ND>(w, lane, acc_s, th, g, xs, r);
+  __syncthreads();
+  if (w > 1 || p >= B) return;
+  double K[ND];
 #pragma unroll
-    for (int d = 0; d < ND; ++d) e.K[d] = kcum[(int64_t)d * (M + 1) + kc];
+  for (int d = 0; d < ND; ++d) K[d] = ec->K[d];
+  if (fgrid) {
+    const int kc = isco_bins(th[0], th[1], fgrid, M, *ec);
+#pragma unroll
+    for (int d = 0; d < ND; ++d) K[d] = kcum[(int64_t)d * (M + 1) + kc];
   }
-  const double nan = __builtin_nan("");
-#pragma unroll 1
-  for (int j = w; j < NPARAM; j += EPG_WAVES) {
-    bool valid;
-    double value;
-    const double gj = epilogue_gradient_pass<ND>(acc, th, g, e, 1.0, j, valid, value);
-    grad[p * NPARAM + j] = valid ? gj : nan;
-    if (j == 0) logl[p] = valid ? value : nan;
-  }
+  gradient_finish<ND>(w, lane, th, K, xs, r, logl + p, grad + p * NPARAM);
 }
 
 hipError_t launch_epilogue(int nd, bool grad, const EventGeom& g, const EventConst* ec, const double* theta,

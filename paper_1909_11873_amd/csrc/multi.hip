@@ -63,8 +63,9 @@ struct MultiIODev {
 };
 
 struct MultiCtl {
-  unsigned int next;       // queue head
+  unsigned long long next; // queue head, in 64ths of an item
   unsigned int total;      // items in the queue
+  unsigned int pad;
   unsigned long long t0;   // device clock at the start of the launch
   unsigned long long tend; // device clock at the end of the epilogue
 };
@@ -78,7 +79,7 @@ __global__ void k_multi_reset(MultiCtl* __restrict__ ctl, unsigned int* __restri
     tev[i] = 0ull;
   }
   if (i == 0) {
-    ctl->next = 0u;
+    ctl->next = 0ull;
     ctl->total = 0u;
     ctl->t0 = wall_clock64();
     ctl->tend = 0ull;
@@ -162,13 +163,13 @@ __global__ __launch_bounds__(BLOCK, (ND <= 3 ? 4 : 3)) void k_multi_bins(
   const int lane = threadIdx.x % WAVE;
   const int total = (int)__builtin_amdgcn_readfirstlane(ctl->total);
   for (;;) {
-    // One ticket per wavefront. Every lane takes part in the atomic (lane 0 adds 1, the others
-    // 0) and the first lane's old value is read back as a scalar, so the loop is wave-uniform:
-    // a per-lane broadcast (a shuffle inside lane-divergent control flow) lets the compiler
-    // separate the lane that takes the ticket from the lanes that read it, and those then
-    // never see the queue advance.
-    const unsigned int ticket = atomicAdd(&ctl->next, lane == 0 ? 1u : 0u);
-    const int it = (int)__builtin_amdgcn_readfirstlane(ticket);
+    // One ticket per wavefront. Every lane takes part in the atomic, and the first lane's old value is
+    // read back as a scalar, so the loop is wave-uniform: an atomic in a branch of one lane, or a
+    // per-lane broadcast, lets the compiler separate the lane that takes the ticket from the others,
+    // which then never see the queue advance. With the same addend in every lane the compiler issues
+    // one atomic of 64 for the wavefront, so tickets count in 64ths.
+    const unsigned long long ticket = atomicAdd(&ctl->next, 1ull) / WAVE;
+    const int it = (int)__builtin_amdgcn_readfirstlane((unsigned int)ticket);
     if (it >= total) break;
     const int2 item = items[it];
     const int2 gp = grp[item.x];
@@ -215,16 +216,13 @@ __global__ __launch_bounds__(BLOCK, (ND <= 3 ? 4 : 3)) void k_multi_bins(
     global_as_ptr<double> part = (global_as_ptr<double>)ev.part;
 #pragma unroll
     for (int z = 0; z < NZ; ++z) part[((int64_t)c * NZ + z) * ev.Bp + p] = tot[z];
-    const unsigned int prev = atomicAdd(&done[e], lane == 0 ? 1u : 0u);
+    const unsigned int prev = atomicAdd(&done[e], 1u);   // in 64ths, as the tickets
     const unsigned int d = __builtin_amdgcn_readfirstlane(prev);
-    if (d + 1u == items_of[e] && lane == 0) tev[e] = wall_clock64();
+    if (d + WAVE == items_of[e] * WAVE && lane == 0) tev[e] = wall_clock64();
   }
 }
 
-// The gradient's epilogue: one workgroup of four wavefronts per group, as k_epilogue_grad. The
-// wavefronts add the group's partial sums over its chunks together, then share the dual-number
-// passes. (With every group walking its bins in up to 163 chunks one lane per point, with all sums
-// of eight chunks in flight, was the faster form; a group now has a handful of chunks.)
+// The gradient's epilogue: one workgroup of four wavefronts per group, as k_epilogue_grad.
 constexpr int MULTI_EPG_WAVES = 4;
 template <int ND>
 __global__ __launch_bounds__(MULTI_EPG_WAVES * WAVE) void k_multi_epilogue_grad(
@@ -232,6 +230,7 @@ __global__ __launch_bounds__(MULTI_EPG_WAVES * WAVE) void k_multi_epilogue_grad(
     const int2* __restrict__ grp, const int* __restrict__ plans, MultiCtl* __restrict__ ctl) {
   constexpr int NZ = nz_of(ND, true);
   __shared__ double acc_s[NZ][WAVE];
+  __shared__ double xs[GRAD_LDS][WAVE];
   const int2 gp = grp[blockIdx.x];
   const MultiEvDev ev = evs[gp.x];
   const MultiIODev o = io[gp.x];
@@ -239,29 +238,20 @@ __global__ __launch_bounds__(MULTI_EPG_WAVES * WAVE) void k_multi_epilogue_grad(
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)gp.y * WAVE + lane;
-  for (int z = w; z < NZ; z += MULTI_EPG_WAVES) {
-    double a = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < n; ++c) a += ev.part[((int64_t)c * NZ + z) * ev.Bp + p];
-    acc_s[z][lane] = a;
-  }
+  const int64_t pc = p < o.B ? p : o.B - 1;
+  gather_share<NZ, MULTI_EPG_WAVES>(ev.part, n, ev.Bp, p, w, lane, acc_s);
+  double th[NPARAM];
+#pragma unroll
+  for (int i = 0; i < NPARAM; ++i) th[i] = o.theta[pc * NPARAM + i];
   __syncthreads();
-  if (p < o.B) {
-    const EventConst ec = *ev.ec;
-    double acc[NZ], th[NPARAM];
+  GradParts<ND> r;
+  gradient_parts<ND>(w, lane, acc_s, th, geoms[gp.x], xs, r);
+  __syncthreads();
+  if (w < 2 && p < o.B) {
+    double K[ND];
 #pragma unroll
-    for (int z = 0; z < NZ; ++z) acc[z] = acc_s[z][lane];
-#pragma unroll
-    for (int i = 0; i < NPARAM; ++i) th[i] = o.theta[p * NPARAM + i];
-    const double nan = __builtin_nan("");
-#pragma unroll 1
-    for (int j = w; j < NPARAM; j += MULTI_EPG_WAVES) {
-      bool valid;
-      double value;
-      const double gj = epilogue_gradient_pass<ND>(acc, th, geoms[gp.x], ec, 1.0, j, valid, value);
-      o.grad[p * NPARAM + j] = valid ? gj : nan;
-      if (j == 0) o.logl[p] = valid ? value : nan;
-    }
+    for (int d = 0; d < ND; ++d) K[d] = ev.ec->K[d];
+    gradient_finish<ND>(w, lane, th, K, xs, r, o.logl + p, o.grad + p * NPARAM);
   }
   if (threadIdx.x == 0) atomicMax(&ctl->tend, wall_clock64());
 }
