@@ -46,6 +46,8 @@ struct gwl_event_s {
   double gmst = 0.0;
   gwl_detector dets[GWL_MAX_DET] = {};
   gwl::EventGeom geom = {};
+  void* slab = nullptr;              // the allocation that holds the tables and constants below
+  void* cal_slab = nullptr;          // and the calibration model's
   void* tab64 = nullptr;             // RowF64<ndet>[M]
   void* tab32 = nullptr;             // RowMixed<ndet>[M]
   gwl::RowGradF32* g32 = nullptr;    // [M]

@@ -171,30 +171,16 @@ struct BandHost {
   int64_t nrows = 0, kvals = 0;
 };
 
-static hipError_t make_bands(gwl_event ev, bool uniform, const BandHost& b, hipStream_t s) {
-  BandGen* gen = nullptr;
-  int2* blk = nullptr;
-  double2* kv = nullptr;
-  hipError_t e = hipMalloc((void**)&ev->bands, sizeof(BandHead));
-  // one scratch allocation: the bands, the workgroups' rows, the kernel values
-  const size_t ng = sizeof(BandGen) * b.gen.size(), nb = sizeof(int2) * b.blk.size();
-  const size_t og = 0, ob = (ng + 255) / 256 * 256, ok = ob + (nb + 255) / 256 * 256;
-  char* scratch = nullptr;
-  if (e == hipSuccess) e = hipMalloc((void**)&scratch, ok + sizeof(double2) * (size_t)(b.kvals + 1));
-  if (e == hipSuccess) {
-    gen = (BandGen*)(scratch + og);
-    blk = (int2*)(scratch + ob);
-    kv = (double2*)(scratch + ok);
-    e = hipMemcpyAsync(ev->bands, &b.head, sizeof(BandHead), hipMemcpyHostToDevice, s);
+// One device allocation for several arrays: take() the offsets, then base + offset (an allocation, and
+// the wait when it is freed, takes longer than preparing a small event's tables).
+struct Slab {
+  size_t bytes = 0;
+  size_t take(size_t n) {
+    const size_t at = bytes;
+    bytes += (n + 255) / 256 * 256;
+    return at;
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(gen, b.gen.data(), ng, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(blk, b.blk.data(), nb, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = launch_bands(ev->ndet, uniform, gen, (int)b.gen.size(), blk, b.nblk, kv, ev->tab64, ev->g64, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (scratch) (void)hipFree(scratch);
-  return e;
-}
+};
 
 // First bins of the calibration's node intervals (nnode - 1 of them, equal in ln f; then M).
 static void cal_intervals(const std::vector<double>& f, int nnode, std::vector<int64_t>& first) {
@@ -302,24 +288,55 @@ static gwl_status event_create(const double* data, const double* psd, const gwl_
   ev->M_loop = bands ? typical_rows(bh.head, M) : M;
   const int64_t rows = M + TAB_PAD + (bh.nrows > 0 ? bh.nrows + TAB_PAD : 0);
   const int nblk = prep_blocks(M);
-  double* blockpart = nullptr;
-  e = hipMalloc(&ev->tab64, row64_bytes(ndet) * rows);
-  if (e == hipSuccess) e = hipMalloc(&ev->tab32, row32_bytes(ndet) * (M + TAB_PAD));
+  Slab keep, work;
+  const size_t o64 = keep.take(row64_bytes(ndet) * rows), o32 = keep.take(row32_bytes(ndet) * (M + TAB_PAD));
+  const size_t og32 = keep.take(sizeof(RowGradF32) * M);
+  const size_t og64 = keep.take(sizeof(RowGradF64) * (bh.nrows > 0 ? rows : M));
+  const size_t oec = keep.take(sizeof(EventConst)), obh = keep.take(bh.nrows > 0 ? sizeof(BandHead) : 0);
+  const size_t wpart = work.take(sizeof(double) * prep_scratch_doubles(ndet, M));
+  const size_t wgen = work.take(sizeof(BandGen) * bh.gen.size()), wblk = work.take(sizeof(int2) * bh.blk.size());
+  const size_t wkv = work.take(sizeof(double2) * (size_t)bh.kvals);
+  char *scratch = nullptr, *slab = nullptr;
+  e = hipMalloc((void**)&slab, keep.bytes);
+  if (e == hipSuccess) {
+    ev->slab = slab;
+    ev->tab64 = slab + o64;
+    ev->tab32 = slab + o32;
+    ev->g32 = (RowGradF32*)(slab + og32);
+    ev->g64 = (RowGradF64*)(slab + og64);
+    ev->ec = (EventConst*)(slab + oec);
+    e = hipMalloc((void**)&scratch, work.bytes);
+  }
   if (e == hipSuccess)
     e = hipMemsetAsync((char*)ev->tab64 + row64_bytes(ndet) * M, 0, row64_bytes(ndet) * TAB_PAD, s);
   if (e == hipSuccess && bh.nrows > 0)
     e = hipMemsetAsync((char*)ev->tab64 + row64_bytes(ndet) * (rows - TAB_PAD), 0, row64_bytes(ndet) * TAB_PAD, s);
   if (e == hipSuccess)
     e = hipMemsetAsync((char*)ev->tab32 + row32_bytes(ndet) * M, 0, row32_bytes(ndet) * TAB_PAD, s);
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->g32, sizeof(RowGradF32) * M);
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->g64, sizeof(RowGradF64) * (bh.nrows > 0 ? rows : M));
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->ec, sizeof(EventConst));
-  if (e == hipSuccess) e = hipMalloc((void**)&blockpart, sizeof(double) * prep_scratch_doubles(ndet, M));
   if (e == hipSuccess)
-    e = launch_prep(ndet, data, psd, fgrid, M, df, ev->tab64, ev->tab32, ev->g32, ev->g64, blockpart, nblk, ev->ec, s);
+    e = launch_prep(ndet, data, psd, fgrid, M, df, ev->tab64, ev->tab32, ev->g32, ev->g64, (double*)(scratch + wpart),
+                    nblk, ev->ec, s);
+  // the band-limited rows, from the grid's (after rejected inputs they are never used)
+  if (e == hipSuccess && bh.nrows > 0) {
+    ev->bands = (BandHead*)(slab + obh);
+    e = hipMemcpyAsync(ev->bands, &bh.head, sizeof(BandHead), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(scratch + wgen, bh.gen.data(), sizeof(BandGen) * bh.gen.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(scratch + wblk, bh.blk.data(), sizeof(int2) * bh.blk.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+      e = launch_bands(ndet, uniform, (const BandGen*)(scratch + wgen), (int)bh.gen.size(), (const int2*)(scratch + wblk),
+                       bh.nblk, (double2*)(scratch + wkv), ev->tab64, ev->g64, s);
+  }
   if (e == hipSuccess) e = hipMemcpyAsync(&ev->ech, ev->ec, sizeof(EventConst), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (blockpart) (void)hipFree(blockpart);
+  if (e == hipSuccess) {
+    ev->ech.uniform = uniform ? 1 : 0;
+    ev->ech.grid_df = step;
+    e = hipMemcpyAsync(ev->ec, &ev->ech, sizeof(EventConst), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+  }
+  if (scratch) (void)hipFree(scratch);
   if (e != hipSuccess) {
     gwl_event_destroy(ev);
     return hip_fail(e, "event preparation");
@@ -328,15 +345,6 @@ static gwl_status event_create(const double* data, const double* psd, const gwl_
     gwl_event_destroy(ev);
     return fail(GWL_E_INVALID, "rejected inputs: every PSD value and frequency must be finite and positive and "
                                "every data value finite");
-  }
-  ev->ech.uniform = uniform ? 1 : 0;
-  ev->ech.grid_df = step;
-  e = hipMemcpyAsync(ev->ec, &ev->ech, sizeof(EventConst), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess && bh.nrows > 0) e = make_bands(ev, uniform, bh, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
-    gwl_event_destroy(ev);
-    return hip_fail(e, "event preparation");
   }
   if (flags & GWL_F_ISCO_CUTOFF) {
     st = isco_tables(ev, fgrid, psd, s);
@@ -405,9 +413,11 @@ gwl_status gwl_event_create_rb(const double* data, const double* psd, const gwl_
   // fiducial coefficients through the ordinary set-up (no offsets, no gain)
   double *th = nullptr, *coef = nullptr, *w = nullptr;
   int64_t* d_idx = nullptr;
+  char* slab = nullptr;
   void *tab64 = nullptr, *tab32 = nullptr;
   RowGradF32* g32 = nullptr;
   RowGradF64* g64 = nullptr;
+  EventConst* ec = nullptr;
   std::vector<double> hcoef((size_t)NCOEF * WAVE);
   const int nd = ev->ndet;
   e = hipMalloc((void**)&th, sizeof(double) * NPARAM);
@@ -438,32 +448,37 @@ gwl_status gwl_event_create_rb(const double* data, const double* psd, const gwl_
   if (e == hipSuccess) e = hipMalloc((void**)&d_idx, sizeof(int64_t) * nedge);
   if (e == hipSuccess) e = hipMemcpyAsync(d_idx, idx.data(), sizeof(int64_t) * nedge, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMalloc((void**)&w, sizeof(double) * rb_scratch_doubles(nd, nedge));
-  if (e == hipSuccess) e = hipMalloc(&tab64, row64_bytes(nd) * (nedge + TAB_PAD));
-  if (e == hipSuccess) e = hipMalloc(&tab32, row32_bytes(nd) * (nedge + TAB_PAD));
+  Slab keep;
+  const size_t o64 = keep.take(row64_bytes(nd) * (nedge + TAB_PAD)), o32 = keep.take(row32_bytes(nd) * (nedge + TAB_PAD));
+  const size_t og32 = keep.take(sizeof(RowGradF32) * nedge), og64 = keep.take(sizeof(RowGradF64) * nedge);
+  const size_t oec = keep.take(sizeof(EventConst));
+  if (e == hipSuccess) e = hipMalloc((void**)&slab, keep.bytes);
+  if (e == hipSuccess) {
+    tab64 = slab + o64;
+    tab32 = slab + o32;
+    g32 = (RowGradF32*)(slab + og32);
+    g64 = (RowGradF64*)(slab + og64);
+    ec = (EventConst*)(slab + oec);
+    e = hipMemcpyAsync(ec, ev->ec, sizeof(EventConst), hipMemcpyDeviceToDevice, s);
+  }
   if (e == hipSuccess) e = hipMemsetAsync((char*)tab64 + row64_bytes(nd) * nedge, 0, row64_bytes(nd) * TAB_PAD, s);
   if (e == hipSuccess) e = hipMemsetAsync((char*)tab32 + row32_bytes(nd) * nedge, 0, row32_bytes(nd) * TAB_PAD, s);
-  if (e == hipSuccess) e = hipMalloc((void**)&g32, sizeof(RowGradF32) * nedge);
-  if (e == hipSuccess) e = hipMalloc((void**)&g64, sizeof(RowGradF64) * nedge);
-  if (e == hipSuccess) e = launch_rb(nd, ev->tab64, ev->g32, ev->g64, d_idx, nedge, w, ev->ec, tab64, tab32, g32, g64, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(&ev->ech, ev->ec, sizeof(EventConst), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = launch_rb(nd, ev->tab64, ev->g32, ev->g64, d_idx, nedge, w, ec, tab64, tab32, g32, g64, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(&ev->ech, ec, sizeof(EventConst), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   (void)hipFree(th);
   (void)hipFree(coef);
   if (d_idx) (void)hipFree(d_idx);
   if (w) (void)hipFree(w);
   if (e != hipSuccess) {
-    if (tab64) (void)hipFree(tab64);
-    if (tab32) (void)hipFree(tab32);
-    if (g32) (void)hipFree(g32);
-    if (g64) (void)hipFree(g64);
+    if (slab) (void)hipFree(slab);
     gwl_event_destroy(ev);
     return hip_fail(e, "relative-binning tables");
   }
   // the event now walks the edges
-  (void)hipFree(ev->tab64);
-  (void)hipFree(ev->tab32);
-  (void)hipFree(ev->g32);
-  (void)hipFree(ev->g64);
+  (void)hipFree(ev->slab);
+  ev->slab = slab;
+  ev->ec = ec;
   ev->tab64 = tab64;
   ev->tab32 = tab32;
   ev->g32 = g32;
@@ -602,12 +617,21 @@ static gwl_status attach_cal(gwl_event ev, const std::vector<double>& frow, cons
   std::vector<double>().swap(ev->band_f);
   std::vector<int>().swap(ev->band_seg);
   ev->cal_slope = 4.0 / (2.0 * M_PI * hx);
-  hipError_t e = hipMalloc((void**)&ev->cal32, sizeof(RowCal32) * (M + TAB_PAD));
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->cal64, sizeof(double) * w.size());
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->calt32, sizeof(float) * (M + TAB_PAD));
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->calt64, sizeof(double) * tl.size());
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->calB, sizeof(double) * basis.size());
-  if (e == hipSuccess) e = hipMalloc((void**)&ev->kcal, sizeof(double) * kc.size());
+  Slab keep;
+  const size_t o32 = keep.take(sizeof(RowCal32) * (M + TAB_PAD)), o64 = keep.take(sizeof(double) * w.size());
+  const size_t ot32 = keep.take(sizeof(float) * (M + TAB_PAD)), ot64 = keep.take(sizeof(double) * tl.size());
+  const size_t ob = keep.take(sizeof(double) * basis.size()), ok = keep.take(sizeof(double) * kc.size());
+  char* slab = nullptr;
+  hipError_t e = hipMalloc((void**)&slab, keep.bytes);
+  if (e == hipSuccess) {
+    ev->cal_slab = slab;
+    ev->cal32 = (RowCal32*)(slab + o32);
+    ev->cal64 = (RowCal64*)(slab + o64);
+    ev->calt32 = (float*)(slab + ot32);
+    ev->calt64 = (double*)(slab + ot64);
+    ev->calB = (double*)(slab + ob);
+    ev->kcal = (double*)(slab + ok);
+  }
   if (e == hipSuccess) e = hipMemcpy(ev->cal32, w32.data(), sizeof(RowCal32) * (M + TAB_PAD), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ev->cal64, w.data(), sizeof(double) * w.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ev->calt32, t32.data(), sizeof(float) * (M + TAB_PAD), hipMemcpyHostToDevice);
@@ -689,20 +713,10 @@ gwl_status gwl_event_destroy(gwl_event ev) {
     if (w.cnt) (void)hipFree(w.cnt);
   }
   ev->ws.clear();
-  if (ev->cal32) (void)hipFree(ev->cal32);
-  if (ev->cal64) (void)hipFree(ev->cal64);
-  if (ev->calt32) (void)hipFree(ev->calt32);
-  if (ev->calt64) (void)hipFree(ev->calt64);
-  if (ev->calB) (void)hipFree(ev->calB);
-  if (ev->kcal) (void)hipFree(ev->kcal);
-  if (ev->tab64) (void)hipFree(ev->tab64);
-  if (ev->tab32) (void)hipFree(ev->tab32);
-  if (ev->g32) (void)hipFree(ev->g32);
-  if (ev->g64) (void)hipFree(ev->g64);
-  if (ev->bands) (void)hipFree(ev->bands);
+  if (ev->cal_slab) (void)hipFree(ev->cal_slab);
+  if (ev->slab) (void)hipFree(ev->slab);
   if (ev->fgrid) (void)hipFree(ev->fgrid);
   if (ev->kcum) (void)hipFree(ev->kcum);
-  if (ev->ec) (void)hipFree(ev->ec);
   delete ev;
   return GWL_OK;
 }
