@@ -291,7 +291,7 @@ gwl_status gwl_multi_launch(gwl_plan pl, const double* const* theta, double* con
 
 gwl_status gwl_plan_destroy(gwl_plan pl);
 
-/* Shape of a plan: the chunk length (rows of a work item) shared by all events, whether events are queued by
+/* Shape of a plan: the chunk length (rows; a work item has four chunks) shared by all events, whether events are queued by
  * descending work (1) or ascending work (0), and the number of work items when every group of points
  * walks a typical group's rows (a launch makes its items from the points). Any pointer may be
  * null. */

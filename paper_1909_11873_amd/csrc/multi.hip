@@ -2,15 +2,22 @@
 // HIP graph (the batch axis of the paper's parallel prior sampling, section 3, extended over
 // events).
 //
-// Work items are (64-point group of an event, chunk of its plan's rows). The set-up of a group makes
-// its plan (gwl_bands.h: the band-limited rows, or the bins, that its points walk), cuts it into chunks of
-// about one length for all events, so that items cost about the same, and appends them to the
-// queue; events are queued shortest first. Every wavefront of the persistent kernel takes items
-// from an atomic counter until the queue is empty; each item writes its own partial sums, which a
-// multi-event epilogue launch adds in chunk order (deterministic, whatever the queue's order). A
-// per-event counter stamps the device clock when the last item of the event completes. The graph
-// is: reset (counters and start stamp, by a kernel) -> per-point set-up and queue for all events ->
+// Work items are (64-point group of an event, four chunks of its plan's rows). The set-up of a group
+// makes its plan (gwl_bands.h: the band-limited rows, or the bins, that its points walk), cuts it into
+// chunks of about one length for all events, so that items cost about the same, and appends them to
+// the queue; events are queued shortest first. A workgroup of the persistent kernel takes every
+// gridDim-th item, a chunk to each of its wavefronts, adds the four sums in LDS and writes the item's
+// partial sums, which a multi-event epilogue launch adds in chunk order (deterministic, whatever the
+// queue's order). Every item and group stamps the device clock into a place of its own; the host takes an
+// event's latency from them. The graph is: reset -> per-point set-up and queue for all events ->
 // persistent loop -> epilogue for all events.
+//
+// What bounds it: the loop's float64 instructions. Queue tickets, completion counters and stamps were
+// device-scope atomics on one address, which the dies take in turn at about 20 ns each: 12,500 of them
+// held 12 float64 gradient events of 4 to 64 s (516,000 rows of 64 points) at 262 us. Items dealt by
+// index and stamps in places of their own: 170 us; one item per workgroup instead of per wavefront keeps
+// that and writes a quarter of the partial sums (the epilogue: 25 -> 16 us), and the 64-event
+// mixed-precision workload takes 1.60 ms for 1.72.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -36,6 +43,8 @@ constexpr int MULTI_EPI_BLOCK = 256;  // points per workgroup of the value's epi
 // bins per chunk of a group that walks its bins: the length that the 64-event workload's tuning found
 // when every group did
 constexpr int MULTI_BIN_CHUNK = 1536;
+constexpr int MULTI_ROUND_ROWS = 96;
+constexpr int MULTI_RED = 4;          // sums reduced per LDS pass
 
 struct MultiEvDev {
   const void* tab64;       // RowF64<ND>: bins (or edges), then the band-limited rows
@@ -53,7 +62,8 @@ struct MultiEvDev {
   double step;             // the grid's spacing
 };
 
-constexpr int PLAN_CHUNKS = PLAN_INTS - 1;  // a group's plan also holds its number of chunks
+// a group's plan also holds its number of items and its first item
+constexpr int PLAN_ITEMS = PLAN_INTS - 1, PLAN_BASE = PLAN_INTS - 2;
 
 struct MultiIODev {
   const double* theta;     // [B][11]
@@ -63,27 +73,14 @@ struct MultiIODev {
 };
 
 struct MultiCtl {
-  unsigned long long next; // queue head, in 64ths of an item
   unsigned int total;      // items in the queue
   unsigned int pad;
   unsigned long long t0;   // device clock at the start of the launch
-  unsigned long long tend; // device clock at the end of the epilogue
 };
 
-__global__ void k_multi_reset(MultiCtl* __restrict__ ctl, unsigned int* __restrict__ done,
-                              unsigned int* __restrict__ items_of, unsigned long long* __restrict__ tev, int E) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < E) {
-    done[i] = 0u;
-    items_of[i] = 0u;
-    tev[i] = 0ull;
-  }
-  if (i == 0) {
-    ctl->next = 0ull;
-    ctl->total = 0u;
-    ctl->t0 = wall_clock64();
-    ctl->tend = 0ull;
-  }
+__global__ void k_multi_reset(MultiCtl* __restrict__ ctl) {
+  ctl->total = 0u;
+  ctl->t0 = wall_clock64();
 }
 
 // device clock stamp (a calibrated event's completion)
@@ -95,8 +92,8 @@ __global__ void k_multi_stamp(unsigned long long* __restrict__ t) { *t = wall_cl
 template <int ND>
 __global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
     const MultiEvDev* __restrict__ evs, const EventGeom* __restrict__ geoms, const MultiIODev* __restrict__ io,
-    const int2* __restrict__ grp, int mixed, int chunk, MultiCtl* __restrict__ ctl, unsigned int* __restrict__ items_of,
-    int2* __restrict__ items, int* __restrict__ plans) {
+    const int2* __restrict__ grp, int mixed, int chunk, MultiCtl* __restrict__ ctl, int2* __restrict__ items,
+    int* __restrict__ plans) {
   __shared__ double rows_s[NCOEF * WAVE];
   __shared__ BandLds bands_s;
   __shared__ int base_s;
@@ -137,43 +134,45 @@ __global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
   if (lane == 0) {
     const int rows = bands_s.plan[2] ? bands_s.plan[0] : ev.M;
-    int n = (rows + chunk - 1) / chunk;
+    int n = (rows + WAVES_PER_BLOCK * chunk - 1) / (WAVES_PER_BLOCK * chunk);
     if (n > ev.nslot) n = ev.nslot;
-    bands_s.plan[3] = (rows + n - 1) / n;
-    bands_s.plan[PLAN_CHUNKS] = n;
-    base_s = (int)atomicAdd(&ctl->total, (unsigned int)n);
-    atomicAdd(&items_of[gp.x], (unsigned int)n);
+    bands_s.plan[3] = (rows + WAVES_PER_BLOCK * n - 1) / (WAVES_PER_BLOCK * n);
+    bands_s.plan[PLAN_ITEMS] = n;
+    bands_s.plan[PLAN_BASE] = base_s = (int)atomicAdd(&ctl->total, (unsigned int)n);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
-  const int n = bands_s.plan[PLAN_CHUNKS], base = base_s;
+  const int n = bands_s.plan[PLAN_ITEMS], base = base_s;
   for (int c = lane; c < n; c += WAVE) items[base + c] = make_int2((int)blockIdx.x, c);
   plans[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }
 
-// Persistent loop: one wavefront per item, items from the shared counter.
+// Wavefronts per SIMD that the register budget must allow. Three detectors' mixed adjoint holds both
+// loops: at four it spilled 168 bytes a lane (64 events: 1.69 ms, 1.60 at three); the float64 one
+// spills 96 at four and still gains (12 events: 169 us, 180 at three).
 template <int ND, bool MIXED, bool GRAD>
-__global__ __launch_bounds__(BLOCK, (ND <= 3 ? 4 : 3)) void k_multi_bins(
+constexpr int multi_waves_per_eu() {
+  return ND > 3 || (ND == 3 && MIXED && GRAD) ? 3 : 4;
+}
+
+// Persistent loop: one workgroup per item, its wavefronts on four consecutive chunks of the group's
+// rows.
+template <int ND, bool MIXED, bool GRAD>
+__global__ __launch_bounds__(BLOCK, (multi_waves_per_eu<ND, MIXED, GRAD>())) void k_multi_bins(
     const MultiEvDev* __restrict__ evs, const MultiIODev* __restrict__ io, const int2* __restrict__ grp,
-    const int2* __restrict__ items, const int* __restrict__ plans, const unsigned int* __restrict__ items_of,
-    MultiCtl* __restrict__ ctl, unsigned int* __restrict__ done, unsigned long long* __restrict__ tev) {
+    const int2* __restrict__ items, const int* __restrict__ plans, const MultiCtl* __restrict__ ctl,
+    unsigned long long* __restrict__ stamp) {
   constexpr int NZ = nz_of(ND, GRAD);
   __shared__ double2 tbl[PH_TBL];  // the float64 phasor table
+  __shared__ double red[WAVES_PER_BLOCK - 1][MULTI_RED][WAVE];
   fill_phasor_table(tbl);
   __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = threadIdx.x % WAVE;
   const int total = (int)__builtin_amdgcn_readfirstlane(ctl->total);
-  for (;;) {
-    // One ticket per wavefront. Every lane takes part in the atomic, and the first lane's old value is
-    // read back as a scalar, so the loop is wave-uniform: an atomic in a branch of one lane, or a
-    // per-lane broadcast, lets the compiler separate the lane that takes the ticket from the others,
-    // which then never see the queue advance. With the same addend in every lane the compiler issues
-    // one atomic of 64 for the wavefront, so tickets count in 64ths.
-    const unsigned long long ticket = atomicAdd(&ctl->next, 1ull) / WAVE;
-    const int it = (int)__builtin_amdgcn_readfirstlane((unsigned int)ticket);
-    if (it >= total) break;
+  for (int it = (int)blockIdx.x; it < total; it += (int)gridDim.x) {
     const int2 item = items[it];
     const int2 gp = grp[item.x];
-    const int e = gp.x, c = item.y;
+    const int e = gp.x, c = item.y * WAVES_PER_BLOCK + w;
     const MultiEvDev ev = evs[e];
     const int* plan = plans + (int64_t)item.x * PLAN_INTS;
     const int64_t B = io[e].B;
@@ -181,7 +180,7 @@ __global__ __launch_bounds__(BLOCK, (ND <= 3 ? 4 : 3)) void k_multi_bins(
     const int64_t pc = p < B ? p : B - 1;
     const bool f64path = plan[2] != 0;                 // scalar branch
     const int rows = f64path ? plan[0] : ev.M, q0 = c * plan[3];
-    const int q1 = q0 + plan[3] < rows ? q0 + plan[3] : rows;
+    const int q1 = q0 + plan[3] < rows ? q0 + plan[3] : rows;   // none when q0 >= q1
     double tot[NZ];
 #pragma unroll
     for (int z = 0; z < NZ; ++z) tot[z] = 0.0;
@@ -214,11 +213,43 @@ __global__ __launch_bounds__(BLOCK, (ND <= 3 ? 4 : 3)) void k_multi_bins(
           });
     }
     global_as_ptr<double> part = (global_as_ptr<double>)ev.part;
+    // the item's four sums, added in chunk order by the first wavefront
 #pragma unroll
-    for (int z = 0; z < NZ; ++z) part[((int64_t)c * NZ + z) * ev.Bp + p] = tot[z];
-    const unsigned int prev = atomicAdd(&done[e], 1u);   // in 64ths, as the tickets
-    const unsigned int d = __builtin_amdgcn_readfirstlane(prev);
-    if (d + WAVE == items_of[e] * WAVE && lane == 0) tev[e] = wall_clock64();
+    for (int z0 = 0; z0 < NZ; z0 += MULTI_RED) {
+      __syncthreads();
+      if (w > 0) {
+#pragma unroll
+        for (int zz = 0; zz < MULTI_RED; ++zz)
+          if (z0 + zz < NZ) red[w - 1][zz][lane] = tot[z0 + zz];
+      }
+      __syncthreads();
+      if (w == 0) {
+#pragma unroll
+        for (int zz = 0; zz < MULTI_RED; ++zz)
+          if (z0 + zz < NZ) {
+#pragma unroll
+            for (int v = 0; v < WAVES_PER_BLOCK - 1; ++v) tot[z0 + zz] += red[v][zz][lane];
+            part[((int64_t)item.y * NZ + z0 + zz) * ev.Bp + p] = tot[z0 + zz];
+          }
+      }
+    }
+    if (threadIdx.x == 0) stamp[it] = wall_clock64();
+  }
+}
+
+// A group's clock stamps: its last item's, and its epilogue's.
+__device__ inline void group_stamps(const unsigned long long* __restrict__ stamp, int n, int lane,
+                                    unsigned long long* __restrict__ out) {
+  unsigned long long t = 0;
+  for (int c = lane; c < n; c += WAVE) t = stamp[c] > t ? stamp[c] : t;
+#pragma unroll
+  for (int off = WAVE / 2; off > 0; off >>= 1) {
+    const unsigned long long o = __shfl_xor(t, off);
+    t = o > t ? o : t;
+  }
+  if (lane == 0) {
+    out[0] = t;
+    out[1] = wall_clock64();
   }
 }
 
@@ -227,14 +258,16 @@ constexpr int MULTI_EPG_WAVES = 4;
 template <int ND>
 __global__ __launch_bounds__(MULTI_EPG_WAVES * WAVE) void k_multi_epilogue_grad(
     const MultiEvDev* __restrict__ evs, const EventGeom* __restrict__ geoms, const MultiIODev* __restrict__ io,
-    const int2* __restrict__ grp, const int* __restrict__ plans, MultiCtl* __restrict__ ctl) {
+    const int2* __restrict__ grp, const int* __restrict__ plans, const unsigned long long* __restrict__ stamp,
+    unsigned long long* __restrict__ gstamp) {
   constexpr int NZ = nz_of(ND, true);
   __shared__ double acc_s[NZ][WAVE];
   __shared__ double xs[GRAD_LDS][WAVE];
   const int2 gp = grp[blockIdx.x];
   const MultiEvDev ev = evs[gp.x];
   const MultiIODev o = io[gp.x];
-  const int n = plans[(int64_t)blockIdx.x * PLAN_INTS + PLAN_CHUNKS];
+  const int n = plans[(int64_t)blockIdx.x * PLAN_INTS + PLAN_ITEMS];
+  const int base = plans[(int64_t)blockIdx.x * PLAN_INTS + PLAN_BASE];
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)gp.y * WAVE + lane;
@@ -253,14 +286,15 @@ __global__ __launch_bounds__(MULTI_EPG_WAVES * WAVE) void k_multi_epilogue_grad(
     for (int d = 0; d < ND; ++d) K[d] = ev.ec->K[d];
     gradient_finish<ND>(w, lane, th, K, xs, r, o.logl + p, o.grad + p * NPARAM);
   }
-  if (threadIdx.x == 0) atomicMax(&ctl->tend, wall_clock64());
+  if (w == 3) group_stamps(stamp + base, n, lane, gstamp + 2 * (int64_t)blockIdx.x);
 }
 
 // The value's epilogue: a thread per point, four groups per workgroup.
 template <int ND>
 __global__ __launch_bounds__(MULTI_EPI_BLOCK) void k_multi_epilogue(
     const MultiEvDev* __restrict__ evs, const MultiIODev* __restrict__ io, const int2* __restrict__ grp, int ngrp,
-    const int* __restrict__ plans, MultiCtl* __restrict__ ctl) {
+    const int* __restrict__ plans, const unsigned long long* __restrict__ stamp,
+    unsigned long long* __restrict__ gstamp) {
   constexpr int NZ = nz_of(ND, false);
   const int g = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (MULTI_EPI_BLOCK / WAVE) + threadIdx.x / WAVE));
   if (g < ngrp) {
@@ -270,11 +304,12 @@ __global__ __launch_bounds__(MULTI_EPI_BLOCK) void k_multi_epilogue(
     const int64_t p = (int64_t)gp.y * WAVE + threadIdx.x % WAVE;
     if (p < o.B) {
       double acc[NZ];
-      gather<NZ>(ev.part, plans[(int64_t)g * PLAN_INTS + PLAN_CHUNKS], ev.Bp, p, acc);
+      gather<NZ>(ev.part, plans[(int64_t)g * PLAN_INTS + PLAN_ITEMS], ev.Bp, p, acc);
       o.logl[p] = epilogue_value_rows<ND, NZ>(acc, ev.coef, ev.Bp, p, *ev.ec, 1.0);
     }
+    const int* plan = plans + (int64_t)g * PLAN_INTS;
+    group_stamps(stamp + plan[PLAN_BASE], plan[PLAN_ITEMS], (int)(threadIdx.x % WAVE), gstamp + 2 * (int64_t)g);
   }
-  if (threadIdx.x == 0) atomicMax(&ctl->tend, wall_clock64());
 }
 
 }  // namespace gwl
@@ -297,8 +332,8 @@ struct gwl_plan_s {
   int2* d_grp = nullptr;              // [ngrp]: event (queue index), point group
   int2* d_items = nullptr;            // the queue: group, chunk
   int* d_plans = nullptr;             // [ngrp][PLAN_INTS]
-  void* d_ctl = nullptr;              // MultiCtl, done[E], items_of[E], tev[E]
-  unsigned long long* h_stamps = nullptr;  // pinned: t0, tend, tev[E]
+  void* d_ctl = nullptr;              // MultiCtl, tev[E] (calibrated events), gstamp[ngrp][2], stamp[items]
+  unsigned long long* h_stamps = nullptr;  // pinned: the control block without the items' stamps
   double* ws = nullptr;
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
@@ -319,9 +354,10 @@ namespace {
 // Set to false to switch the multi-event plan off.
 constexpr bool kMultiEnabled = true;
 
-// offset of the events' time stamps behind the control block and the two counters per event
-size_t tev_offset(int E) { return sizeof(gwl::MultiCtl) + 2 * sizeof(unsigned int) * (size_t)E; }
-size_t ctl_bytes(int E) { return tev_offset(E) + sizeof(unsigned long long) * E; }
+// the control block: the calibrated events' stamps, the groups' (last item, epilogue), the items'
+constexpr size_t kTevOffset = sizeof(gwl::MultiCtl);
+size_t gstamp_offset(int E) { return kTevOffset + sizeof(unsigned long long) * (size_t)E; }
+size_t stamp_offset(int E, int ngrp) { return gstamp_offset(E) + 2 * sizeof(unsigned long long) * (size_t)ngrp; }
 
 // precision of calibrated event e's own kernels in plan pl (as its single call would take)
 bool mixed_cal(const gwl_plan_s* pl, int e) { return pl->mixed && use_mixed(pl->evs[e], GWL_MIXED); }
@@ -356,20 +392,19 @@ hipError_t enqueue_multi_nd(gwl_plan pl, hipStream_t s) {
   const int E = pl->E;
   unsigned char* ctl = (unsigned char*)pl->d_ctl;
   gwl::MultiCtl* c = (gwl::MultiCtl*)ctl;
-  unsigned int* done = (unsigned int*)(ctl + sizeof(gwl::MultiCtl));
-  unsigned int* items_of = done + E;
-  unsigned long long* tev = (unsigned long long*)(ctl + tev_offset(E));
+  unsigned long long* gstamp = (unsigned long long*)(ctl + gstamp_offset(E));
+  unsigned long long* stamp = (unsigned long long*)(ctl + stamp_offset(E, pl->ngrp));
   const gwl::MultiEvDev* evs = pl->d_evs;
   const gwl::EventGeom* geoms = pl->d_geoms;
   const gwl::MultiIODev* io = pl->d_io;
   const int2* grp = pl->d_grp;
-  hipLaunchKernelGGL(gwl::k_multi_reset, dim3((E + 255) / 256), dim3(256), 0, s, c, done, items_of, tev, E);
+  hipLaunchKernelGGL(gwl::k_multi_reset, dim3(1), dim3(1), 0, s, c);
   if (pl->ngrp == 0) return hipGetLastError();   // no point outside calibrated events: only the reset
   hipLaunchKernelGGL(gwl::k_multi_setup<ND>, dim3(pl->ngrp), dim3(gwl::MULTI_SETUP_WAVES * gwl::WAVE), 0, s, evs, geoms,
-                     io, grp, pl->mixed ? 1 : 0, pl->chunk, c, items_of, pl->d_items, pl->d_plans);
+                     io, grp, pl->mixed ? 1 : 0, pl->chunk, c, pl->d_items, pl->d_plans);
 #define GWL_MB(MX, GR)                                                                                         \
   hipLaunchKernelGGL((gwl::k_multi_bins<ND, MX, GR>), dim3(pl->grid), dim3(gwl::BLOCK), 0, s, evs, io, grp,    \
-                     (const int2*)pl->d_items, (const int*)pl->d_plans, (const unsigned int*)items_of, c, done, tev)
+                     (const int2*)pl->d_items, (const int*)pl->d_plans, (const gwl::MultiCtl*)c, stamp)
   if (pl->mixed) {
     if (pl->grad) GWL_MB(true, true); else GWL_MB(true, false);
   } else {
@@ -378,11 +413,11 @@ hipError_t enqueue_multi_nd(gwl_plan pl, hipStream_t s) {
 #undef GWL_MB
   if (pl->grad) {
     hipLaunchKernelGGL(gwl::k_multi_epilogue_grad<ND>, dim3(pl->ngrp), dim3(gwl::MULTI_EPG_WAVES * gwl::WAVE), 0, s, evs,
-                       geoms, io, grp, (const int*)pl->d_plans, c);
+                       geoms, io, grp, (const int*)pl->d_plans, (const unsigned long long*)stamp, gstamp);
   } else {
     constexpr int per = gwl::MULTI_EPI_BLOCK / gwl::WAVE;
     hipLaunchKernelGGL(gwl::k_multi_epilogue<ND>, dim3((pl->ngrp + per - 1) / per), dim3(gwl::MULTI_EPI_BLOCK), 0, s,
-                       evs, io, grp, pl->ngrp, (const int*)pl->d_plans, c);
+                       evs, io, grp, pl->ngrp, (const int*)pl->d_plans, (const unsigned long long*)stamp, gstamp);
   }
   return hipGetLastError();
 }
@@ -454,8 +489,6 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
   for (int e = 0; e < E; ++e)
     if (evs[e]->ncal > 0) pl->cal.push_back(e);
 
-  // one chunk length for all events: the largest power of two in [128, 4096] rows that still gives at
-  // least four items per resident wavefront
   hipError_t err = hipSuccess;
   int occ = 0, ncu = 0, clk = 0;
   err = occupancy(nd, pl->mixed, pl->grad, &occ);
@@ -468,29 +501,34 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
   if (occ < 1) occ = 1;
   pl->grid = occ * ncu;
   pl->clock_khz = (double)clk;
-  const int64_t resident = (int64_t)pl->grid * WAVES_PER_BLOCK;
   auto items_for = [&](int chunk) {
     int64_t n = 0;
     for (int e = 0; e < E; ++e) {
       if (B_e[e] == 0 || evs[e]->ncal > 0) continue;
-      n += ((B_e[e] + WAVE - 1) / WAVE) * ((evs[e]->M_loop + chunk - 1) / chunk);
+      const int64_t len = (int64_t)WAVES_PER_BLOCK * chunk;
+      n += ((B_e[e] + WAVE - 1) / WAVE) * ((evs[e]->M_loop + len - 1) / len);
     }
     return n;
   };
-  int chunk = 128;
-  for (int c = 4096; c >= 128; c >>= 1) {
-    if (items_for(c) >= 4 * resident) {
-      chunk = c;
-      break;
-    }
-  }
+  // one chunk length for all events: the shortest with which the items of typical groups fill a whole
+  // number of rounds of the resident workgroups to nineteen twentieths at most, as many rounds (up to
+  // four) as keep it near MULTI_ROUND_ROWS, and 512 rows at most. On 12 events of 4 to 64 s in float64:
+  // 168 to 171 us at 48 to 96 rows, 185 at 128, 247 at 384; on 64 events 1.55 ms at 256, 1.60 at 4096
+  auto shortest = [&](int64_t rounds) {
+    int c = 32;
+    while (c < 512 && 20 * items_for(c) > 19 * rounds * pl->grid) c += 8;
+    return c;
+  };
+  int chunk = shortest(1);
+  if (chunk > MULTI_ROUND_ROWS) chunk = shortest(std::min(4, (chunk + MULTI_ROUND_ROWS - 1) / MULTI_ROUND_ROWS));
   if (chunk_req > 0) chunk = chunk_req;
   const int64_t total = items_for(chunk);
   // most chunks of a group of event e: enough for half as many rows again as a typical group's, and for
   // its bins in chunks of MULTI_BIN_CHUNK
   auto slots = [&](const gwl_event ev) {
-    const int64_t rows = std::min<int64_t>((ev->M_loop + ev->M_loop / 2 + chunk - 1) / chunk, (ev->M + chunk - 1) / chunk);
-    const int64_t bins = (ev->M + std::max(chunk, MULTI_BIN_CHUNK) - 1) / std::max(chunk, MULTI_BIN_CHUNK);
+    const int64_t len = (int64_t)WAVES_PER_BLOCK * chunk, blen = (int64_t)WAVES_PER_BLOCK * std::max(chunk, MULTI_BIN_CHUNK);
+    const int64_t rows = std::min<int64_t>((ev->M_loop + ev->M_loop / 2 + len - 1) / len, (ev->M + len - 1) / len);
+    const int64_t bins = (ev->M + blen - 1) / blen;
     return std::max<int64_t>(1, std::max(rows, bins));
   };
   int64_t capacity = 0, ngroups = 0;
@@ -561,10 +599,10 @@ gwl_status build_plan(const gwl_event* evs, int E, const int64_t* B_e, gwl_preci
   if (err == hipSuccess) err = hipMalloc((void**)&pl->d_grp, sizeof(int2) * (grp.empty() ? 1 : grp.size()));
   if (err == hipSuccess) err = hipMalloc((void**)&pl->d_items, sizeof(int2) * (size_t)(capacity > 0 ? capacity : 1));
   if (err == hipSuccess) err = hipMalloc((void**)&pl->d_plans, sizeof(int) * PLAN_INTS * (grp.empty() ? 1 : grp.size()));
-  if (err == hipSuccess) err = hipMalloc(&pl->d_ctl, ctl_bytes(E));
+  if (err == hipSuccess) err = hipMalloc(&pl->d_ctl, stamp_offset(E, pl->ngrp) + sizeof(unsigned long long) * (size_t)(capacity > 0 ? capacity : 1));
   if (err == hipSuccess) err = hipHostMalloc((void**)&pl->h_io, sizeof(MultiIODev) * E, hipHostMallocDefault);
   if (err == hipSuccess)
-    err = hipHostMalloc((void**)&pl->h_stamps, sizeof(unsigned long long) * (2 + E), hipHostMallocDefault);
+    err = hipHostMalloc((void**)&pl->h_stamps, stamp_offset(E, pl->ngrp), hipHostMallocDefault);
   if (err == hipSuccess) err = hipMemcpy(pl->d_evs, hev.data(), sizeof(MultiEvDev) * E, hipMemcpyHostToDevice);
   if (err == hipSuccess) err = hipMemcpy(pl->d_geoms, hgeo.data(), sizeof(EventGeom) * E, hipMemcpyHostToDevice);
   if (err == hipSuccess && !grp.empty())
@@ -680,7 +718,7 @@ gwl_status gwl_multi_launch(gwl_plan pl, const double* const* theta, double* con
   // calibrated events: their own set-up, bin-loop and epilogue kernels, each followed by a clock
   // stamp in the event's slot, dealt in turn to the plan's side streams after the graph (one small
   // event at a time leaves most of the chip idle); the caller's stream then waits for them all
-  unsigned long long* tev_dev = (unsigned long long*)((unsigned char*)pl->d_ctl + tev_offset(pl->E));
+  unsigned long long* tev_dev = (unsigned long long*)((unsigned char*)pl->d_ctl + kTevOffset);
   if (!pl->cal.empty()) {
     constexpr int NS = gwl_plan_s::kCalStreams;
     err = hipEventRecord(pl->cal_fork, s);
@@ -712,26 +750,33 @@ gwl_status gwl_multi_launch(gwl_plan pl, const double* const* theta, double* con
     if (jerr != hipSuccess) return hip_fail(jerr, "multi-event launch");
   }
   if (event_latency_us) {
-    const unsigned char* ctl = (const unsigned char*)pl->d_ctl;
-    const size_t tev_off = tev_offset(pl->E);
-    err = hipMemcpyAsync(pl->h_stamps, ctl + offsetof(MultiCtl, t0), sizeof(unsigned long long) * 2,
-                         hipMemcpyDeviceToHost, s);
-    if (err == hipSuccess)
-      err = hipMemcpyAsync(pl->h_stamps + 2, ctl + tev_off, sizeof(unsigned long long) * pl->E,
-                           hipMemcpyDeviceToHost, s);
+    err = hipMemcpyAsync(pl->h_stamps, pl->d_ctl, stamp_offset(pl->E, pl->ngrp), hipMemcpyDeviceToHost, s);
     if (err == hipSuccess) err = hipStreamSynchronize(s);
     if (err != hipSuccess) return hip_fail(err, "latency read-back");
-    const unsigned long long t0 = pl->h_stamps[0], tend = pl->h_stamps[1];
-    unsigned long long tbins = t0;
-    for (int q = 0; q < pl->E; ++q)
-      if (pl->evs[pl->order[q]]->ncal == 0) tbins = std::max(tbins, pl->h_stamps[2 + q]);
+    const unsigned char* h = (const unsigned char*)pl->h_stamps;
+    const unsigned long long t0 = ((const gwl::MultiCtl*)h)->t0;
+    const unsigned long long* tcal = (const unsigned long long*)(h + kTevOffset);
+    const unsigned long long* gs = (const unsigned long long*)(h + gstamp_offset(pl->E));
+    // each event's last item, the last item and the end of the epilogue
+    std::vector<unsigned long long> tev(tcal, tcal + pl->E);
+    unsigned long long tbins = t0, tend = t0;
+    int g = 0;
+    for (int q = 0; q < pl->E; ++q) {
+      const int e = pl->order[q];
+      if (pl->evs[e]->ncal > 0) continue;
+      tev[q] = t0;
+      for (const int g1 = g + (int)((pl->B[e] + WAVE - 1) / WAVE); g < g1; ++g) {
+        tev[q] = std::max(tev[q], gs[2 * g]);
+        tend = std::max(tend, gs[2 * g + 1]);
+      }
+      tbins = std::max(tbins, tev[q]);
+    }
     // an event's results exist once its last item is done and the final epilogue launch has run
     const double epi_us = tend > tbins ? (double)(tend - tbins) * 1e3 / pl->clock_khz : 0.0;
     for (int q = 0; q < pl->E; ++q) {
       const int e = pl->order[q];
-      const unsigned long long te = pl->h_stamps[2 + q];
       const double extra = pl->evs[e]->ncal > 0 ? 0.0 : epi_us;   // calibrated: stamped after its epilogue
-      event_latency_us[e] = pl->B[e] == 0 ? 0.0 : (double)(te - t0) * 1e3 / pl->clock_khz + extra;
+      event_latency_us[e] = pl->B[e] == 0 ? 0.0 : (double)(tev[q] - t0) * 1e3 / pl->clock_khz + extra;
     }
   }
   return GWL_OK;

@@ -383,7 +383,7 @@ class MultiPlan:
         return logls, grads, (list(lat) if latency else None)
 
     def info(self):
-        """(chunk length in bins, queued by descending work, number of work items)."""
+        """(chunk length in rows, queued by descending work, number of work items of four chunks)."""
         c, d, n = ctypes.c_int(), ctypes.c_int(), ctypes.c_int64()
         _check("gwl_plan_info", lib().gwl_plan_info(self._h, ctypes.byref(c), ctypes.byref(d), ctypes.byref(n)))
         return c.value, bool(d.value), n.value
