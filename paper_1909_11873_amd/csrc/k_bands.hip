@@ -195,7 +195,8 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
       f1 = std::max(f1, c.f1);
     }
   }
-  if (ncand == 0) {
+  // (the slope of f^(1/3) ln f turns at exp(-3/2) Hz, and an interval's slopes have to be monotone)
+  if (ncand == 0 || f0 < 0.25) {
     head.npanel = head.nseg = 0;
     return;
   }
@@ -203,16 +204,6 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
   head.nbrk = nbrk;
   const double lr = log(f1 / f0) / nbrk;
   for (int i = 0; i <= nbrk; ++i) basis_slopes(f0 * exp(lr * i), head.gp[i]);
-  for (int i = 0; i < nbrk; ++i) {
-    for (int m = 0; m < NBASIS; ++m) head.dg[i][m] = fabs(head.gp[i + 1][m] - head.gp[i][m]);
-    // f^(1/3) ln f: its slope turns at ln f = -3/2
-    const double xa = log(f0) + lr * i, xb = xa + lr;
-    if (xa < -1.5 && xb > -1.5) {
-      double g[NBASIS];
-      basis_slopes(exp(-1.5), g);
-      head.dg[i][6] = fabs(g[6] - head.gp[i][6]) + fabs(g[6] - head.gp[i + 1][6]);
-    }
-  }
   int c = 0;
   for (int s = 0; s < head.nseg; ++s) {
     head.c0[s] = c;

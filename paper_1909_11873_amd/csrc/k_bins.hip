@@ -204,6 +204,13 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     if (!SETUP || sh.W < 3) fill_phasor_table(tbl);
     else if (w >= 2) fill_phasor_table(tbl, 2 * WAVE);
   }
+  double* slopes_s = rows_s + CO_CR * WAVE;                    // (these rows stay unused here)
+  if constexpr (SETUP && BANDS) {
+    if (sh.W < 3) band_load(bh, slopes_s);
+    else if (w >= 2) band_load(bh, slopes_s, 2 * WAVE);
+  }
+  BandPre pre;
+  if constexpr (SETUP && BANDS) pre = band_fetch(bh, w, lane);
   // in-kernel set-up: the intrinsic half on wavefront 0, the extrinsic half on wavefront 1 (on
   // wavefront 0 too when the workgroup has one)
   if constexpr (SETUP) {
@@ -232,11 +239,11 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     in_range = rows_in_range<ND>(a, T, ec);
     if (!in_range) a[0] = __builtin_nan("");
     if constexpr (BANDS) {                                     // the group's plan, by the whole workgroup
-      band_ranges<ND>(bh, a, T, w, sh.W, lane, bands_s);
+      band_ranges<ND>(slopes_s, pre.nbrk, a, T, w, sh.W, lane, bands_s);
       __syncthreads();
-      band_hold(bh, w, sh.W, lane, bands_s);
+      band_hold(bh, pre, slopes_s, w, sh.W, lane, bands_s);
       __syncthreads();
-      if (w == 0) band_plan(bh, M, LOOP == LOOP_MIXED_BANDS, sh.nchunk, lane, bands_s);
+      if (w == 0) band_plan(pre, slopes_s, M, LOOP == LOOP_MIXED_BANDS, sh.nchunk, lane, bands_s);
       __syncthreads();
     }
   }

@@ -29,17 +29,17 @@ namespace gwl {
 
 // Set-up of a calibrated call: the point model's rows as k_setup writes them (two wavefronts, one
 // per half of the model), and the calibration node values turned from theta's columns 11.. into
-// rows calc [ncal][Bp], each of the two copying half of them; every row of a point with a non-finite node
-// value is NaN. With band-limited rows four wavefronts bound the group's arrival times as k_setup's
+// rows calc [ncal][Bp], two more wavefronts copying half of them each; every row of a point with a
+// non-finite node value is NaN. With band-limited rows the four bound the group's arrival times as k_setup's
 // do, widened by the calibration phase: within a node interval (and a quarter beyond) the spline's slope
 // is at most four times the largest difference of neighbouring node values per node spacing.
-constexpr int SETUP_CAL_WAVES = 2, SETUP_CAL_WAVES_BANDS = 4;
+constexpr int SETUP_CAL_WAVES = 4;
 template <int ND>
-__global__ __launch_bounds__(SETUP_CAL_WAVES_BANDS * WAVE) void k_setup_cal(
+__global__ __launch_bounds__(SETUP_CAL_WAVES * WAVE) void k_setup_cal(
     EventGeom g, const EventConst* __restrict__ ec, const BandHead* __restrict__ bh, double slope, int64_t M, bool mixed,
     CalShape sh, const double* __restrict__ theta, int P, int ncal, int64_t B, int64_t Bp, double* __restrict__ coef,
     double* __restrict__ calc, int* __restrict__ plan) {
-  __shared__ double rows_s[NCOEF * WAVE];
+  alignas(16) __shared__ double rows_s[NCOEF * WAVE];
   __shared__ int ok_s[2][WAVE];
   __shared__ double diff_s[2][WAVE];
   __shared__ BandLds bands_s;
@@ -47,9 +47,14 @@ __global__ __launch_bounds__(SETUP_CAL_WAVES_BANDS * WAVE) void k_setup_cal(
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // < Bp: Bp is a multiple of 64
   const int64_t pc = p < B ? p : B - 1;                  // padding lanes repeat the last point
+  BandPre pre;
+  if (bh) pre = band_fetch(bh, w, lane);
+  double* slopes_s = rows_s + CO_CR * WAVE;              // (these rows go to memory only)
   if (w < 2) {
     setup_halves<ND>(w, lane, theta + pc * P, g, ec, rows_s);
-    const int half = (ncal + 1) / 2, j0 = w * half, j1 = w == 0 ? half : ncal;
+  } else {                                             // meanwhile the node values, half each
+    if (bh) band_load(bh, slopes_s, 2 * WAVE);
+    const int half = (ncal + 1) / 2, j0 = (w - 2) * half, j1 = w == 2 ? half : ncal;
     bool ok = true;
     double diff = 0.0, last = j0 > 0 ? theta[pc * P + NPARAM + j0 - 1] : 0.0;
     for (int j = j0; j < j1; ++j) {
@@ -61,8 +66,8 @@ __global__ __launch_bounds__(SETUP_CAL_WAVES_BANDS * WAVE) void k_setup_cal(
       if (node > sh.nnode) diff = fmax(diff, fabs(v - last));
       last = v;
     }
-    ok_s[w][lane] = ok ? 1 : 0;
-    diff_s[w][lane] = diff;
+    ok_s[w - 2][lane] = ok ? 1 : 0;
+    diff_s[w - 2][lane] = diff;
   }
   __syncthreads();
   const bool ok = ok_s[0][lane] && ok_s[1][lane];
@@ -74,12 +79,13 @@ __global__ __launch_bounds__(SETUP_CAL_WAVES_BANDS * WAVE) void k_setup_cal(
 #pragma unroll
   for (int d = 0; d < ND; ++d) T[d] = rows_s[(CO_T + d) * WAVE + lane];
   if (!ok || !rows_in_range<ND>(a, T, ec)) a[0] = __builtin_nan("");
-  band_ranges<ND>(bh, a, T, w, SETUP_CAL_WAVES_BANDS, lane, bands_s, slope * fmax(diff_s[0][lane], diff_s[1][lane]));
+  band_ranges<ND>(slopes_s, pre.nbrk, a, T, w, SETUP_CAL_WAVES, lane, bands_s,
+                  slope * fmax(diff_s[0][lane], diff_s[1][lane]));
   __syncthreads();
-  band_hold(bh, w, SETUP_CAL_WAVES_BANDS, lane, bands_s);
+  band_hold(bh, pre, slopes_s, w, SETUP_CAL_WAVES, lane, bands_s);
   __syncthreads();
   if (w != 0) return;
-  band_plan_cal(bh, M, mixed, sh.nchunk, lane, bands_s);
+  band_plan_cal(pre, slopes_s, M, mixed, sh.nchunk, lane, bands_s);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
   plan[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }
@@ -534,8 +540,7 @@ static hipError_t cal_nd(bool mixed, bool grad, const EventGeom& g, const EventC
                          double* calc, double* part, int* plan, double* logl, double* gradout, hipStream_t s) {
   const int ncal = 2 * sh.nnode * ND;
   if (Bp % WAVE != 0 || B < 1 || B > Bp || (t.bands && !plan)) return hipErrorInvalidValue;
-  const int waves = t.bands ? SETUP_CAL_WAVES_BANDS : SETUP_CAL_WAVES;
-  hipLaunchKernelGGL(k_setup_cal<ND>, dim3((unsigned)(Bp / WAVE)), dim3(waves * WAVE), 0, s, g, ec, t.bands, t.slope, M,
+  hipLaunchKernelGGL(k_setup_cal<ND>, dim3((unsigned)(Bp / WAVE)), dim3(SETUP_CAL_WAVES * WAVE), 0, s, g, ec, t.bands, t.slope, M,
                      mixed, sh, theta, P, ncal, B, Bp, coef, calc, plan);
   const int* pl = t.bands ? plan : nullptr;
   const dim3 grid((unsigned)(sh.gper * NXCD)), block(BLOCK);

@@ -30,13 +30,17 @@ __global__ __launch_bounds__(SETUP_WAVES_BANDS * WAVE) void k_setup(EventGeom g,
                                                                     const double* __restrict__ theta, int64_t B,
                                                                     int64_t Bp, double* __restrict__ coef,
                                                                     int* __restrict__ plan) {
-  __shared__ double rows_s[NCOEF * WAVE];
+  alignas(16) __shared__ double rows_s[NCOEF * WAVE];
   __shared__ BandLds bands_s;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // < Bp: Bp is a multiple of 64
   const int64_t pc = p < B ? p : B - 1;                  // padding lanes repeat the last point
+  BandPre pre;
+  if (bh) pre = band_fetch(bh, w, lane);
+  double* slopes_s = rows_s + CO_CR * WAVE;                // (these rows go to memory only)
   if (w < 2) setup_halves<ND>(w, lane, theta + pc * NPARAM, g, ec, rows_s);
+  else if (bh) band_load(bh, slopes_s, 2 * WAVE);
   __syncthreads();
   if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ec, true, coef, Bp, p);
   if (!bh) return;
@@ -46,12 +50,12 @@ __global__ __launch_bounds__(SETUP_WAVES_BANDS * WAVE) void k_setup(EventGeom g,
 #pragma unroll
   for (int d = 0; d < ND; ++d) T[d] = rows_s[(CO_T + d) * WAVE + lane];
   if (!rows_in_range<ND>(a, T, ec)) a[0] = __builtin_nan("");
-  band_ranges<ND>(bh, a, T, w, SETUP_WAVES_BANDS, lane, bands_s);
+  band_ranges<ND>(slopes_s, pre.nbrk, a, T, w, SETUP_WAVES_BANDS, lane, bands_s);
   __syncthreads();
-  band_hold(bh, w, SETUP_WAVES_BANDS, lane, bands_s);
+  band_hold(bh, pre, slopes_s, w, SETUP_WAVES_BANDS, lane, bands_s);
   __syncthreads();
   if (w != 0) return;
-  band_plan(bh, M, mixed, nchunk, lane, bands_s);
+  band_plan(pre, slopes_s, M, mixed, nchunk, lane, bands_s);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
   plan[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }

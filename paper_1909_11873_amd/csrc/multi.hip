@@ -94,7 +94,7 @@ __global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
     const MultiEvDev* __restrict__ evs, const EventGeom* __restrict__ geoms, const MultiIODev* __restrict__ io,
     const int2* __restrict__ grp, int mixed, int chunk, MultiCtl* __restrict__ ctl, int2* __restrict__ items,
     int* __restrict__ plans) {
-  __shared__ double rows_s[NCOEF * WAVE];
+  alignas(16) __shared__ double rows_s[NCOEF * WAVE];
   __shared__ BandLds bands_s;
   __shared__ int base_s;
   const int2 gp = grp[blockIdx.x];
@@ -105,7 +105,11 @@ __global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)gp.y * WAVE + lane;
   const int64_t pc = p < o.B ? p : o.B - 1;
+  BandPre pre;
+  if (ev.bands) pre = band_fetch(ev.bands, w, lane);
+  double* slopes_s = rows_s + CO_CR * WAVE;                // (these rows go to memory only)
   if (w < 2) setup_halves<ND>(w, lane, o.theta + pc * NPARAM, geo, ev.ec, rows_s);
+  else if (ev.bands) band_load(ev.bands, slopes_s, 2 * WAVE);
   __syncthreads();
   if (w < 2) setup_rows_write<ND>(w, lane, rows_s, ev.ec, true, ev.coef, ev.Bp, p);
   if (ev.bands) {
@@ -115,12 +119,12 @@ __global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
 #pragma unroll
     for (int d = 0; d < ND; ++d) T[d] = rows_s[(CO_T + d) * WAVE + lane];
     if (!rows_in_range<ND>(a, T, ev.ec)) a[0] = __builtin_nan("");
-    band_ranges<ND>(ev.bands, a, T, w, MULTI_SETUP_WAVES, lane, bands_s);
+    band_ranges<ND>(slopes_s, pre.nbrk, a, T, w, MULTI_SETUP_WAVES, lane, bands_s);
     __syncthreads();
-    band_hold(ev.bands, w, MULTI_SETUP_WAVES, lane, bands_s);
+    band_hold(ev.bands, pre, slopes_s, w, MULTI_SETUP_WAVES, lane, bands_s);
     __syncthreads();
     if (w != 0) return;
-    band_plan(ev.bands, ev.M, mixed && !ev.f64, 1, lane, bands_s);
+    band_plan(pre, slopes_s, ev.M, mixed && !ev.f64, 1, lane, bands_s);
   } else {
     if (w != 0) return;
     if (lane == 0) {                                   // the bins as one piece
