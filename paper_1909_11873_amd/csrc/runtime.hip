@@ -836,16 +836,25 @@ gwl_status gwl_logl_batch_live(gwl_event ev, const double* theta, int64_t B, con
   gwl_status st = check_device(ev->device);
   if (st != GWL_OK) return st;
   const bool mixed = use_mixed(ev, prec);
-  // the shape for B, with at least enough workgroups per point group that a quarter of the point
-  // groups still give every CU two workgroups (chunks of at least 16 rows): a partly live batch
-  // then still fills the chip. The G workgroup sums go to the separate epilogue kernel (the
-  // set-up in either kernel): at these workgroup counts the last-arriver's device-scope fences
-  // cost more than the second launch (on c1 shapes with 8192 points, 240 against 196 us)
-  LoopShape sh = choose_shape(ev, B, mixed, false);
-  const int64_t want = (4 * 2 * 256 + sh.npg - 1) / sh.npg;
-  const int64_t gcap = std::max<int64_t>(1, ev->M_loop / (16 * (int64_t)sh.W));
-  const int G = (int)std::min<int64_t>(std::max<int64_t>(sh.G, want), std::max<int64_t>(gcap, sh.G));
-  sh = make_shape(B, ev->M, sh.W, G, sh.setup, 1);
+  // On band-limited rows: eight wavefronts a workgroup, of which two are resident on a CU, and as many
+  // workgroups a point group as are resident with all of the batch live (16 rows a wavefront at
+  // least). 8,192 points of three detectors and 8 s at 10, 40, 60 and 100 % live: 34, 34, 44 and 45 us;
+  // twice as many workgroups 28, 35, 48 and 57, half as many 45 throughout.
+  LoopShape sh = make_shape(B, ev->M, 8, 1, 1, 1);
+  const int64_t fill = std::max<int64_t>(1, 2 * 256 / sh.npg), most = std::max<int64_t>(1, ev->M_loop / (16 * 8));
+  sh = make_shape(B, ev->M, 8, (int)std::min(fill, most), 1, 1);
+  if (!ev->bands || sh.chunk <= kBandMinChunk) {
+    // On the bins: the shape for B, with at least enough workgroups per point group that a quarter of the
+    // point groups still give every CU two workgroups (chunks of at least 16 bins): a partly live batch
+    // then still fills the chip. The G workgroup sums go to the separate epilogue kernel (the
+    // set-up in either kernel): at these workgroup counts the last-arriver's device-scope fences
+    // cost more than the second launch (on c1 shapes with 8192 points, 240 against 196 us)
+    sh = choose_shape(ev, B, mixed, false);
+    const int64_t want = (4 * 2 * 256 + sh.npg - 1) / sh.npg;
+    const int64_t gcap = std::max<int64_t>(1, ev->M / (32 * (int64_t)sh.W));
+    const int G = (int)std::min<int64_t>(std::max<int64_t>(sh.G, want), std::max<int64_t>(gcap, sh.G));
+    sh = make_shape(B, ev->M, sh.W, G, sh.setup, 1);
+  }
   return run_logl(ev, theta, B, mixed, false, sh, logl, nullptr, (hipStream_t)stream, live);
 }
 
