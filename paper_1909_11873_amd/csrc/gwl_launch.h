@@ -31,6 +31,7 @@ struct LoopShape {
   int gper;     // workgroups per die: ceil(npg / NXCD) G (pgmaj), else ceil(items / NXCD)
   int setup;    // 1: set-up inside the evaluation kernel
   int sepepi;   // 1: the value's reduction over the G workgroups and its epilogue in a second kernel
+  int order;    // 1: the points are taken in the order that launch_order leaves in the workspace
   int pgmaj;    // 1: the dies take the point groups in turn (the set-up rows outweigh the table)
 };
 LoopShape make_shape(int64_t B, int64_t M, int W, int G, int setup, int sepepi = 0);
@@ -48,7 +49,11 @@ size_t prep_scratch_doubles(int nd, int64_t M);  // size of `blockpart`
 struct BandHead;
 hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, const double* theta, int64_t B, int64_t Bp,
                         double* coef, hipStream_t s, const BandHead* bands = nullptr, int64_t M = 0,
-                        bool mixed = false, int nchunk = 0, int* plan = nullptr);
+                        bool mixed = false, int nchunk = 0, int* plan = nullptr, const int* perm = nullptr);
+
+// an order of the points in which neighbours arrive at about the same time and have about the same chirp
+// mass: perm[B], a permutation within every kOrderBlock points, from theta rows of P columns
+hipError_t launch_order(const double* theta, int P, int64_t B, int* perm, hipStream_t s);
 
 // band-limited rows: the bands of a grid (host; head.ncand = 0: none), and their rows made from
 // the grid's rows in tab (row numbers as head.cand[].row0); kv holds kvals kernel values
@@ -67,7 +72,8 @@ hipError_t launch_bands(int nd, bool uniform, const BandGen* gen, int ncand, con
 // fgrid [M] and kcum [nd][M + 1] (running sums of the K_det terms) for an event with the ISCO
 // cut-off, else both null; rot: a float64 call on a uniform grid may take the detectors after
 // the first by rotation (ignored with the cut-off and in mixed precision); live (device, may be
-// null): only the first *live points are evaluated and written
+// null): only the first *live points are evaluated and written; perm (may be null): point p of the
+// groups is theta's row perm[p], and its value goes to logl[perm[p]] (the other kernels' perm likewise)
 struct EvalArgs {
   const void *tab64, *tab32;
   const RowGradF64* gtab;
@@ -83,6 +89,7 @@ struct EvalArgs {
   double* logl;
   const double *fgrid, *kcum;
   const int64_t* live;
+  const int* perm;
 };
 hipError_t launch_eval(int nd, bool mixed, bool grad, bool rot, const EvalArgs& x, const LoopShape& sh, hipStream_t s);
 
@@ -92,14 +99,15 @@ hipError_t launch_eval(int nd, bool mixed, bool grad, bool rot, const EvalArgs& 
 // launch_eval
 hipError_t launch_value_epilogue(int nd, const EventConst* ec, const double* theta, const double* coef,
                                  int64_t B, int64_t Bp, int G, const double* part, double* logl, const double* fgrid,
-                                 const double* kcum, int64_t M, const int64_t* live, hipStream_t s);
+                                 const double* kcum, int64_t M, const int64_t* live, const int* perm, hipStream_t s);
 
 // epilogue: partial sums [nchunk][nz][Bp] -> logL[B] (and grad[B][11]); the value alone reads the
 // set-up rows `coef`, the gradient evaluates the point model from theta
 hipError_t launch_epilogue(int nd, bool grad, const EventGeom& g, const EventConst* ec,
                            const double* theta, const double* coef, int64_t B, int64_t Bp, int nchunk,
                            const double* part, double* logl, double* gradout, hipStream_t s,
-                           const double* fgrid = nullptr, const double* kcum = nullptr, int64_t M = 0);
+                           const double* fgrid = nullptr, const double* kcum = nullptr, int64_t M = 0,
+                           const int* perm = nullptr);
 
 // float32 rows from float64 rows: tab32 = (basis, u / ec->uref)
 hipError_t launch_prep_mixed(int nd, const void* tab64, int64_t M, const EventConst* ec, void* tab32, hipStream_t s);
@@ -130,7 +138,8 @@ struct CalTables {
 };
 hipError_t launch_cal(int nd, bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const CalTables& t,
                       const double* theta, int P, int64_t B, int64_t Bp, int64_t M, const CalShape& sh, double* coef,
-                      double* calc, double* part, int* plan, double* logl, double* gradout, hipStream_t s);
+                      double* calc, double* part, int* plan, const int* perm, double* logl, double* gradout,
+                      hipStream_t s);
 
 // model strain on a grid: out[B][nd][M][2]
 hipError_t launch_waveform(int nd, const EventGeom& g, const double* coef, int64_t B, int64_t Bp,

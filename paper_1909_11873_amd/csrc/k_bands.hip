@@ -20,6 +20,11 @@ namespace {
 constexpr double kPanelRatio = 1.5;   // of a panel's ends: t(f) of a chirp changes by 2 to 3 across one
 constexpr int kWide = 4;              // wide segments (from one of the last panels to the top)
 constexpr int kMinBins = 64;          // of a panel: no row set is shorter than about 50 rows
+// Bands off the centre, for groups that hold a part of the arrival times (launch_order's, or a narrow
+// prior's): half-widths of 32 to 91 ms, up to 0.13 s from zero and further on the side of earlier times
+// by half the longest chirp, 0.7 half-widths apart (half a half-width: 1 % fewer rows with a seventh more
+// bands to choose from)
+constexpr double kSideTb0 = 0.032, kSideTb1 = 0.1, kSideReach = 0.13, kSideStep = 0.7;
 constexpr double kTbMin = 6.371e6 / kC;  // narrowest band: detectors' arrival times alone differ by +-R/c
 constexpr int64_t kMaxGrid = (int64_t)1 << 26;
 
@@ -77,6 +82,7 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
     double f0, f1;
   };
   std::vector<std::vector<Cand>> segs;
+  bool side = true;
   auto add_segment = [&](int p) {                              // from panel p: itself, or to the top
     const bool wide = (int)segs.size() >= np;
     const int64_t ka = ends[p], kb = wide ? M : ends[p + 1], nb = kb - ka;
@@ -139,6 +145,13 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
         const double lim = 1.6 * tau / (1.0 + m);
         for (double tb = lim / 6.0; tb < lim * grow; tb *= grow) want.push_back({-m * tb, tb});
       }
+    // off the centre: the wide segments and the node intervals, where chirps of ten solar masses are short
+    const double tau10 = tau * pow(10.0, -5.0 / 3.0);
+    if (side && (wide || !nodes.empty()) && tau10 < 2.0)
+      for (double tb = kSideTb0; tb < kSideTb1; tb *= exp2(0.5))
+        for (int k = 1; k * kSideStep * tb <= kSideReach + 0.5 * std::min(tau10, 0.3); ++k)
+          for (const int sign : {1, -1})
+            if (sign < 0 || k * kSideStep * tb <= kSideReach) want.push_back({sign * k * kSideStep * tb, tb});
     // the widest band around zero comes from the bins; where it has far fewer rows than bins the others
     // are summed from its rows, which is far less work (its error adds to theirs: about 1e-14)
     Cand root;
@@ -181,8 +194,18 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
     }
     segs.push_back(keep);
   };
-  for (int p = 0; p < np; ++p) add_segment(p);
-  for (int p = std::max(0, np - 1 - kWide); p < np - 1 && nodes.empty(); ++p) add_segment(p);
+  auto add_segments = [&] {
+    segs.clear();
+    for (int p = 0; p < np; ++p) add_segment(p);
+    for (int p = std::max(0, np - 1 - kWide); p < np - 1 && nodes.empty(); ++p) add_segment(p);
+  };
+  add_segments();
+  size_t all = 0;
+  for (const auto& l : segs) all += l.size();
+  if (all > MAXCAND) {
+    side = false;
+    add_segments();
+  }
   head.nseg = (int)segs.size();
   // the intervals on which t(f) is bounded, over every frequency that a row has
   double f0 = flo, f1 = fhi;

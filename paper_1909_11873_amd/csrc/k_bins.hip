@@ -65,6 +65,7 @@ LoopShape make_shape(int64_t B, int64_t M, int W, int G, int setup, int sepepi) 
   s.gper = s.pgmaj ? (s.npg + NXCD - 1) / NXCD * G : (s.items + NXCD - 1) / NXCD;
   s.setup = setup ? 1 : 0;
   s.sepepi = (sepepi && G > 1) ? 1 : 0;
+  s.order = 0;
   return s;
 }
 
@@ -135,7 +136,8 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     const double* __restrict__ theta, EventGeom geo, const EventConst* __restrict__ ec,
     const BandHead* __restrict__ bh, const int* __restrict__ plan, double* __restrict__ coef, int64_t B, int64_t Bp,
     int64_t M, LoopShape sh, double* __restrict__ part, unsigned int* __restrict__ cnt, double* __restrict__ logl,
-    const double* __restrict__ fgrid, const double* __restrict__ kcum, const int64_t* __restrict__ live) {
+    const double* __restrict__ fgrid, const double* __restrict__ kcum, const int64_t* __restrict__ live,
+    const int* __restrict__ perm) {
   constexpr int NZ = nz_of(ND, GRAD);
   constexpr bool TBL = LOOP != LOOP_MIXED;                     // the float64 phasor table
   constexpr bool BANDS = LOOP == LOOP_F64_BANDS || LOOP == LOOP_MIXED_BANDS;
@@ -187,6 +189,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
   // padding lanes repeat the last point (of the whole batch: a group's plan, and with it a point's
   // bits, do not depend on how many of its rows are live)
   const int64_t pc = p < Ball ? p : Ball - 1;
+  const int64_t pt = BANDS && perm ? perm[pc] : pc;            // the point's row of theta
   const int64_t c = (int64_t)g * sh.W + w;
   const int64_t k0l = c * sh.chunk;
   const int k0 = (int)(k0l < M ? k0l : M);
@@ -218,7 +221,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     if (w == 0 || w == wx) {
       double th[NPARAM];
 #pragma unroll
-      for (int i = 0; i < NPARAM; ++i) th[i] = theta[pc * NPARAM + i];
+      for (int i = 0; i < NPARAM; ++i) th[i] = theta[pt * NPARAM + i];
       if (w == 0) setup_lds_intrinsic(th, ec, rows_s, lane);
       if (w == wx) setup_lds_extrinsic<ND>(th, geo, ec, rows_s, lane);
     }
@@ -388,7 +391,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
         qi[d] = coef[(CO_QI + d) * Bp + pc];
       }
     }
-    if (p < B) logl[p] = value_from_rows<ND, NZ>(tot, amp, c0f, qr, qi, e);
+    if (p < B) logl[BANDS && perm ? perm[p] : p] = value_from_rows<ND, NZ>(tot, amp, c0f, qr, qi, e);
   }
 }
 
@@ -399,7 +402,7 @@ static hipError_t eval_loop(bool cut, bool rot, const EvalArgs& x, const LoopSha
 #define GWL_EVAL(ST, CU, RO)                                                                                        \
   hipLaunchKernelGGL((k_eval<ND, LOOP, GRAD, ST, CU, RO>), grid, block, lds, s, (const RowF64<ND>*)x.tab64,         \
                      (const RowMixed<ND>*)x.tab32, x.gtab, x.theta, *x.geo, x.ec, x.bands, x.plan, x.coef, x.B, x.Bp, \
-                     x.M, sh, x.part, x.cnt, x.logl, x.fgrid, x.kcum, x.live)
+                     x.M, sh, x.part, x.cnt, x.logl, x.fgrid, x.kcum, x.live, x.perm)
   const bool setup = sh.setup != 0;
   if constexpr (LOOP == LOOP_F64 || LOOP == LOOP_MIXED) {
     if (cut) {
@@ -438,7 +441,8 @@ __global__ __launch_bounds__(EPI_BLOCK) void k_value_epilogue(const EventConst* 
                                                               int G, const double* __restrict__ part,
                                                               double* __restrict__ logl, const double* __restrict__ fgrid,
                                                               const double* __restrict__ kcum, int64_t M,
-                                                              const int64_t* __restrict__ live) {
+                                                              const int64_t* __restrict__ live,
+                                                              const int* __restrict__ perm) {
   constexpr int NZ = nz_of(ND, false);
   const int64_t p = (int64_t)blockIdx.x * EPI_BLOCK + threadIdx.x;
   if (live) {
@@ -468,19 +472,19 @@ __global__ __launch_bounds__(EPI_BLOCK) void k_value_epilogue(const EventConst* 
     qr[d] = coef[(CO_QR + d) * Bp + p];
     qi[d] = coef[(CO_QI + d) * Bp + p];
   }
-  logl[p] = value_from_rows<ND, NZ>(tot, amp, c0f, qr, qi, e);
+  logl[perm ? perm[p] : p] = value_from_rows<ND, NZ>(tot, amp, c0f, qr, qi, e);
 }
 
 hipError_t launch_value_epilogue(int nd, const EventConst* ec, const double* theta, const double* coef,
                                  int64_t B, int64_t Bp, int G, const double* part, double* logl, const double* fgrid,
-                                 const double* kcum, int64_t M, const int64_t* live, hipStream_t s) {
+                                 const double* kcum, int64_t M, const int64_t* live, const int* perm, hipStream_t s) {
   if (!coef || !part || G < 1) return hipErrorInvalidValue;
   const bool cut = fgrid != nullptr;
   if (cut && !kcum) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((B + EPI_BLOCK - 1) / EPI_BLOCK));
 #define GWL_VEPI(N, CU)                                                                                       \
   hipLaunchKernelGGL((k_value_epilogue<N, CU>), grid, dim3(EPI_BLOCK), 0, s, ec, theta, coef, B, Bp, G, \
-                     part, logl, fgrid, kcum, M, live)
+                     part, logl, fgrid, kcum, M, live, perm)
 #define GWL_VEPI_ND(N)                                               \
   case N:                                                            \
     if (cut) GWL_VEPI(N, true); else GWL_VEPI(N, false);             \

@@ -38,7 +38,7 @@ template <int ND>
 __global__ __launch_bounds__(SETUP_CAL_WAVES * WAVE) void k_setup_cal(
     EventGeom g, const EventConst* __restrict__ ec, const BandHead* __restrict__ bh, double slope, int64_t M, bool mixed,
     CalShape sh, const double* __restrict__ theta, int P, int ncal, int64_t B, int64_t Bp, double* __restrict__ coef,
-    double* __restrict__ calc, int* __restrict__ plan) {
+    double* __restrict__ calc, int* __restrict__ plan, const int* __restrict__ perm) {
   alignas(16) __shared__ double rows_s[NCOEF * WAVE];
   __shared__ int ok_s[2][WAVE];
   __shared__ double diff_s[2][WAVE];
@@ -46,7 +46,8 @@ __global__ __launch_bounds__(SETUP_CAL_WAVES * WAVE) void k_setup_cal(
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // < Bp: Bp is a multiple of 64
-  const int64_t pc = p < B ? p : B - 1;                  // padding lanes repeat the last point
+  int64_t pc = p < B ? p : B - 1;                        // padding lanes repeat the last point
+  if (perm) pc = perm[pc];
   BandPre pre;
   if (bh) pre = band_fetch(bh, w, lane);
   double* slopes_s = rows_s + CO_CR * WAVE;              // (these rows go to memory only)
@@ -406,7 +407,8 @@ __device__ __forceinline__ double cal_r(const double* __restrict__ K1, const dou
 template <int ND, bool GRAD>
 __global__ __launch_bounds__(epc_waves(GRAD) * WAVE) void k_epilogue_cal(
     EventGeom g, const EventConst* __restrict__ ec, const double* __restrict__ kcal, const double* __restrict__ theta,
-    int P, int64_t B, int64_t Bp, CalShape sh, const int* __restrict__ plan, const double* __restrict__ coef,
+    int P, int64_t B, int64_t Bp, CalShape sh, const int* __restrict__ plan, const int* __restrict__ perm,
+    const double* __restrict__ coef,
     const double* __restrict__ calc, const double* __restrict__ part, double* __restrict__ logl,
     double* __restrict__ grad) {
   constexpr int NZU = nz_of(ND, GRAD), NNODE = 8 * ND, NW = epc_waves(GRAD);
@@ -416,16 +418,17 @@ __global__ __launch_bounds__(epc_waves(GRAD) * WAVE) void k_epilogue_cal(
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)blockIdx.x * WAVE + lane;   // p < Bp: the partial sums and set-up rows have Bp rows
+  int64_t pt = p < B ? p : B - 1;                        // the point's row of theta and of the results
+  if (perm) pt = perm[pt];
   const int n = sh.nnode, nchunk = sh.nchunk;
   gather_share<NZU, NW>(part, nchunk, Bp, p, w, lane, acc_s);
   if constexpr (GRAD) {
-    const int64_t pc = p < B ? p : B - 1;
     double th[NPARAM];
     GradParts<ND> r;
     __syncthreads();
     if (w < 2) {
 #pragma unroll
-      for (int i = 0; i < NPARAM; ++i) th[i] = theta[pc * P + i];
+      for (int i = 0; i < NPARAM; ++i) th[i] = theta[pt * P + i];
       gradient_parts<ND>(w, lane, acc_s, th, g, xs, r);
     }
     const double amp = coef[CO_AMP * Bp + p];            // NaN for an invalid point
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(epc_waves(GRAD) * WAVE) void k_epilogue_cal(
       const double* K2 = K1 + n;
       const double qr = coef[(int64_t)(CO_QR + d) * Bp + p], qi = coef[(int64_t)(CO_QI + d) * Bp + p];
       const double hh = amp * amp * (qr * qr + qi * qi);
-      double* out = grad + p * P + NPARAM + 2 * n * d + (kind ? n : 0);
+      double* out = grad + pt * P + NPARAM + 2 * n * d + (kind ? n : 0);
       const int wbase = (kind ? 4 * ND : 0) + 4 * d;
       double ks = 0.0;   // the amplitude task also sums K_det's calibration term
       auto finish = [&](int i, double m) {
@@ -508,7 +511,7 @@ __global__ __launch_bounds__(epc_waves(GRAD) * WAVE) void k_epilogue_cal(
     double K[ND];
 #pragma unroll
     for (int d = 0; d < ND; ++d) K[d] = ec->K[d] + ks_s[d][lane];
-    gradient_finish<ND>(w, lane, th, K, xs, r, logl + p, grad + p * P);
+    gradient_finish<ND>(w, lane, th, K, xs, r, logl + pt, grad + pt * P);
   } else {
     // the K_det terms start with the wavefront after the one that took the last sum
     int t = w - NZU % NW;
@@ -530,18 +533,19 @@ __global__ __launch_bounds__(epc_waves(GRAD) * WAVE) void k_epilogue_cal(
     double acc[NZU];
 #pragma unroll
     for (int z = 0; z < NZU; ++z) acc[z] = acc_s[z][lane];
-    logl[p] = epilogue_value_rows<ND, NZU>(acc, coef, Bp, p, ek, 1.0);
+    logl[pt] = epilogue_value_rows<ND, NZU>(acc, coef, Bp, p, ek, 1.0);
   }
 }
 
 template <int ND>
 static hipError_t cal_nd(bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const CalTables& t,
                          const double* theta, int P, int64_t B, int64_t Bp, int64_t M, const CalShape& sh, double* coef,
-                         double* calc, double* part, int* plan, double* logl, double* gradout, hipStream_t s) {
+                         double* calc, double* part, int* plan, const int* perm, double* logl, double* gradout,
+                         hipStream_t s) {
   const int ncal = 2 * sh.nnode * ND;
   if (Bp % WAVE != 0 || B < 1 || B > Bp || (t.bands && !plan)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_setup_cal<ND>, dim3((unsigned)(Bp / WAVE)), dim3(SETUP_CAL_WAVES * WAVE), 0, s, g, ec, t.bands, t.slope, M,
-                     mixed, sh, theta, P, ncal, B, Bp, coef, calc, plan);
+  hipLaunchKernelGGL(k_setup_cal<ND>, dim3((unsigned)(Bp / WAVE)), dim3(SETUP_CAL_WAVES * WAVE), 0, s, g, ec, t.bands, t.slope,
+                     M, mixed, sh, theta, P, ncal, B, Bp, coef, calc, plan, perm);
   const int* pl = t.bands ? plan : nullptr;
   const dim3 grid((unsigned)(sh.gper * NXCD)), block(BLOCK);
 #define GWL_CB(MX, GR)                                                                                              \
@@ -558,7 +562,7 @@ static hipError_t cal_nd(bool mixed, bool grad, const EventGeom& g, const EventC
 #undef GWL_CB
   const dim3 egrid((unsigned)((B + WAVE - 1) / WAVE)), eblock(epc_waves(grad) * WAVE);
 #define GWL_CE(GR)                                                                                                   \
-  hipLaunchKernelGGL((k_epilogue_cal<ND, GR>), egrid, eblock, 0, s, g, ec, t.kcal, theta, P, B, Bp, sh, pl,          \
+  hipLaunchKernelGGL((k_epilogue_cal<ND, GR>), egrid, eblock, 0, s, g, ec, t.kcal, theta, P, B, Bp, sh, pl, perm,    \
                      (const double*)coef, (const double*)calc, (const double*)part, logl, gradout)
   if (grad) GWL_CE(true); else GWL_CE(false);
 #undef GWL_CE
@@ -567,10 +571,11 @@ static hipError_t cal_nd(bool mixed, bool grad, const EventGeom& g, const EventC
 
 hipError_t launch_cal(int nd, bool mixed, bool grad, const EventGeom& g, const EventConst* ec, const CalTables& t,
                       const double* theta, int P, int64_t B, int64_t Bp, int64_t M, const CalShape& sh, double* coef,
-                      double* calc, double* part, int* plan, double* logl, double* gradout, hipStream_t s) {
+                      double* calc, double* part, int* plan, const int* perm, double* logl, double* gradout,
+                      hipStream_t s) {
   switch (nd) {
 #define GWL_CN(N) \
-  case N: return cal_nd<N>(mixed, grad, g, ec, t, theta, P, B, Bp, M, sh, coef, calc, part, plan, logl, gradout, s);
+  case N: return cal_nd<N>(mixed, grad, g, ec, t, theta, P, B, Bp, M, sh, coef, calc, part, plan, perm, logl, gradout, s);
     GWL_CN(1)
     GWL_CN(2)
     GWL_CN(3)

@@ -2,6 +2,7 @@
 // launch sequencing, tile choice. All computation happens in the kernels.
 #include <hip/hip_runtime.h>
 
+#include <limits.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -762,11 +763,11 @@ static CalShape cal_shape(const gwl_event_s* ev, int64_t B, bool grad) {
 }
 
 // set-up rows, calibration rows, sums per chunk, window moments per piece, a plan per point group
-static size_t cal_bytes(const gwl_event_s* ev, const CalShape& sh, bool grad) {
+static size_t cal_bytes(const gwl_event_s* ev, const CalShape& sh, bool grad, bool order) {
   const size_t Bp = (size_t)sh.npg * WAVE, nd = ev->ndet, n = ev->ncal;
   return sizeof(double) * Bp * (NCOEF + 2 * n * nd + sh.nchunk * (size_t)nz_of((int)nd, grad) +
                                 (sh.nchunk + n - 2) * (size_t)nz_win((int)nd, grad)) +
-         sizeof(int) * PLAN_INTS * (size_t)sh.npg;
+         sizeof(int) * PLAN_INTS * (size_t)sh.npg + (order ? sizeof(int) * Bp : 0);
 }
 
 }  // namespace gwl
@@ -781,12 +782,19 @@ static gwl_status run_logl_cal(gwl_event ev, const double* theta, int64_t B, boo
   const CalShape sh = cal_shape(ev, B, grad);
   const int64_t Bp = (int64_t)sh.npg * WAVE;
   const int ncal = 2 * n * nd;
-  const size_t bytes = cal_bytes(ev, sh, grad);
+  bool order = in_order(ev, B, grad, INT_MAX);
+  size_t bytes = cal_bytes(ev, sh, grad, order);
   void* ws = ws_given;
   if (ws_given) {
     if (ws_bytes < bytes) return fail(GWL_E_INTERNAL, "calibrated loop: workspace of %zu bytes, %zu needed", ws_bytes, bytes);
   } else {
     gwl_status st = event_workspace(ev, s, bytes, 0, &ws);
+    if (st != GWL_OK && order) {                       // no room for the order: the caller's own
+      clear_error();
+      order = false;
+      bytes = cal_bytes(ev, sh, grad, order);
+      st = event_workspace(ev, s, bytes, 0, &ws);
+    }
     if (st != GWL_OK) return st;
   }
   double* coef = (double*)ws;
@@ -795,8 +803,11 @@ static gwl_status run_logl_cal(gwl_event ev, const double* theta, int64_t B, boo
   int* plan = (int*)(part + ((size_t)sh.nchunk * nz_of(nd, grad) + (size_t)(sh.nchunk + n - 2) * nz_win(nd, grad)) * Bp);
   const CalTables t = {ev->tab64, ev->tab32, ev->g64, ev->g32, ev->cal64, ev->cal32, ev->calt64, ev->calt32, ev->calB,
                        ev->kcal, ev->bands, ev->cal_slope};
-  const hipError_t e = launch_cal(nd, mixed, grad, ev->geom, ev->ec, t, theta, NPARAM + ncal, B, Bp, ev->M, sh, coef,
-                                  calc, part, plan, logl, gradout, s);
+  int* perm = order ? plan + (size_t)PLAN_INTS * sh.npg : nullptr;
+  hipError_t e = perm ? launch_order(theta, NPARAM + ncal, B, perm, s) : hipSuccess;
+  if (e == hipSuccess)
+    e = launch_cal(nd, mixed, grad, ev->geom, ev->ec, t, theta, NPARAM + ncal, B, Bp, ev->M, sh, coef, calc, part, plan,
+                   perm, logl, gradout, s);
   if (e != hipSuccess) return hip_fail(e, "launch");
   return GWL_OK;
 }
@@ -942,7 +953,7 @@ size_t workspace_bytes(int64_t Bp, const LoopShape& sh, int nd, bool grad) {
   const size_t coef = coef_in_workspace(sh, grad) ? (size_t)NCOEF * Bp : 0;
   const size_t part = (grad || sh.G > 1) ? (size_t)sh.G * nz_of(nd, grad) * Bp : 0;
   const size_t plan = sh.setup ? 0 : sizeof(int) * PLAN_INTS * (size_t)(Bp / WAVE);
-  return sizeof(double) * (coef + part) + plan;
+  return sizeof(double) * (coef + part) + plan + (sh.order ? sizeof(int) * (size_t)Bp : 0);
 }
 
 size_t workspace_counters(const LoopShape& sh, bool grad) {
@@ -950,13 +961,19 @@ size_t workspace_counters(const LoopShape& sh, bool grad) {
 }
 
 // Set-up, bin loop and epilogue on `s`, in the event's workspace for `s`.
-gwl_status run_logl(gwl_event ev, const double* theta, int64_t B, bool mixed, bool grad, const LoopShape& sh,
+gwl_status run_logl(gwl_event ev, const double* theta, int64_t B, bool mixed, bool grad, const LoopShape& shape,
                     double* logl, double* gradout, hipStream_t s, const int64_t* live) {
+  LoopShape sh = shape;
   const int64_t Bp = (int64_t)sh.npg * WAVE;
   void* ws = nullptr;
   unsigned int* cnt = nullptr;
   gwl_status st = event_workspace(ev, s, workspace_bytes(Bp, sh, ev->ndet, grad), workspace_counters(sh, grad), &ws,
                                   &cnt);
+  if (st != GWL_OK && sh.order) {                      // no room for the order: the caller's own
+    clear_error();
+    sh.order = 0;
+    st = event_workspace(ev, s, workspace_bytes(Bp, sh, ev->ndet, grad), workspace_counters(sh, grad), &ws, &cnt);
+  }
   if (st != GWL_OK) return st;
   hipError_t e = enqueue_logl(ev, theta, B, mixed, grad, sh, (double*)ws, cnt, logl, gradout, s, live);
   if (e != hipSuccess) return hip_fail(e, "launch");
@@ -1022,7 +1039,7 @@ gwl_status event_workspace(gwl_event ev, hipStream_t s, size_t bytes, size_t ncn
 
 size_t call_workspace_bytes(const gwl_event_s* ev, int64_t B, bool mixed, bool grad) {
   const int64_t Bp = (B + WAVE - 1) / WAVE * WAVE;
-  if (ev->ncal > 0) return cal_bytes(ev, cal_shape(ev, B, grad), grad);
+  if (ev->ncal > 0) return cal_bytes(ev, cal_shape(ev, B, grad), grad, in_order(ev, B, grad, INT_MAX));
   return workspace_bytes(Bp, choose_shape(ev, B, mixed, grad), ev->ndet, grad);
 }
 
@@ -1061,22 +1078,25 @@ hipError_t enqueue_logl(gwl_event ev, const double* theta, int64_t B, bool mixed
   const size_t npart = (grad || sh.G > 1) ? (size_t)sh.G * nz_of(ev->ndet, grad) * Bp : 0;
   int* plan = sh.setup ? nullptr : (int*)(ws + (with_coef ? (size_t)NCOEF * Bp : 0) + npart);
   const BandHead* bands = sh.chunk > kBandMinChunk ? ev->bands : nullptr;
-  hipError_t e = hipSuccess;
-  if (!sh.setup)
-    e = launch_setup(ev->ndet, ev->geom, ev->ec, theta, B, Bp, coef, s, bands, ev->M, mixed, sh.nchunk, plan);
+  int* perm = sh.order && bands && !live
+                  ? (int*)(ws + (with_coef ? (size_t)NCOEF * Bp : 0) + npart) + (sh.setup ? 0 : (size_t)PLAN_INTS * sh.npg)
+                  : nullptr;
+  hipError_t e = perm ? launch_order(theta, NPARAM, B, perm, s) : hipSuccess;
+  if (e == hipSuccess && !sh.setup)
+    e = launch_setup(ev->ndet, ev->geom, ev->ec, theta, B, Bp, coef, s, bands, ev->M, mixed, sh.nchunk, plan, perm);
   hipEvent_t pa = nullptr, pb = nullptr;
   const bool prof = e == hipSuccess && prof_begin(s, pa, pb);
   const EvalArgs x = {ev->tab64, ev->tab32, ev->g64, theta, &ev->geom, ev->ec, bands, plan, coef, B, Bp, ev->M,
-                      part, cnt, logl, ev->fgrid, ev->kcum, live};
+                      part, cnt, logl, ev->fgrid, ev->kcum, live, perm};
   if (e == hipSuccess) e = launch_eval(ev->ndet, mixed, grad, ev->ech.uniform != 0, x, sh, s);
   // the value's reduction over the G workgroups in its own kernel (timed with the evaluation)
   if (e == hipSuccess && !grad && sh.G > 1 && sh.sepepi)
     e = launch_value_epilogue(ev->ndet, ev->ec, theta, coef, B, Bp, sh.G, part, logl, ev->fgrid, ev->kcum, ev->M, live,
-                              s);
+                              perm, s);
   if (prof) prof_end(s, pa, pb);
   if (e == hipSuccess && grad)
     e = launch_epilogue(ev->ndet, true, ev->geom, ev->ec, theta, coef, B, Bp, sh.G, part, logl, gradout, s, ev->fgrid,
-                        ev->kcum, ev->M);
+                        ev->kcum, ev->M, perm);
   return e;
 }
 

@@ -196,13 +196,19 @@ void choose_multi_shape(const gwl_event* evs, int E, const int64_t* B_e, bool mi
 }
 
 LoopShape choose_shape(const gwl_event_s* ev, int64_t B, bool mixed, bool grad) {
+  LoopShape sh = heuristic_shape(B, ev->M, ev->M_loop, mixed, grad);
   {
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_cache.find(make_key(ev->ndet, mixed, grad, ev->M, B));
     if (it != g_cache.end())
-      return make_shape(B, ev->M, it->second.W, it->second.G, it->second.setup, it->second.sepepi);
+      sh = make_shape(B, ev->M, it->second.W, it->second.G, it->second.setup, it->second.sepepi);
   }
-  return heuristic_shape(B, ev->M, ev->M_loop, mixed, grad);
+  sh.order = in_order(ev, B, grad, sh.chunk);
+  return sh;
+}
+
+bool in_order(const gwl_event_s* ev, int64_t B, bool grad, int chunk) {
+  return ev->bands && B >= (grad || ev->ncal > 0 ? 8192 : 16384) && chunk > kBandMinChunk;
 }
 
 }  // namespace gwl
@@ -233,7 +239,8 @@ gwl_status gwl_autotune(const char* cache_path, gwl_event ev, int64_t B, gwl_pre
   const int64_t npg = (B + WAVE - 1) / WAVE;
   std::vector<LoopShape> shapes;
   auto add1 = [&](int W, int G, int setup, int sepepi) {
-    const LoopShape sh = make_shape(B, ev->M, W, G, setup, sepepi);
+    LoopShape sh = make_shape(B, ev->M, W, G, setup, sepepi);
+    sh.order = in_order(ev, B, grad, sh.chunk);
     if ((int64_t)sh.items * sh.W > 65536 && !(sh.W == h.W && sh.G == h.G)) return;
     for (const LoopShape& u : shapes)
       if (u.W == sh.W && u.G == sh.G && u.setup == sh.setup && u.sepepi == sh.sepepi) return;

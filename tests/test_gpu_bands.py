@@ -213,3 +213,71 @@ def test_calibrated_rows_match_every_bin(kind, nd, nodes, sigma, f_hi):
         assert e.max() <= lim and c.max() <= lim, (prec, e.max(), c.max())
     ev.close()
     plain.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,n", [("prior", 16384), ("prior", 17473), ("late", 16385), ("invalid", 16448),
+                                    ("same", 16385)])
+@pytest.mark.parametrize("nodes", [0, 5])
+def test_ordered_points_match_small_calls(kind, n, nodes):
+    """A large call takes its points in an order of its own, a call of 1,000 in the caller's: other groups
+    and so other rows, each within the rows' error of the bins. Every value and gradient belongs to its
+    point; points alike in mass and time, infinite ones and a last block of one point included."""
+    spec, f, psd, data, dets = event_inputs(1, f_hi=300.0, ndet=2)
+    ev = gw.Event(torch.tensor(data, device=DEV), torch.tensor(psd, device=DEV), dets, torch.tensor(f, device=DEV),
+                  spec.df, calibration_nodes=nodes)
+    th = _points("prior" if kind == "same" else kind, n, 21)
+    rng = np.random.default_rng(22)
+    if kind == "same":
+        th[:, 0], th[:, 10] = 30.0, 0.01
+        th[5, 10], th[6, 0], th[7, 10] = np.inf, np.nan, 1e300
+    if nodes:
+        th = np.concatenate([th, 0.05 * rng.standard_normal((n, 2 * nodes * 2))], axis=1)
+    t = torch.tensor(th, device=DEV)
+    dn = math.sqrt(sum(float((4 * spec.df * np.abs(d) ** 2 / s).sum()) for d, s in zip(data, psd)))
+    for prec in ("fp64", "mixed"):
+        want, gwant = (torch.cat(x).cpu().numpy() for x in
+                       zip(*(gw.logl_grad(t[i:i + 1000].contiguous(), ev, prec) for i in range(0, n, 1000))))
+        ok = np.isfinite(want)
+        hn = dn + np.sqrt(np.maximum(dn ** 2 - 2.0 * want[ok], 0.0))
+        tol = 2e-13 * hn * dn + 2e-9 if prec == "fp64" else 2e-3
+        v, g = (x.cpu().numpy() for x in gw.logl_grad(t, ev, prec))
+        for got in (gw.logl(t, ev, prec).cpu().numpy(), v):
+            assert np.array_equal(np.isfinite(got), ok)
+            assert (np.abs(got[ok] - want[ok]) <= tol).all(), (prec, np.abs(got[ok] - want[ok]).max())
+        assert np.array_equal(np.isfinite(g), np.isfinite(gwant))
+        lim = 2e-9 if prec == "fp64" else 1e-3
+        assert scaled_grad_error(g[ok][:, :11], gwant[ok][:, :11]).max() <= lim
+        if nodes:
+            c = np.abs(g[ok][:, 11:] - gwant[ok][:, 11:]) / np.abs(gwant[ok][:, 11:]).max(axis=1, keepdims=True)
+            assert c.max() <= lim
+    ev.close()
+
+
+@pytest.mark.gpu
+def test_capture_without_room_for_the_order():
+    """On a capturing stream whose workspace is too small for the points' order a large call keeps the
+    caller's order, as it needs no workspace otherwise; each replay gives the eager call's values."""
+    spec, f, psd, data, dets = event_inputs(1, f_hi=120.0, ndet=1)
+    ev = gw.Event(torch.tensor(data, device=DEV), torch.tensor(psd, device=DEV), dets, torch.tensor(f, device=DEV),
+                  spec.df)
+    n = 600000
+    t = torch.tensor(_points("prior", 4096, 31), device=DEV).repeat(-(-n // 4096), 1)[:n].contiguous()
+    want = gw.logl(t, ev, "fp64")
+    out = torch.empty_like(want)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        gw.logl(t[:64].contiguous(), ev, "fp64")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        out.copy_(gw.logl(t, ev, "fp64"))
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        ok = torch.isfinite(want)
+        assert torch.equal(torch.isfinite(out), ok)
+        scale = float(want[ok].abs().max())
+        assert float((out[ok] - want[ok]).abs().max()) <= 1e-11 * scale + 2e-9
+    ev.close()
