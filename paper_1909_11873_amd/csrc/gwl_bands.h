@@ -87,6 +87,19 @@ __device__ inline float wave_max_hi(float v) {
   return dpp_max<0x143>(v);  // row_bcast:31
 }
 
+// sums over the lanes up to each of the first 16, and v one lane up (0 in lane 0)
+template <int CTRL>
+__device__ inline int dpp_or_zero(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+}
+__device__ inline int sums_16(int v) {
+  v += dpp_or_zero<0x111>(v);  // row_shr:1
+  v += dpp_or_zero<0x112>(v);
+  v += dpp_or_zero<0x114>(v);
+  return v + dpp_or_zero<0x118>(v);
+}
+__device__ inline int lane_up(int v) { return dpp_or_zero<0x111>(v); }
+
 // The steps are a chain of short reads by few wavefronts, bound by latency. They read what they need of the
 // head without waiting for memory in turn: the slopes go to LDS while the point model runs, the bands
 // and segments to registers before it, and a band's extremes come from two windows instead of a loop over
@@ -220,7 +233,8 @@ __device__ inline int band_of_segment(const BandPre& own, int lane, const BandLd
 __device__ inline void band_plan(const BandPre& own, const double* slopes_s, int64_t M, bool mixed, int nchunk, int lane,
                                  BandLds& s) {
   const int2* rows_s = reinterpret_cast<const int2*>(slopes_s);
-  const int ns = own.nseg, np = own.npanel;
+  static_assert(MAXPANEL <= 16, "sums_16");
+  const int ns = __builtin_amdgcn_readfirstlane(own.nseg), np = __builtin_amdgcn_readfirstlane(own.npanel);
   int rows = 0, row0 = 0, cand = -1, first = 0;
   if (lane < ns) {
     cand = band_of_segment(own, lane, s);
@@ -233,28 +247,19 @@ __device__ inline void band_plan(const BandPre& own, const double* slopes_s, int
       rows = b.y;
     }
   }
-  // rows of the panels before each panel
-  int pre = lane < np ? rows : 0;
-#pragma unroll
-  for (int off = 1; off < 16; off <<= 1) {
-    const int o = __shfl_up(pre, off);
-    if (lane >= off) pre += o;
+  // rows of the panels up to each panel, and the cheapest wide segment (0: none)
+  const int pre = sums_16(lane < np ? rows : 0), excl = lane_up(pre);
+  int all = __builtin_amdgcn_readlane(pre, np - 1), wide = 0;
+  for (int j = np; j < ns; ++j) {
+    const int n = __builtin_amdgcn_readlane(excl, __builtin_amdgcn_readlane(first, j)) + __builtin_amdgcn_readlane(rows, j);
+    if (__builtin_amdgcn_readlane(cand, j) >= 0 && n < all) {
+      all = n;
+      wide = j;
+    }
   }
-  const int total = __shfl(pre, np - 1);
-  int excl = __shfl_up(pre, 1);
-  if (lane == 0) excl = 0;
-  const int below = __shfl(excl, first);
-  unsigned long long key = ~0ull;
-  if (lane == 0) key = (unsigned long long)total << 6;
-  else if (lane >= np && lane < ns && cand >= 0) key = ((unsigned long long)(below + rows) << 6) | (unsigned)lane;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const unsigned long long o = __shfl_xor(key, off);
-    key = o < key ? o : key;
-  }
-  const int wide = (int)(key & 63), all = (int)(key >> 6);   // wide = 0: none
-  const int nf = wide ? __shfl(first, wide) : np;            // panels that stay
-  const int wrows = __shfl(rows, wide), wrow0 = __shfl(row0, wide), wcand = __shfl(cand, wide);
+  const int nf = wide ? __builtin_amdgcn_readlane(first, wide) : np;            // panels that stay
+  const int wrows = __builtin_amdgcn_readlane(rows, wide), wrow0 = __builtin_amdgcn_readlane(row0, wide),
+            wcand = __builtin_amdgcn_readlane(cand, wide);
   if (wide && lane == nf) {
     rows = wrows;
     row0 = wrow0;
@@ -295,9 +300,8 @@ __device__ inline void band_plan_cal(const BandPre& own, const double* slopes_s,
     s.plan[4 + 2 * lane] = b.x;
     s.plan[5 + 2 * lane] = rows;
   }
-  int all = rows;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) all += __shfl_xor(all, off);
+  static_assert(MAXNODE - 1 <= 16, "sums_16");
+  const int all = __builtin_amdgcn_readlane(sums_16(rows), 15);
   if (lane == 0) {
     const bool f64 = !mixed || 5 * (int64_t)all <= 4 * M;
     s.plan[0] = all;
