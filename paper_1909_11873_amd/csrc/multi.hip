@@ -40,9 +40,9 @@ namespace gwl {
 
 constexpr int MULTI_SETUP_WAVES = 4;  // wavefronts per group of 64 points in the set-up
 constexpr int MULTI_EPI_BLOCK = 256;  // points per workgroup of the value's epilogue
-// bins per chunk of a group that walks its bins: the length that the 64-event workload's tuning found
-// when every group did
-constexpr int MULTI_BIN_CHUNK = 1536;
+// bins per chunk of a group that walks its bins, at least (an item has four): 12 float64 events whose
+// points arrive all over the segment, mostly on bins: 3.20 ms at 1,536, 2.75 at 384
+constexpr int MULTI_BIN_CHUNK = 384;
 constexpr int MULTI_ROUND_ROWS = 96;
 constexpr int MULTI_RED = 4;          // sums reduced per LDS pass
 
