@@ -38,6 +38,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_k_eval_mixed_c1.txt")
 # loaded so that timed launches use a fixed, tuned shape; --retune measures them again
 TUNE_FILE = os.path.join(ROOT, "paper_1909_11873_amd", "tuning_gfx950.json")
 KERNEL_SOURCES = ["paper_1909_11873_amd/csrc/k_bins.hip", "paper_1909_11873_amd/csrc/gwl_bins.h",
+                  "paper_1909_11873_amd/csrc/gwl_bands.h",
                   "paper_1909_11873_amd/csrc/gwl_common.h", "paper_1909_11873_amd/csrc/gwl_device.h",
                   "paper_1909_11873_amd/csrc/gwl_epilogue.h", "paper_1909_11873_amd/csrc/gwl_launch.h"]
 
@@ -120,10 +121,14 @@ def layout_key(shape) -> str:
 
 
 def kernel_name(nd: int, mixed: bool, grad: bool, shape) -> str:
-    """The evaluation kernel's name as the profiler prints it: k_eval<ND, MIXED, GRAD, SETUP, CUT,
-    ROT> (no ISCO cut; the float64 loop on the workloads' uniform grids rotates the phasors)."""
+    """The evaluation kernel's name as the profiler prints it: k_eval<ND, LOOP, GRAD, SETUP, CUT,
+    ROT> (no ISCO cut). LOOP: 0 float64 and 1 mixed over every bin, which launches with chunks of at most
+    20 bins take, 2 and 3 over band-limited rows; the float64 loops on the workloads' uniform grids
+    rotate the phasors."""
     b = lambda x: "true" if x else "false"
-    return f"gwl::k_eval<{nd}, {b(mixed)}, {b(grad)}, {b(shape['setup'])}, false, {b(not mixed)}>"
+    rows = shape["chunk_bins"] > 20
+    return (f"gwl::k_eval<{nd}, {int(bool(mixed)) + 2 * rows}, {b(grad)}, {b(shape['setup'])}, false, "
+            f"{b(rows or not mixed)}>")
 
 
 WARM_S = 0.3
@@ -818,7 +823,9 @@ def main():
     roof.update({"traffic": traffic if prec == "mixed" and args.config == 1 else None, "kernel": head["kernel"],
                  "kernel_ms": head["kernel_ms_median"], "kernel_ms_mean": head["kernel_ms_mean"],
                  "timing": ("median over 50 launches of HIP events on its stream around the evaluation kernel and, "
-                           "where the launch shape has one, its value-epilogue kernel")})
+                           "where the launch shape has one, its value-epilogue kernel"),
+                 "work": ("priced as the direct sum over every bin; a launch that walks band-limited rows does less, "
+                          "so its fraction may exceed 1")})
     line = {
         "metric": metric,
         "value": head["value"], "unit": "evals/s", "n_gpus": 1, "steps": steps_head, "warmup": args.warmup,
