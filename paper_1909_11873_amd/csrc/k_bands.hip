@@ -275,7 +275,9 @@ __global__ __launch_bounds__(256) void k_band_kernel(const BandGen* __restrict__
 }
 
 // The rows: one wavefront per four neighbouring rows of a band, its lanes over the sources within
-// their windows (each source is read once for the four rows).
+// their windows (each source is read once for the four rows). Bound by L2 reads of the sources; 8 s, three
+// detectors, 118,000 rows: 134 us in the two launches; 128 s: 650 (9.9 ms when every band was summed from
+// the bins).
 constexpr int BR_ROWS = 4;
 constexpr int BR_WAVES = 4;
 template <int ND>

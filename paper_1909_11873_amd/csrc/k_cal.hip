@@ -196,6 +196,10 @@ constexpr int cal_waves_per_eu() {
   return (MIXED && GRAD) ? 2 : 1;
 }
 
+// The loop, a wavefront per chunk: equal shares of a group's rows, each walked interval by interval. Bound by
+// float64 issue. Three detectors, 8 s, 10 nodes: values of 16,384 points 847 us a call on every bin, 158 on
+// rows, 138 with the points in order (the loop 148 and 113); gradients of 8,192 822, 190 and 168 (119 and
+// 91). Chunks that ended at the intervals' ends made uneven work: 342 us and 510.
 // With a plan the float64 kernel takes the groups on float64 rows (all of them in a float64 call) and the
 // mixed kernel the others: two launches, so that each keeps its own registers.
 template <int ND, bool MIXED, bool GRAD>

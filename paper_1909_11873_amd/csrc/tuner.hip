@@ -161,7 +161,7 @@ namespace gwl {
 // and a point's sums come from at most 32 workgroups. The set-up runs in the kernel, whose later
 // workgroups then overlap it, and the sums of several workgroups go to the second kernel: both were the
 // faster form at every size tried from 1 to 65,536 points (on 1 to 3 detectors, 4 to 128 s; for
-// instance 16,384 points at three detectors and 8 s 117 us against 123 with the set-up apart).
+// instance gradients of 16,384 points at three detectors and 8 s 117 us against 123 with the set-up apart).
 // Where that many wavefronts leave so few bins each that the bins are walked directly
 // (kBandMinChunk), the split is chosen for the bins, at least 8 a wavefront.
 LoopShape heuristic_shape(int64_t B, int64_t M, int64_t rows, bool mixed, bool grad) {
