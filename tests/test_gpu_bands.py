@@ -281,3 +281,56 @@ def test_capture_without_room_for_the_order():
         scale = float(want[ok].abs().max())
         assert float((out[ok] - want[ok]).abs().max()) <= 1e-11 * scale + 2e-9
     ev.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lo,hi", [(0.07, 0.11), (-0.13, -0.09), (0.125, 0.16)])
+@pytest.mark.parametrize("nodes", [0, 8])
+def test_bands_off_the_centre(lo, hi, nodes):
+    """Groups of heavy systems that arrive within 40 ms of one another, away from zero, take the bands
+    centred near them; against the same bins with two neighbours swapped, which have no rows."""
+    spec, f, psd, data, dets = event_inputs(1, f_hi=900.0)
+    k = len(f) // 2
+    swap = np.r_[0:k, k + 1, k, k + 2:len(f)]
+    mk = lambda i: gw.Event(torch.tensor(np.ascontiguousarray(data[:, i]), device=DEV),
+                            torch.tensor(np.ascontiguousarray(psd[:, i]), device=DEV), dets,
+                            torch.tensor(f[i], device=DEV), spec.df, calibration_nodes=nodes)
+    ev, plain = mk(np.arange(len(f))), mk(swap)
+    rng = np.random.default_rng(41)
+    th = synth.prior_draw(rng, 200, mc_range=(40.0, 60.0))
+    th[:, 10] = rng.uniform(lo, hi, len(th))
+    if nodes:
+        th = np.concatenate([th, 0.05 * rng.standard_normal((len(th), 2 * nodes * 3))], axis=1)
+    t = torch.tensor(th, device=DEV)
+    dn = math.sqrt(sum(float((4 * spec.df * np.abs(d) ** 2 / s).sum()) for d, s in zip(data, psd)))
+    for prec in ("fp64", "mixed"):
+        want, gwant = (x.cpu().numpy() for x in gw.logl_grad(t, plain, prec))
+        hn = dn + np.sqrt(np.maximum(dn ** 2 - 2.0 * want, 0.0))
+        tol = 1e-13 * hn * dn + 1e-9 if prec == "fp64" else 1e-3
+        v, g = (x.cpu().numpy() for x in gw.logl_grad(t, ev, prec))
+        for got in (v, gw.logl(t, ev, prec).cpu().numpy()):
+            assert (np.abs(got - want) <= tol).all(), (prec, np.abs(got - want).max())
+        assert scaled_grad_error(g[:, :11], gwant[:, :11]).max() <= (2e-9 if prec == "fp64" else 1e-3)
+    ev.close()
+    plain.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,live", [(65, 64), (8192, 1), (8192, 3277), (33000, 32769), (33000, 0)])
+def test_live_calls_on_rows(batch, live):
+    """Live-length calls over their range of workgroups per group, many to one: the live points' values,
+    to the rows' error, and no other written."""
+    spec, f, psd, data, dets = event_inputs(1, f_hi=700.0)
+    ev = gw.Event(torch.tensor(data, device=DEV), torch.tensor(psd, device=DEV), dets, torch.tensor(f, device=DEV),
+                  spec.df)
+    t = torch.tensor(_points("prior", 4096, 51), device=DEV).repeat(-(-batch // 4096), 1)[:batch].contiguous()
+    dn = math.sqrt(sum(float((4 * spec.df * np.abs(d) ** 2 / s).sum()) for d, s in zip(data, psd)))
+    want = gw.logl(t[:1000].contiguous(), ev, "fp64")
+    out = torch.full((batch,), -1.0, dtype=torch.float64, device=DEV)
+    gw.logl_live(t, torch.tensor(live, dtype=torch.int64, device=DEV), ev, "fp64", out=out)
+    n = min(live, 1000)
+    w = want[:n].cpu().numpy()[:min(n, batch)]
+    hn = dn + np.sqrt(np.maximum(dn ** 2 - 2.0 * w, 0.0))
+    assert (np.abs(out[:len(w)].cpu().numpy() - w) <= 2e-13 * hn * dn + 2e-9).all()
+    assert bool((out[live:] == -1.0).all()) and bool((out[:live] != -1.0).all())
+    ev.close()
