@@ -155,26 +155,35 @@ __global__ void k_fill_theta(double* theta, int64_t B, int P) {
 namespace gwl {
 
 // Shapes without a measured entry. `rows` is what a typical group walks (its bins, or its band-limited
-// rows). About 4,096 wavefronts (four per SIMD; more measured no faster, the float64 loop's registers
-// allow five), 16 per workgroup (8 for the gradient, and for batches that fill the chip by themselves),
-// while a wavefront keeps 6 rows (12 for the gradient, whose partial sums are three times as many)
-// and a point's sums come from at most 32 workgroups. The set-up runs in the kernel, whose later
-// workgroups then overlap it, and the sums of several workgroups go to the second kernel: both were the
-// faster form at every size tried from 1 to 65,536 points (on 1 to 3 detectors, 4 to 128 s; for
-// instance gradients of 16,384 points at three detectors and 8 s 117 us against 123 with the set-up apart).
-// Where that many wavefronts leave so few bins each that the bins are walked directly
+// rows). A CU holds 16 of the loop's wavefronts at a time (its registers), so the launch is as many
+// workgroups as fit 4,096 wavefronts together, of 16 or of 8 wavefronts, whichever fills them better: a few
+// more would wait for a second round with a set-up of its own. A wavefront keeps 6 rows (8 for the gradient,
+// whose partial sums are three times as many; where that is the limit 16, and 8 wavefronts) and a point's sums come from at most 32 workgroups; batches that
+// fill the chip by themselves take 8 wavefronts. On three detectors and 8 s, with as many workgroups as make at
+// least 4,096 wavefronts and now: 9,000 values 67 and 45 us, 28,000 113 and 83, gradients of 4,000 59 and
+// 42; two detectors, 17 s: 6,000 values 49 and 32, gradients of 3,001 47 and 33. The set-up runs in the
+// kernel, whose later workgroups then overlap it, and the sums of several workgroups go to the second
+// kernel: both were the faster form at every size tried from 1 to 65,536 points.
+// Where that many wavefronts leave a value's call so few bins each that the bins are walked directly
 // (kBandMinChunk), the split is chosen for the bins, at least 8 a wavefront.
 LoopShape heuristic_shape(int64_t B, int64_t M, int64_t rows, bool mixed, bool grad) {
   (void)mixed;
+  constexpr int64_t kResident = 4096;
   const int64_t npg = (B + WAVE - 1) / WAVE;
-  const int W = grad || npg >= 512 ? 8 : 16;
-  const int64_t fill = std::min<int64_t>(32, (4096 + npg * W - 1) / (npg * W));
+  const int64_t g16 = kResident / (16 * npg), g8 = std::max<int64_t>(1, kResident / (8 * npg));
+  const bool few = grad && rows < 8 * 16 * g16;          // gradients of few points: the rows are the limit
+  const int W = !few && 16 * g16 >= 8 * g8 ? 16 : 8;
+  // between a half and three quarters of one round: two workgroups a group, whose second round runs beside the
+  // first one's end (20,000 gradients at two detectors and 17 s: 92 us, 116 with one; 28,000 values, 0.86 of a
+  // round: 92, 84 with one)
+  const bool twice = npg > kResident / 16 && npg <= kResident / 8 * 3 / 4;
+  const int64_t fill = std::min<int64_t>(32, twice ? 2 : (W == 16 ? g16 : g8));
   auto split = [&](int64_t n, int64_t least) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(fill, (n + least * W - 1) / (least * W)));
   };
   const LoopShape direct = make_shape(B, M, W, split(M, 8), 1, 1);
-  if (rows < M && direct.chunk <= kBandMinChunk) return direct;
-  return make_shape(B, M, W, split(rows, grad ? 12 : 6), 1, 1);
+  if (!(grad && rows < M) && direct.chunk <= kBandMinChunk) return direct;
+  return make_shape(B, M, W, split(rows, few ? 16 : (grad ? 8 : 6)), 1, 1);
 }
 
 hipError_t fill_theta(double* theta, int64_t B, hipStream_t s, int P) {
