@@ -752,8 +752,16 @@ static CalShape cal_shape(const gwl_event_s* ev, int64_t B, bool grad) {
   const int n = ev->ncal;
   sh.nnode = n;
   sh.npg = (int)((B + WAVE - 1) / WAVE);
-  const int64_t fill = ((grad ? 2048 : 4096) + sh.npg - 1) / sh.npg;
-  sh.nchunk = (int)std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(fill, 4), ev->M_loop / 24, 128}));
+  // Workgroups of four chunks resident together, by the loops' registers: as many of them as fit, or one a
+  // group more where that leaves a quarter of them empty, and 48 rows a chunk at least (the epilogue walks the
+  // chunks in turn). Three detectors, 8 s, 10 nodes, with as many as make 4,096 wavefronts (gradients 2,048) of
+  // 24 rows and now: values of 1,000 points 62 and 55 us, 9,000 123 and 102, 20,000 198 and 172; gradients
+  // of 1,000 135 and 95, 5,000 153 and 129. (At 12, 24, 40, 60 and 90 rows gradients of 1,000 points take
+  // 172, 135, 101, 93 and 94, values of 3,000 78, 78, 72, 69 and 79.)
+  const int64_t fit = grad ? (ev->ndet == 1 ? 1024 : (ev->ndet == 2 ? 768 : 512)) : 1024;
+  int64_t nbc = std::max<int64_t>(1, fit / sh.npg);
+  if (4 * nbc * sh.npg < 3 * fit) ++nbc;
+  sh.nchunk = (int)std::max<int64_t>(1, std::min<int64_t>({WAVES_PER_BLOCK * nbc, ev->M_loop / 48, 128}));
   sh.nbc = (sh.nchunk + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
   sh.items = sh.npg * sh.nbc;
   sh.gper = (sh.items + NXCD - 1) / NXCD;
