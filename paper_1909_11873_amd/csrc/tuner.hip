@@ -158,7 +158,7 @@ namespace gwl {
 // rows). A CU holds 16 of the loop's wavefronts at a time (its registers), so the launch is as many
 // workgroups as fit 4,096 wavefronts together, of 16 or of 8 wavefronts, whichever fills them better: a few
 // more would wait for a second round with a set-up of its own. A wavefront keeps 6 rows (8 for the gradient,
-// whose partial sums are three times as many; where that is the limit 16, and 8 wavefronts) and a point's sums come from at most 32 workgroups; batches that
+// whose partial sums are three times as many; where that is the limit 12, and 8 wavefronts) and a point's sums come from at most 32 workgroups; batches that
 // fill the chip by themselves take 8 wavefronts. On three detectors and 8 s, with as many workgroups as make at
 // least 4,096 wavefronts and now: 9,000 values 67 and 45 us, 28,000 113 and 83, gradients of 4,000 59 and
 // 42; two detectors, 17 s: 6,000 values 49 and 32, gradients of 3,001 47 and 33. The set-up runs in the
@@ -183,7 +183,7 @@ LoopShape heuristic_shape(int64_t B, int64_t M, int64_t rows, bool mixed, bool g
   };
   const LoopShape direct = make_shape(B, M, W, split(M, 8), 1, 1);
   if (!(grad && rows < M) && direct.chunk <= kBandMinChunk) return direct;
-  return make_shape(B, M, W, split(rows, few ? 16 : (grad ? 8 : 6)), 1, 1);
+  return make_shape(B, M, W, split(rows, few ? 12 : (grad ? 8 : 6)), 1, 1);
 }
 
 hipError_t fill_theta(double* theta, int64_t B, hipStream_t s, int P) {
