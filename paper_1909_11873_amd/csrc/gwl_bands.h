@@ -21,6 +21,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "gwl_common.h"
@@ -34,6 +35,14 @@ constexpr int MAXCAND = 512;    // bands of all segments
 constexpr int PLAN_INTS = 64;   // a group's plan: rows in all, pieces, float64 path, rows per chunk;
                                 // then per piece its first row, its rows and its band (-1: bins)
 constexpr double BAND_FILL = 0.98;  // share of a band's half-width that a group may use
+// A calibrated event's rows lie at most a quarter of the frequency, and CAL_REACH node spacings (in ln f, hx
+// each), beyond their interval: cal_reach spacings. The interval's Catmull-Rom cubic, run on x spacings beyond,
+// has slope weights (1 + 4x + 3x^2) / 2, (1 - 6x - 6x^2) / 2 and (2x + 3x^2) / 2 on the differences of the
+// nodes around it, whose magnitudes add to 6x (1 + x) from x = 0.2 on and to 1.5 at most up to there and within the
+// interval: cal_slope times the largest difference bounds the slope per spacing.
+constexpr double CAL_REACH = 0.75;
+inline double cal_reach(double hx) { return fmin(0.22314355131420976 / hx, CAL_REACH); }   // ln 1.25
+inline double cal_slope(double reach) { return fmax(1.5, 6.0 * reach * (1.0 + reach)); }
 
 struct BandCand {
   double t0, tb;      // centre and half-width of the band (s)

@@ -52,7 +52,7 @@ void basis_slopes(double f, double (&g)[NBASIS]) {
 //
 // `nodes`, when given, are the first bins of segments that rows may not be shared across (the last
 // element is M): the calibration's node intervals, on each of which the model's factor is one cubic. The
-// rows' frequencies then stay within a quarter of the interval's ends, where that cubic is tame.
+// rows' frequencies then stay within cal_reach node spacings of the interval's ends, where that cubic is tame.
 void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t row_base,
                 const std::vector<int64_t>& nodes, BandHead& head, std::vector<BandGen>& gen, int64_t& nrows,
                 int64_t& kvals) {
@@ -74,6 +74,7 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
   ends.push_back(M);
   if (!nodes.empty()) ends = nodes;
   const int np = (int)ends.size() - 1;
+  const double hx = log(fhi / flo) / np, reach = nodes.empty() ? 0.0 : exp(cal_reach(hx) * hx);
   if (np > MAXSEG) return;
   head.npanel = np;
   struct Cand {
@@ -95,8 +96,8 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
       segs.push_back(list);
       return;
     }
-    const double fa = f[(size_t)ka], flow = (nodes.empty() ? 0.5 : 0.8) * fa;
-    const double fhigh = nodes.empty() ? HUGE_VAL : 1.25 * f[(size_t)kb - 1];
+    const double fa = f[(size_t)ka], flow = nodes.empty() ? 0.5 * fa : fa / reach;
+    const double fhigh = nodes.empty() ? HUGE_VAL : reach * f[(size_t)kb - 1];
     const double width = f[(size_t)kb - 1] - fa, df = uniform ? step : width / (double)(nb - 1);
     // the band of the fewest rows centred at t0 with half-width tb or a little more, of sources from
     // fs over ws (c.rows = 0: none)

@@ -31,8 +31,8 @@ namespace gwl {
 // per half of the model), and the calibration node values turned from theta's columns 11.. into
 // rows calc [ncal][Bp], two more wavefronts copying half of them each; every row of a point with a
 // non-finite node value is NaN. With band-limited rows the four bound the group's arrival times as k_setup's
-// do, widened by the calibration phase: within a node interval (and a quarter beyond) the spline's slope
-// is at most four times the largest difference of neighbouring node values per node spacing.
+// do, widened by the calibration phase: over a node interval's rows the spline's slope per node spacing is at
+// most cal_slope (gwl_bands.h) times the largest difference of neighbouring node values.
 constexpr int SETUP_CAL_WAVES = 4;
 template <int ND>
 __global__ __launch_bounds__(SETUP_CAL_WAVES * WAVE) void k_setup_cal(

@@ -617,7 +617,7 @@ static gwl_status attach_cal(gwl_event ev, const std::vector<double>& frow, cons
   }
   std::vector<double>().swap(ev->band_f);
   std::vector<int>().swap(ev->band_seg);
-  ev->cal_slope = 4.0 / (2.0 * M_PI * hx);
+  ev->cal_slope = cal_slope(cal_reach(hx)) / (2.0 * M_PI * hx);
   Slab keep;
   const size_t o32 = keep.take(sizeof(RowCal32) * (M + TAB_PAD)), o64 = keep.take(sizeof(double) * w.size());
   const size_t ot32 = keep.take(sizeof(float) * (M + TAB_PAD)), ot64 = keep.take(sizeof(double) * tl.size());

@@ -334,3 +334,37 @@ def test_live_calls_on_rows(batch, live):
     assert (np.abs(out[:len(w)].cpu().numpy() - w) <= 2e-13 * hn * dn + 2e-9).all()
     assert bool((out[live:] == -1.0).all()) and bool((out[:live] != -1.0).all())
     ev.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nodes,f_lo,f_hi,duration,sigma", [
+    (16, 20.0, 60.0, 256.0, 0.1), (16, 30.0, 120.0, 128.0, 0.1), (16, 20.0, 200.0, 8.0, 0.3), (12, 20.0, 700.0, 8.0, 0.1)])
+def test_calibrated_rows_on_narrow_bands(nodes, f_lo, f_hi, duration, sigma):
+    """Node spacings of 0.07 to 0.3 in ln f, every group of 64 points one point: nothing but the bound on the
+    calibration phase's slope widens the group's arrival times. Against the same bins with two neighbours
+    swapped, which have no rows; bounds as for other calibrated rows."""
+    df = 1.0 / duration
+    f = synth.freq_grid(f_lo, f_hi, df)
+    psd = synth.psd_fit(f)[None]
+    dets = np.array([synth.detector_rad("D1")])
+    data = synth.noise(77, psd[0], df)[None] + o.strain_all(synth.THETA0_BBH, dets, f).numpy()
+    k = len(f) // 2
+    swap = np.r_[0:k, k + 1, k, k + 2:len(f)]
+    mk = lambda i: gw.Event(torch.tensor(np.ascontiguousarray(data[:, i]), device=DEV),
+                            torch.tensor(np.ascontiguousarray(psd[:, i]), device=DEV), dets,
+                            torch.tensor(f[i], device=DEV), df, calibration_nodes=nodes)
+    ev, plain = mk(np.arange(len(f))), mk(swap)
+    rng = np.random.default_rng(61)
+    th = synth.prior_draw(rng, 24, mc_range=(20.0, 60.0))
+    th = np.repeat(np.concatenate([th, sigma * rng.standard_normal((24, 2 * nodes))], axis=1), 64, axis=0)
+    t = torch.tensor(th, device=DEV)
+    dn = math.sqrt(float((4 * df * np.abs(data) ** 2 / psd).sum()))
+    want, gwant = (x.cpu().numpy() for x in gw.logl_grad(t, plain, "fp64"))
+    hn = dn + np.sqrt(np.maximum(dn ** 2 - 2.0 * want, 0.0))
+    v, g = (x.cpu().numpy() for x in gw.logl_grad(t, ev, "fp64"))
+    for got in (v, gw.logl(t, ev, "fp64").cpu().numpy()):
+        assert (np.abs(got - want) <= 1e-13 * hn * dn + 1e-9).all(), (np.abs(got - want) / (hn * dn)).max()
+    c = np.abs(g[:, 11:] - gwant[:, 11:]) / np.abs(gwant[:, 11:]).max(axis=1, keepdims=True)
+    assert scaled_grad_error(g[:, :11], gwant[:, :11]).max() <= 2e-9 and c.max() <= 2e-9
+    ev.close()
+    plain.close()
