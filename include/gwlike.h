@@ -198,9 +198,9 @@ gwl_status gwl_logl_batch(gwl_event ev, const double* theta, int64_t B, gwl_prec
  * live a device int64 read by the kernels when they run (values above B count as B, below 1 as
  * none). The launch is sized for B, so the call can be captured once and replayed for batches
  * of any length up to B, e.g. the shrinkage draws of the slice-sampling chains still moving
- * (gwl_slice_draws sets *live). Point groups past *live leave the evaluation kernel at once; the
- * launch splits each point group's bins over enough workgroups that a quarter of the point groups
- * still fill the chip. Not for calibrated events (GWL_E_UNSUPPORTED).
+ * (gwl_slice_draws sets *live). Point groups past *live leave the evaluation kernel at once. A point's
+ * value has the same bits whichever points are live beside it and whatever the rows past *live hold.
+ * Not for calibrated events (GWL_E_UNSUPPORTED).
  */
 gwl_status gwl_logl_batch_live(gwl_event ev, const double* theta, int64_t B, const int64_t* live, gwl_precision prec,
                                double* logl, void* stream);

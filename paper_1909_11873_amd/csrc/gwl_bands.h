@@ -34,6 +34,7 @@ constexpr int MAXBRK = 63;      // frequency intervals on which t(f) is bounded
 constexpr int MAXCAND = 512;    // bands of all segments
 constexpr int PLAN_INTS = 64;   // a group's plan: rows in all, pieces, float64 path, rows per chunk;
                                 // then per piece its first row, its rows and its band (-1: bins)
+constexpr int MAXLEV = 3;       // levels: fixed choices of bands, from which a point alone takes its rows
 constexpr double BAND_FILL = 0.98;  // share of a band's half-width that a group may use
 // A calibrated event's rows lie at most a quarter of the frequency, and CAL_REACH node spacings (in ln f, hx
 // each), beyond their interval: cal_reach spacings. The interval's Catmull-Rom cubic, run on x spacings beyond,
@@ -50,14 +51,24 @@ struct BandCand {
   int row0, rows;     // its rows in the event's tables
   int i0, i1;         // the intervals that its rows' frequencies reach over
 };
+// A level: a fixed choice of bands (and bins), in the form of a group's plan, and the interval limits within
+// which t(f) has to lie for them to hold a point. Live-length calls walk levels: which of the batch's points are
+// live, and what the rows past them hold, must not show in a point's bits.
+struct BandLevel {
+  int rows, np;
+  int piece[3 * (MAXPANEL + 2)];   // per piece its first row, its rows and its band (-1: bins)
+  double lo[MAXBRK], hi[MAXBRK];
+};
 struct BandHead {
   int nbrk, ncand, nseg, npanel;
+  int nlev[2];             // levels of a float64 and of a mixed-precision call (fewest rows first)
   int c0[MAXSEG + 1];      // each segment's bands, fewest rows first
   int first[MAXSEG];       // the panel that a segment starts with
   int k0[MAXSEG];          // its bins
   int bins[MAXSEG];
   alignas(16) double gp[MAXBRK + 1][NBASIS];  // g_m'(f) at the interval ends (each g_m' is monotone between them)
   BandCand cand[MAXCAND];
+  BandLevel lev[MAXLEV + 1];   // the last: every bin, for a point that no level holds
 };
 
 // How a band's rows are made (host to device, at event creation).
@@ -79,6 +90,7 @@ struct BandLds {
   float2 r[MAXBRK + 1];                      // lowest and highest t per interval over the group
   unsigned long long ok[MAXCAND / 64 + 1];   // bands that hold the group
   int plan[PLAN_INTS];
+  unsigned long long fit[MAXLEV];            // the points that each level holds
 };
 
 template <int CTRL>
@@ -147,14 +159,12 @@ __device__ __forceinline__ BandPre band_fetch(const BandHead* __restrict__ bh, i
   return f;
 }
 
-// Step 1, by nw wavefronts that each hold the group's 64 points: bounds of t(f) over the group, each
-// wavefront on its share of the intervals. Every g_m' is monotone, so over an interval t lies within
-// (t_i + t_i+1 -+ sum_m |a_m| |change of g_m'|) / 2. Points with a NaN coefficient do not count
-// (their value is NaN on any rows).
+// Bounds of each point's t(f) over the intervals [w nbrk / nw, (w + 1) nbrk / nw): fn(interval, low, high).
+// Every g_m' is monotone, so over an interval t lies within (t_i + t_i+1 -+ sum_m |a_m| |change of g_m'|) / 2.
 // `slope`: a further phase, of at most `slope` cycles per unit of ln f.
-template <int ND>
-__device__ inline void band_ranges(const double* slopes_s, int nbrk, const double (&a)[NBASIS], const double (&T)[ND],
-                                   int w, int nw, int lane, BandLds& s, double slope = 0.0) {
+template <int ND, class Fn>
+__device__ __forceinline__ void band_bounds(const double* slopes_s, int nbrk, const double (&a)[NBASIS],
+                                            const double (&T)[ND], int w, int nw, double slope, Fn fn) {
   double tlo = T[0], thi = T[0];
 #pragma unroll
   for (int d = 1; d < ND; ++d) {
@@ -180,11 +190,41 @@ __device__ inline void band_ranges(const double* slopes_s, int nbrk, const doubl
     }
     const double mid = t + t1;
     t = t1;
-    float hi = (float)fma(0.5, mid + v, thi), nlo = -(float)fma(0.5, mid - v, tlo);
+    fn(i, fma(0.5, mid - v, tlo), fma(0.5, mid + v, thi));
+  }
+}
+
+// Step 1, by nw wavefronts that each hold the group's 64 points: bounds of t(f) over the group, each
+// wavefront on its share of the intervals. Points with a NaN coefficient do not count (their value is NaN on
+// any rows).
+template <int ND>
+__device__ inline void band_ranges(const double* slopes_s, int nbrk, const double (&a)[NBASIS], const double (&T)[ND],
+                                   int w, int nw, int lane, BandLds& s, double slope = 0.0) {
+  band_bounds<ND>(slopes_s, nbrk, a, T, w, nw, slope, [&](int i, double l, double h) {
+    float hi = (float)h, nlo = -(float)l;
     const bool nan = !(hi == hi) || !(nlo == nlo);
     hi = wave_max_hi(nan ? -__builtin_inff() : hi);
     nlo = wave_max_hi(nan ? -__builtin_inff() : nlo);
     if (lane == WAVE - 1) s.r[i] = make_float2(-nlo, hi);
+  });
+}
+
+// In its place for levels: the points that each level holds, by their own t(f) alone, into s.fit (all ones
+// before). A NaN fits: its point's value is NaN on any rows.
+template <int ND>
+__device__ inline void band_fit(const BandHead* __restrict__ bh, const double* slopes_s, const double (&a)[NBASIS],
+                                const double (&T)[ND], int w, int nw, int lane, BandLds& s) {
+  bool ok[MAXLEV];
+#pragma unroll
+  for (int l = 0; l < MAXLEV; ++l) ok[l] = true;
+  band_bounds<ND>(slopes_s, bh->nbrk, a, T, w, nw, 0.0, [&](int i, double lo, double hi) {
+#pragma unroll
+    for (int l = 0; l < MAXLEV; ++l) ok[l] = ok[l] && !(lo < bh->lev[l].lo[i]) && !(hi > bh->lev[l].hi[i]);
+  });
+#pragma unroll
+  for (int l = 0; l < MAXLEV; ++l) {
+    const unsigned long long m = __ballot(ok[l]);
+    if (lane == 0) atomicAnd(&s.fit[l], m);
   }
 }
 

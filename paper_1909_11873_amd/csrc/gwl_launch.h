@@ -32,6 +32,7 @@ struct LoopShape {
   int setup;    // 1: set-up inside the evaluation kernel
   int sepepi;   // 1: the value's reduction over the G workgroups and its epilogue in a second kernel
   int order;    // 1: the points are taken in the order that launch_order leaves in the workspace
+  int levels;   // 1 (live-length calls): every point walks the rows of its own level (gwl_bands.h)
   int pgmaj;    // 1: the dies take the point groups in turn (the set-up rows outweigh the table)
 };
 LoopShape make_shape(int64_t B, int64_t M, int W, int G, int setup, int sepepi = 0);

@@ -53,6 +53,7 @@ struct gwl_event_s {
   gwl::RowGradF32* g32 = nullptr;    // [M]
   gwl::RowGradF64* g64 = nullptr;    // [M]
   gwl::BandHead* bands = nullptr;    // band-limited rows, kept in tab64 and g64 after the bins (null: none)
+  int nlev[2] = {0, 0};              // its levels in a float64 and a mixed-precision call
   int64_t M_loop = 0;                // rows that a typical point's loop walks (launch shapes)
   double* fgrid = nullptr;           // [M] grid frequencies (ISCO cut-off only)
   double* kcum = nullptr;            // [ndet][M + 1] running sums of the K_det terms (ISCO cut-off only)
@@ -83,6 +84,8 @@ gwl_status check_device(int dev);
 gwl_status make_geom(const gwl_detector* dets, int ndet, double gmst, EventGeom& g);
 size_t row64_bytes(int nd);
 size_t row32_bytes(int nd);
+// launch shape of a live-length call of capacity B
+LoopShape live_shape(const gwl_event_s* ev, int64_t B, bool mixed);
 // workspace of an evaluation launch: set-up rows [NCOEF][Bp] unless the kernel does the set-up,
 // then workgroup partial sums [G][nz][Bp] for the gradient or when G > 1 (doubles), and npg
 // completion counters for the value when G > 1

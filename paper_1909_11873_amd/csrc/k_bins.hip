@@ -72,7 +72,7 @@ LoopShape make_shape(int64_t B, int64_t M, int W, int G, int setup, int sepepi) 
   s.gper = s.pgmaj ? (s.npg + NXCD - 1) / NXCD * G : (s.items + NXCD - 1) / NXCD;
   s.setup = setup ? 1 : 0;
   s.sepepi = (sepepi && G > 1) ? 1 : 0;
-  s.order = 0;
+  s.order = s.levels = 0;
   return s;
 }
 
@@ -115,8 +115,13 @@ __device__ inline double value_from_rows(const double (&acc)[NZ], double amp, do
 // What a launch's loop walks. LOOP_F64, LOOP_MIXED: every bin (or relative-binning edge), in float64
 // or mixed precision. LOOP_F64_BANDS: the pieces of each group's plan, in float64.
 // LOOP_MIXED_BANDS: a group of points whose plan's rows are clearly fewer than its bins walks the
-// plan in float64, another every bin in mixed precision.
-enum { LOOP_F64 = 0, LOOP_MIXED = 1, LOOP_F64_BANDS = 2, LOOP_MIXED_BANDS = 3 };
+// plan in float64, another every bin in mixed precision. LOOP_F64_LEVELS, LOOP_MIXED_LEVELS (live-length
+// calls): every point walks the rows of the first level that holds it, in float64, or where none does
+// every bin (in mixed precision in a mixed call), whatever its group's other points walk: the group walks
+// each level that one of its lanes needs, and a lane keeps its own's sums. A point's bits then do not depend on which other points
+// are live, nor on what the rows past the live ones hold. Levels have about a tenth more rows than plans of 64 prior
+// draws (1,860 and 1,610 a group; three detectors, 8 s), and choosing one takes two barriers less.
+enum { LOOP_F64 = 0, LOOP_MIXED = 1, LOOP_F64_BANDS = 2, LOOP_MIXED_BANDS = 3, LOOP_F64_LEVELS = 4, LOOP_MIXED_LEVELS = 5 };
 
 // The tables are `const __restrict__` kernel arguments, so the compiler reads their wave-uniform
 // rows with scalar loads.
@@ -148,6 +153,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
   constexpr int NZ = nz_of(ND, GRAD);
   constexpr bool TBL = LOOP != LOOP_MIXED;                     // the float64 phasor table
   constexpr bool BANDS = LOOP == LOOP_F64_BANDS || LOOP == LOOP_MIXED_BANDS;
+  constexpr bool LEVELS = LOOP == LOOP_F64_LEVELS || LOOP == LOOP_MIXED_LEVELS;
   extern __shared__ double lds[];
   double* rows_s = lds;                                        // [NCOEF][64] when SETUP
   double* tail = lds + (SETUP ? NCOEF * WAVE : 0);             // table, then the reduction buffer
@@ -182,7 +188,6 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     pg = item - g * sh.npg;
   }
   // live: only the first *live points are evaluated (a batch whose length the device decides)
-  const int64_t Ball = B;
   if (live) {
     const int64_t nl = *live;
     B = nl < B ? nl : B;
@@ -193,9 +198,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
   const int lane = (int)(threadIdx.x % WAVE);
   const int64_t p = (int64_t)pg * WAVE + lane;
-  // padding lanes repeat the last point (of the whole batch: a group's plan, and with it a point's
-  // bits, do not depend on how many of its rows are live)
-  const int64_t pc = p < Ball ? p : Ball - 1;
+  const int64_t pc = p < B ? p : B - 1;                        // padding lanes repeat the last (live) point
   const int64_t pt = BANDS && perm ? perm[pc] : pc;            // the point's row of theta
   const int64_t c = (int64_t)g * sh.W + w;
   const int64_t k0l = c * sh.chunk;
@@ -215,9 +218,12 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     else if (w >= 2) fill_phasor_table(tbl, 2 * WAVE);
   }
   double* slopes_s = rows_s + CO_CR * WAVE;                    // (these rows stay unused here)
-  if constexpr (SETUP && BANDS) {
+  if constexpr (SETUP && (BANDS || LEVELS)) {
     if (sh.W < 3) band_load(bh, slopes_s);
     else if (w >= 2) band_load(bh, slopes_s, 2 * WAVE);
+  }
+  if constexpr (LEVELS) {
+    if (threadIdx.x < MAXLEV) bands_s.fit[threadIdx.x] = ~0ull;
   }
   BandPre pre;
   if constexpr (SETUP && BANDS) pre = band_fetch(bh, w, lane);
@@ -240,6 +246,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
 #pragma unroll
   for (int z = 0; z < NZ; ++z) tot[z] = 0.0;
   bool in_range = true;
+  int level = 0;                                               // the lane's (-1: a padding lane's, none)
   if constexpr (SETUP) {
 #pragma unroll
     for (int m = 0; m < NBASIS; ++m) a[m] = rows_s[(CO_A + m) * WAVE + lane];
@@ -255,6 +262,14 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
       __syncthreads();
       if (w == 0) band_plan(pre, slopes_s, M, LOOP == LOOP_MIXED_BANDS, sh.nchunk, lane, bands_s);
       __syncthreads();
+    }
+    if constexpr (LEVELS) {
+      band_fit<ND>(bh, slopes_s, a, T, w, sh.W, lane, bands_s);
+      __syncthreads();
+      level = bh->nlev[LOOP == LOOP_MIXED_LEVELS];
+      for (int l = level - 1; l >= 0; --l)
+        if ((bands_s.fit[l] >> lane) & 1) level = l;
+      if (p >= B) level = -1;
     }
   }
   // c_det = E Q_det from the set-up rows (the adjoint's projection factors)
@@ -277,38 +292,64 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     if constexpr (SETUP) return __builtin_amdgcn_readfirstlane(bands_s.plan[i]);
     else return plan[(int64_t)pg * PLAN_INTS + i];
   };
-  bool f64path = LOOP != LOOP_MIXED;
-  if constexpr (LOOP == LOOP_MIXED_BANDS) f64path = get(2) != 0;     // scalar branch
-  if (!f64path) {
-    if constexpr (LOOP == LOOP_MIXED || LOOP == LOOP_MIXED_BANDS) {
-      float cr[ND], ci[ND];
-      if constexpr (GRAD) {
-        mixed_factors<ND>(ec, crd, cid, cr, ci);
-      } else {
+  // this chunk's bins in mixed precision, or rows [ka, kb) in float64 (a and T in table units), into the sums z
+  auto mixed_bins = [&](double (&z)[NZ]) {
+    float cr[ND], ci[ND];
+    if constexpr (GRAD) {
+      mixed_factors<ND>(ec, crd, cid, cr, ci);
+    } else {
 #pragma unroll
-        for (int d = 0; d < ND; ++d) cr[d] = ci[d] = 0.0f;
+      for (int d = 0; d < ND; ++d) cr[d] = ci[d] = 0.0f;
+    }
+    bin_loop_mixed<ND, GRAD, const RowMixed<ND>*, const RowGradF64*, CUT>(tab32, gtab, k0, k1, a, T, cr, ci, z, kc);
+    mixed_units<ND, GRAD>(ec, z);
+  };
+  auto walk = [&](int ka, int kb, double step, double (&z)[NZ]) {
+    if constexpr (ROT)
+      bin_loop_f64_rot<ND, GRAD, const RowF64<ND>*, const RowGradF64*>(tab, gtab, ka, kb, a, T, crd, cid, tbl, step, z);
+    else
+      bin_loop_f64<ND, GRAD, const RowF64<ND>*, const RowGradF64*, CUT>(tab, gtab, ka, kb, a, T, crd, cid, tbl, z, kc);
+  };
+  if constexpr (LEVELS) {
+    // Every level that one of the lanes needs, for all of them (a branch of the wavefront keeps the rows in scalar
+    // registers: in a branch of the lanes the loop took twice as long), each lane keeping its own's sums.
+    const int nlev = bh->nlev[LOOP == LOOP_MIXED_LEVELS];
+    auto keep = [&](int l, const double (&z)[NZ]) {
+#pragma unroll
+      for (int j = 0; j < NZ; ++j) tot[j] = level == l ? z[j] : tot[j];
+    };
+    if constexpr (LOOP == LOOP_MIXED_LEVELS) {
+      if (__ballot(level == nlev)) {
+        double z[NZ] = {};
+        mixed_bins(z);
+        keep(nlev, z);
       }
-      bin_loop_mixed<ND, GRAD, const RowMixed<ND>*, const RowGradF64*, CUT>(tab32, gtab, k0, k1, a, T, cr, ci, tot,
-                                                                            kc);
-      mixed_units<ND, GRAD>(ec, tot);
+    }
+    to_table_units<ND>(a, T);
+    for (int l = 0; l < nlev + (LOOP == LOOP_F64_LEVELS ? 1 : 0); ++l) {
+      if (!__ballot(level == l)) continue;
+      double z[NZ] = {};
+      const BandLevel& v = bh->lev[l < nlev ? l : MAXLEV];
+      const int chunk = (v.rows + sh.nchunk - 1) / sh.nchunk;
+      const int q0 = (int)c * chunk, q1 = q0 + chunk < v.rows ? q0 + chunk : v.rows;
+      // (the numbers of a plan, whose pieces follow from the fourth on)
+      for_pieces(bh, ec->grid_df, q0, q1, [&](int i) { return i == 1 ? v.np : v.piece[i - 4]; },
+                 [&](int ka, int kb, double step) { walk(ka, kb, step, z); });
+      keep(l, z);
     }
   } else {
-    if constexpr (LOOP != LOOP_MIXED) {
+    bool f64path = LOOP != LOOP_MIXED;
+    if constexpr (LOOP == LOOP_MIXED_BANDS) f64path = get(2) != 0;   // scalar branch
+    if (!f64path) {
+      if constexpr (LOOP == LOOP_MIXED || LOOP == LOOP_MIXED_BANDS) mixed_bins(tot);
+    } else if constexpr (LOOP != LOOP_MIXED) {
       to_table_units<ND>(a, T);
-      auto walk = [&](int ka, int kb, double step) {
-        if constexpr (ROT)
-          bin_loop_f64_rot<ND, GRAD, const RowF64<ND>*, const RowGradF64*>(tab, gtab, ka, kb, a, T, crd, cid, tbl, step,
-                                                                           tot);
-        else
-          bin_loop_f64<ND, GRAD, const RowF64<ND>*, const RowGradF64*, CUT>(tab, gtab, ka, kb, a, T, crd, cid, tbl, tot,
-                                                                            kc);
-      };
       if constexpr (BANDS) {
         const int rows = get(0), chunk = get(3);
         const int q0 = (int)c * chunk, q1 = q0 + chunk < rows ? q0 + chunk : rows;
-        for_pieces(bh, ec->grid_df, q0, q1, get, walk);
+        for_pieces(bh, ec->grid_df, q0, q1, get, [&](int ka, int kb, double step) { walk(ka, kb, step, tot); });
       } else {
-        walk(k0, k1, ec->grid_df);
+        walk(k0, k1, ec->grid_df, tot);
       }
     }
   }
@@ -411,19 +452,24 @@ static hipError_t eval_loop(bool cut, bool rot, const EvalArgs& x, const LoopSha
                      (const RowMixed<ND>*)x.tab32, x.gtab, x.theta, *x.geo, x.ec, x.bands, x.plan, x.coef, x.B, x.Bp, \
                      x.M, sh, x.part, x.cnt, x.logl, x.fgrid, x.kcum, x.live, x.perm)
   const bool setup = sh.setup != 0;
-  if constexpr (LOOP == LOOP_F64 || LOOP == LOOP_MIXED) {
-    if (cut) {
-      if (setup) GWL_EVAL(true, true, false); else GWL_EVAL(false, true, false);
-      return hipGetLastError();
+  if constexpr (LOOP == LOOP_F64_LEVELS || LOOP == LOOP_MIXED_LEVELS) {   // the set-up in the kernel (launch_eval)
+    if (rot) GWL_EVAL(true, false, true); else GWL_EVAL(true, false, false);
+    return hipGetLastError();
+  } else {
+    if constexpr (LOOP == LOOP_F64 || LOOP == LOOP_MIXED) {
+      if (cut) {
+        if (setup) GWL_EVAL(true, true, false); else GWL_EVAL(false, true, false);
+        return hipGetLastError();
+      }
     }
-  }
-  if constexpr (LOOP != LOOP_MIXED) {
-    if (rot) {
-      if (setup) GWL_EVAL(true, false, true); else GWL_EVAL(false, false, true);
-      return hipGetLastError();
+    if constexpr (LOOP != LOOP_MIXED) {
+      if (rot) {
+        if (setup) GWL_EVAL(true, false, true); else GWL_EVAL(false, false, true);
+        return hipGetLastError();
+      }
     }
+    if (setup) GWL_EVAL(true, false, false); else GWL_EVAL(false, false, false);
   }
-  if (setup) GWL_EVAL(true, false, false); else GWL_EVAL(false, false, false);
 #undef GWL_EVAL
   return hipGetLastError();
 }
@@ -432,6 +478,9 @@ template <int ND>
 static hipError_t eval_nd(bool mixed, bool grad, bool cut, bool rot, const EvalArgs& x, const LoopShape& sh,
                           hipStream_t s) {
 #define GWL_LOOP(L) grad ? eval_loop<ND, L, true>(cut, rot, x, sh, s) : eval_loop<ND, L, false>(cut, rot, x, sh, s)
+  if (sh.levels)
+    return mixed ? eval_loop<ND, LOOP_MIXED_LEVELS, false>(cut, rot, x, sh, s)
+                 : eval_loop<ND, LOOP_F64_LEVELS, false>(cut, rot, x, sh, s);
   if (x.bands) return mixed ? (GWL_LOOP(LOOP_MIXED_BANDS)) : (GWL_LOOP(LOOP_F64_BANDS));
   return mixed ? (GWL_LOOP(LOOP_MIXED)) : (GWL_LOOP(LOOP_F64));
 #undef GWL_LOOP
@@ -515,6 +564,7 @@ hipError_t launch_eval(int nd, bool mixed, bool grad, bool rot, const EvalArgs& 
   if (!sh.setup && (!x.coef || (x.bands && !x.plan))) return hipErrorInvalidValue;
   const bool cut = x.fgrid != nullptr;
   if (cut && (!x.kcum || x.bands)) return hipErrorInvalidValue;
+  if (sh.levels ? grad || !x.bands || !sh.setup || x.perm : x.live && x.bands) return hipErrorInvalidValue;
   switch (nd) {
     case 1: return eval_nd<1>(mixed, grad, cut, rot, x, sh, s);
     case 2: return eval_nd<2>(mixed, grad, cut, rot, x, sh, s);

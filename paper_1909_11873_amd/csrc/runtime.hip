@@ -273,7 +273,7 @@ static gwl_status event_create(const double* data, const double* psd, const gwl_
   double step = 1.0;
   const bool uniform = grid_is_uniform(fh, step);
   BandHost bh;
-  bh.head.ncand = 0;
+  memset(&bh.head, 0, sizeof bh.head);
   if (bands) {
     std::vector<int64_t> nodes;
     if (nnode > 0) cal_intervals(fh, nnode, nodes);
@@ -287,6 +287,7 @@ static gwl_status event_create(const double* data, const double* psd, const gwl_
         }
   }
   ev->M_loop = bands ? typical_rows(bh.head, M) : M;
+  for (int i = 0; i < 2; ++i) ev->nlev[i] = bh.head.nlev[i];
   const int64_t rows = M + TAB_PAD + (bh.nrows > 0 ? bh.nrows + TAB_PAD : 0);
   const int nblk = prep_blocks(M);
   Slab keep, work;
@@ -770,6 +771,32 @@ static CalShape cal_shape(const gwl_event_s* ev, int64_t B, bool grad) {
   return sh;
 }
 
+// Launch shape of a live-length call.
+LoopShape live_shape(const gwl_event_s* ev, int64_t B, bool mixed) {
+  // On band-limited rows: eight wavefronts a workgroup, of which two are resident on a CU, and as many
+  // workgroups a point group as are resident with all of the batch live (16 rows a wavefront at
+  // least). 8,192 points of three detectors and 8 s at 10, 40, 60 and 100 % live: 34, 35, 45 and 45 us;
+  // twice as many workgroups 29, 35, 47 and 57, half as many 46 to 47.
+  LoopShape sh = make_shape(B, ev->M, 8, 1, 1, 1);
+  const int64_t fill = std::max<int64_t>(1, 2 * 256 / sh.npg), most = std::max<int64_t>(1, ev->M_loop / (16 * 8));
+  sh = make_shape(B, ev->M, 8, (int)std::min(fill, most), 1, 1);
+  if (ev->nlev[mixed] > 0 && sh.chunk > kBandMinChunk) {
+    sh.levels = 1;
+    return sh;
+  }
+  // On the bins: the shape for B, with at least enough workgroups per point group that a quarter of the
+  // point groups still give every CU two workgroups (chunks of at least 16 bins): a partly live batch
+  // then still fills the chip. The G workgroup sums go to the separate epilogue kernel (the
+  // set-up in either kernel): at these workgroup counts the last-arriver's device-scope fences
+  // cost more than the second launch (on c1 shapes with 8192 points, 240 against 196 us)
+  sh = choose_shape(ev, B, mixed, false);
+  const int64_t want = (4 * 2 * 256 + sh.npg - 1) / sh.npg;
+  const int64_t gcap = std::max<int64_t>(1, ev->M / (32 * (int64_t)sh.W));
+  const int G = (int)std::min<int64_t>(std::max<int64_t>(sh.G, want), std::max<int64_t>(gcap, sh.G));
+  sh = make_shape(B, ev->M, sh.W, G, sh.setup, 1);
+  return sh;
+}
+
 // set-up rows, calibration rows, sums per chunk, window moments per piece, a plan per point group
 static size_t cal_bytes(const gwl_event_s* ev, const CalShape& sh, bool grad, bool order) {
   const size_t Bp = (size_t)sh.npg * WAVE, nd = ev->ndet, n = ev->ncal;
@@ -855,25 +882,7 @@ gwl_status gwl_logl_batch_live(gwl_event ev, const double* theta, int64_t B, con
   gwl_status st = check_device(ev->device);
   if (st != GWL_OK) return st;
   const bool mixed = use_mixed(ev, prec);
-  // On band-limited rows: eight wavefronts a workgroup, of which two are resident on a CU, and as many
-  // workgroups a point group as are resident with all of the batch live (16 rows a wavefront at
-  // least). 8,192 points of three detectors and 8 s at 10, 40, 60 and 100 % live: 34, 34, 44 and 45 us;
-  // twice as many workgroups 28, 35, 48 and 57, half as many 45 throughout.
-  LoopShape sh = make_shape(B, ev->M, 8, 1, 1, 1);
-  const int64_t fill = std::max<int64_t>(1, 2 * 256 / sh.npg), most = std::max<int64_t>(1, ev->M_loop / (16 * 8));
-  sh = make_shape(B, ev->M, 8, (int)std::min(fill, most), 1, 1);
-  if (!ev->bands || sh.chunk <= kBandMinChunk) {
-    // On the bins: the shape for B, with at least enough workgroups per point group that a quarter of the
-    // point groups still give every CU two workgroups (chunks of at least 16 bins): a partly live batch
-    // then still fills the chip. The G workgroup sums go to the separate epilogue kernel (the
-    // set-up in either kernel): at these workgroup counts the last-arriver's device-scope fences
-    // cost more than the second launch (on c1 shapes with 8192 points, 240 against 196 us)
-    sh = choose_shape(ev, B, mixed, false);
-    const int64_t want = (4 * 2 * 256 + sh.npg - 1) / sh.npg;
-    const int64_t gcap = std::max<int64_t>(1, ev->M / (32 * (int64_t)sh.W));
-    const int G = (int)std::min<int64_t>(std::max<int64_t>(sh.G, want), std::max<int64_t>(gcap, sh.G));
-    sh = make_shape(B, ev->M, sh.W, G, sh.setup, 1);
-  }
+  const LoopShape sh = live_shape(ev, B, mixed);
   return run_logl(ev, theta, B, mixed, false, sh, logl, nullptr, (hipStream_t)stream, live);
 }
 
@@ -1085,7 +1094,7 @@ hipError_t enqueue_logl(gwl_event ev, const double* theta, int64_t B, bool mixed
   double* part = (grad || sh.G > 1) ? ws + (with_coef ? (size_t)NCOEF * Bp : 0) : nullptr;
   const size_t npart = (grad || sh.G > 1) ? (size_t)sh.G * nz_of(ev->ndet, grad) * Bp : 0;
   int* plan = sh.setup ? nullptr : (int*)(ws + (with_coef ? (size_t)NCOEF * Bp : 0) + npart);
-  const BandHead* bands = sh.chunk > kBandMinChunk ? ev->bands : nullptr;
+  const BandHead* bands = (live ? sh.levels != 0 : sh.chunk > kBandMinChunk) ? ev->bands : nullptr;
   int* perm = sh.order && bands && !live
                   ? (int*)(ws + (with_coef ? (size_t)NCOEF * Bp : 0) + npart) + (sh.setup ? 0 : (size_t)PLAN_INTS * sh.npg)
                   : nullptr;

@@ -86,3 +86,44 @@ def test_live_rejections():
     with pytest.raises(gw.GWLError):
         gw.logl_live(thc, torch.tensor(3, dtype=torch.int64, device=DEV), cev)
     cev.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("cfg,B,f_hi,ndet", [(1, 700, 700.0, None), (1, 8192, 700.0, 2), (1, 300, 700.0, 1), (0, 1000, None, None),
+                                             (1, 33000, 300.0, 4)])
+def test_a_points_bits_are_its_own(cfg, B, f_hi, ndet, prec):
+    """Whatever the rows past *live hold (other draws, points far away in time, NaN, infinities) and whichever
+    points share its group of 64, a live point's value has the same bits: points of every level of rows and of
+    none, in two orders, and NaN only where the point itself is outside the model's domain."""
+    spec, f, psd, data, dets = event_inputs(cfg, f_hi=f_hi, ndet=ndet)
+    t = lambda x: torch.tensor(x, device=DEV)
+    ev = gw.Event(t(data), t(psd), dets, t(f), spec.df)
+    th = np.tile(synth.theta_batch(spec, min(B, 4096)), (-(-B // 4096), 1))[:B]
+    rng = np.random.default_rng(7)
+    th[:, 0] = rng.uniform(1.0, 60.0, B)
+    far = rng.random(B)
+    th[:, 10] = np.where(far < 0.7, 0.1, np.where(far < 0.85, 0.28, 0.4 / spec.df)) * rng.uniform(-1.0, 1.0, B)
+    th[17, 1] = 1.5
+    live = B - 131
+    n = torch.tensor(live, dtype=torch.int64, device=DEV)
+
+    def call(rows):
+        out = torch.full((B,), -3.0, dtype=torch.float64, device=DEV)
+        gw.logl_live(t(rows), n, ev, prec, out=out)
+        assert bool((out[live:] == -3.0).all())
+        return out[:live].cpu().numpy()
+    want = call(th)
+    assert np.isnan(want).sum() == 1 and np.isnan(want[17])
+    for column, value in ((slice(None), 0.0), (10, 1e3), (10, 1e300), (0, np.nan), (slice(None), np.inf)):
+        rows = th.copy()
+        rows[live:, column] = value
+        assert np.array_equal(call(rows), want, equal_nan=True), (column, value)
+    order = rng.permutation(live)
+    rows = th.copy()
+    rows[:live] = th[order]
+    assert np.array_equal(call(rows), want[order], equal_nan=True)
+    full = gw.logl(t(th), ev, prec).cpu().numpy()[:live]
+    ok = np.isfinite(want)
+    tol = 1e-9 * np.maximum(np.abs(full[ok]), 1.0) if prec == "fp64" else 1e-3
+    assert (np.abs(want[ok] - full[ok]) <= tol).all()
+    ev.close()
