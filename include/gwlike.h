@@ -206,9 +206,9 @@ gwl_status gwl_logl_batch_live(gwl_event ev, const double* theta, int64_t B, con
                                double* logl, void* stream);
 
 /*
- * Grow the event's workspace on `stream` to what a gwl_logl_batch (with_grad = 0) or
- * gwl_logl_grad (with_grad = 1) call with these arguments needs, so that such calls allocate
- * nothing, also under graph capture. Must not be called while `stream` is capturing (it may
+ * Grow the event's workspace on `stream` to what a gwl_logl_batch or gwl_logl_batch_live
+ * (with_grad = 0) or a gwl_logl_grad (with_grad = 1) call with these arguments needs, so that such calls
+ * allocate nothing, also under graph capture. Must not be called while `stream` is capturing (it may
  * allocate, and then returns GWL_E_INVALID there). Growing synchronises `stream` before the old
  * buffer is freed. The workspace lives until the event is destroyed.
  */

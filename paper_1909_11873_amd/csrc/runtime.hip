@@ -901,8 +901,14 @@ gwl_status gwl_event_reserve(gwl_event ev, int64_t B, gwl_precision prec, int wi
   if (st != GWL_OK) return st;
   void* ws = nullptr;
   const bool mixed = use_mixed(ev, prec), grad = with_grad != 0;
-  const size_t ncnt = ev->ncal > 0 ? 0 : workspace_counters(choose_shape(ev, B, mixed, grad), grad);
-  return event_workspace(ev, (hipStream_t)stream, call_workspace_bytes(ev, B, mixed, grad), ncnt, &ws);
+  size_t bytes = call_workspace_bytes(ev, B, mixed, grad), ncnt = 0;
+  if (ev->ncal == 0) ncnt = workspace_counters(choose_shape(ev, B, mixed, grad), grad);
+  if (ev->ncal == 0 && !grad) {                        // a live-length call of this size, whose shape is its own
+    const LoopShape sh = live_shape(ev, B, mixed);
+    bytes = std::max(bytes, workspace_bytes((int64_t)sh.npg * WAVE, sh, ev->ndet, false));
+    ncnt = std::max(ncnt, workspace_counters(sh, false));
+  }
+  return event_workspace(ev, (hipStream_t)stream, bytes, ncnt, &ws);
 }
 
 gwl_status gwl_launch_shape(gwl_event ev, int64_t B, gwl_precision prec, int with_grad, int* nchunk,

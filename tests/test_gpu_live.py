@@ -127,3 +127,27 @@ def test_a_points_bits_are_its_own(cfg, B, f_hi, ndet, prec):
     tol = 1e-9 * np.maximum(np.abs(full[ok]), 1.0) if prec == "fp64" else 1e-3
     assert (np.abs(want[ok] - full[ok]) <= tol).all()
     ev.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("B,f_hi", [(100, 700.0), (16384, 2048.0), (40000, 2048.0)])
+def test_a_reserved_live_call_is_captured(B, f_hi, prec):
+    """gwl_event_reserve for a value call of this size also covers the live-length call, whose launch has a shape
+    of its own: captured with no call before it, it replays the eager call's values."""
+    spec, ev = _event(1, f_hi)
+    th = torch.tensor(np.tile(synth.theta_batch(spec, 100), (-(-B // 100), 1))[:B], device=DEV)
+    live = torch.tensor(B - 3, dtype=torch.int64, device=DEV)
+    out = torch.zeros(B, dtype=torch.float64, device=DEV)
+    s = torch.cuda.Stream()
+    gw.reserve(ev, B, prec, stream=s)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        gw.logl_live(th, live, ev, prec, out=out)
+    want = gw.logl_live(th, live, ev, prec)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[:B - 3], want[:B - 3]) and bool((out[B - 3:] == 0.0).all())
+    ev.close()
