@@ -37,7 +37,10 @@ gwl_status fail(gwl_status st, const char* fmt, ...) {
   return st;
 }
 
+// The error is the caller's from here on: it is taken out of the runtime's own record, which the launch
+// wrappers read back, so that a call after it (an entry point's retry in less memory, or the next one) does not report it again.
 gwl_status hip_fail(hipError_t e, const char* what) {
+  (void)hipGetLastError();
   if (e == hipErrorOutOfMemory) return fail(GWL_E_NOMEM, "%s: %s", what, hipGetErrorString(e));
   return fail(GWL_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }

@@ -1,5 +1,7 @@
 """The largest shapes the path is meant for: a batch of 2^22 points and a grid of 2^22 + 1 bins
 (a 2048 s segment, 20-2068 Hz), each against the FP64 oracle on sampled points."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -84,4 +86,28 @@ def test_large_coalescence_times_and_the_phase_limit():
         assert np.isfinite(got[5])                    # 2e8 s x 2048 Hz < 2^39 cycles
         v, g = gw.logl_grad(th, ev, prec)
         assert np.isnan(v.cpu().numpy()[4]) and np.all(np.isnan(g.cpu().numpy()[4]))
+    ev.close()
+
+
+def test_a_call_that_finds_no_memory_leaves_no_error():
+    """A calibrated gradient of 2^30 points needs some five terabytes of workspace: it is refused (with the points'
+    order and without), and the calls after it run as if it had not been made."""
+    f = synth.freq_grid(20.0, 300.0, 0.25)
+    s = synth.psd_fit(f)
+    dets = np.array([synth.detector_rad(n) for n in ("D1", "D2", "D3")])
+    psd = np.stack([s] * 3)
+    data = np.stack([synth.noise(40 + i, s, 0.25) for i in range(3)])
+    ev = gw.Event(torch.tensor(data, device=DEV), torch.tensor(psd, device=DEV), dets, torch.tensor(f, device=DEV), 0.25,
+                  calibration_nodes=16)
+    th = torch.tensor(np.concatenate([synth.prior_draw(np.random.default_rng(3), 70), np.zeros((70, 96))], axis=1),
+                      device=DEV)
+    want, gwant = gw.logl_grad(th, ev, "fp64")
+    # at least the window moments of 15 intervals: the call ends at the allocation, before anything is launched
+    assert 8 * (1 << 30) * 24 * 15 > 4 * torch.cuda.get_device_properties(0).total_memory
+    p = ctypes.c_void_p(th.data_ptr())
+    for _ in range(2):
+        assert gw.lib().gwl_logl_grad(ev.handle, p, 1 << 30, gw.GWL_FP64, p, p, None) == -4
+        got, ggot = gw.logl_grad(th, ev, "fp64")
+        assert torch.equal(got, want) and torch.equal(ggot, gwant)
+    torch.cuda.synchronize()
     ev.close()
