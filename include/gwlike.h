@@ -333,7 +333,10 @@ gwl_status gwl_launch_shape(gwl_event ev, int64_t B, gwl_precision prec, int wit
 gwl_status gwl_launch_layout(gwl_event ev, int64_t B, gwl_precision prec, int with_grad, int* waves, int* groups,
                              int* setup);
 
-/* Load tile choices from a JSON cache written by gwl_autotune (missing file = GWL_E_INVALID). */
+/* Load tile choices from a JSON cache written by gwl_autotune or gwl_multi_autotune (missing file =
+ * GWL_E_INVALID). A single event's shape is taken whenever it was measured (one from before band-limited
+ * rows, with a workgroup for every few hundred bins, is a valid launch but seldom the best: measure it
+ * again); a plan's only where the file says that its chunk lengths count rows. */
 gwl_status gwl_autotune_load(const char* cache_path);
 
 /*

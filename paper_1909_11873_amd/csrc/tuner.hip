@@ -79,13 +79,19 @@ Key make_key(int nd, bool mixed, bool grad, int64_t M, int64_t B) {
   return Key{nd, mixed ? 1 : 0, grad ? 1 : 0, M, pow2_ceil((B + WAVE - 1) / WAVE)};
 }
 
+// A plan's chunk counts rows, of which an item has four chunks. Files from when it counted the bins of an item
+// lack this mark, and their plan entries are passed over: taken as rows they make items up to ten times too long.
+const char* const kChunkMark = "\"chunks\": \"rows\"";
+
 // Read every "{...}" entry line of a cache file written by save_cache().
 bool load_cache(const char* path) {
   FILE* f = fopen(path, "r");
   if (!f) return false;
   char line[512];
+  bool row_chunks = false;
   std::lock_guard<std::mutex> lk(g_mu);
   while (fgets(line, sizeof line, f)) {
+    if (strstr(line, kChunkMark)) row_chunks = true;
     Key k;
     Entry e;
     long long M;
@@ -103,7 +109,7 @@ bool load_cache(const char* path) {
     } else if (sscanf(line, " {\"multi\": 1, \"ndet\": %d, \"mixed\": %d, \"grad\": %d, \"events\": %d, \"sig\": \"%llx\", "
                       "\"chunk\": %d, \"descending\": %d, \"ms\": %lf}",
                       &mk.nd, &mk.mixed, &mk.grad, &mk.E, &mk.sig, &me.chunk, &me.descending, &me.ms) == 8) {
-      g_mcache[mk] = me;
+      if (row_chunks) g_mcache[mk] = me;
     }
   }
   fclose(f);
@@ -114,7 +120,7 @@ bool save_cache(const char* path) {
   FILE* f = fopen(path, "w");
   if (!f) return false;
   std::lock_guard<std::mutex> lk(g_mu);
-  fprintf(f, "{\"arch\": \"gfx950\", \"entries\": [\n");
+  fprintf(f, "{\"arch\": \"gfx950\", %s, \"entries\": [\n", kChunkMark);
   size_t i = 0;
   const size_t n = g_cache.size() + g_mcache.size();
   for (const auto& kv : g_cache) {

@@ -1,4 +1,6 @@
 """Multi-event persistent launch (HIP graph) against single-event calls and the FP64 oracle."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -301,3 +303,27 @@ def test_many_small_events_in_one_plan(events, grad):
             assert np.abs(l.cpu().numpy() - sv.cpu().numpy()).max() <= 2e-4
     finally:
         plan.close()
+
+
+def test_plan_shapes_count_rows(events, tmp_path):
+    """A cache file whose plan chunks count the bins of an item, as they did before band-limited rows, says nothing
+    of the kind in its first line: its plan entries are passed over; one that says rows is taken."""
+    evs = [e["ev"] for e in events]
+    path = str(tmp_path / "tune.json")
+    gw.multi_autotune(evs, BATCHES, "fp64", with_grad=True, cache_path=path)
+    first, rest = open(path).read().split("\n", 1)
+
+    def chunk_after(head):
+        text = re.sub(r'("multi": 1.*"chunk": )\d+', r"\g<1>7777", rest)
+        (tmp_path / "old.json").write_text(head + "\n" + text)
+        gw.autotune_load(str(tmp_path / "old.json"))
+        plan = gw.MultiPlan(evs, BATCHES, "fp64", with_grad=True)
+        chunk = plan.info()[0]
+        plan.close()
+        return chunk
+    try:
+        tuned = gw.MultiPlan(evs, BATCHES, "fp64", with_grad=True).info()[0]
+        assert chunk_after('{"arch": "gfx950", "entries": [') == tuned != 7777
+        assert chunk_after(first) == 7777
+    finally:
+        gw.autotune_load(path)
