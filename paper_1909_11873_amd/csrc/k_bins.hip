@@ -292,24 +292,8 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     if constexpr (SETUP) return __builtin_amdgcn_readfirstlane(bands_s.plan[i]);
     else return plan[(int64_t)pg * PLAN_INTS + i];
   };
-  // this chunk's bins in mixed precision, or rows [ka, kb) in float64 (a and T in table units), into the sums z
-  auto mixed_bins = [&](double (&z)[NZ]) {
-    float cr[ND], ci[ND];
-    if constexpr (GRAD) {
-      mixed_factors<ND>(ec, crd, cid, cr, ci);
-    } else {
-#pragma unroll
-      for (int d = 0; d < ND; ++d) cr[d] = ci[d] = 0.0f;
-    }
-    bin_loop_mixed<ND, GRAD, const RowMixed<ND>*, const RowGradF64*, CUT>(tab32, gtab, k0, k1, a, T, cr, ci, z, kc);
-    mixed_units<ND, GRAD>(ec, z);
-  };
-  auto walk = [&](int ka, int kb, double step, double (&z)[NZ]) {
-    if constexpr (ROT)
-      bin_loop_f64_rot<ND, GRAD, const RowF64<ND>*, const RowGradF64*>(tab, gtab, ka, kb, a, T, crd, cid, tbl, step, z);
-    else
-      bin_loop_f64<ND, GRAD, const RowF64<ND>*, const RowGradF64*, CUT>(tab, gtab, ka, kb, a, T, crd, cid, tbl, z, kc);
-  };
+  // (written out for levels and for plans: with the loops in functions of their sums that both call, the
+  // three-detector adjoint spilled 28 to 60 registers for 6)
   if constexpr (LEVELS) {
     // Every level that one of the lanes needs, for all of them (a branch of the wavefront keeps the rows in scalar
     // registers: in a branch of the lanes the loop took twice as long), each lane keeping its own's sums.
@@ -321,7 +305,9 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     if constexpr (LOOP == LOOP_MIXED_LEVELS) {
       if (__ballot(level == nlev)) {
         double z[NZ] = {};
-        mixed_bins(z);
+        const float none[ND] = {};
+        bin_loop_mixed<ND, GRAD>(tab32, gtab, k0, k1, a, T, none, none, z);
+        mixed_units<ND, GRAD>(ec, z);
         keep(nlev, z);
       }
     }
@@ -333,23 +319,48 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
       const int chunk = (v.rows + sh.nchunk - 1) / sh.nchunk;
       const int q0 = (int)c * chunk, q1 = q0 + chunk < v.rows ? q0 + chunk : v.rows;
       // (the numbers of a plan, whose pieces follow from the fourth on)
-      for_pieces(bh, ec->grid_df, q0, q1, [&](int i) { return i == 1 ? v.np : v.piece[i - 4]; },
-                 [&](int ka, int kb, double step) { walk(ka, kb, step, z); });
+      for_pieces(
+          bh, ec->grid_df, q0, q1, [&](int i) { return i == 1 ? v.np : v.piece[i - 4]; },
+          [&](int ka, int kb, double step) {
+            if constexpr (ROT) bin_loop_f64_rot<ND, GRAD>(tab, gtab, ka, kb, a, T, crd, cid, tbl, step, z);
+            else bin_loop_f64<ND, GRAD>(tab, gtab, ka, kb, a, T, crd, cid, tbl, z);
+          });
       keep(l, z);
     }
   } else {
     bool f64path = LOOP != LOOP_MIXED;
     if constexpr (LOOP == LOOP_MIXED_BANDS) f64path = get(2) != 0;   // scalar branch
     if (!f64path) {
-      if constexpr (LOOP == LOOP_MIXED || LOOP == LOOP_MIXED_BANDS) mixed_bins(tot);
-    } else if constexpr (LOOP != LOOP_MIXED) {
-      to_table_units<ND>(a, T);
-      if constexpr (BANDS) {
-        const int rows = get(0), chunk = get(3);
-        const int q0 = (int)c * chunk, q1 = q0 + chunk < rows ? q0 + chunk : rows;
-        for_pieces(bh, ec->grid_df, q0, q1, get, [&](int ka, int kb, double step) { walk(ka, kb, step, tot); });
-      } else {
-        walk(k0, k1, ec->grid_df, tot);
+      if constexpr (LOOP == LOOP_MIXED || LOOP == LOOP_MIXED_BANDS) {
+        float cr[ND], ci[ND];
+        if constexpr (GRAD) {
+          mixed_factors<ND>(ec, crd, cid, cr, ci);
+        } else {
+#pragma unroll
+          for (int d = 0; d < ND; ++d) cr[d] = ci[d] = 0.0f;
+        }
+        bin_loop_mixed<ND, GRAD, const RowMixed<ND>*, const RowGradF64*, CUT>(tab32, gtab, k0, k1, a, T, cr, ci, tot,
+                                                                              kc);
+        mixed_units<ND, GRAD>(ec, tot);
+      }
+    } else {
+      if constexpr (LOOP != LOOP_MIXED) {
+        to_table_units<ND>(a, T);
+        auto walk = [&](int ka, int kb, double step) {
+          if constexpr (ROT)
+            bin_loop_f64_rot<ND, GRAD, const RowF64<ND>*, const RowGradF64*>(tab, gtab, ka, kb, a, T, crd, cid, tbl, step,
+                                                                             tot);
+          else
+            bin_loop_f64<ND, GRAD, const RowF64<ND>*, const RowGradF64*, CUT>(tab, gtab, ka, kb, a, T, crd, cid, tbl, tot,
+                                                                              kc);
+        };
+        if constexpr (BANDS) {
+          const int rows = get(0), chunk = get(3);
+          const int q0 = (int)c * chunk, q1 = q0 + chunk < rows ? q0 + chunk : rows;
+          for_pieces(bh, ec->grid_df, q0, q1, get, walk);
+        } else {
+          walk(k0, k1, ec->grid_df);
+        }
       }
     }
   }
