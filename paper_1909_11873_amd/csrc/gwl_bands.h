@@ -45,6 +45,14 @@ constexpr double CAL_REACH = 0.75;
 inline double cal_reach(double hx) { return fmin(0.22314355131420976 / hx, CAL_REACH); }   // ln 1.25
 inline double cal_slope(double reach) { return fmax(1.5, 6.0 * reach * (1.0 + reach)); }
 
+// Rows that a group of a call may have and still walk them in float64: any number in a float64 call; in a
+// mixed-precision one as many as take the time of its M bins in mixed precision. Measured on every bin, float64 to mixed (three
+// detectors, 8 s; 65,536 values, 16,384 gradients, and with 10 calibration nodes 16,384 and 8,192): 1,553 and 1,403 us,
+// 696 and 545, 991 and 708, 824 and 659.
+__host__ __device__ inline int float64_most(bool mixed, bool grad, bool cal, int64_t M) {
+  return mixed ? (int)(M * (cal ? (grad ? 80 : 71) : (grad ? 78 : 90)) / 100) : 0x7fffffff;
+}
+
 struct BandCand {
   double t0, tb;      // centre and half-width of the band (s)
   double step;        // spacing of its rows (Hz)
@@ -276,11 +284,9 @@ __device__ inline int band_of_segment(const BandPre& own, int lane, const BandLd
 
 // Step 3, after a barrier, by one wavefront: the plan. Lane j holds segment j; the panels below
 // one wide segment (the cheapest, or none) and that segment are the pieces, neighbouring panels
-// that keep their bins one piece. `mixed`: a group whose rows are not clearly fewer than its bins
-// keeps the mixed-precision loop over all of them (the float64 loop over the rows costs about
-// 47 issue slots a row at three detectors against 38 a bin).
-__device__ inline void band_plan(const BandPre& own, const double* slopes_s, int64_t M, bool mixed, int nchunk, int lane,
-                                 BandLds& s) {
+// that keep their bins one piece. `most`: a group of more rows keeps the mixed-precision loop over its bins
+// (float64_most).
+__device__ inline void band_plan(const BandPre& own, const double* slopes_s, int most, int nchunk, int lane, BandLds& s) {
   const int2* rows_s = reinterpret_cast<const int2*>(slopes_s);
   static_assert(MAXPANEL <= 16, "sums_16");
   const int ns = __builtin_amdgcn_readfirstlane(own.nseg), np = __builtin_amdgcn_readfirstlane(own.npanel);
@@ -329,7 +335,7 @@ __device__ inline void band_plan(const BandPre& own, const double* slopes_s, int
     s.plan[6 + 3 * idx] = cand;
   }
   if (lane == 0) {
-    const bool f64 = !mixed || 5 * (int64_t)all <= 4 * M;
+    const bool f64 = all <= most;
     s.plan[0] = all;
     s.plan[1] = (int)__popcll(heads);
     s.plan[2] = f64 ? 1 : 0;
@@ -339,7 +345,7 @@ __device__ inline void band_plan(const BandPre& own, const double* slopes_s, int
 
 // Step 3 on a calibrated event, whose segments are the calibration's node intervals: the plan keeps
 // the intervals apart, from plan[4 + 2 j] each interval's first row and its rows.
-__device__ inline void band_plan_cal(const BandPre& own, const double* slopes_s, int64_t M, bool mixed, int nchunk,
+__device__ inline void band_plan_cal(const BandPre& own, const double* slopes_s, int64_t M, int most, int nchunk,
                                      int lane, BandLds& s) {
   const int cand = band_of_segment(own, lane, s);
   int rows = 0;
@@ -352,7 +358,7 @@ __device__ inline void band_plan_cal(const BandPre& own, const double* slopes_s,
   static_assert(MAXNODE - 1 <= 16, "sums_16");
   const int all = __builtin_amdgcn_readlane(sums_16(rows), 15);
   if (lane == 0) {
-    const bool f64 = !mixed || 5 * (int64_t)all <= 4 * M;
+    const bool f64 = all <= most;
     s.plan[0] = all;
     s.plan[2] = f64 ? 1 : 0;
     s.plan[3] = ((f64 ? all : (int)M) + nchunk - 1) / nchunk;

@@ -46,11 +46,11 @@ int prep_blocks(int64_t M);
 size_t prep_scratch_doubles(int nd, int64_t M);  // size of `blockpart`
 
 // per-point set-up: theta[B][11] -> coef[NCOEF][Bp] (ec may be null); with band-limited rows also
-// each 64-point group's plan [npg][PLAN_INTS] for nchunk chunks (gwl_bands.h)
+// each 64-point group's plan [npg][PLAN_INTS] for nchunk chunks (gwl_bands.h; most: float64_most's)
 struct BandHead;
 hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, const double* theta, int64_t B, int64_t Bp,
-                        double* coef, hipStream_t s, const BandHead* bands = nullptr, int64_t M = 0,
-                        bool mixed = false, int nchunk = 0, int* plan = nullptr, const int* perm = nullptr);
+                        double* coef, hipStream_t s, const BandHead* bands = nullptr, int most = 0,
+                        int nchunk = 0, int* plan = nullptr, const int* perm = nullptr);
 
 // an order of the points in which neighbours arrive at about the same time and have about the same chirp
 // mass: perm[B], a permutation within every kOrderBlock points, from theta rows of P columns

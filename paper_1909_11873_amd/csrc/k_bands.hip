@@ -106,7 +106,7 @@ void plan_levels(BandHead& h, int64_t M) {
     for (; n > 0 && h.lev[n - 1].rows > best; --n) h.lev[n] = h.lev[n - 1];
     h.lev[n] = v;
   }
-  while (h.nlev[1] < h.nlev[0] && 5 * (int64_t)h.lev[h.nlev[1]].rows <= 4 * M) ++h.nlev[1];
+  while (h.nlev[1] < h.nlev[0] && h.lev[h.nlev[1]].rows <= float64_most(true, false, false, M)) ++h.nlev[1];
 }
 
 }  // namespace

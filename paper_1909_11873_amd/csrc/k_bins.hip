@@ -260,7 +260,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
       __syncthreads();
       band_hold(bh, pre, slopes_s, w, sh.W, lane, bands_s);
       __syncthreads();
-      if (w == 0) band_plan(pre, slopes_s, M, LOOP == LOOP_MIXED_BANDS, sh.nchunk, lane, bands_s);
+      if (w == 0) band_plan(pre, slopes_s, float64_most(LOOP == LOOP_MIXED_BANDS, GRAD, false, M), sh.nchunk, lane, bands_s);
       __syncthreads();
     }
     if constexpr (LEVELS) {

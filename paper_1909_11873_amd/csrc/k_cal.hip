@@ -36,7 +36,7 @@ namespace gwl {
 constexpr int SETUP_CAL_WAVES = 4;
 template <int ND>
 __global__ __launch_bounds__(SETUP_CAL_WAVES * WAVE) void k_setup_cal(
-    EventGeom g, const EventConst* __restrict__ ec, const BandHead* __restrict__ bh, double slope, int64_t M, bool mixed,
+    EventGeom g, const EventConst* __restrict__ ec, const BandHead* __restrict__ bh, double slope, int64_t M, int most,
     CalShape sh, const double* __restrict__ theta, int P, int ncal, int64_t B, int64_t Bp, double* __restrict__ coef,
     double* __restrict__ calc, int* __restrict__ plan, const int* __restrict__ perm) {
   alignas(16) __shared__ double rows_s[NCOEF * WAVE];
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(SETUP_CAL_WAVES * WAVE) void k_setup_cal(
   band_hold(bh, pre, slopes_s, w, SETUP_CAL_WAVES, lane, bands_s);
   __syncthreads();
   if (w != 0) return;
-  band_plan_cal(pre, slopes_s, M, mixed, sh.nchunk, lane, bands_s);
+  band_plan_cal(pre, slopes_s, M, most, sh.nchunk, lane, bands_s);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
   plan[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }
@@ -549,7 +549,7 @@ static hipError_t cal_nd(bool mixed, bool grad, const EventGeom& g, const EventC
   const int ncal = 2 * sh.nnode * ND;
   if (Bp % WAVE != 0 || B < 1 || B > Bp || (t.bands && !plan)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_setup_cal<ND>, dim3((unsigned)(Bp / WAVE)), dim3(SETUP_CAL_WAVES * WAVE), 0, s, g, ec, t.bands, t.slope,
-                     M, mixed, sh, theta, P, ncal, B, Bp, coef, calc, plan, perm);
+                     M, float64_most(mixed, grad, true, M), sh, theta, P, ncal, B, Bp, coef, calc, plan, perm);
   const int* pl = t.bands ? plan : nullptr;
   const dim3 grid((unsigned)(sh.gper * NXCD)), block(BLOCK);
 #define GWL_CB(MX, GR)                                                                                              \

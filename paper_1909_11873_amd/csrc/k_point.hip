@@ -27,8 +27,7 @@ constexpr int SETUP_WAVES = 2, SETUP_WAVES_BANDS = 4;
 
 template <int ND>
 __global__ __launch_bounds__(SETUP_WAVES_BANDS * WAVE) void k_setup(EventGeom g, const EventConst* __restrict__ ec,
-                                                                    const BandHead* __restrict__ bh, int64_t M,
-                                                                    bool mixed, int nchunk,
+                                                                    const BandHead* __restrict__ bh, int most, int nchunk,
                                                                     const double* __restrict__ theta, int64_t B,
                                                                     int64_t Bp, double* __restrict__ coef,
                                                                     int* __restrict__ plan,
@@ -59,19 +58,18 @@ __global__ __launch_bounds__(SETUP_WAVES_BANDS * WAVE) void k_setup(EventGeom g,
   band_hold(bh, pre, slopes_s, w, SETUP_WAVES_BANDS, lane, bands_s);
   __syncthreads();
   if (w != 0) return;
-  band_plan(pre, slopes_s, M, mixed, nchunk, lane, bands_s);
+  band_plan(pre, slopes_s, most, nchunk, lane, bands_s);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS from the lanes that wrote it
   plan[(int64_t)blockIdx.x * PLAN_INTS + lane] = bands_s.plan[lane];
 }
 
 hipError_t launch_setup(int nd, const EventGeom& g, const EventConst* ec, const double* theta, int64_t B, int64_t Bp,
-                        double* coef, hipStream_t s, const BandHead* bands, int64_t M, bool mixed, int nchunk,
-                        int* plan, const int* perm) {
+                        double* coef, hipStream_t s, const BandHead* bands, int most, int nchunk, int* plan, const int* perm) {
   if (Bp % WAVE != 0 || B < 1 || B > Bp) return hipErrorInvalidValue;
   if (bands && (!ec || !plan || nchunk < 1)) return hipErrorInvalidValue;
   dim3 grid((unsigned)(Bp / WAVE)), block((unsigned)((bands ? SETUP_WAVES_BANDS : SETUP_WAVES) * WAVE));
 #define GWL_SETUP(N) \
-  case N: hipLaunchKernelGGL(k_setup<N>, grid, block, 0, s, g, ec, bands, M, mixed, nchunk, theta, B, Bp, coef, plan, perm); break;
+  case N: hipLaunchKernelGGL(k_setup<N>, grid, block, 0, s, g, ec, bands, most, nchunk, theta, B, Bp, coef, plan, perm); break;
   switch (nd) {
     GWL_SETUP(1)
     GWL_SETUP(2)

@@ -92,7 +92,7 @@ __global__ void k_multi_stamp(unsigned long long* __restrict__ t) { *t = wall_cl
 template <int ND>
 __global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
     const MultiEvDev* __restrict__ evs, const EventGeom* __restrict__ geoms, const MultiIODev* __restrict__ io,
-    const int2* __restrict__ grp, int mixed, int chunk, MultiCtl* __restrict__ ctl, int2* __restrict__ items,
+    const int2* __restrict__ grp, int mixed, int grad, int chunk, MultiCtl* __restrict__ ctl, int2* __restrict__ items,
     int* __restrict__ plans) {
   alignas(16) __shared__ double rows_s[NCOEF * WAVE];
   __shared__ BandLds bands_s;
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(MULTI_SETUP_WAVES * WAVE) void k_multi_setup(
     band_hold(ev.bands, pre, slopes_s, w, MULTI_SETUP_WAVES, lane, bands_s);
     __syncthreads();
     if (w != 0) return;
-    band_plan(pre, slopes_s, ev.M, mixed && !ev.f64, 1, lane, bands_s);
+    band_plan(pre, slopes_s, float64_most(mixed && !ev.f64, grad != 0, false, ev.M), 1, lane, bands_s);
   } else {
     if (w != 0) return;
     if (lane == 0) {                                   // the bins as one piece
@@ -405,7 +405,7 @@ hipError_t enqueue_multi_nd(gwl_plan pl, hipStream_t s) {
   hipLaunchKernelGGL(gwl::k_multi_reset, dim3(1), dim3(1), 0, s, c);
   if (pl->ngrp == 0) return hipGetLastError();   // no point outside calibrated events: only the reset
   hipLaunchKernelGGL(gwl::k_multi_setup<ND>, dim3(pl->ngrp), dim3(gwl::MULTI_SETUP_WAVES * gwl::WAVE), 0, s, evs, geoms,
-                     io, grp, pl->mixed ? 1 : 0, pl->chunk, c, pl->d_items, pl->d_plans);
+                     io, grp, pl->mixed ? 1 : 0, pl->grad ? 1 : 0, pl->chunk, c, pl->d_items, pl->d_plans);
 #define GWL_MB(MX, GR)                                                                                         \
   hipLaunchKernelGGL((gwl::k_multi_bins<ND, MX, GR>), dim3(pl->grid), dim3(gwl::BLOCK), 0, s, evs, io, grp,    \
                      (const int2*)pl->d_items, (const int*)pl->d_plans, (const gwl::MultiCtl*)c, stamp)

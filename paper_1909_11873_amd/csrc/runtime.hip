@@ -1109,7 +1109,8 @@ hipError_t enqueue_logl(gwl_event ev, const double* theta, int64_t B, bool mixed
                   : nullptr;
   hipError_t e = perm ? launch_order(theta, NPARAM, B, perm, s) : hipSuccess;
   if (e == hipSuccess && !sh.setup)
-    e = launch_setup(ev->ndet, ev->geom, ev->ec, theta, B, Bp, coef, s, bands, ev->M, mixed, sh.nchunk, plan, perm);
+    e = launch_setup(ev->ndet, ev->geom, ev->ec, theta, B, Bp, coef, s, bands,
+                     float64_most(mixed, grad, false, ev->M), sh.nchunk, plan, perm);
   hipEvent_t pa = nullptr, pb = nullptr;
   const bool prof = e == hipSuccess && prof_begin(s, pa, pb);
   const EvalArgs x = {ev->tab64, ev->tab32, ev->g64, theta, &ev->geom, ev->ec, bands, plan, coef, B, Bp, ev->M,
