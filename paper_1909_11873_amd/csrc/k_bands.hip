@@ -45,13 +45,16 @@ void basis_slopes(double f, double (&g)[NBASIS]) {
 }
 
 // Lowest chirp mass (solar masses) and largest arrival time (s) that a level holds: black-hole and
-// neutron-star binaries near the data's time origin, and black holes that arrive within half a second. (With the
-// detectors' delays and the post-Newtonian terms: all of 12,000 draws of |t_c| to 0.1 s with masses from 10, and from 1,
-// and of 8,000 of |t_c| to 0.5 s with masses from 10.) A group walks every level that one of its points needs, so few
-// levels are better than many, and `share` is the most that a level's rows may be of the bins. The last one is for
-// long segments: 8,192 points of which 40 % are live, three detectors, 8 s (rows 0.26 of the bins), without it and
-// with it: t_c within 0.5 s 149 and 86 us, all over the segment 149 and 201 (104 on every bin).
-constexpr struct { double mc, t, share; } kLevels[MAXLEV] = {{10.0, 0.15, 0.9}, {1.0, 0.13, 0.9}, {10.0, 0.53, 0.125}};
+// neutron-star binaries near the data's time origin, and black holes that arrive within half a second. `late`:
+// heavy systems with aligned spins arrive up to late f^(-2/3) after that (s, f in Hz; masses of 10 to 60, spins to
+// 0.9: 0.12 s at 66 Hz, 0.02 at 1,160). A group walks every level that one of its points needs, and one that walks two
+// can be the last of a launch (19,000 points of which one in 8,192 needed the second: 101 us for 53), so a level is
+// to hold all of a prior (the first: all of 300,000 draws with |t_c| to 0.1 s on six grids), and few levels are better than
+// many. `share` is the most that a level's rows may be of the bins. The last one is for long segments: 8,192 points
+// of which 40 % are live, three detectors, 8 s (rows 0.26 of the bins), without it and with it: t_c within 0.5 s
+// 171 and 86 us, all over the segment 170 and 201 (104 on every bin).
+constexpr struct { double mc, t, late, share; } kLevels[MAXLEV] = {
+    {10.0, 0.13, 1.6, 0.9}, {1.0, 0.13, 0.0, 0.9}, {10.0, 0.53, 0.0, 0.125}};
 
 // The levels of an event whose bands are in `head`.
 void plan_levels(BandHead& h, int64_t M) {
@@ -64,8 +67,8 @@ void plan_levels(BandHead& h, int64_t M) {
     BandLevel v;
     memset(&v, 0, sizeof v);
     for (int i = 0; i < MAXBRK; ++i) v.lo[i] = -HUGE_VAL, v.hi[i] = HUGE_VAL;
-    // the lowest t(f) on an interval: the Newtonian chirp's, a tenth longer, at its lower end
-    const double chirp = 1.1 * 5.0 / 256.0 * pow(want.mc * kTsun, -5.0 / 3.0) * pow(M_PI, -8.0 / 3.0) * 0.6;
+    // the lowest t(f) on an interval: the Newtonian chirp's, 8 % longer, at its lower end
+    const double chirp = 1.08 * 5.0 / 256.0 * pow(want.mc * kTsun, -5.0 / 3.0) * pow(M_PI, -8.0 / 3.0) * 0.6;
     int band[MAXSEG], rows[MAXSEG];
     for (int s = 0; s < h.nseg; ++s) {
       band[s] = -1;
@@ -73,7 +76,8 @@ void plan_levels(BandHead& h, int64_t M) {
       for (int c = h.c0[s]; c < h.c0[s + 1] && band[s] < 0; ++c) {
         const BandCand& b = h.cand[c];
         const double lim = BAND_FILL * b.tb;
-        if (want.t - b.t0 <= lim && b.t0 + want.t - chirp * h.gp[b.i0][0] <= lim) band[s] = c, rows[s] = b.rows;
+        const double late = want.late * 2.25 * h.gp[b.i0][7] * h.gp[b.i0][7];   // (g_7' = 2/3 f^(-1/3))
+        if (want.t + late - b.t0 <= lim && b.t0 + want.t - chirp * h.gp[b.i0][0] <= lim) band[s] = c, rows[s] = b.rows;
       }
     }
     // the panels below the cheapest wide segment (or all of them), and that segment
