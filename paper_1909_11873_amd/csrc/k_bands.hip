@@ -130,8 +130,10 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
   nrows = kvals = 0;
   const int64_t M = (int64_t)f.size();
   if (M < 2 * kMinBins || M > kMaxGrid) return;
-  for (int64_t k = 0; k < M; ++k)
-    if (!(f[(size_t)k] > 0.0) || !isfinite(f[(size_t)k]) || (k > 0 && !(f[(size_t)k] > f[(size_t)k - 1]))) return;
+  if (!(f.front() > 0.0) || !isfinite(f.back())) return;
+  int rising = 1;                                              // (with which all are positive and finite)
+  for (size_t k = 1; k < f.size(); ++k) rising &= f[k] > f[k - 1];
+  if (!rising) return;
   const double flo = f.front(), fhi = f.back();
   // panels: ends in a geometric sequence, each at least kMinBins bins
   const int P = std::min(MAXPANEL, std::max(1, (int)ceil(log(fhi / flo) / log(kPanelRatio) - 1e-9)));
