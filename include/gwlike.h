@@ -333,6 +333,16 @@ gwl_status gwl_launch_shape(gwl_event ev, int64_t B, gwl_precision prec, int wit
 gwl_status gwl_launch_layout(gwl_event ev, int64_t B, gwl_precision prec, int with_grad, int* waves, int* groups,
                              int* setup);
 
+/*
+ * What a gwl_logl_batch (with_grad = 0) or gwl_logl_grad (with_grad = 1) call on these points walks, summed
+ * over the points: rows in float64 (band-limited rows, or in a float64 call the bins or edges) and bins
+ * in mixed precision. The direct sum would be B times the event's M in one of them. theta: device, as
+ * in those calls. For measurement and tests: allocates, synchronises `stream`, and must not be called
+ * while it is capturing. Any output pointer may be null.
+ */
+gwl_status gwl_call_rows(gwl_event ev, const double* theta, int64_t B, gwl_precision prec, int with_grad,
+                         int64_t* float64_rows, int64_t* mixed_bins, void* stream);
+
 /* Load tile choices from a JSON cache written by gwl_autotune or gwl_multi_autotune (missing file =
  * GWL_E_INVALID). A single event's shape is taken whenever it was measured (one from before band-limited
  * rows, with a workgroup for every few hundred bins, is a valid launch but seldom the best: measure it

@@ -808,6 +808,11 @@ static size_t cal_bytes(const gwl_event_s* ev, const CalShape& sh, bool grad, bo
          sizeof(int) * PLAN_INTS * (size_t)sh.npg + (order ? sizeof(int) * Bp : 0);
 }
 
+// The plans in that workspace.
+static int* cal_plan(const gwl_event_s* ev, const CalShape& sh, bool grad, void* ws) {
+  return (int*)((char*)ws + cal_bytes(ev, sh, grad, false)) - (size_t)PLAN_INTS * sh.npg;
+}
+
 }  // namespace gwl
 
 extern "C" {
@@ -838,7 +843,7 @@ static gwl_status run_logl_cal(gwl_event ev, const double* theta, int64_t B, boo
   double* coef = (double*)ws;
   double* calc = coef + (size_t)NCOEF * Bp;
   double* part = calc + (size_t)ncal * Bp;
-  int* plan = (int*)(part + ((size_t)sh.nchunk * nz_of(nd, grad) + (size_t)(sh.nchunk + n - 2) * nz_win(nd, grad)) * Bp);
+  int* plan = cal_plan(ev, sh, grad, ws);
   const CalTables t = {ev->tab64, ev->tab32, ev->g64, ev->g32, ev->cal64, ev->cal32, ev->calt64, ev->calt32, ev->calB,
                        ev->kcal, ev->bands, ev->cal_slope};
   int* perm = order ? plan + (size_t)PLAN_INTS * sh.npg : nullptr;
@@ -936,6 +941,60 @@ gwl_status gwl_launch_layout(gwl_event ev, int64_t B, gwl_precision prec, int wi
   if (waves) *waves = sh.W;
   if (groups) *groups = sh.G;
   if (setup) *setup = sh.setup;
+  return GWL_OK;
+}
+
+gwl_status gwl_call_rows(gwl_event ev, const double* theta, int64_t B, gwl_precision prec, int with_grad,
+                         int64_t* float64_rows, int64_t* mixed_bins, void* stream) {
+  clear_error();
+  if (!ev) return fail(GWL_E_INVALID, "event is null");
+  if (B < 0 || B > kMaxBatch) return fail(GWL_E_SHAPE, "B=%lld outside [0, %lld]", (long long)B, (long long)kMaxBatch);
+  if (prec != GWL_FP64 && prec != GWL_MIXED) return fail(GWL_E_INVALID, "unknown precision %d", (int)prec);
+  if (B > 0 && !theta) return fail(GWL_E_INVALID, "theta must be a device pointer");
+  gwl_status st = check_device(ev->device);
+  if (st != GWL_OK) return st;
+  const bool mixed = use_mixed(ev, prec), grad = with_grad != 0, cal = ev->ncal > 0;
+  hipStream_t s = (hipStream_t)stream;
+  int64_t n[2] = {0, 0};                               // float64 rows, mixed bins
+  const LoopShape sh = choose_shape(ev, std::max<int64_t>(B, 1), mixed, grad);
+  if (B > 0 && ev->bands && (cal || sh.chunk > kBandMinChunk)) {
+    const CalShape cs = cal ? cal_shape(ev, B, grad) : CalShape{};
+    const int64_t npg = (B + WAVE - 1) / WAVE, Bp = npg * WAVE, P = NPARAM + 2 * ev->ncal * ev->ndet;
+    const bool order = cal ? in_order(ev, B, grad, INT_MAX) : sh.order != 0;
+    Slab slab;
+    const size_t ows = slab.take(cal ? cal_bytes(ev, cs, grad, order) : sizeof(double) * NCOEF * (size_t)Bp);
+    const size_t oplan = slab.take(sizeof(int) * PLAN_INTS * (size_t)npg), operm = slab.take(sizeof(int) * (size_t)Bp);
+    const size_t oout = slab.take(cal ? sizeof(double) * (size_t)(B * (grad ? P + 1 : 1)) : 0);
+    char* p = nullptr;
+    hipError_t e = hipMalloc((void**)&p, slab.bytes);
+    int* plan = (int*)(p + oplan);
+    if (e == hipSuccess && cal) {                      // the whole call: its plans stay in its workspace
+      st = run_logl_cal(ev, theta, B, mixed, grad, (double*)(p + oout), (double*)(p + oout) + B, s, p + ows,
+                        cal_bytes(ev, cs, grad, order));
+      plan = cal_plan(ev, cs, grad, p + ows);
+    } else if (e == hipSuccess) {
+      int* perm = order ? (int*)(p + operm) : nullptr;
+      if (perm) e = launch_order(theta, NPARAM, B, perm, s);
+      if (e == hipSuccess)
+        e = launch_setup(ev->ndet, ev->geom, ev->ec, theta, B, Bp, (double*)(p + ows), s, ev->bands,
+                         float64_most(mixed, grad, false, ev->M), 1, plan, perm);
+    }
+    std::vector<int> h((size_t)npg * PLAN_INTS);
+    if (e == hipSuccess && st == GWL_OK)
+      e = hipMemcpyAsync(h.data(), plan, sizeof(int) * h.size(), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (p) (void)hipFree(p);
+    if (e != hipSuccess) return hip_fail(e, "rows of a call");
+    if (st != GWL_OK) return st;
+    for (int64_t g = 0; g < npg; ++g) {
+      const int* pl = &h[(size_t)g * PLAN_INTS];
+      n[pl[2] ? 0 : 1] += std::min<int64_t>(WAVE, B - g * WAVE) * (pl[2] ? pl[0] : ev->M);
+    }
+  } else {
+    n[mixed ? 1 : 0] = B * ev->M;
+  }
+  if (float64_rows) *float64_rows = n[0];
+  if (mixed_bins) *mixed_bins = n[1];
   return GWL_OK;
 }
 

@@ -80,6 +80,7 @@ def lib() -> ctypes.CDLL:
         "gwl_autotune": ([ctypes.c_char_p, vp, i64, cint, cint], cint),
         "gwl_autotune_load": ([ctypes.c_char_p], cint),
         "gwl_launch_shape": ([vp, i64, cint, cint, ctypes.POINTER(cint), ctypes.POINTER(cint)], cint),
+        "gwl_call_rows": ([vp, vp, i64, cint, cint, ctypes.POINTER(i64), ctypes.POINTER(i64), vp], cint),
         "gwl_event_reserve": ([vp, i64, cint, cint, vp], cint),
         "gwl_launch_layout": ([vp, i64, cint, cint, ctypes.POINTER(cint), ctypes.POINTER(cint), ctypes.POINTER(cint)],
                               cint),
@@ -442,6 +443,16 @@ def launch_layout(ev: Event, batch: int, precision="mixed", with_grad: bool = Fa
     _check("gwl_launch_layout", lib().gwl_launch_layout(ev.handle, int(batch), _prec(precision), int(bool(with_grad)),
                                                         ctypes.byref(w), ctypes.byref(g), ctypes.byref(st)))
     return w.value, g.value, bool(st.value)
+
+
+def call_rows(theta: torch.Tensor, ev: Event, precision="mixed", with_grad: bool = False):
+    """(rows in float64, bins in mixed precision) that a logl or logl_grad call on these points walks, summed over
+    the points (gwl_call_rows; synchronises). The direct sum would be batch times bins in one of them."""
+    theta = _theta(theta, ev)
+    rows, bins = ctypes.c_int64(), ctypes.c_int64()
+    _check("gwl_call_rows", lib().gwl_call_rows(ev.handle, _ptr(theta), theta.shape[0], _prec(precision),
+                                                int(bool(with_grad)), ctypes.byref(rows), ctypes.byref(bins), _stream(theta)))
+    return rows.value, bins.value
 
 
 def autotune_load(cache_path: str) -> None:

@@ -368,3 +368,70 @@ def test_calibrated_rows_on_narrow_bands(nodes, f_lo, f_hi, duration, sigma):
     assert scaled_grad_error(g[:, :11], gwant[:, :11]).max() <= 2e-9 and c.max() <= 2e-9
     ev.close()
     plain.close()
+
+
+def _both(cfg, nodes, f_hi, nd):
+    """An event and the same bins with two neighbours swapped, which have no rows; |d|."""
+    spec, f, psd, data, dets = event_inputs(cfg, f_hi=f_hi, ndet=nd)
+    k = len(f) // 2
+    swap = np.r_[0:k, k + 1, k, k + 2:len(f)]
+    mk = lambda i: gw.Event(torch.tensor(np.ascontiguousarray(data[:, i]), device=DEV),
+                            torch.tensor(np.ascontiguousarray(psd[:, i]), device=DEV), dets,
+                            torch.tensor(f[i], device=DEV), spec.df, calibration_nodes=nodes)
+    dn = math.sqrt(sum(float((4 * spec.df * np.abs(d) ** 2 / s).sum()) for d, s in zip(data, psd)))
+    return mk(np.arange(len(f))), mk(swap), len(f), dn
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("nodes", [0, 6])
+@pytest.mark.parametrize("n", [257, 20000])
+def test_which_calls_walk_rows(prec, grad, nodes, n):
+    """What the comparisons of rows with bins rest on: points near the origin walk far fewer rows than bins, in
+    float64; points all over the segment the bins, in the call's precision (in a large call's order a group holds a
+    part of them, and may still find rows); an event without rows every bin."""
+    ev, plain, M, _ = _both(1, nodes, 1024.0, 3)
+    for kind, most in (("prior", 0.35), ("narrow", 0.3), ("wide", 0.8), ("late", 1.0)):
+        th = _points("narrow" if kind == "narrow" else kind, n, 5)
+        if nodes:
+            th = np.concatenate([th, 0.05 * np.random.default_rng(1).standard_normal((n, 6 * nodes))], axis=1)
+        t = torch.tensor(th, device=DEV)
+        rows, bins = gw.call_rows(t, ev, prec, grad)
+        if kind == "late" and n > 16384:
+            assert 0.9 * n * M < rows + bins <= n * M
+        elif kind == "late":
+            assert (rows, bins) == ((n * M, 0) if prec == "fp64" else (0, n * M))
+        else:
+            assert bins == 0 and 100 * n < rows < most * n * M, (kind, rows / (n * M), bins)
+        assert gw.call_rows(t, plain, prec, grad) == ((n * M, 0) if prec == "fp64" else (0, n * M))
+    ev.close()
+    plain.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nodes", [0, 6])
+@pytest.mark.parametrize("mass", [12.0, 60.0])
+def test_bands_up_to_their_limits(mass, nodes):
+    """Groups of one point each, whose arrival times step by a millisecond from -0.35 to 0.65 s: some reach each
+    band's limit to within a hundredth of its half-width before the next one takes over."""
+    ev, plain, M, dn = _both(1, nodes, 700.0, 2)
+    th = np.repeat(synth.THETA0_BBH[None], 1024, axis=0)
+    th[:, 0] = mass
+    th[:, 10] = -0.35 + 1e-3 * np.arange(1024)
+    if nodes:
+        th = np.concatenate([th, 0.1 * np.random.default_rng(3).standard_normal((1024, 4 * nodes))], axis=1)
+    sizes = set()
+    for i in range(0, 1024, 100):
+        t = torch.tensor(np.repeat(th[i:i + 100], 64, axis=0), device=DEV)
+        want, gwant = (x.cpu().numpy() for x in gw.logl_grad(t, plain, "fp64"))
+        v, g = (x.cpu().numpy() for x in gw.logl_grad(t, ev, "fp64"))
+        hn = dn + np.sqrt(np.maximum(dn ** 2 - 2.0 * want, 0.0))
+        for got in (v, gw.logl(t, ev, "fp64").cpu().numpy()):
+            assert (np.abs(got - want) <= 1e-13 * hn * dn + 1e-9).all(), (np.abs(got - want) / (hn * dn)).max()
+        assert scaled_grad_error(g[:, :11], gwant[:, :11]).max() <= 2e-9
+        for j in range(0, 100, 9):
+            sizes.add(gw.call_rows(t[64 * j:64 * j + 64], ev, "fp64", True)[0])
+    assert len(sizes) >= 10                                    # many bands took their turn
+    ev.close()
+    plain.close()
