@@ -83,6 +83,17 @@ def roofline(ndet: int, mixed: bool, nbins: float, npoints: float, seconds: floa
     return achieved / 1e12, peak / 1e12, achieved / peak
 
 
+def walked(ndet: int, grad: bool, rows, npoints: float, seconds: float):
+    """The same for what the launch walked (gwlike.call_rows): float64 rows at the work of the loop that takes the
+    detectors after the first by rotation (uniform grids: 14 flops each for a value's recurrence, 12 in place of
+    the shift and the phasor's 18 for the gradient), and bins in mixed precision."""
+    f64 = (16 + 18 + 12 * (ndet - 1) + 14 * ndet - 1 + 16) if grad else 16 + 26 + 14 * (ndet - 1)
+    m64, m32, mtr = work_per_point_bin(ndet, True, grad)
+    tmin = rows[0] * f64 / PEAK_FP64 + rows[1] * (m64 / PEAK_FP64 + m32 / PEAK_FP32 + mtr / PEAK_TRANS)
+    return {"float64_rows_per_point": rows[0] / npoints, "mixed_bins_per_point": rows[1] / npoints,
+            "achieved": (rows[0] * f64 + rows[1] * (m64 + m32 + mtr)) / seconds / 1e12, "frac": tmin / seconds}
+
+
 def NPARAM_ALL(nd: int, nodes: int) -> int:
     return 11 + 2 * nodes * nd
 
@@ -251,13 +262,14 @@ def gpu_leg(cfg: int, steps: int, warmup: int, parity_inputs, tune_out=None, rb_
             gw.autotune(ev, B, prec, with_grad=False, cache_path=tune_out)
             gw.autotune(ev, min(B, 16384), prec, with_grad=True, cache_path=tune_out)
     t_tune = time.perf_counter() - t_tune
-    shapes = {}
+    shapes, rows = {}, {}
     for key, (bb, prec, gr) in {"mixed": (B, "mixed", False), "fp64": (B, "fp64", False),
                                 "mixed_grad": (min(B, 16384), "mixed", True),
                                 "fp64_grad": (min(B, 16384), "fp64", True)}.items():
         nchunk, chunk = gw.launch_shape(ev, bb, prec, gr)
         waves, groups, setup = gw.launch_layout(ev, bb, prec, gr)
         shapes[key] = {"nchunk": nchunk, "chunk_bins": chunk, "waves": waves, "groups": groups, "setup": setup}
+        rows[key] = gw.call_rows(theta[:bb], ev, prec, gr)
 
     def timed(fn, k, w):
         """(wall seconds of k calls, mean bin-loop kernel seconds over k more calls). The wall clock
@@ -401,6 +413,7 @@ def gpu_leg(cfg: int, steps: int, warmup: int, parity_inputs, tune_out=None, rb_
         "B": B, "M": M, "ndet": nd, "prep_ms": prep_ms, "parity": parity, "autotune_s": t_tune,
         "shapes": shapes,
         "mixed_wall": out["mixed"][0], "mixed_kern": out["mixed"][1], "mixed_steps": out["mixed"][2],
+        "rows": rows,
         "mixed_kern_median": out["mixed"][3], "mixed_call_median": out["mixed"][4],
         "fp64_wall": out["fp64"][0], "fp64_kern": out["fp64"][1], "fp64_steps": out["fp64"][2],
         "fp64_kern_median": out["fp64"][3], "fp64_call_median": out["fp64"][4],
@@ -796,11 +809,13 @@ def main():
     mixed_line = {"value": B * r["mixed_steps"] / r["mixed_wall"], "kernel": kernel_name(nd, True, False, sh["mixed"]),
                   "kernel_ms_median": r["mixed_kern_median"] * 1e3, "kernel_ms_mean": r["mixed_kern"] * 1e3,
                   "call_ms_median": r["mixed_call_median"] * 1e3,
-                  "roofline": {"bound": "alu", "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": frac}}
+                  "roofline": {"bound": "alu", "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": frac,
+                               "walked": walked(nd, False, r["rows"]["mixed"], B, r["mixed_kern_median"])}}
     fp64_line = {"value": r["fp64_evals"], "kernel": kernel_name(nd, False, False, sh["fp64"]),
                  "kernel_ms_median": r["fp64_kern_median"] * 1e3, "kernel_ms_mean": r["fp64_kern"] * 1e3,
                  "call_ms_median": r["fp64_call_median"] * 1e3,
-                 "roofline": {"bound": "alu", "achieved": a64, "peak": p64, "unit": "TFLOP/s", "frac": f64}}
+                 "roofline": {"bound": "alu", "achieved": a64, "peak": p64, "unit": "TFLOP/s", "frac": f64,
+                              "walked": walked(nd, False, r["rows"]["fp64"], B, r["fp64_kern_median"])}}
     if args.config == 0:       # a float64 workload: the float64 kernel is the headline
         metric = f"logL evals/sec ({band}) FP64; frac VALU FP64 peak"
         head, other, other_name = fp64_line, mixed_line, "mixed"
@@ -810,7 +825,9 @@ def main():
         head = {"value": r["grad_mixed_evals"], "kernel": kernel_name(nd, True, True, sh["mixed_grad"]),
                 "kernel_ms_median": r["grad_mixed_kern_median"] * 1e3, "kernel_ms_mean": r["grad_mixed_kern"] * 1e3,
                 "call_ms_median": r["grad_mixed_call_median"] * 1e3,
-                "roofline": {"bound": "alu", "achieved": agm, "peak": pgm, "unit": "TFLOP/s", "frac": fgm}}
+                "roofline": {"bound": "alu", "achieved": agm, "peak": pgm, "unit": "TFLOP/s", "frac": fgm,
+                             "walked": walked(nd, True, r["rows"]["mixed_grad"], r["grad_batch"],
+                                              r["grad_mixed_kern_median"])}}
         other, other_name = mixed_line, "forward_mixed"
         steps_head, wall_head, dtype, prec = r["grad_steps"], r["grad_mixed_wall"], "f64+f32", "mixed"
         B = r["grad_batch"]
@@ -824,8 +841,8 @@ def main():
                  "kernel_ms": head["kernel_ms_median"], "kernel_ms_mean": head["kernel_ms_mean"],
                  "timing": ("median over 50 launches of HIP events on its stream around the evaluation kernel and, "
                            "where the launch shape has one, its value-epilogue kernel"),
-                 "work": ("priced as the direct sum over every bin; a launch that walks band-limited rows does less, "
-                          "so its fraction may exceed 1")})
+                 "work": ("achieved and frac price the direct sum over every bin, of which a launch on band-limited "
+                          "rows does a part (its frac may exceed 1); walked prices the rows and bins it walked")})
     line = {
         "metric": metric,
         "value": head["value"], "unit": "evals/s", "n_gpus": 1, "steps": steps_head, "warmup": args.warmup,

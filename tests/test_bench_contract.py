@@ -60,3 +60,15 @@ def test_committed_traffic_summary_parses():
     if bench.kernel_hash() not in text:
         pytest.skip("the kernel sources changed since the traffic counters were taken")
     assert bench.read_traffic(layout) == pytest.approx(float(text.split("hbm_bytes_per_launch:")[1].split()[0]))
+
+
+def test_walked_rows_are_priced_at_their_own_loops():
+    # three detectors: 70 flops a float64 row (16 phase, 26 for the first detector, 14 for each other), adjoint
+    # 115 (16, 18 and 12 each for the phasors, 57 for the moments); no row at all is no fraction
+    got = bench.walked(3, False, (2.0e9, 0), 1.0e6, 70 * 2.0e9 / bench.PEAK_FP64)
+    assert got["frac"] == pytest.approx(1.0) and got["float64_rows_per_point"] == 2000.0
+    got = bench.walked(3, True, (2.0e9, 0), 1.0e6, 2 * 115 * 2.0e9 / bench.PEAK_FP64)
+    assert got["frac"] == pytest.approx(0.5)
+    _, _, direct = bench.roofline(3, True, 16225, 65536, 1.0e-3)
+    assert bench.walked(3, False, (0, 16225 * 65536), 65536, 1.0e-3)["frac"] == pytest.approx(direct)
+    assert bench.walked(1, True, (0, 0), 1, 1.0)["frac"] == 0.0
