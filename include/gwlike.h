@@ -177,9 +177,14 @@ gwl_status gwl_event_info(gwl_event ev, int* ndet, int64_t* M, double* df);
  * logL for a batch (paper Eq. 2, as the ratio above).
  *   theta  device, float64 [B][11];  logl device, float64 [B].
  *   prec   GWL_FP64: every step in float64.
- *          GWL_MIXED: float64 for the post-Newtonian phase, the time-shift term and its
- *          reduction modulo one cycle, and for every per-point scalar and reduction; float32
- *          for the per-bin phasor, complex multiply-accumulate over short blocks of bins.
+ *          GWL_MIXED: groups of 64 points whose arrival times let them walk clearly fewer band-limited rows
+ *          than the grid has bins do so in float64; the others walk every bin with float64
+ *          for the post-Newtonian phase, the time-shift term and its reduction modulo one cycle, and for
+ *          every per-point scalar and reduction, and float32 for the per-bin phasor and the complex
+ *          multiply-accumulate over short blocks of bins.
+ * On rows a point's value depends, to the last bits, on the points that it is evaluated with (in mixed precision
+ * to the mixed loop's own error, about 1e-8 of logL, where another point sends its group to the bins): groups are 64
+ * neighbours, in large calls after an ordering within 1,024. The same call gives the same bits.
  * B = 0 is a no-op. The call allocates nothing once the event's workspace on `stream` is large
  * enough: the event keeps one workspace per stream, grown (outside graph capture only) by the
  * first call that needs more. On a stream that is capturing a graph a call that would need to
@@ -252,7 +257,7 @@ gwl_status gwl_waveform(const double* theta, int64_t B, const gwl_detector* dets
 /*
  * Several events of uneven size in one persistent launch (the batch axis of the paper's
  * parallel prior sampling, section 3, extended across events).
- * gwl_multi_plan_create builds the work list (event, point group, bin range), sizes the
+ * gwl_multi_plan_create lists the work (event, point group; each launch cuts the groups' rows into items), sizes the
  * workspace for the given per-event batch sizes B_e, picks tile shapes, and captures the whole
  * evaluation (queue reset, per-point set-up, persistent kernel, per-event finalisation) in a
  * HIP graph bound to the events. The events must outlive the plan. Calibrated events (of

@@ -121,8 +121,8 @@ gwl_status run_logl(gwl_event ev, const double* theta, int64_t B, bool mixed, bo
 gwl_status run_calibrated(gwl_event ev, const double* theta, int64_t B, bool mixed, bool grad, double* logl,
                           double* gradout, hipStream_t s, void* ws, size_t ws_bytes);
 
-// The event's workspace on stream s, grown to at least `bytes` if needed (zero-filled when it
-// grows). Growing is refused while s is capturing a graph (GWL_E_INVALID): the caller reserves it
+// The event's workspace on stream s, grown to at least `bytes` and `ncnt` counters (zero when new) if
+// needed. Growing is refused while s is capturing a graph (GWL_E_INVALID): the caller reserves it
 // beforehand with gwl_event_reserve or an ordinary call of the same size.
 gwl_status event_workspace(gwl_event ev, hipStream_t s, size_t bytes, size_t ncnt, void** out,
                            unsigned int** cnt = nullptr);

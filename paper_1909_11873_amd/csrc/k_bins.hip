@@ -15,8 +15,8 @@
 // workgroup writes its partial sums and the last one to finish (a counter per point group, after
 // an agent-scope release/acquire) adds the G of them in workgroup order: every sum is taken in a
 // fixed order, so results are bitwise reproducible for a given shape. The gradient's epilogue
-// (eleven forward-mode passes through the point model, over 250 registers) runs as its own kernel
-// on the G partial sums.
+// (forward-mode derivatives through the point model, on two wavefronts per 64 points) runs as its own
+// kernel on the G partial sums.
 //
 // The per-point set-up (phase coefficients, shifts, projection factors) either comes from the
 // set-up kernel's rows or is computed here and handed to every wavefront through LDS

@@ -5,9 +5,10 @@
 // 11 + 2 n det .. : n amplitude values, then n phase values in radians).
 //
 // The bin loop is the ordinary one with one more complex factor per (point, detector, bin):
-// the spline value is a four-term dot product of per-bin weights (RowCal, wave-uniform) with the
-// point's four window node values (VGPRs, fixed over a node interval, so chunks never cross an
-// interval). <h_cal|h_cal> needs no per-bin work: with K_k = 4 df f_k^-7/3 / S_k,
+// the spline value is a cubic in the bin's position within its node interval, its coefficients formed from
+// the point's four window node values when the walk enters the interval (VGPRs; a chunk may cross several
+// intervals); the four-term weights of the same cubic (RowCal, wave-uniform) serve the adjoint's node moments.
+// <h_cal|h_cal> needs no per-bin work: with K_k = 4 df f_k^-7/3 / S_k,
 //   sum_k K_k (1 + dA_k)^2 = K + 2 alpha.K1 + alpha.K2.alpha,
 // K1_j = sum_k K_k w_kj and K2_jl = sum_k K_k w_kj w_kl computed once per event (alpha the
 // amplitude node values, w_kj the spline weight of node j at bin k).

@@ -748,15 +748,15 @@ gwl_status gwl_event_info(gwl_event ev, int* ndet, int64_t* M, double* df) {
 namespace gwl {
 
 // Launch shape of a calibrated call: every point group's rows in nchunk equal shares, one wavefront
-// each, for about as many wavefronts as the chip holds at the loop's registers (four per SIMD for the
-// value, two for the adjoint: a part-filled second round costs a whole one), of at least 24 rows.
+// each.
 static CalShape cal_shape(const gwl_event_s* ev, int64_t B, bool grad) {
   CalShape sh;
   memset(&sh, 0, sizeof sh);
   const int n = ev->ncal;
   sh.nnode = n;
   sh.npg = (int)((B + WAVE - 1) / WAVE);
-  // Workgroups of four chunks resident together, by the loops' registers: as many of them as fit, or one a
+  // Workgroups of four chunks resident together, by the loops' registers (four wavefronts per SIMD for values,
+  // two for three detectors' gradients; a part-filled second round costs a whole one): as many of them as fit, or one a
   // group more where that leaves a quarter of them empty, and 48 rows a chunk at least (the epilogue walks the
   // chunks in turn). Three detectors, 8 s, 10 nodes, with as many as make 4,096 wavefronts (gradients 2,048) of
   // 24 rows and now: values of 1,000 points 62 and 55 us, 9,000 123 and 102, 20,000 198 and 172; gradients
