@@ -52,9 +52,11 @@ void basis_slopes(double f, double (&g)[NBASIS]) {
 // to hold all of a prior (the first: all of 300,000 draws with |t_c| to 0.1 s on six grids), and few levels are better than
 // many. `share` is the most that a level's rows may be of the bins. The last one is for long segments: 8,192 points
 // of which 40 % are live, three detectors, 8 s (rows 0.26 of the bins), without it and with it: t_c within 0.5 s
-// 171 and 86 us, all over the segment 170 and 201 (104 on every bin).
-constexpr struct { double mc, t, late, share; } kLevels[MAXLEV] = {
-    {10.0, 0.13, 1.6, 0.9}, {1.0, 0.13, 0.0, 0.9}, {10.0, 0.53, 0.0, 0.125}};
+// 148 and 86 us, all over the segment 147 and 201 (104 on every bin). `strict`: a level that takes only the
+// times it is for and not the bands' margins, into which heavy systems just beyond the first level would draw their
+// groups on the way to the bins (all over the segment 170).
+constexpr struct { double mc, t, late, share; bool strict; } kLevels[MAXLEV] = {
+    {10.0, 0.13, 1.6, 0.9, false}, {1.0, 0.13, 1.6, 0.9, true}, {10.0, 0.53, 0.0, 0.125, false}};
 
 // The levels of an event whose bands are in `head`.
 void plan_levels(BandHead& h, int64_t M) {
@@ -66,9 +68,13 @@ void plan_levels(BandHead& h, int64_t M) {
   for (const auto& want : kLevels) {
     BandLevel v;
     memset(&v, 0, sizeof v);
-    for (int i = 0; i < MAXBRK; ++i) v.lo[i] = -HUGE_VAL, v.hi[i] = HUGE_VAL;
     // the lowest t(f) on an interval: the Newtonian chirp's, 8 % longer, at its lower end
     const double chirp = 1.08 * 5.0 / 256.0 * pow(want.mc * kTsun, -5.0 / 3.0) * pow(M_PI, -8.0 / 3.0) * 0.6;
+    auto late = [&](int i) { return want.late * 2.25 * h.gp[i][7] * h.gp[i][7]; };   // (g_7' = 2/3 f^(-1/3))
+    for (int i = 0; i < MAXBRK; ++i) {
+      v.lo[i] = want.strict && i < h.nbrk ? chirp * h.gp[i][0] - want.t : -HUGE_VAL;
+      v.hi[i] = want.strict && i < h.nbrk ? want.t + late(i) : HUGE_VAL;
+    }
     int band[MAXSEG], rows[MAXSEG];
     for (int s = 0; s < h.nseg; ++s) {
       band[s] = -1;
@@ -76,8 +82,7 @@ void plan_levels(BandHead& h, int64_t M) {
       for (int c = h.c0[s]; c < h.c0[s + 1] && band[s] < 0; ++c) {
         const BandCand& b = h.cand[c];
         const double lim = BAND_FILL * b.tb;
-        const double late = want.late * 2.25 * h.gp[b.i0][7] * h.gp[b.i0][7];   // (g_7' = 2/3 f^(-1/3))
-        if (want.t + late - b.t0 <= lim && b.t0 + want.t - chirp * h.gp[b.i0][0] <= lim) band[s] = c, rows[s] = b.rows;
+        if (want.t + late(b.i0) - b.t0 <= lim && b.t0 + want.t - chirp * h.gp[b.i0][0] <= lim) band[s] = c, rows[s] = b.rows;
       }
     }
     // the panels below the cheapest wide segment (or all of them), and that segment
@@ -349,7 +354,7 @@ __global__ __launch_bounds__(256) void k_band_kernel(const BandGen* __restrict__
 
 // The rows: one wavefront per four neighbouring rows of a band, its lanes over the sources within
 // their windows (each source is read once for the four rows). Bound by L2 reads of the sources; 8 s, three
-// detectors, 118,000 rows: 134 us in the two launches; 128 s: 650 (9.9 ms when every band was summed from
+// detectors, 118,000 rows: 369 us in the two launches; 128 s: 779 (9.9 ms when every band was summed from
 // the bins).
 constexpr int BR_ROWS = 4;
 constexpr int BR_WAVES = 4;
