@@ -64,8 +64,9 @@ struct BandCand {
 // live, and what the rows past them hold, must not show in a point's bits.
 struct BandLevel {
   int rows, np;
-  int piece[3 * (MAXPANEL + 2)];   // per piece its first row, its rows and its band (-1: bins)
-  double lo[MAXBRK], hi[MAXBRK];
+  int row0[MAXPANEL + 2], n[MAXPANEL + 2];   // per piece its first row, its rows
+  double step[MAXPANEL + 2];                 // and their spacing (Hz)
+  double2 lim[MAXBRK + 1];                   // lowest and highest t per interval
 };
 struct BandHead {
   int nbrk, ncand, nseg, npanel;
@@ -98,6 +99,9 @@ struct BandLds {
   float2 r[MAXBRK + 1];                      // lowest and highest t per interval over the group
   unsigned long long ok[MAXCAND / 64 + 1];   // bands that hold the group
   int plan[PLAN_INTS];
+};
+struct LevelLds {                            // in its place where points take levels
+  double2 lim[MAXLEV][MAXBRK + 1];           // the levels' limits
   unsigned long long fit[MAXLEV];            // the points that each level holds
 };
 
@@ -144,6 +148,13 @@ __device__ inline void band_load(const BandHead* __restrict__ bh, double* slopes
   const double2* src = reinterpret_cast<const double2*>(&bh->gp[0][0]);
   double2* dst = reinterpret_cast<double2*>(slopes_s);
   for (int i = (int)threadIdx.x - first; i < BAND_LDS / 2; i += (int)blockDim.x - first) dst[i] = src[i];
+}
+
+// With levels, beside the slopes, by the same threads: their limits (read from memory on the way, they kept every
+// wavefront waiting once an interval).
+__device__ inline void level_load(const BandHead* __restrict__ bh, int nlev, LevelLds& s, int first) {
+  for (int i = (int)threadIdx.x - first; i < nlev * (MAXBRK + 1); i += (int)blockDim.x - first)
+    (&s.lim[0][0])[i] = bh->lev[i / (MAXBRK + 1)].lim[i % (MAXBRK + 1)];
 }
 
 // A lane's band (the first of its turns in step 2) and segment (step 3), requested ahead.
@@ -220,19 +231,23 @@ __device__ inline void band_ranges(const double* slopes_s, int nbrk, const doubl
 // In its place for levels: the points that each level holds, by their own t(f) alone, into s.fit (all ones
 // before). A NaN fits: its point's value is NaN on any rows.
 template <int ND>
-__device__ inline void band_fit(const BandHead* __restrict__ bh, const double* slopes_s, const double (&a)[NBASIS],
-                                const double (&T)[ND], int w, int nw, int lane, BandLds& s) {
+__device__ inline void band_fit(int nlev, int nbrk, const double* slopes_s, const double (&a)[NBASIS],
+                                const double (&T)[ND], int w, int nw, int lane, LevelLds& s) {
   bool ok[MAXLEV];
 #pragma unroll
   for (int l = 0; l < MAXLEV; ++l) ok[l] = true;
-  band_bounds<ND>(slopes_s, bh->nbrk, a, T, w, nw, 0.0, [&](int i, double lo, double hi) {
+  band_bounds<ND>(slopes_s, nbrk, a, T, w, nw, 0.0, [&](int i, double lo, double hi) {
 #pragma unroll
-    for (int l = 0; l < MAXLEV; ++l) ok[l] = ok[l] && !(lo < bh->lev[l].lo[i]) && !(hi > bh->lev[l].hi[i]);
+    for (int l = 0; l < MAXLEV; ++l) {
+      if (l >= nlev) break;
+      const double2 m = s.lim[l][i];
+      ok[l] = ok[l] && !(lo < m.x) && !(hi > m.y);
+    }
   });
 #pragma unroll
   for (int l = 0; l < MAXLEV; ++l) {
     const unsigned long long m = __ballot(ok[l]);
-    if (lane == 0) atomicAnd(&s.fit[l], m);
+    if (l < nlev && lane == 0) atomicAnd(&s.fit[l], m);
   }
 }
 

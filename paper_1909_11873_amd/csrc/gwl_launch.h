@@ -36,7 +36,7 @@ struct LoopShape {
   int pgmaj;    // 1: the dies take the point groups in turn (the set-up rows outweigh the table)
 };
 LoopShape make_shape(int64_t B, int64_t M, int W, int G, int setup, int sepepi = 0);
-size_t eval_lds_doubles(bool table, bool rows, const LoopShape& sh);
+size_t eval_lds_doubles(bool table, size_t plan_bytes, const LoopShape& sh);
 
 // event preparation: per-bin tables, K_det and the float32 scale
 hipError_t launch_prep(int nd, const double* data, const double* psd, const double* fgrid, int64_t M, double df,

@@ -58,13 +58,13 @@ void basis_slopes(double f, double (&g)[NBASIS]) {
 constexpr struct { double mc, t, late, share; bool strict; } kLevels[MAXLEV] = {
     {10.0, 0.13, 1.6, 0.9, false}, {1.0, 0.13, 1.6, 0.9, true}, {10.0, 0.53, 0.0, 0.125, false}};
 
-// The levels of an event whose bands are in `head`.
-void plan_levels(BandHead& h, int64_t M) {
+// The levels of an event whose bands are in `head`, bins `step` apart.
+void plan_levels(BandHead& h, int64_t M, double step) {
   h.nlev[0] = h.nlev[1] = 0;
   BandLevel& every = h.lev[MAXLEV];
   every.np = 1;
-  every.rows = every.piece[1] = (int)M;
-  every.piece[2] = -1;
+  every.rows = every.n[0] = (int)M;
+  every.step[0] = step;
   for (const auto& want : kLevels) {
     BandLevel v;
     memset(&v, 0, sizeof v);
@@ -72,8 +72,8 @@ void plan_levels(BandHead& h, int64_t M) {
     const double chirp = 1.08 * 5.0 / 256.0 * pow(want.mc * kTsun, -5.0 / 3.0) * pow(M_PI, -8.0 / 3.0) * 0.6;
     auto late = [&](int i) { return want.late * 2.25 * h.gp[i][7] * h.gp[i][7]; };   // (g_7' = 2/3 f^(-1/3))
     for (int i = 0; i < MAXBRK; ++i) {
-      v.lo[i] = want.strict && i < h.nbrk ? chirp * h.gp[i][0] - want.t : -HUGE_VAL;
-      v.hi[i] = want.strict && i < h.nbrk ? want.t + late(i) : HUGE_VAL;
+      v.lim[i].x = want.strict && i < h.nbrk ? chirp * h.gp[i][0] - want.t : -HUGE_VAL;
+      v.lim[i].y = want.strict && i < h.nbrk ? want.t + late(i) : HUGE_VAL;
     }
     int band[MAXSEG], rows[MAXSEG];
     for (int s = 0; s < h.nseg; ++s) {
@@ -94,19 +94,18 @@ void plan_levels(BandHead& h, int64_t M) {
     const int stay = wide < 0 ? h.npanel : h.first[wide];
     for (int j = 0; j < stay + (wide < 0 ? 0 : 1); ++j) {
       const int s = j < stay ? j : wide, c = band[s];
-      if (c < 0 && v.np > 0 && v.piece[3 * v.np - 1] < 0) {    // neighbouring panels' bins
-        v.piece[3 * v.np - 2] += rows[s];
+      if (c < 0 && j > 0 && band[j - 1] < 0) {                 // neighbouring panels' bins
+        v.n[v.np - 1] += rows[s];
         continue;
       }
-      int* piece = v.piece + 3 * v.np++;
-      piece[0] = c < 0 ? h.k0[s] : h.cand[c].row0;
-      piece[1] = rows[s];
-      piece[2] = c;
+      v.row0[v.np] = c < 0 ? h.k0[s] : h.cand[c].row0;
+      v.n[v.np] = rows[s];
+      v.step[v.np++] = c < 0 ? step : h.cand[c].step;
       if (c < 0) continue;
       const BandCand& b = h.cand[c];
       for (int i = b.i0; i <= b.i1; ++i) {
-        v.lo[i] = std::max(v.lo[i], b.t0 - BAND_FILL * b.tb);
-        v.hi[i] = std::min(v.hi[i], b.t0 + BAND_FILL * b.tb);
+        v.lim[i].x = std::max(v.lim[i].x, b.t0 - BAND_FILL * b.tb);
+        v.lim[i].y = std::min(v.lim[i].y, b.t0 + BAND_FILL * b.tb);
       }
     }
     v.rows = best;
@@ -331,7 +330,7 @@ void plan_bands(const std::vector<double>& f, bool uniform, double step, int64_t
           if (gen[j].src0 == -1 && gen[j].nsrc == gen[i].rows) gen[j].src0 = -2 - gen[i].row0;
   for (BandGen& g : gen)
     if (g.src0 < -1) g.src0 = -2 - g.src0;
-  if (nodes.empty()) plan_levels(head, M);
+  if (nodes.empty()) plan_levels(head, M, step);
 }
 
 // K(x) exp(-2 pi i t0 d) at x nodes, d Hz from a row (d >= 0; conjugate below)

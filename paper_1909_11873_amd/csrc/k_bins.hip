@@ -81,11 +81,11 @@ LoopShape make_shape(int64_t B, int64_t M, int W, int G, int setup, int sepepi) 
 // cross-wavefront reduction reuses, or,
 // without the table, the reduction buffer alone ((W - 1) x RED_Z x 64).
 constexpr int RED_Z = 4;  // sums reduced per LDS pass
-size_t eval_lds_doubles(bool table, bool rows, const LoopShape& sh) {
+size_t eval_lds_doubles(bool table, size_t plan_bytes, const LoopShape& sh) {
   const size_t coef = sh.setup ? (size_t)NCOEF * WAVE : 0;
   const size_t red = (size_t)(sh.W - 1) * RED_Z * WAVE;
   const size_t tbl = table ? (size_t)2 * PH_TBL : 0;
-  const size_t plan = sh.setup && rows ? (sizeof(BandLds) + 15) / 16 * 2 : 0;
+  const size_t plan = sh.setup ? (plan_bytes + 15) / 16 * 2 : 0;
   return coef + (red > tbl + plan ? red : tbl + plan);
 }
 
@@ -163,6 +163,7 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
   // the group's plan when SETUP, after the table (all LDS is dynamic: a static object in front would
   // leave the table's 16-byte entries at an 8-byte offset, which costs more than half the rate)
   BandLds& bands_s = *reinterpret_cast<BandLds*>(tail + 2 * PH_TBL);
+  LevelLds& levels_s = *reinterpret_cast<LevelLds*>(tail + 2 * PH_TBL);
 
   // sh.pgmaj: each die takes whole point groups, all G workgroups of each (a point group's set-up
   // rows are read by one die only): a contiguous range of point-group-major items (balanced to
@@ -224,8 +225,10 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
     if (sh.W < 3) band_load(bh, slopes_s);
     else if (w >= 2) band_load(bh, slopes_s, 2 * WAVE);
   }
+  const int nlev = LEVELS ? bh->nlev[LOOP == LOOP_MIXED_LEVELS] : 0;
   if constexpr (LEVELS) {
-    if (threadIdx.x < MAXLEV) bands_s.fit[threadIdx.x] = ~0ull;
+    if (w >= 2 || sh.W < 3) level_load(bh, nlev, levels_s, sh.W < 3 ? 0 : 2 * WAVE);
+    if (threadIdx.x < MAXLEV) levels_s.fit[threadIdx.x] = ~0ull;
   }
   BandPre pre;
   if constexpr (SETUP && BANDS) pre = band_fetch(bh, w, lane);
@@ -266,11 +269,11 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
       __syncthreads();
     }
     if constexpr (LEVELS) {
-      band_fit<ND>(bh, slopes_s, a, T, w, sh.W, lane, bands_s);
+      band_fit<ND>(nlev, bh->nbrk, slopes_s, a, T, w, sh.W, lane, levels_s);
       __syncthreads();
-      level = bh->nlev[LOOP == LOOP_MIXED_LEVELS];
-      for (int l = level - 1; l >= 0; --l)
-        if ((bands_s.fit[l] >> lane) & 1) level = l;
+      level = nlev;
+      for (int l = nlev - 1; l >= 0; --l)
+        if ((levels_s.fit[l] >> lane) & 1) level = l;
       if (p >= B) level = -1;
     }
   }
@@ -299,7 +302,6 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
   if constexpr (LEVELS) {
     // Every level that one of the lanes needs, for all of them (a branch of the wavefront keeps the rows in scalar
     // registers: in a branch of the lanes the loop took twice as long), each lane keeping its own's sums.
-    const int nlev = bh->nlev[LOOP == LOOP_MIXED_LEVELS];
     auto keep = [&](int l, const double (&z)[NZ]) {
 #pragma unroll
       for (int j = 0; j < NZ; ++j) tot[j] = level == l ? z[j] : tot[j];
@@ -320,13 +322,15 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
       const BandLevel& v = bh->lev[l < nlev ? l : MAXLEV];
       const int chunk = (v.rows + sh.nchunk - 1) / sh.nchunk;
       const int q0 = (int)c * chunk, q1 = q0 + chunk < v.rows ? q0 + chunk : v.rows;
-      // (the numbers of a plan, whose pieces follow from the fourth on)
-      for_pieces(
-          bh, ec->grid_df, q0, q1, [&](int i) { return i == 1 ? v.np : v.piece[i - 4]; },
-          [&](int ka, int kb, double step) {
-            if constexpr (ROT) bin_loop_f64_rot<ND, GRAD>(tab, gtab, ka, kb, a, T, crd, cid, tbl, step, z);
-            else bin_loop_f64<ND, GRAD>(tab, gtab, ka, kb, a, T, crd, cid, tbl, z);
-          });
+      int base = 0;
+      for (int i = 0; i < v.np && base < q1; ++i) {            // as for_pieces
+        const int lo = q0 > base ? q0 - base : 0, hi = q1 - base < v.n[i] ? q1 - base : v.n[i];
+        base += v.n[i];
+        if (lo >= hi) continue;
+        const int ka = v.row0[i] + lo, kb = v.row0[i] + hi;
+        if constexpr (ROT) bin_loop_f64_rot<ND, GRAD>(tab, gtab, ka, kb, a, T, crd, cid, tbl, v.step[i], z);
+        else bin_loop_f64<ND, GRAD>(tab, gtab, ka, kb, a, T, crd, cid, tbl, z);
+      }
       keep(l, z);
     }
   } else {
@@ -459,7 +463,8 @@ __attribute__((amdgpu_waves_per_eu(eval_waves_per_eu<ND, LOOP, GRAD, SETUP, CUT,
 template <int ND, int LOOP, bool GRAD>
 static hipError_t eval_loop(bool cut, bool rot, const EvalArgs& x, const LoopShape& sh, hipStream_t s) {
   const dim3 grid((unsigned)(sh.gper * NXCD)), block((unsigned)(sh.W * WAVE));
-  const size_t lds = eval_lds_doubles(LOOP != LOOP_MIXED, LOOP > LOOP_MIXED, sh) * sizeof(double);
+  const size_t plan_bytes = LOOP >= LOOP_F64_LEVELS ? sizeof(LevelLds) : (LOOP > LOOP_MIXED ? sizeof(BandLds) : 0);
+  const size_t lds = eval_lds_doubles(LOOP != LOOP_MIXED, plan_bytes, sh) * sizeof(double);
 #define GWL_EVAL(ST, CU, RO)                                                                                        \
   hipLaunchKernelGGL((k_eval<ND, LOOP, GRAD, ST, CU, RO>), grid, block, lds, s, (const RowF64<ND>*)x.tab64,         \
                      x.gtab, x.theta, *x.geo, x.ec, x.coef, x.B, x.Bp, x.M, sh, x.part, x.cnt, x.logl, x.fgrid,     \
