@@ -121,7 +121,7 @@ __device__ inline double value_from_rows(const double (&acc)[NZ], double amp, do
 // each level that one of its lanes needs, and a lane keeps its own's sums. A point's bits then do not depend
 // on which other points are live, nor on what the rows past the live ones hold. Levels have about a sixth more
 // rows than plans of 64 prior draws (1,872 and 1,610 a group; three detectors, 8 s), and choosing one takes two
-// barriers less: 8,192 points of which 40 % are live 34.3 us with plans, 34.7 with levels, 104 on every bin.
+// barriers less: 8,192 points of which 40 % are live 34.05 us with plans, 34.15 with levels, 104 on every bin.
 enum { LOOP_F64 = 0, LOOP_MIXED = 1, LOOP_F64_BANDS = 2, LOOP_MIXED_BANDS = 3, LOOP_F64_LEVELS = 4, LOOP_MIXED_LEVELS = 5 };
 
 // The tables are `const __restrict__` kernel arguments, so the compiler reads their wave-uniform
