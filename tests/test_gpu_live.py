@@ -151,3 +151,41 @@ def test_a_reserved_live_call_is_captured(B, f_hi, prec):
         torch.cuda.synchronize()
         assert torch.equal(out[:B - 3], want[:B - 3]) and bool((out[B - 3:] == 0.0).all())
     ev.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("nd,duration,f_hi,uniform", [(3, 8.0, 400.0, False), (1, 8.0, 700.0, False), (2, 64.0, 300.0, True),
+                                                      (3, 128.0, 250.0, False)])
+def test_live_calls_over_grids(nd, duration, f_hi, uniform, prec):
+    """Levels on grids without a fixed step (no rotation of the phasors) and on long segments, where there are three:
+    points of each and of none against the same bins with two neighbours swapped, which have no rows."""
+    df = 1.0 / duration
+    f = synth.freq_grid(20.0, f_hi, df)
+    if not uniform:
+        f = f + 0.2 * df * np.sin(np.arange(len(f)) * 1.7)
+    psd = np.stack([synth.psd_fit(f)] * nd)
+    dets = np.array([synth.detector_rad(n) for n in ("D1", "D2", "D3")[:nd]])
+    data = np.stack([synth.noise(700 + i, psd[i], df) for i in range(nd)])
+    k = len(f) // 2
+    swap = np.r_[0:k, k + 1, k, k + 2:len(f)]
+    mk = lambda i: gw.Event(torch.tensor(np.ascontiguousarray(data[:, i]), device=DEV),
+                            torch.tensor(np.ascontiguousarray(psd[:, i]), device=DEV), dets,
+                            torch.tensor(f[i], device=DEV), df)
+    ev, plain = mk(np.arange(len(f))), mk(swap)
+    rng = np.random.default_rng(17)
+    th = synth.prior_draw(rng, 500)
+    th[:, 0] = rng.uniform(1.0, 60.0, 500)
+    th[:, 4] = 100.0
+    kind = rng.integers(0, 4, 500)
+    th[kind == 1, 10] = rng.uniform(-0.5, 0.5, (kind == 1).sum())
+    th[kind == 2, 10] = rng.uniform(-0.4, 0.4, (kind == 2).sum()) * duration
+    t = torch.tensor(th, device=DEV)
+    n = torch.tensor(437, dtype=torch.int64, device=DEV)
+    got = gw.logl_live(t, n, ev, prec)[:437].cpu().numpy()
+    want = gw.logl(t, plain, prec)[:437].cpu().numpy()
+    dn = np.sqrt(sum(float((4 * df * np.abs(d) ** 2 / s).sum()) for d, s in zip(data, psd)))
+    hn = dn + np.sqrt(np.maximum(dn ** 2 - 2.0 * want, 0.0))
+    tol = 1e-13 * hn * dn + 1e-9 if prec == "fp64" else 1e-3
+    assert (np.abs(got - want) <= tol).all(), np.abs(got - want).max()
+    ev.close()
+    plain.close()
